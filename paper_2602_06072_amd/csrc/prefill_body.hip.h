@@ -159,11 +159,7 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
 }
 
 // o / l to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
-__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], float l) {
-    {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
-        l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
+__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], const float l) {
     if (u.qrow < 0) return;
     const float inv = l > 0.f ? 1.f / l : 0.f;
     const int64_t obase = (static_cast<int64_t>(u.qrow) * a.Hq + u.head) * D;
@@ -189,11 +185,7 @@ __device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUni
 // 16..31 in qb); the 16-byte chunks of a row are XOR-swizzled with the row number, which keeps
 // both sides off bank conflicts.
 __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB],
-                                                  float l, unsigned char* qa, unsigned char* qb) {
-    {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
-        l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
+                                                  const float l, unsigned char* qa, unsigned char* qb) {
     constexpr int CPR = D / 8, RPI = 64 / CPR;     // 16-byte chunks per row; rows per store instruction
     const float inv = l > 0.f ? 1.f / l : 0.f;
     const int rr = u.n & 15;
@@ -274,21 +266,49 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
 // into Q instead would save that instruction but costs another rounding of Q to bf16: 2^-9
 // relative per element, which for scores of a few units' spread is an error of 0.03 .. 0.04 in
 // the output, measured.)
-//   m_ref   reference that the exponentials are taken against, in the exp2 domain; it only has to
-//           stay within 2^13 of the running maximum, so it moves rarely ("lazy" rescaling);
-//   m_set   the row has seen a key (m_ref means something);  l  this lane's share of the row sum.
-// Fast path of a half tile (16 scores per lane): p = exp2(x), pairs rounded to bf16, row sums of
-// the rounded pairs by dot2, no maximum.  The increment of the sum tells whether the reference is
-// still good: if any lane's increment exceeds 2^13 (or a row has no reference yet) the whole wave
-// redoes the half tile on the slow path below, which finds the maximum, moves the reference and
-// rescales what has been accumulated.  Scores that are still in the making (the other half tile's)
-// are raw and meet the new reference when their turn comes.
+//   m_ref   reference that the exponentials are taken against, in the exp2 domain.  It is set kSlack
+//           above the row maximum it was taken from and only has to stay within a few dozen octaves
+//           of the running one (bf16 and fp32 share their exponent range, so a probability of 2^-12
+//           is as exact as one of 1), so it moves rarely ("lazy" rescaling).  kUnset: no key seen
+//           yet (every visible score then asks for the slow path); kNoRow: no query in this lane
+//           (every probability is 0);
+//   lsum[0] the row sum, over both halves of the wave.
+// Fast path of a half tile (16 scores per lane): p = exp2(x), pairs rounded to bf16, no maximum, no
+// sum.  The sum of a row is left to the matrix pipe: one v_mfma_f32_16x16x32_bf16 per 16 keys
+// whose A operand holds ones where they bring the sum of a query's P into register 0 of both
+// lanes that carry it (row_sum_selector).  It sums the ROUNDED probabilities, the numbers that go into P.V: a
+// probability is taken against a reference that may lie far from the row maximum, so even a
+// dominant one is not a round number, and its rounding error (2^-9 relative) has to cancel between
+// numerator and denominator.  (With the unrounded values in the sum a row that one key dominates is
+// off by 1.4e-2, with the rounded ones by 5e-3, measured.)  A v_dot2_f32_bf16 per pair gives the same
+// sum but costs as much as two and a half multiply-adds: in a loop of this kernel's mix (two
+// waves per SIMD) 2.4 ns of 26.6 per 32x32x16 MFMA; the small MFMAs cost under 1.  On the whole kernel:
+// 32 chunks of a 70B-shaped layer 11.85 -> 11.50 ms, 64 ragged prompts 436 -> 416 us, 8 long prompts
+// with D = 64 604 -> 593 us.
+// Whether the reference is still good shows in the exponent bits of the packed pairs: if any
+// probability is 2 or more (bit 14 of a bf16) the whole wave redoes the half tile on the slow path below,
+// which finds the maximum, moves the reference and rescales what has been accumulated.  Scores that
+// are still in the making (the other half tile's) are raw and meet the new reference when their
+// turn comes.
 struct HalfSoftmax {
-    float l0, l1;
+    uint32_t any;                                  // all packed pairs or'ed together
     uint32_t pw[8];
 };
-constexpr float kIncLimit = 8192.f;                // 2^13
+constexpr float kSlack = 12.f;                     // a fresh reference lies this far above the row maximum
 constexpr float kRaiseBy = 8.f;                    // a set reference is only raised by more than this
+constexpr float kUnset = -1e30f, kNoRow = 1e30f;
+constexpr uint32_t kTooLarge = 0x40004000u;        // a bf16 of 2 or more in either half
+
+// A operand of the row-sum MFMA.  The B operand is P as the 32x32x16 MFMA takes it: lane l holds
+// eight keys of query l & 31.  Seen as the operand of a 16x16x32 MFMA its lane group g = l / 16 is
+// column l & 15, contraction block g; queries 0..15 sit in blocks 0 and 2, queries 16..31 in blocks
+// 1 and 3.  Lane l receives rows 4 (l / 16) .. + 3 of its column: row 4 g takes the ones of the
+// blocks with g's parity, the other rows are zero.
+__device__ __forceinline__ bf16x8 row_sum_selector(int lane) {
+    const int row = lane & 15, block = lane >> 4;
+    const uint32_t w = (row & 3) == 0 && ((row >> 2) & 1) == (block & 1) ? 0x3F803F80u : 0u;
+    return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
+}
 
 // max without the canonicalising self-maximum that fmaxf() costs per operand (scores are never NaN;
 // -inf is ordinary here).  Not volatile: the compiler schedules these like any arithmetic.
@@ -304,13 +324,8 @@ __device__ __forceinline__ float max2f(float a, float b) {
 }
 
 // Slice C (0..7) of the fast path: pair C of the half tile, in two stages, so that the conversion
-// never waits for its exponentials: stage A (fma, exp) right behind MFMA C, stage B (round, sum,
-// pack) behind MFMA C + 1 (1.4 % on the whole kernel; a third stage between fma and exp: nothing).
-// The row sum takes the ROUNDED pair, the same numbers that go into P.V: a probability is taken
-// against a reference that may lie far from the row maximum, so even a dominant one is not a round
-// number, and its rounding error (2^-9 relative) has to cancel between numerator and denominator.
-// (Measured: with the unrounded values in the sum a row that one key dominates is off by 1.4e-2,
-// with the rounded ones by 5e-3, like a kernel that takes exp against the maximum.)
+// never waits for its exponentials: stage A (fma, exp) right behind MFMA C, stage B (round, pack)
+// behind MFMA C + 1 (1.4 % on the whole kernel; a third stage between fma and exp: nothing).
 template <int C>
 __device__ __forceinline__ floatx2 slice_a(const floatx16& s, const float sc, const float m_ref) {
     floatx2 pp;
@@ -320,56 +335,44 @@ __device__ __forceinline__ floatx2 slice_a(const floatx16& s, const float sc, co
 }
 template <int C>
 __device__ __forceinline__ void slice_b(const floatx2 pp, HalfSoftmax& h) {
-    const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
-    if constexpr (C & 1) h.l1 = __builtin_amdgcn_fdot2_f32_bf16(pb, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, h.l1, false);
-    else h.l0 = __builtin_amdgcn_fdot2_f32_bf16(pb, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, h.l0, false);
-    h.pw[C] = __builtin_bit_cast(uint32_t, pb);
+    h.pw[C] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
+    if constexpr (C == 0) h.any = h.pw[0];
+    else if constexpr (C == 7) h.any |= h.pw[7];
+    else if constexpr ((C & 1) == 0) h.any |= h.pw[C - 1] | h.pw[C];    // one v_or3_b32 every other slice
 }
 
-// Slow path of a half tile (wave-uniform, rare): s holds the scores relative to the current
-// reference.  First the scalars: the row maximum (both lanes of a row agree through the swap),
-// the shift `delta` of the reference for the rows that need one, the factor alpha for what has
-// been accumulated so far.  The caller then shifts the scores, recomputes the probabilities and
-// rescales, each in a branch of its own that holds nothing but updates in place: written as one
-// block, the paths join with the 64 accumulators in fresh registers, more than the kernel has.
-__device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, float& m_ref, bool& m_set,
-                                                     float& delta, float& alpha) {
+// Slow path of a half tile (wave-uniform, rare): s holds the raw scores.  First the scalars: the
+// row maximum (both lanes of a row agree through the swap), the new reference for the rows that
+// need one, the factor alpha for what has been accumulated so far (0 for a row's first keys,
+// when there is nothing).  The caller then recomputes the probabilities and rescales, each in a
+// branch of its own that holds nothing but updates in place: written as one block, the paths join
+// with the 64 accumulators in fresh registers, more than the kernel has.
+__device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const float sc, float& m_ref, float& alpha) {
     float mx = max3f(max3f(max3f(max2f(s[0], s[1]), s[2], s[3]), s[4], s[5]), s[6], s[7]);
     mx = max3f(max3f(max3f(max3f(mx, s[8], s[9]), s[10], s[11]), s[12], s[13]), s[14], s[15]);
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
     mx = max2f(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-    const bool seen = mx > -INFINITY;              // the row has a visible key in this half tile
-    delta = (seen && (!m_set || mx > kRaiseBy)) ? mx : 0.f;
-    alpha = m_set ? __builtin_amdgcn_exp2f(-delta) : 1.f;   // nothing accumulated before the first key
-    m_set = m_set || seen;
-    m_ref += delta;
+    const float fresh = __builtin_fmaf(mx, sc, kSlack);     // -inf for a row without a visible key here
+    const float next = fresh > m_ref + kRaiseBy ? fresh : m_ref;
+    alpha = __builtin_amdgcn_exp2f(m_ref - next);
+    m_ref = next;
 }
-__device__ __forceinline__ void softmax_redo(floatx16& s, HalfSoftmax& h, float delta) {
-    h.l0 = 0.f; h.l1 = 0.f;
+__device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, const float sc, const float m_ref) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         floatx2 pp;
-        pp[0] = __builtin_amdgcn_exp2f(s[2 * q] - delta);
-        pp[1] = __builtin_amdgcn_exp2f(s[2 * q + 1] - delta);
-        const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
-        if (q & 1) h.l1 = __builtin_amdgcn_fdot2_f32_bf16(pb, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, h.l1, false);
-        else h.l0 = __builtin_amdgcn_fdot2_f32_bf16(pb, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, h.l0, false);
-        h.pw[q] = __builtin_bit_cast(uint32_t, pb);
+        pp[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q], sc, -m_ref));
+        pp[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q + 1], sc, -m_ref));
+        h.pw[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
     }
 }
 #define PK_SOFTMAX_CHECK(S, H)                                                                 \
     {                                                                                          \
-        const bool slow = __builtin_amdgcn_ballot_w64((H.l0 + H.l1) > kIncLimit || !m_set) != 0; \
-        float delta = 0.f, alpha = 1.f;                                                        \
+        const bool slow = __builtin_amdgcn_ballot_w64((H.any & kTooLarge) != 0) != 0;          \
+        float alpha = 1.f;                                                                     \
         /* the empty asm statements keep the compiler from computing the rare branches always */ \
-        if (slow) {                                                                            \
-            asm volatile("");                                                                  \
-            /* exponents of two relative to the present reference */                           \
-            _Pragma("unroll") for (int e = 0; e < 16; ++e) S[e] = __builtin_fmaf(S[e], sc, -m_ref); \
-            softmax_slow_scalars(S, m_ref, m_set, delta, alpha);                               \
-        }                                                                                      \
-        if (slow) { asm volatile(""); softmax_redo(S, H, delta); }                             \
-        l = l * alpha + (H.l0 + H.l1);                                                         \
+        if (slow) { asm volatile(""); softmax_slow_scalars(S, sc, m_ref, alpha); }             \
+        if (slow) { asm volatile(""); softmax_redo(S, H, sc, m_ref); lsum[0] *= alpha; }       \
         if (slow) {                                                                            \
             _Pragma("unroll") for (int b = 0; b < DB; ++b)                                     \
                 _Pragma("unroll") for (int e = 0; e < 16; ++e) o[b][e] *= alpha;               \
@@ -389,7 +392,7 @@ __device__ __forceinline__ void pin_slice_inputs(floatx16& acc, floatx16& s) {
 }
 template <int C>
 __device__ __forceinline__ void pin_slice_outputs(bf16x8& next_operand, HalfSoftmax& h) {
-    asm volatile("" : "+v"(next_operand), "+v"(h.pw[C]), "+v"(h.l0), "+v"(h.l1));
+    asm volatile("" : "+v"(next_operand), "+v"(h.pw[C]));
 }
 
 // -inf for the keys of half `half` of a tile that a query row may not see (outside [lo, hi_t)):
@@ -423,6 +426,8 @@ __device__ __forceinline__ bf16x8 stream_operand(const unsigned char* k_cur, con
     else return k_operand(k_next, off, 0, K - 4 * KS);
 }
 #define PK_REFILL(K0) ring[i & 3] = stream_operand<(K0) + i + 4>(lds + k_cur, lds + v_cur, lds + k_next, off)
+// the row sums of 16 keys, next to the first of the MFMAs that take the same P
+#define PK_ROW_SUM(P) if constexpr (i % DB == 0) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[i / DB], lsum, 0, 0, 0)
 #define PK_SLICE(C, S, H, ACC, BODY)                                                          \
     {                                                                                          \
         constexpr int i = C;                                                                   \
@@ -511,9 +516,9 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     for (int b = 0; b < DB; ++b)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[b][e] = 0.f;
-    // rows without a query count as "set" so that they never ask for the slow path
-    float m_ref = 0.f, l = 0.f;
-    bool m_set = u.qrow < 0;
+    float m_ref = u.qrow < 0 ? kNoRow : kUnset;    // rows without a query never ask for the slow path
+    floatx4 lsum = {0.f, 0.f, 0.f, 0.f};
+    const bf16x8 ones = row_sum_selector(u.lane);
     const floatx16 zero16 = {};
     const float sc = a.scale * kLog2e;             // raw score -> exponent of two (the API admits only finite scale > 0)
 
@@ -580,7 +585,6 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         PK_EIGHT(s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s0, 0, 0, 0);
                  PK_REFILL(0); PK_COPY_STEP(i));
         HalfSoftmax h0, h1;
-        h0.l0 = 0.f; h0.l1 = 0.f; h1.l0 = 0.f; h1.l1 = 0.f;
         if (masked) mask_half(s0, 0, u.lo, hi_t, k_start, u.hlf);    // unmasked tiles skip the compares
         PK_SLICES(s0, h0, s1, s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s1, 0, 0, 0);
                   PK_REFILL(KS));
@@ -591,14 +595,14 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
             p0[t] = __builtin_bit_cast(bf16x8, u32x4{h0.pw[4 * t], h0.pw[4 * t + 1], h0.pw[4 * t + 2], h0.pw[4 * t + 3]});
         if (masked) mask_half(s1, 1, u.lo, hi_t, k_start, u.hlf);
         PK_SLICES(s1, h1, o[i % DB], o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p0[i / DB], o[i % DB], 0, 0, 0);
-                  PK_REFILL(2 * KS));
+                  PK_ROW_SUM(p0); PK_REFILL(2 * KS));
         PK_SOFTMAX_CHECK(s1, h1)
 #pragma unroll
         for (int t = 0; t < 2; ++t)
             p1[t] = __builtin_bit_cast(bf16x8, u32x4{h1.pw[4 * t], h1.pw[4 * t + 1], h1.pw[4 * t + 2], h1.pw[4 * t + 3]});
         // phase 4; its last refills are the first operands of the next tile
         PK_EIGHT(o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p1[i / DB], o[i % DB], 0, 0, 0);
-                 PK_REFILL(3 * KS));
+                 PK_ROW_SUM(p1); PK_REFILL(3 * KS));
         PK_TILE_END();
     }
     // trailing tiles that this wave skips: it only takes part in the copies and in the barriers
@@ -612,8 +616,8 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // n_kv and n_kv + 1 (after the final rotation: k_next and v_cur), and a wave's copies only
     // ever touch its own quarter of a stage: those two quarters stage this wave's output.
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
-    if (a.out_f32) store_output(a, u, o, l);
-    else store_output_bf16(a, u, o, l, lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
+    if (a.out_f32) store_output(a, u, o, lsum[0]);
+    else store_output_bf16(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
 }
 
 #undef PK_COPY_TILE
@@ -628,6 +632,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #undef PK_SLICES
 #undef PK_EIGHT
 #undef PK_REFILL
+#undef PK_ROW_SUM
 #undef PK_WAIT_ALL_COPIES
 #undef PK_CODE
 

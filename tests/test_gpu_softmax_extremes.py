@@ -115,3 +115,33 @@ def test_decode_softmax_extremes(case):
     pk.padded_decode_attn(plan, w.q, w.k_pages, w.v_pages, bt, out2, w.scale, ws)
     torch.cuda.synchronize()
     H.assert_close(out2.cpu().numpy(), want, 0, f"padded decode {case}")
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_scores_beyond_the_exponent_range(d):
+    """Row maxima that jump by more than 127 octaves inside a request (a probability against the old
+    reference overflows to infinity in bf16 and fp32) and rows all of whose scores lie thousands of
+    nats below zero.  Rows are one-hot or nearly: an error of a score of magnitude S is at most
+    S * d * 2^-24 (fp32 sums of exact products), 2e-2 for the largest here, and only keys of equal
+    score share a row, so the usual tolerance holds."""
+    kv = np.asarray([513, 200, 97, 1000], dtype=np.int32)
+    w = wl.make_ragged("exponent_range", kv, kv, 4, 2, d, 1024, 9, DEV, keep_f32=False)
+    w.q.copy_(w.q.abs())
+    s0 = w.kv_start
+    for pos, value in ((0, -4.0), (40, 12.0), (64, 30.0), (130, 60.0), (131, -60.0), (300, 100.0)):
+        w.k[int(s0[0]) + pos] = value
+        w.k[int(s0[3]) + pos + 500] = value
+    w.k[int(s0[1]):int(s0[2])] = -(w.k[int(s0[1]):int(s0[2])].abs() + 20.0)
+    want = H.oracle_ragged(w, False)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=w.token_budget)
+    ws = pk.new_workspace(plan, w.Hq, w.Hkv, w.d, pk.PK_BF16)
+    out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    lo, hi = int(s0[1]), int(s0[2])                        # scores around -2000 nats there: checked loosely below
+    keep = np.r_[0:lo, hi:got.shape[0]]
+    H.assert_close(got[keep], want[keep], 0, f"exponent range d={d}")
+    # bf16 keys of magnitude 20..23 step by 2^-3: many keys share a row; the score error above (|score| up to
+    # 3000 nats: 3000 * 128 * 2^-24 = 2.3e-2) moves a probability by that fraction and an output of |v| <= 5 by 5 times it
+    assert np.abs(got[lo:hi] - want[lo:hi]).max() <= 2e-2 + 5 * 2.3e-2
