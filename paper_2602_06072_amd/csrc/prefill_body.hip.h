@@ -2,7 +2,7 @@
 // arithmetic and same operand scheme as prefill.hip (S^T = K.Q^T, O^T += V^T.P^T with
 // v_mfma_f32_32x32x16_bf16, one wave per 32 query rows, key tiles of 64), but
 //   * K/V tiles go HBM/L2 -> LDS directly (buffer_load ... lds, 16 bytes per lane, no staging
-//     registers, hardware bounds check); rows are unpadded and the 16-byte chunks of a row are
+//     registers, hardware bounds check) into slabs of 64 columns; the 16-byte chunks of a row are
 //     XOR-swizzled -- the swizzle is applied on the global side of the copy, so that both the K
 //     row reads (ds_read_b128) and the V transpose reads (ds_read_b64_tr_b16) are free of bank
 //     conflicts;
@@ -15,7 +15,7 @@
 // Device code only: included by prefill_pipe.hip (the prefill launch) and by mixed_step.hip (the
 // fused prefill + decode launch).  The includer defines PK_D (the head dimension) and PK_DNS (the
 // namespace this instance goes into) first; the file may be included once per head dimension.
-// With PK_D = 64 a row is 128 bytes, a tile 8 KiB (two 1-KiB copy instructions per wave) and a
+// With PK_D = 64 a tile is 8 KiB (two 1-KiB copy instructions per wave) and a
 // half tile four MFMAs instead of eight, each followed by two softmax slices instead of one.
 #include <cstdint>
 
@@ -31,43 +31,38 @@ namespace {
 namespace PK_DNS {
 
 constexpr int BM = 128, BN = 64, D = PK_D;
-constexpr int ROWB = D * 2;                        // bytes per K/V row in LDS (unpadded)
+constexpr int ROWB = D * 2;                        // bytes per K/V row in global memory
 constexpr int TILE_BYTES = BN * ROWB;              // 16 KiB (8 KiB for D = 64)
 constexpr int KS = D / 16, DB = D / 32;
 constexpr int PIECES = TILE_BYTES / 4096;          // 1-KiB copy instructions per wave and tile
 constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that one wave fills
 
+// A stage in LDS is one slab per 64 columns: 64 rows of 128 bytes (eight 16-byte chunks).  Whatever
+// the head dimension, four K and four V addresses per lane then reach every operand with constant
+// offsets, eight additions to the stage's address per key tile; with rows of 256 bytes it took eight of
+// each and 24 additions, every sixth vector instruction of the loop (70B-shaped chunks 11.02 -> 10.91 ms,
+// 8 long prompts with D = 64, where the addresses are carried over the tile now, 573 -> 565 us).
+constexpr int SLAB_ROWB = 128, SLAB = BN * SLAB_ROWB;
+
 typedef bf16x4 __attribute__((address_space(3))) * lds_bf16x4_ptr;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-// chunk position p of row `row` holds logical chunk p ^ swz(row)
-#if PK_D == 128
-__device__ __forceinline__ int swz(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-#else
-// 128-byte rows: two rows share a line of the 64 banks, so rows of the same parity need eight
-// different values (K row reads of 16 consecutive rows), and rows r and r + 2 must differ in
-// bit 2 (the transpose reads take 64 bytes from each of four consecutive rows)
+// Chunk position p of row `row` holds logical chunk p ^ swz(row).  Two 128-byte rows share a line of
+// the 64 banks, so rows of the same parity need eight different values (K row reads of 16
+// consecutive rows), and rows r and r + 2 must differ in bit 2 (the transpose reads take 64 bytes
+// from each of four consecutive rows).
 __device__ __forceinline__ int swz(int row) { const int x = (row >> 1) & 7; return ((x & 1) << 2) | (x >> 1); }
-#endif
 
 struct LaneOffsets {
-    int k[KS];          // K operand read: row n, logical chunk 2 st + hlf (add 32 kb rows)
-    int v1[DB];         // V transpose read of column block b, rows +0..3 (add (32 kb + 16 t) rows); the read
-                        // of rows +8..11 is at (v1 ^ 32) + 8 rows: its swizzle differs in one bit
-#if PK_D == 64
-    int v2[DB];         // (128-byte rows: the read of rows +8..11 has an offset of its own)
-#endif
+    int k[4];           // K operand read: row n, logical chunk 2 (st & 3) + hlf of a slab
+    int v1[2], v2[2];   // V transpose reads of column block b & 1 of a slab, rows +0..3 and +8..11
     int g[PIECES];      // global byte offsets of this lane's copy instructions
 };
 
 __device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneOffsets& lo, int kb, int t, int b) {
-    const unsigned char* p = vs + (32 * kb + 16 * t) * ROWB;
-    const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + lo.v1[b]));
-#if PK_D == 128
-    const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 8 * ROWB + (lo.v1[b] ^ 32)));
-#else
-    const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + lo.v2[b]));
-#endif
+    const unsigned char* p = vs + (b >> 1) * SLAB + (32 * kb + 16 * t) * SLAB_ROWB;
+    const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + lo.v1[b & 1]));
+    const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + lo.v2[b & 1]));
     return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
@@ -114,36 +109,21 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
 
     const int fl = swz(u.n);
 #pragma unroll
-    for (int st = 0; st < KS; ++st) off.k[st] = u.n * ROWB + (((2 * st + u.hlf) ^ fl) << 4);
+    for (int st = 0; st < 4; ++st) off.k[st] = u.n * SLAB_ROWB + (((2 * st + u.hlf) ^ fl) << 4);
     const int i16 = u.lane & 15, gl = (u.lane >> 4) & 1, r4 = i16 >> 2;
     const int rowl = 4 * u.hlf + r4, byte = (i16 & 1) * 8;
-#if PK_D == 128
-    const int f1 = (r4 << 2) | u.hlf;  // rows +8: (hlf + 2) & 3 = hlf ^ 2, i.e. chunk ^ 2, byte offset ^ 32
 #pragma unroll
-    for (int b = 0; b < DB; ++b) {
+    for (int b = 0; b < 2; ++b) {
         const int c = 4 * b + 2 * gl + ((i16 & 3) >> 1);
-        off.v1[b] = rowl * ROWB + ((c ^ f1) << 4) + byte;
-    }
-    const int r_in = u.lane >> 4, pos = u.lane & 15;   // a copy instruction takes 4 rows of 16 chunks
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int row = 16 * u.wave + 4 * q + r_in;
-        off.g[q] = static_cast<int>(row * u.row_bytes + u.kvh * ROWB + ((pos ^ swz(row)) << 4));
-    }
-#else
-#pragma unroll
-    for (int b = 0; b < DB; ++b) {
-        const int c = 4 * b + 2 * gl + ((i16 & 3) >> 1);
-        off.v1[b] = rowl * ROWB + ((c ^ swz(rowl)) << 4) + byte;
-        off.v2[b] = (rowl + 8) * ROWB + ((c ^ swz(rowl + 8)) << 4) + byte;
+        off.v1[b] = rowl * SLAB_ROWB + ((c ^ swz(rowl)) << 4) + byte;
+        off.v2[b] = (rowl + 8) * SLAB_ROWB + ((c ^ swz(rowl + 8)) << 4) + byte;
     }
     const int r_in = u.lane >> 3, pos = u.lane & 7;    // a copy instruction takes 8 rows of 8 chunks
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) {
-        const int row = 16 * u.wave + 8 * q + r_in;
-        off.g[q] = static_cast<int>(row * u.row_bytes + u.kvh * ROWB + ((pos ^ swz(row)) << 4));
+        const int row = 16 * u.wave + 8 * (q & 1) + r_in;
+        off.g[q] = static_cast<int>(row * u.row_bytes + u.kvh * ROWB + (q >> 1) * SLAB_ROWB + ((pos ^ swz(row)) << 4));
     }
-#endif
     // Q operand: lane (n, hlf) holds Q[row n][16s + 8hlf .. +8], as it is in memory: the MFMAs
     // deliver raw scores, exact products of the bf16 inputs summed in fp32.  Only requested here;
     // the first K/V copies follow at once, so that the two round trips to memory overlap.
@@ -212,8 +192,7 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is 16 instructions of 1 KiB (four per wave; eight and
-// two for D = 64), each
-// lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the end
+// two for D = 64), each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the end
 // of the array arrive as zeros (the descriptor's size is what is left of the array; a tile past
 // the end of the key-tile list gets size 0: zeros, no memory traffic).  The copy is issued from
 // inline assembly on purpose: the compiler makes every later LDS read wait for all copies it
@@ -240,7 +219,7 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
         RS[3] = 0x00020000u;                                                                 \
     }
 // this wave's piece Q (0..3) of a tile into the stage at byte offset DST
-#define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + (Q) * 1024, off.g[Q])
+#define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) >> 1) * SLAB + ((Q) & 1) * 1024, off.g[Q])
 #define PK_COPY_TILE(SRC, KSTART, DST, ENABLED)                                              \
     {                                                                                        \
         PK_TILE_DESC(rs_, SRC, KSTART, ENABLED)                                              \
@@ -408,8 +387,8 @@ __device__ __forceinline__ void mask_half(floatx16& s, int half, int lo, int hi_
 }
 
 // operand x (0..7) of a half tile: K rows of contraction step x; V^T block (t, b) = (x / 4, x % 4)
-__device__ __forceinline__ bf16x8 k_operand(const unsigned char* ks, const LaneOffsets& lo, int half, int x) {
-    return *reinterpret_cast<const bf16x8*>(ks + lo.k[x] + half * 32 * ROWB);
+__device__ __forceinline__ bf16x8 k_operand(const unsigned char* const (&kp)[4], int half, int x) {
+    return *reinterpret_cast<const bf16x8*>(kp[x & 3] + (x >> 2) * SLAB + half * 32 * SLAB_ROWB);
 }
 __device__ __forceinline__ bf16x8 v_operand_x(const unsigned char* vs, const LaneOffsets& lo, int half, int x) {
     return v_operand(vs, lo, half, x / DB, x % DB);
@@ -419,13 +398,16 @@ __device__ __forceinline__ bf16x8 v_operand_x(const unsigned char* vs, const Lan
 // MFMA k takes ring[k % 4] and then refills that slot with operand k + 4, so that every LDS read
 // has four MFMAs (and their vector slices) to land.
 template <int K>
-__device__ __forceinline__ bf16x8 stream_operand(const unsigned char* k_cur, const unsigned char* v_cur,
-                                                 const unsigned char* k_next, const LaneOffsets& off) {
-    if constexpr (K < 2 * KS) return k_operand(k_cur, off, K / KS, K % KS);
+__device__ __forceinline__ bf16x8 stream_operand(const unsigned char* const (&kp)[4], const unsigned char* v_cur,
+                                                 const LaneOffsets& off) {
+    if constexpr (K < 2 * KS) return k_operand(kp, K / KS, K % KS);
     else if constexpr (K < 4 * KS) return v_operand_x(v_cur, off, (K - 2 * KS) / KS, K % KS);
-    else return k_operand(k_next, off, 0, K - 4 * KS);
+    else return k_operand(kp, 0, K - 4 * KS);      // (by then the addresses are those of the next tile)
 }
-#define PK_REFILL(K0) ring[i & 3] = stream_operand<(K0) + i + 4>(lds + k_cur, lds + v_cur, lds + k_next, off)
+// kp: this lane's four K addresses in the stage that is read; they move on to the next stage before
+// phase 4, so that they are computed once per tile
+#define PK_REFILL(K0) ring[i & 3] = stream_operand<(K0) + i + 4>(kp, lds + v_cur, off)
+#define PK_K_ADDRESSES(STAGE) _Pragma("unroll") for (int x = 0; x < 4; ++x) kp[x] = lds + (STAGE) + off.k[x];
 // the row sums of 16 keys, next to the first of the MFMAs that take the same P
 #define PK_ROW_SUM(P) if constexpr (i % DB == 0) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[i / DB], lsum, 0, 0, 0)
 #define PK_SLICE(C, S, H, ACC, BODY)                                                          \
@@ -522,8 +504,8 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     const floatx16 zero16 = {};
     const float sc = a.scale * kLog2e;             // raw score -> exponent of two (the API admits only finite scale > 0)
 
-    // this wave's quarter of a stage, as a scalar
-    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * WAVE_PART);
+    // this wave's 16 rows of a slab, as a scalar
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * 16 * SLAB_ROWB);
     // window of tile-list entries: e0 = tile j, e1 = tile j+1, e2 = tile j+2 (e3 is fetched for the next turn)
     int e0s, e0i, e1s, e1i, e2s, e2i;
     entry(0, e0s, e0i); entry(1, e1s, e1i); entry(2, e2s, e2i);
@@ -535,8 +517,10 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     __syncthreads();
 
     bf16x8 ring[4];                                 // LDS operands of the next four MFMAs
+    const unsigned char* kp[4];
+    PK_K_ADDRESSES(0)
 #pragma unroll
-    for (int x = 0; x < 4; ++x) ring[x] = k_operand(lds, off, 0, x);
+    for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
     int k_cur = 0, k_next = TILE_BYTES, k_fill = 2 * TILE_BYTES;   // K stage read now / next / filled now
     int v_cur = 3 * TILE_BYTES, v_fill = 4 * TILE_BYTES;
     // Tile j: while S0 is computed, V(j+1) and K(j+2) are requested into the stages of V(j-1) and
@@ -572,8 +556,9 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         PK_TILE_END();
     }
     if (u.n_lead > 0) {
+        PK_K_ADDRESSES(k_cur)
 #pragma unroll
-        for (int x = 0; x < 4; ++x) ring[x] = k_operand(lds + k_cur, off, 0, x);
+        for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
     }
     for (; j < u.n_active; ++j) {
         // a tile that this wave could skip inside its active range is computed as a masked one
@@ -601,6 +586,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         for (int t = 0; t < 2; ++t)
             p1[t] = __builtin_bit_cast(bf16x8, u32x4{h1.pw[4 * t], h1.pw[4 * t + 1], h1.pw[4 * t + 2], h1.pw[4 * t + 3]});
         // phase 4; its last refills are the first operands of the next tile
+        PK_K_ADDRESSES(k_next)
         PK_EIGHT(o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p1[i / DB], o[i % DB], 0, 0, 0);
                  PK_ROW_SUM(p1); PK_REFILL(3 * KS));
         PK_TILE_END();
@@ -633,6 +619,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #undef PK_EIGHT
 #undef PK_REFILL
 #undef PK_ROW_SUM
+#undef PK_K_ADDRESSES
 #undef PK_WAIT_ALL_COPIES
 #undef PK_CODE
 
