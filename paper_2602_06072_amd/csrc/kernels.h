@@ -43,6 +43,23 @@ int launch_decode_merge_bf16(const DecodeArgs& a, void* stream);   // the LSE me
 int static_scratch_address(void** ptr);
 int launch_decode_f32(const DecodeArgs& a, void* stream);
 
+// Division of 0 <= x < 2^31 by a launch constant as a multiplication: x / d = x * mul >> (31 + shift), exact
+// because mul = ceil(2^(31 + shift) / d) with 2^shift >= d.  (A division by a kernel argument is a
+// sequence of some forty dependent instructions that every workgroup runs before it knows its work.)
+struct FastDiv {
+    uint32_t mul, shift;
+    static FastDiv by(uint32_t d) {
+        uint32_t s = 0;
+        while ((1u << s) < d) ++s;
+        return {static_cast<uint32_t>(((uint64_t{1} << (31 + s)) + d - 1) / d), s};
+    }
+#if defined(__HIPCC__)
+    __device__ __forceinline__ int operator()(int x) const {
+        return static_cast<int>(static_cast<uint64_t>(static_cast<uint32_t>(x)) * mul >> (31 + shift));
+    }
+#endif
+};
+
 struct PrefillArgs {
     const void* q; const void* k; const void* v; void* out;
     const int32_t* tiles; int32_t n_tiles;
@@ -53,6 +70,7 @@ struct PrefillArgs {
     int Hq; int Hkv; int d; float scale; int out_f32;
     int xcd_swizzle;                                // 1: place the heads of a KV head on one XCD
     int pipeline;                                   // 0: K/V tiles copied straight into LDS; 1: staged through registers
+    int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: Hq / Hkv, divisions by it and by Hkv
 };
 #if defined(__HIPCC__)
 // Row `local` (0..127) of query tile `tile`: its Q row (-1: padding) and its key range [lo, hi).

@@ -41,7 +41,7 @@ constexpr int kRun = 256;
             const int grp = x / (2 * kRun), pos = x % (2 * kRun);                                    \
             if (pos >= kRun) { /* a decode workgroup: four (work item, KV head) pairs */              \
                 const int unit = ((grp * kRun + pos - kRun) * 4) + static_cast<int>(threadIdx.x >> 6); \
-                const int item = unit / da.Hkv, kvh = unit % da.Hkv;                                 \
+                const int item = pa.by_hkv(unit), kvh = unit - item * da.Hkv;                        \
                 if (item >= da.n_items) return;                                                      \
                 if (item < da.n_wide) decode_body<D, 2, 2>(da, item, kvh);                           \
                 else decode_body<D, 1, 1>(da, item, kvh);                                            \
@@ -61,9 +61,12 @@ PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64)
 }  // namespace
 
 // bf16, d = 128 or 64.  Returns a hipError_t as int.
-int launch_mixed_step_bf16(const PrefillArgs& pa, const DecodeArgs& da, void* stream) {
+int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& da, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int r = pa.Hq / pa.Hkv;
+    PrefillArgs pa = args;
+    const int r = pa.heads_per_kv = pa.Hq / pa.Hkv;
+    pa.by_r = FastDiv::by(static_cast<uint32_t>(r));
+    pa.by_hkv = FastDiv::by(static_cast<uint32_t>(pa.Hkv));
     const int64_t pairs = static_cast<int64_t>(pa.n_tiles) * pa.Hkv;
     const int64_t n_prefill = (pairs + 7) / 8 * 8 * r;                      // as in the prefill launch (XCD map)
     const int64_t units = static_cast<int64_t>(da.n_items) * da.Hkv;

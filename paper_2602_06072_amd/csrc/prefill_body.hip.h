@@ -69,6 +69,7 @@ __device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneO
 // What a workgroup works on, and this lane's share of it.
 struct WorkUnit {
     int head, kvh, n_kv, n_lead, n_active, wave, lane, n, hlf;   // this wave computes key tiles [n_lead, n_active)
+    int rows;                          // which 32 of the tile's 128 rows this wave has
     int ks0, ks1;                      // first key rows of the tile's first two key tiles
     int qrow, lo, hi;                  // this lane's query row (-1: padding) and its key range [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
@@ -79,16 +80,14 @@ struct WorkUnit {
 // Decodes the workgroup id, loads the row metadata and the Q operand, derives the lane offsets.
 // Returns false for grid padding and for query tiles without key tiles.
 __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[KS]) {
-    const int r = a.Hq / a.Hkv;
-    int tile;
-    if (a.xcd_swizzle) {               // see prefill.hip: the r heads of a KV head stay on one XCD
-        const int x = block, c = x & 7, y = x >> 3, j = y % r, slot = y / r;
-        const int64_t p = static_cast<int64_t>(slot) * 8 + c;
-        if (p >= static_cast<int64_t>(a.n_tiles) * a.Hkv) return false;
-        tile = static_cast<int>(p / a.Hkv); u.kvh = static_cast<int>(p % a.Hkv); u.head = u.kvh * r + j;
-    } else {
-        tile = block / a.Hq; u.head = block % a.Hq; u.kvh = u.head / r;
-    }
+    // Consecutive workgroup ids go round-robin over the 8 XCDs: the r heads of one (tile, KV head) pair
+    // stay on one XCD and adjacent in time, so that its L2 serves their K/V tiles.
+    const int y = block >> 3, slot = a.by_r(y), p = slot * 8 + (block & 7);
+    const int tile = a.by_hkv(p);
+    if (tile >= a.n_tiles) return false;
+    u.kvh = p - tile * a.Hkv;
+    const int r = a.heads_per_kv;
+    u.head = u.kvh * r + (y - slot * r);
     // everything about the tile in one 64-byte scalar load, including the first key rows of its first
     // key tiles: the first K/V copies do not wait for the key-tile list
     typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
@@ -100,9 +99,13 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     const int tid = threadIdx.x;
     u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    u.n_active = u.n_kv - ((desc[3] >> (8 * u.wave)) & 0xFF);
-    u.n_lead = min((desc[2] >> (8 * u.wave)) & 0xFF, u.n_active);
-    prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.wave * 32 + u.n, u.qrow, u.lo, u.hi);
+    // Wave w of every workgroup runs on SIMD w, and the last rows of a causal tile see more key tiles than
+    // the first: every other set of 256 workgroups (a set is one per compute unit) deals the rows in
+    // reverse, so that the two workgroups of a compute unit load its SIMDs evenly.
+    u.rows = (block >> 8) & 1 ? 3 - u.wave : u.wave;
+    u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
+    u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
+    prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + u.n, u.qrow, u.lo, u.hi);
     u.row_bytes = static_cast<int64_t>(a.Hkv) * ROWB;
     u.row_bytes32 = static_cast<uint32_t>(a.Hkv) * ROWB;
     u.total_rows32 = static_cast<uint32_t>(a.total_kv_rows);
@@ -126,15 +129,12 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     }
     // Q operand: lane (n, hlf) holds Q[row n][16s + 8hlf .. +8], as it is in memory: the MFMAs
     // deliver raw scores, exact products of the bf16 inputs summed in fp32.  Only requested here;
-    // the first K/V copies follow at once, so that the two round trips to memory overlap.
+    // the first K/V copies follow at once, so that the two round trips to memory overlap.  Lanes without
+    // a query read row 0: their probabilities are 0 whatever the score (kNoRow).
     const uint16_t* qp = static_cast<const uint16_t*>(a.q) +
                          (static_cast<int64_t>(u.qrow < 0 ? 0 : u.qrow) * a.Hq + u.head) * D + 8 * u.hlf;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        u32x4 raw = {0u, 0u, 0u, 0u};
-        if (u.qrow >= 0) raw = *reinterpret_cast<const u32x4*>(qp + 16 * s);
-        qf[s] = __builtin_bit_cast(bf16x8, raw);
-    }
+    for (int s = 0; s < KS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * s));
     return true;
 }
 
@@ -179,16 +179,22 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
             *reinterpret_cast<uint2*>(wrow + (((4 * b + q4) ^ (rr & (CPR - 1))) << 4)) =
                 make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
         }
+    // all look-ups and reads before the first store: one by one, each would wait for its own LDS round trips
     const int chunk = u.lane & (CPR - 1);
+    int q_row[32 / RPI];
+    u32x4 v[32 / RPI];
 #pragma unroll
     for (int k = 0; k < 32 / RPI; ++k) {
         const int row = RPI * k + u.lane / CPR, r2 = row & 15;
-        const u32x4 v = *reinterpret_cast<const u32x4*>((row < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
-        const int qrow = __shfl(u.qrow, row, 64);
-        if (qrow >= 0)
-            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) +
-                                      (static_cast<int64_t>(qrow) * a.Hq + u.head) * D + 8 * chunk) = v;
+        q_row[k] = __shfl(u.qrow, row, 64);
+        v[k] = *reinterpret_cast<const u32x4*>((row < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
     }
+    asm volatile("" ::: "memory");                 // (the reads stay before the branches below)
+#pragma unroll
+    for (int k = 0; k < 32 / RPI; ++k)
+        if (q_row[k] >= 0)
+            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) +
+                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * D + 8 * chunk) = v[k];
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is 16 instructions of 1 KiB (four per wave; eight and
@@ -226,7 +232,7 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
         _Pragma("unroll") for (int q = 0; q < PIECES; ++q) PK_COPY_PIECE(rs_, DST, q);       \
     }
 #define PK_WAIT_ALL_COPIES() __builtin_amdgcn_s_waitcnt(0x0F70)      /* vmcnt(0) */
-#define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.wave)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
+#define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
 
 // ---------------------------------------------------------------------------------------------
 // Kernel A (default).  Two workgroups per CU (80 KiB of LDS each: three stages for K, two for V).
@@ -320,6 +326,19 @@ __device__ __forceinline__ void slice_b(const floatx2 pp, HalfSoftmax& h) {
     else if constexpr ((C & 1) == 0) h.any |= h.pw[C - 1] | h.pw[C];    // one v_or3_b32 every other slice
 }
 
+__device__ __forceinline__ float row_max(const floatx16& s) {      // both lanes of a row agree through the swap
+    float mx = max3f(max3f(max3f(max2f(s[0], s[1]), s[2], s[3]), s[4], s[5]), s[6], s[7]);
+    mx = max3f(max3f(max3f(max3f(mx, s[8], s[9]), s[10], s[11]), s[12], s[13]), s[14], s[15]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return max2f(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+}
+// A wave's first half tile: nothing has been accumulated, so the rows that see a key here take their
+// reference before the exponentials (on the slow path they would be computed twice and the 64
+// accumulators, all zero, rescaled: 0.4 us of vector work per query tile).
+__device__ __forceinline__ void first_reference(const floatx16& s, const float sc, float& m_ref) {
+    m_ref = max2f(m_ref, __builtin_fmaf(row_max(s), sc, kSlack));
+}
+
 // Slow path of a half tile (wave-uniform, rare): s holds the raw scores.  First the scalars: the
 // row maximum (both lanes of a row agree through the swap), the new reference for the rows that
 // need one, the factor alpha for what has been accumulated so far (0 for a row's first keys,
@@ -327,11 +346,7 @@ __device__ __forceinline__ void slice_b(const floatx2 pp, HalfSoftmax& h) {
 // branch of its own that holds nothing but updates in place: written as one block, the paths join
 // with the 64 accumulators in fresh registers, more than the kernel has.
 __device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const float sc, float& m_ref, float& alpha) {
-    float mx = max3f(max3f(max3f(max2f(s[0], s[1]), s[2], s[3]), s[4], s[5]), s[6], s[7]);
-    mx = max3f(max3f(max3f(max3f(mx, s[8], s[9]), s[10], s[11]), s[12], s[13]), s[14], s[15]);
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    mx = max2f(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-    const float fresh = __builtin_fmaf(mx, sc, kSlack);     // -inf for a row without a visible key here
+    const float fresh = __builtin_fmaf(row_max(s), sc, kSlack);     // -inf for a row without a visible key here
     const float next = fresh > m_ref + kRaiseBy ? fresh : m_ref;
     alpha = __builtin_amdgcn_exp2f(m_ref - next);
     m_ref = next;
@@ -374,14 +389,14 @@ __device__ __forceinline__ void pin_slice_outputs(bf16x8& next_operand, HalfSoft
     asm volatile("" : "+v"(next_operand), "+v"(h.pw[C]));
 }
 
-// -inf for the keys of half `half` of a tile that a query row may not see (outside [lo, hi_t)):
-// one unsigned comparison per score, (key - lo) < (hi_t - lo).
-__device__ __forceinline__ void mask_half(floatx16& s, int half, int lo, int hi_t, int k_start, int hlf) {
-    const uint32_t span = static_cast<uint32_t>(max(hi_t - lo, 0));
-    const uint32_t base = static_cast<uint32_t>(k_start + 4 * hlf + 32 * half - lo);
+// -inf for the keys of half `half` of a tile that a query row may not see.  A key tile lies inside the
+// keys of one request, so a row either sees it from its first key on (up to its causal limit) or, being
+// another request's, not at all: `visible` counts the tile's keys, from the first, that it sees.
+__device__ __forceinline__ void mask_half(floatx16& s, int half, int visible, int hlf) {
+    const int left = visible - 4 * hlf - 32 * half;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-        if (base + static_cast<uint32_t>(8 * (e >> 2) + (e & 3)) >= span) s[e] = -INFINITY;
+        if (left <= 8 * (e >> 2) + (e & 3)) s[e] = -INFINITY;
         asm volatile("" : "+v"(s[e]));   // ties the selects to this place, behind the caller's branch
     }
 }
@@ -562,15 +577,18 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     }
     for (; j < u.n_active; ++j) {
         // a tile that this wave could skip inside its active range is computed as a masked one
-        const bool masked = PK_CODE(e0i) != 2;
-        const int k_start = e0s;
-        const int hi_t = min(u.hi, k_start + (e0i & 0xFF));   // keys past the tile's valid count are foreign
+        const bool masked = PK_CODE(e0i) != 2, special = masked || j == u.n_lead;
+        // (keys past the tile's valid count are foreign)
+        const int visible = u.lo <= e0s ? min(u.hi - e0s, e0i & 0xFF) : 0;
         PK_TILE_BEGIN();
         floatx16 s0, s1;
         PK_EIGHT(s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s0, 0, 0, 0);
                  PK_REFILL(0); PK_COPY_STEP(i));
         HalfSoftmax h0, h1;
-        if (masked) mask_half(s0, 0, u.lo, hi_t, k_start, u.hlf);    // unmasked tiles skip the compares
+        if (special) {                              // (one branch in the common case)
+            if (masked) mask_half(s0, 0, visible, u.hlf);
+            if (j == u.n_lead) { asm volatile(""); first_reference(s0, sc, m_ref); }
+        }
         PK_SLICES(s0, h0, s1, s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s1, 0, 0, 0);
                   PK_REFILL(KS));
         PK_SOFTMAX_CHECK(s0, h0)
@@ -578,7 +596,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #pragma unroll
         for (int t = 0; t < 2; ++t)
             p0[t] = __builtin_bit_cast(bf16x8, u32x4{h0.pw[4 * t], h0.pw[4 * t + 1], h0.pw[4 * t + 2], h0.pw[4 * t + 3]});
-        if (masked) mask_half(s1, 1, u.lo, hi_t, k_start, u.hlf);
+        if (masked) mask_half(s1, 1, visible, u.hlf);
         PK_SLICES(s1, h1, o[i % DB], o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p0[i / DB], o[i % DB], 0, 0, 0);
                   PK_ROW_SUM(p0); PK_REFILL(2 * KS));
         PK_SOFTMAX_CHECK(s1, h1)

@@ -26,16 +26,15 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_dma64_kernel(PrefillArgs 
 
 }  // namespace
 
-int launch_prefill_bf16_pipe(const PrefillArgs& a, void* stream) {
-    const int r = a.Hq / a.Hkv;
-    int64_t grid;
-    if (a.xcd_swizzle) {
-        const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
-        grid = (pairs + 7) / 8 * 8 * r;
-    } else {
-        grid = static_cast<int64_t>(a.n_tiles) * a.Hq;
-    }
+int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
+    PrefillArgs a = args;
+    a.heads_per_kv = a.Hq / a.Hkv;
+    a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv));
+    a.by_hkv = FastDiv::by(static_cast<uint32_t>(a.Hkv));
+    const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
+    const int64_t grid = (pairs + 7) / 8 * 8 * a.heads_per_kv;
     if (grid == 0) return 0;
+    if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
     if (a.d == 128)
         hipLaunchKernelGGL(prefill_bf16_dma_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
                            static_cast<hipStream_t>(stream), a);
