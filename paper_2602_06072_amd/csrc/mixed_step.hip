@@ -3,12 +3,15 @@
 // step in ONE launch.  Prefill is bound by the matrix pipe, decode by HBM; side by side on a
 // compute unit they use what the other leaves idle.  The two kernels launched one after the other
 // cannot do that, and launched on two streams they hardly overlap: the prefill workgroups take
-// every register and LDS slot first.  Here the roles are dealt by workgroup number instead: while
-// decode work remains, runs of prefill workgroups alternate with runs of decode workgroups (four
-// waves, one (work item, KV head) pair each), so that each compute unit tends to hold one prefill
-// and one decode workgroup; the prefill workgroups keep their numbers modulo 8, i.e. their XCD, so
-// the heads of a KV head still share an L2.  The LSE merge of the decode partials is a
-// second, short launch.
+// every register and LDS slot first.  Here the roles are dealt by workgroup number instead: runs of
+// prefill workgroups and runs of decode workgroups (four waves, one (work item, KV head) pair each),
+// the decode runs spread evenly over the launch; the prefill workgroups keep their numbers modulo 8,
+// i.e. their XCD, so the heads of a KV head still share an L2.  The LSE merge of the decode partials
+// is a second, short launch.
+// What bounds it (32 chunks of a 70B-shaped layer + 480 decode rows, 12.52 ms): the prefill tiles alone
+// take 11.0 ms; with every decode load served by an L2 the step takes 11.5 ms, with decode items of
+// two tiles 11.05 ms.  The slots that decode workgroups take cost half a millisecond, streaming 17.9 GB
+// next to the prefill tiles the other one (2.9 ms when nothing else runs).
 #include "decode_body.hip.h"
 #define PK_D 128
 #define PK_DNS d128
@@ -24,35 +27,49 @@
 namespace pk {
 namespace {
 
-// Workgroups are handed to the compute units of an XCD one per unit before any unit gets its second:
-// a run of kRun = 8 XCDs x 32 units prefill workgroups followed by as many decode workgroups gives
-// every unit one of each (as long as both kinds last).
+// Workgroup numbers are dealt in runs of kRun of one kind (kRun a multiple of 8: every workgroup keeps
+// its XCD).  `cycles` cycles of one decode run and `stride - 1` prefill runs come first, then what is
+// left of the longer kind.  Spread over the launch, the decode runs load the memory system evenly;
+// alternating one by one until the decode work is gone they saturate it for the first quarter of the
+// launch, and the prefill tiles of that stretch wait: 12.68 -> 12.52 ms for the step above, small steps
+// unchanged.  Runs of 64 measure the same, runs of 8 13.0 ms (workgroups go to the compute units of an XCD
+// one per unit before any unit gets its second: short runs put two of a kind on one unit).
 constexpr int kRun = 256;
+
+struct MixedOrder {
+    int n_prefill, n_decode;            // workgroups of each kind
+    int cycles, stride;                 // stretch in which both kinds are dealt: cycles x stride runs
+    int rest_is_decode;                 // which kind is left behind it
+    FastDiv by_stride;
+};
+
+// run `y` of the launch: the run's number among its kind
+__device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& decode) {
+    const int c = m.by_stride(y), r = y - c * m.stride;
+    if (c >= m.cycles) {
+        decode = m.rest_is_decode != 0;
+        return y - (decode ? m.cycles * (m.stride - 1) : m.cycles);
+    }
+    decode = r == 1;                    // a prefill run first: the heaviest tiles start at once
+    return decode ? c : c * (m.stride - 1) + (r == 0 ? 0 : r - 1);
+}
 
 // one kernel per head dimension (NS: the namespace of the prefill body, D: the head dimension)
 #define PK_MIXED_STEP_KERNEL(NAME, NS, D)                                                            \
-    __global__ __launch_bounds__(256, 2) void NAME(PrefillArgs pa, DecodeArgs da, int n_prefill_blocks, \
-                                                   int n_decode_blocks) {                            \
+    __global__ __launch_bounds__(256, 2) void NAME(PrefillArgs pa, DecodeArgs da, MixedOrder m) {     \
         __shared__ __align__(1024) unsigned char lds[5 * NS::TILE_BYTES];                             \
         const int x = static_cast<int>(blockIdx.x);                                                  \
-        const int decode_groups = (n_decode_blocks + kRun - 1) / kRun;                               \
-        int prefill_block;                                                                           \
-        if (x / (2 * kRun) < decode_groups) {                                                        \
-            const int grp = x / (2 * kRun), pos = x % (2 * kRun);                                    \
-            if (pos >= kRun) { /* a decode workgroup: four (work item, KV head) pairs */              \
-                const int unit = ((grp * kRun + pos - kRun) * 4) + static_cast<int>(threadIdx.x >> 6); \
-                const int item = pa.by_hkv(unit), kvh = unit - item * da.Hkv;                        \
-                if (item >= da.n_items) return;                                                      \
-                if (item < da.n_wide) decode_body<D, 2, 2>(da, item, kvh);                           \
-                else decode_body<D, 1, 1>(da, item, kvh);                                            \
-                return;                                                                              \
-            }                                                                                        \
-            prefill_block = grp * kRun + pos;                                                        \
-        } else {                                                                                     \
-            prefill_block = x - decode_groups * kRun;                                                \
+        bool decode;                                                                                 \
+        const int block = run_of(m, x / kRun, decode) * kRun + x % kRun;                             \
+        if (decode) { /* four (work item, KV head) pairs */                                          \
+            const int unit = block * 4 + static_cast<int>(threadIdx.x >> 6);                         \
+            const int item = pa.by_hkv(unit), kvh = unit - item * da.Hkv;                            \
+            if (item >= da.n_items) return;                                                          \
+            if (item < da.n_wide) decode_body<D, 2, 2>(da, item, kvh);                               \
+            else decode_body<D, 1, 1>(da, item, kvh);                                                \
+            return;                                                                                  \
         }                                                                                            \
-        if (prefill_block >= n_prefill_blocks) return;                                               \
-        NS::prefill_tile_body(pa, prefill_block, lds);                                               \
+        if (block < m.n_prefill) NS::prefill_tile_body(pa, block, lds);                              \
     }
 PK_MIXED_STEP_KERNEL(mixed_step_kernel, d128, 128)
 PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64)
@@ -71,19 +88,21 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& da, void* 
     const int64_t n_prefill = (pairs + 7) / 8 * 8 * r;                      // as in the prefill launch (XCD map)
     const int64_t units = static_cast<int64_t>(da.n_items) * da.Hkv;
     const int64_t n_decode = (units + 3) / 4;
-    const int64_t decode_groups = (n_decode + kRun - 1) / kRun;
-    // prefill workgroups beyond the interleaved stretch follow it; if there are fewer prefill than
-    // decode groups the stretch is padded with workgroups that exit at once
-    const int64_t grid = decode_groups * 2 * kRun + (n_prefill > decode_groups * kRun ? n_prefill - decode_groups * kRun : 0);
+    const int64_t p_runs = (n_prefill + kRun - 1) / kRun, d_runs = (n_decode + kRun - 1) / kRun;
+    const int64_t grid = (p_runs + d_runs) * kRun;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
+    MixedOrder m{};
+    m.n_prefill = static_cast<int>(n_prefill); m.n_decode = static_cast<int>(n_decode);
+    m.cycles = static_cast<int>(p_runs < d_runs ? p_runs : d_runs);
+    m.stride = 1 + static_cast<int>(d_runs > 0 && p_runs > d_runs ? p_runs / d_runs : 1);
+    m.rest_is_decode = d_runs > p_runs;
+    m.by_stride = FastDiv::by(static_cast<uint32_t>(m.stride));
     if (pa.d != da.d || (pa.d != 128 && pa.d != 64)) return static_cast<int>(hipErrorInvalidValue);
     if (grid > 0) {
         if (pa.d == 128)
-            hipLaunchKernelGGL(mixed_step_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, pa, da,
-                               static_cast<int>(n_prefill), static_cast<int>(n_decode));
+            hipLaunchKernelGGL(mixed_step_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, pa, da, m);
         else
-            hipLaunchKernelGGL(mixed_step64_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, pa, da,
-                               static_cast<int>(n_prefill), static_cast<int>(n_decode));
+            hipLaunchKernelGGL(mixed_step64_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, pa, da, m);
     }
     const int e = static_cast<int>(hipGetLastError());
     if (e != 0) return e;

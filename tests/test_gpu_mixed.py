@@ -54,6 +54,16 @@ def test_mixed_step_small(case):
     H.assert_close(fus_d.cpu().numpy(), H.oracle_paged_decode(d, False), 0, f"mixed step {case}: decode half")
 
 
+@pytest.mark.parametrize("prefill, rows", [(40, 12), (33, 260), (16, 300), (9, 64)])
+def test_mixed_step_order_of_workgroups(prefill, rows):
+    """Runs of 256 workgroups: 5 prefill to 1 decode, 5 to 3 (two left over), 2 to 3 (one decode run left over),
+    2 to 1 with a remainder in both kinds."""
+    p = wl.small_ragged(seed=90, n=prefill, lo=100, hi=128, Hq=32, Hkv=8, d=64, token_budget=2048, ctx_hi=70,
+                        device=DEV, keep_f32=False)
+    d = wl.small_paged(seed=91, n=rows, lo=1, hi=120, Hq=32, Hkv=8, d=64, token_budget=2048, device=DEV, keep_f32=False)
+    run_both(p, d, p.token_budget, d.token_budget, torch.bfloat16)
+
+
 def test_mixed_step_with_an_empty_half_and_bad_arguments():
     p = wl.small_ragged(seed=82, n=3, lo=5, hi=100, Hq=4, Hkv=2, d=128, token_budget=200, device=DEV, keep_f32=False)
     d = wl.small_paged(seed=83, n=4, lo=1, hi=100, Hq=4, Hkv=2, d=128, token_budget=200, device=DEV, keep_f32=False)
