@@ -40,14 +40,21 @@ bool shape_ok(int Hq, int Hkv, int d, int dtype, std::string& why) {
 
 // Pinned host staging for the table copies.  A copy from pageable memory blocks the host until the
 // stream has drained; from pinned memory it is asynchronous, so the planning of the next batch
-// overlaps the kernels of the current one.  Buffers are recycled once the event recorded behind
-// their copy has completed; the pool only grows while every buffer is still in flight.
+// overlaps the kernels of the current one.  Buffers are recycled once the kernel that reads them has
+// stored its stamp behind them, or once the event recorded behind a copy command has completed; the
+// pool only grows while every buffer is still in flight.
 struct Staging {
     void* ptr = nullptr;
     size_t cap = 0;
-    hipEvent_t done = nullptr;
-    bool used = false;                              // an event has been recorded for it
+    uint32_t* done = nullptr;                       // pinned word behind the buffer: stamp of the last finished upload kernel
+    uint32_t stamp = 0;                             // stamp of the last upload kernel that was launched
+    hipEvent_t copied = nullptr;
+    bool used = false;                              // `copied` has been recorded for it
     bool busy = false;                              // handed out and not yet released by copy_tables
+
+    bool in_flight() const {
+        return __atomic_load_n(done, __ATOMIC_ACQUIRE) != stamp || (used && hipEventQuery(copied) != hipSuccess);
+    }
 };
 std::mutex g_staging_mutex;
 std::vector<Staging> g_staging;
@@ -56,12 +63,17 @@ std::vector<Staging> g_staging;
 Staging* staging_acquire(size_t bytes, bool may_allocate) {
     std::lock_guard<std::mutex> lock(g_staging_mutex);
     for (Staging& s : g_staging)
-        if (!s.busy && s.cap >= bytes && (!s.used || hipEventQuery(s.done) == hipSuccess)) { s.busy = true; return &s; }
+        if (!s.busy && s.cap >= bytes && !s.in_flight()) { s.busy = true; return &s; }
     if (!may_allocate || g_staging.size() >= 64) return nullptr;     // fall back to a pageable copy
     Staging s;
     s.cap = (bytes + (1u << 20) - 1) >> 20 << 20;
-    if (hipHostMalloc(&s.ptr, s.cap, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
-    if (hipEventCreateWithFlags(&s.done, hipEventDisableTiming) != hipSuccess) {
+    // coherent: the upload kernel must not meet what an L2 kept of the buffer's last contents
+    if (hipHostMalloc(&s.ptr, s.cap + 256, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError(); return nullptr;
+    }
+    s.done = reinterpret_cast<uint32_t*>(static_cast<char*>(s.ptr) + s.cap);
+    *s.done = 0;
+    if (hipEventCreateWithFlags(&s.copied, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError(); (void)hipHostFree(s.ptr); return nullptr;
     }
     s.busy = true;
@@ -70,11 +82,24 @@ Staging* staging_acquire(size_t bytes, bool may_allocate) {
     return &g_staging.back();
 }
 
-// recorded: the event behind the copy has been recorded (otherwise the buffer is free at once)
+// recorded: the event behind the copy has been recorded (otherwise only the stamp says when the buffer is free)
 void staging_release(Staging* s, bool recorded) {
     std::lock_guard<std::mutex> lock(g_staging_mutex);
     s->used = recorded;
     s->busy = false;
+}
+
+// Tables up to this size go through the upload kernel.  A bind and a small kernel, copy command against upload
+// kernel: workspace of 5 KB 16.6 / 12.1 us, 50 KB 24.3 / 12.1, 240 KB 26.5 / 13.7, 810 KB 31.9 / 35.6, 3.6 MB 57.9 / 149.
+constexpr size_t kUploadKernelBytes = 256u << 10;
+
+// A captured upload must find the same bytes at every replay: it is left to the copy command, whose buffer
+// never comes back (its event completes only outside the graph).
+bool upload_by_kernel(size_t bytes, hipStream_t st) {
+    if (bytes > kUploadKernelBytes) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return status == hipStreamCaptureStatusNone;
 }
 
 int copy_tables(void* dst, const void* src, size_t bytes, void* stream, bool may_allocate = true) {
@@ -82,6 +107,14 @@ int copy_tables(void* dst, const void* src, size_t bytes, void* stream, bool may
     Staging* s = staging_acquire(bytes, may_allocate);
     if (!s) return static_cast<int>(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
     std::memcpy(s->ptr, src, bytes);
+    if (may_allocate && upload_by_kernel(bytes, st)) {      // (the first launch of a kernel may load its code)
+        const int e = launch_upload(s->ptr, dst, static_cast<int64_t>(bytes), s->done, s->stamp + 1, stream);
+        // on an error the kernel may or may not have been queued: wait, and take the stamp that is there
+        if (e != 0) (void)hipStreamSynchronize(st);
+        s->stamp = e == 0 ? s->stamp + 1 : __atomic_load_n(s->done, __ATOMIC_ACQUIRE);
+        staging_release(s, false);
+        return e;
+    }
     hipError_t e = hipMemcpyAsync(dst, s->ptr, bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) {
         // the copy may or may not have been queued: keep the buffer out of circulation until the stream drains
@@ -89,7 +122,7 @@ int copy_tables(void* dst, const void* src, size_t bytes, void* stream, bool may
         staging_release(s, false);
         return static_cast<int>(e);
     }
-    e = hipEventRecord(s->done, st);
+    e = hipEventRecord(s->copied, st);
     if (e != hipSuccess) (void)hipStreamSynchronize(st);    // no event to wait for: drain instead
     staging_release(s, e == hipSuccess);
     return static_cast<int>(e);

@@ -6,6 +6,10 @@
 
 namespace pk {
 
+// Copies `bytes` (a multiple of 16) from pinned host memory to device memory, then stores `stamp` to the
+// pinned host word `done`.
+int launch_upload(const void* src, void* dst, int64_t bytes, uint32_t* done, uint32_t stamp, void* stream);
+
 struct ReorgArgs {
     const void* k_pages; const void* v_pages;       // [num_blocks][page][Hkv][d]
     const int32_t* block_table; int32_t max_blocks; int32_t page_size; int64_t num_blocks;
