@@ -36,75 +36,97 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
 }
 
 // out[i, h, :] = sum_j exp(lse_j - lse) o_j over the request's partial slots (consecutive).
-// Workgroup = (request, head), WAVES waves; wave w takes slots w, w + WAVES, ... four at a time
-// (all loads of a batch are issued before the first use), every lane owns D/64 columns; with
-// more than one wave the partial sums meet in LDS.  One wave is enough when no request has more
-// than a handful of partial results (short launches then end sooner).  Requests with a single
+// Workgroup = (request, 256 / D heads): a lane owns four columns of one head and a wave's load is 1 KiB of one
+// slot.  Wave w takes slots w, w + WAVES, ... in batches of kBatch, weighted against the batch's own
+// maximum (an earlier sum is rescaled), so that the partial results and their lse are requested together
+// instead of one after the other; with more than one wave the sums meet in LDS.  Requests with a single
 // work item were written by the decode kernel and are skipped.
+constexpr int kBatch = 8;
+
 template <int D, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void decode_merge_kernel(DecodeArgs a) {
-    constexpr int CPL = D / 64;                    // columns per lane
-    __shared__ float red_acc[WAVES][D];
-    __shared__ float red_tot[WAVES];
-    const int i = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int HPW = 256 / D;                   // heads per workgroup
+    __shared__ floatx4 red_acc[WAVES][64];
+    __shared__ float red_m[WAVES][64], red_tot[WAVES][64];
+    const int i = blockIdx.x, lane = threadIdx.x & 63;
+    const int wave = WAVES > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     const int p0 = a.req_part_start[i], p1 = a.req_part_start[i + 1];
     if (p1 <= p0) return;
-    const float* lse_base = a.part_lse + h;
-    float mx = -INFINITY;
-    for (int p = p0 + lane; p < p1; p += 64) mx = fmaxf(mx, lse_base[static_cast<int64_t>(p) * a.Hq]);
-    mx = wave_max(mx);
-    float acc[CPL], tot = 0.f;
+    const int h = blockIdx.y * HPW + lane * 4 / D, col = lane * 4 % D;
+    const int hr = h < a.Hq ? h : a.Hq - 1;        // (lanes beyond the last head repeat it and store nothing)
+    const float* lse_base = a.part_lse + hr;
+    const float* o_base = a.part_o + static_cast<int64_t>(hr) * D + col;
+    const int64_t o_stride = static_cast<int64_t>(a.Hq) * D;
+    float m = -INFINITY, tot = 0.f;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int p = p0 + wave; p < p1; p += kBatch * WAVES) {
+        float lse[kBatch];
+        floatx4 v[kBatch];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-    for (int p = p0 + wave; p < p1; p += 4 * WAVES) {
-        float lse[4], v[4][CPL];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
             const int q = p + WAVES * u;
             lse[u] = q < p1 ? lse_base[static_cast<int64_t>(q) * a.Hq] : -INFINITY;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
-                v[u][c] = q < p1 ? a.part_o[(static_cast<int64_t>(q) * a.Hq + h) * D + lane * CPL + c] : 0.f;
+            v[u] = q < p1 ? *reinterpret_cast<const floatx4*>(o_base + q * o_stride) : floatx4{0.f, 0.f, 0.f, 0.f};
         }
+        float m_new = m;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float w = (lse[u] == -INFINITY) ? 0.f : expf(lse[u] - mx);
+        for (int u = 0; u < kBatch; ++u) m_new = fmaxf(m_new, lse[u]);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = expf(m - m_use);
+        tot *= alpha;
+        acc *= alpha;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float w = expf(lse[u] - m_use);
             tot += w;
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[c] = fmaf(w, v[u][c], acc[c]);
+            for (int c = 0; c < 4; ++c) acc[c] = fmaf(w, v[u][c], acc[c]);
         }
+        m = m_new;
     }
     if constexpr (WAVES > 1) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) red_acc[wave][lane * CPL + c] = acc[c];
-        if (lane == 0) red_tot[wave] = tot;
+        red_acc[wave][lane] = acc;
+        red_m[wave][lane] = m;
+        red_tot[wave][lane] = tot;
         __syncthreads();
         if (wave != 0) return;
+        float mx = m;
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) mx = fmaxf(mx, red_m[w][lane]);
+        const float m_use = mx == -INFINITY ? 0.f : mx;
         tot = 0.f;
+        acc = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) tot += red_tot[w];
+        for (int w = 0; w < WAVES; ++w) {
+            const float f = expf(red_m[w][lane] - m_use);
+            tot = fmaf(f, red_tot[w][lane], tot);
+            const floatx4 x = red_acc[w][lane];
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            acc[c] = 0.f;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) acc[c] += red_acc[w][lane * CPL + c];
+            for (int c = 0; c < 4; ++c) acc[c] = fmaf(f, x[c], acc[c]);
         }
     }
+    if (h >= a.Hq) return;
     const float inv = tot > 0.f ? 1.f / tot : 0.f;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        const int col = lane * CPL + c;
-        const int64_t dst = (static_cast<int64_t>(i) * a.Hq + h) * D + col;
-        if (a.out_f32) static_cast<float*>(a.out)[dst] = acc[c] * inv;
-        else static_cast<uint16_t*>(a.out)[dst] = float_to_bf16_bits(acc[c] * inv);
-    }
+    const int64_t dst = (static_cast<int64_t>(i) * a.Hq + h) * D + col;
+    if (a.out_f32)
+        *reinterpret_cast<float4*>(static_cast<float*>(a.out) + dst) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+    else
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + dst) =
+            make_uint2(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv));
 }
+
+// One wave takes up to two batches: with 16 partial results a request, four waves that meet in LDS take as
+// long (72.7 and 72.5 us for 16 families of 8, 69.8 and 69.4 us for a tree of 128) and occupy four times the
+// wave slots.  The kernel is bound by its three dependent round trips to memory (slot range, partial results,
+// output); one column pair per lane, one head per workgroup and the maximum before the sum took
+// four: decode and merge 12.2 -> 11.4 us for four requests, 72.3 -> 69.4 us for that tree.
+constexpr int kOneWaveParts = 2 * kBatch;
 
 template <int D>
 void launch_merge(const DecodeArgs& a, hipStream_t st) {
     if (a.n > 0 && a.max_parts > 0) {
-        const dim3 mgrid(static_cast<unsigned>(a.n), static_cast<unsigned>(a.Hq));
-        if (a.max_parts <= 8) hipLaunchKernelGGL((decode_merge_kernel<D, 1>), mgrid, dim3(64), 0, st, a);
+        const dim3 mgrid(static_cast<unsigned>(a.n), static_cast<unsigned>((a.Hq + 256 / D - 1) / (256 / D)));
+        if (a.max_parts <= kOneWaveParts) hipLaunchKernelGGL((decode_merge_kernel<D, 1>), mgrid, dim3(64), 0, st, a);
         else hipLaunchKernelGGL((decode_merge_kernel<D, 4>), mgrid, dim3(256), 0, st, a);
     }
 }

@@ -132,6 +132,27 @@ def test_decode_bf16_output_and_many_members():
     assert plan.num_groups == 1
 
 
+@pytest.mark.parametrize("out_f32", [True, False])
+@pytest.mark.parametrize("heads", [(1, 1, 64), (3, 1, 64), (5, 5, 64), (1, 1, 128), (3, 3, 128), (8, 2, 128)])
+@pytest.mark.parametrize("most", [2, 8, 9, 16, 17, 33, 70])
+def test_decode_merge_of_partial_results(most, heads, out_f32):
+    """Requests of 1..`most` partial results (work items of 32 tokens): batches of eight, one wave and four; heads
+    that do not fill the merge's workgroups of 256 columns."""
+    Hq, Hkv, d = heads
+    kv = np.asarray([32 * most, 1, 32 * most - 31, 32 * (most // 2) + 1, 33], dtype=np.int32)
+    w = to_dev(wl.make_paged(f"merge{most}", kv, Hq, Hkv, d, 4096, 16, 40 + most, keep_f32=False))
+    ones = np.ones_like(kv)
+    plan = pk.pack_plan(kv, ones, None, None, 4096)
+    plan.tune(pk.TUNE_DECODE_SPLIT, 32)
+    ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
+    kv_buf = pk.new_kv_buf(plan, Hkv, d, pk.PK_BF16)
+    pk.kv_reorganize(plan, w.k_pages, w.v_pages, torch.from_numpy(w.block_table).to(DEV), kv_buf, ws)
+    out = torch.full(w.q.shape, float("nan"), dtype=torch.float32 if out_f32 else torch.bfloat16, device=DEV)
+    pk.packed_decode_attn(plan, w.q, kv_buf, out, w.scale, Hkv, ws)
+    torch.cuda.synchronize()
+    H.assert_close(out.float().cpu().numpy(), H.oracle_paged_decode(w, False), 0, f"merge of {most}, {heads}")
+
+
 # ---------------------------------------------------------------- prefill
 @pytest.mark.parametrize("use_f32", [True, False])
 @pytest.mark.parametrize("case", ["plain", "ctx", "tiny_requests", "d64", "oversize"])
