@@ -7,14 +7,21 @@
 // contiguous bytes), staged in LDS, and written out as whole contiguous tiles,
 // so both the HBM reads and the HBM writes are coalesced; the shuffle into
 // MFMA operand order happens in LDS.  HBM-bound: 2 * D * 2 bytes read and the
-// same written per token and head.
+// same written per token and head (2.52 GB in 424 us).
 #include "common.hip.h"
 #include "kernels.h"
 
 namespace pk {
 namespace {
 
-template <int D>
+template <bool KEEP>
+__device__ __forceinline__ void store_chunk(const u32x4& v, u32x4* p) {
+    if constexpr (KEEP) *p = v;
+    else __builtin_nontemporal_store(v, p);
+}
+
+// KEEP: the tiles are written through the caches in the ordinary way, not past them (keep_in_cache)
+template <int D, bool KEEP>
 __global__ __launch_bounds__(256) void reorg_bf16_kernel(ReorgArgs a) {
     constexpr int CH = D / 8;                     // 16-byte chunks per token row
     constexpr int KP = D * 2 + 16;                // LDS pitch of K rows (bytes)
@@ -66,7 +73,7 @@ __global__ __launch_bounds__(256) void reorg_bf16_kernel(ReorgArgs a) {
     for (int o = tid; o < 32 * CH; o += 256) {
         const int l = o & 63, s = (o >> 6) % (D / 32), u = o / (64 * (D / 32));
         const int tok = 16 * u + (l & 15), c = 4 * s + (l >> 4);
-        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(k_s + tok * KP + c * 16), tile + o);
+        store_chunk<KEEP>(*reinterpret_cast<const u32x4*>(k_s + tok * KP + c * 16), tile + o);
     }
     // V part: chunk (t, l)[j] = V[kappa(l/16, j)][16t + l%16]
     for (int o = tid; o < 32 * CH; o += 256) {
@@ -83,7 +90,7 @@ __global__ __launch_bounds__(256) void reorg_bf16_kernel(ReorgArgs a) {
         w[1] = e[2] | (static_cast<uint32_t>(e[3]) << 16);
         w[2] = e[4] | (static_cast<uint32_t>(e[5]) << 16);
         w[3] = e[6] | (static_cast<uint32_t>(e[7]) << 16);
-        __builtin_nontemporal_store(w, tile + 32 * CH + o);
+        store_chunk<KEEP>(w, tile + 32 * CH + o);
     }
 }
 
@@ -126,13 +133,27 @@ int launch_append_bf16(const AppendArgs& a, void* stream) {
     return static_cast<int>(hipGetLastError());
 }
 
+// Stores past the caches are the right ones for a buffer that no cache can hold, and for one so small that the
+// pages it is gathered from stay cached with it.  Between the two the 256-MiB memory-side cache takes the
+// ordinary stores in and writes them back behind the launch.  Re-layout alone / with the decode behind it,
+// past / through the caches (us): 61 MiB 22.5/41.3 and 23.7/42.7; 91 MiB 32.8/55.9 and 33.1/55.5; 122 MiB
+// 43.9/71.6 and 42.3/69.8; 184 MiB 65.5/101.7 and 61.8/95.9; 245 MiB 87.3/132.9 and 79.1/125.1; 306 MiB
+// 108/164 and 115/154; 490 MiB 173/257 and 183/260; 1.2 GiB 424 and 446 alone.
+static bool keep_in_cache(int64_t bytes) { return bytes > (int64_t{96} << 20) && bytes <= (int64_t{256} << 20); }
+
+template <int D>
+static void launch_reorg_d(const ReorgArgs& a, dim3 grid, hipStream_t st) {
+    if (keep_in_cache(a.buf_tokens * a.Hkv * D * 4)) hipLaunchKernelGGL((reorg_bf16_kernel<D, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((reorg_bf16_kernel<D, false>), grid, dim3(256), 0, st, a);
+}
+
 int launch_reorg_bf16(const ReorgArgs& a, void* stream) {
     const int64_t n_tiles = a.buf_tokens / 32;
     if (n_tiles == 0) return 0;
     dim3 grid(static_cast<unsigned>(n_tiles), static_cast<unsigned>(a.Hkv));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (a.d == 128) hipLaunchKernelGGL(reorg_bf16_kernel<128>, grid, dim3(256), 0, st, a);
-    else if (a.d == 64) hipLaunchKernelGGL(reorg_bf16_kernel<64>, grid, dim3(256), 0, st, a);
+    if (a.d == 128) launch_reorg_d<128>(a, grid, st);
+    else if (a.d == 64) launch_reorg_d<64>(a, grid, st);
     else return static_cast<int>(hipErrorInvalidValue);
     return static_cast<int>(hipGetLastError());
 }

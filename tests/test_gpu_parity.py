@@ -91,6 +91,38 @@ def test_kv_reorganize_matches_cpu_gather(use_f32, families, headroom):
                 assert np.all(raw[:, b] == 0)
 
 
+@pytest.mark.parametrize("heads", [(8, 128), (4, 64)])
+@pytest.mark.parametrize("mib, more", [(96, 0), (96, 1), (256, 0), (256, 1)])
+def test_kv_reorganize_by_size_of_the_buffer(mib, more, heads):
+    """Both sides of the sizes between which the tiles are written through the caches."""
+    Hkv, d = heads
+    tokens = (mib << 20) // (Hkv * d * 4)
+    kv = np.asarray([tokens // 2 + 5, tokens // 4 - 17, tokens // 4 - 17 + 32 * more], dtype=np.int32)
+    w = wl.make_paged("sized", kv, Hkv, Hkv, d, 1 << 24, 16, 7, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(kv, np.ones_like(kv), None, None, 1 << 24)
+    assert plan.num_groups == 1 and (plan.kv_buf_bytes(Hkv, d, pk.PK_BF16) > (mib << 20)) == bool(more)
+    ws = pk.new_workspace(plan, Hkv, Hkv, d, pk.PK_BF16)
+    buf = pk.new_kv_buf(plan, Hkv, d, pk.PK_BF16, fill=0x7F)
+    bt = torch.from_numpy(w.block_table).to(DEV)
+    pk.kv_reorganize(plan, w.k_pages, w.v_pages, bt, buf, ws)
+    nb = plan.buf_tokens // 32                      # token-major views of the two halves of every tile (layout: packinfer.h)
+    tiles = buf.view(torch.int16)[: Hkv * nb * 64 * d].view(Hkv, nb, 2, 32 * d)
+    K = tiles[:, :, 0].reshape(Hkv, nb, 2, d // 32, 4, 16, 8).permute(0, 1, 2, 5, 3, 4, 6).reshape(Hkv, nb * 32, d)
+    V = tiles[:, :, 1].reshape(Hkv, nb, d // 16, 4, 16, 2, 4).permute(0, 1, 5, 3, 6, 2, 4).reshape(Hkv, nb * 32, d)
+    seen = 0
+    for g in plan.groups():
+        for (req, _, lp, soff, lq) in g["members"]:
+            pos = torch.arange(lq, device=DEV)
+            blk = bt[req].long()[pos // 16]
+            at = g["buf_base"] + soff
+            for pages, got in ((w.k_pages, K), (w.v_pages, V)):
+                want = pages[blk, pos % 16].view(torch.int16).permute(1, 0, 2)
+                assert torch.equal(got[:, at: at + lq], want)
+            seen += lq
+    assert seen == int(kv.sum())
+    torch.cuda.synchronize()
+
+
 # ---------------------------------------------------------------- decode
 @pytest.mark.parametrize("use_f32", [True, False])
 @pytest.mark.parametrize("case", ["plain", "families", "gqa8", "mha", "d64_headroom"])
