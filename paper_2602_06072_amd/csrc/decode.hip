@@ -23,7 +23,8 @@ namespace {
 // Work items with at most 16 query rows: one column tile, tile loads double buffered.
 template <int D>
 __global__ __launch_bounds__(64) void decode_bf16_kernel(DecodeArgs a) {
-    decode_body<D, 1, 1>(a, blockIdx.x, blockIdx.y);
+    const int item = a.by_hkv(blockIdx.x), kvh = blockIdx.x - item * a.Hkv;
+    decode_body<D, 1, 1>(a, item, kvh);
 }
 
 // Batches with shared prefixes: the first n_wide work items carry 17..32 query rows (two column
@@ -31,8 +32,9 @@ __global__ __launch_bounds__(64) void decode_bf16_kernel(DecodeArgs a) {
 // the chip together; occupancy, not register prefetch, hides the load latency here.
 template <int D>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_bf16_mixed_kernel(DecodeArgs a) {
-    if (static_cast<int>(blockIdx.x) < a.n_wide) decode_body<D, 2, 2>(a, blockIdx.x, blockIdx.y);
-    else decode_body<D, 1, 2>(a, blockIdx.x, blockIdx.y);
+    const int item = a.by_hkv(blockIdx.x), kvh = blockIdx.x - item * a.Hkv;
+    if (item < a.n_wide) decode_body<D, 2, 2>(a, item, kvh);
+    else decode_body<D, 1, 2>(a, item, kvh);
 }
 
 // out[i, h, :] = sum_j exp(lse_j - lse) o_j over the request's partial slots (consecutive).
@@ -134,7 +136,13 @@ void launch_merge(const DecodeArgs& a, hipStream_t st) {
 template <int D>
 int launch_d(const DecodeArgs& a, hipStream_t st) {
     if (a.n_items > 0) {
-        dim3 grid(static_cast<unsigned>(a.n_items), static_cast<unsigned>(a.Hkv));
+        // The KV head is the fastest index.  Workgroup numbers go round-robin over the eight XCDs, so that (with
+        // eight KV heads) an XCD streams the tiles of one head, an eighth of the buffer, instead of touching
+        // all of it: 200 requests with D = 64 83.4 -> 76.2 us, a tree of 128 69.0 -> 63.1 us, 16 families of 8
+        // 72.4 -> 68.5 us, 256 requests of 32..32768 tokens 213.9 -> 205.5 us.
+        const int64_t waves = static_cast<int64_t>(a.n_items) * a.Hkv;
+        if (waves > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
+        const dim3 grid(static_cast<unsigned>(waves));
         if (a.n_wide > 0) hipLaunchKernelGGL(decode_bf16_mixed_kernel<D>, grid, dim3(64), 0, st, a);
         else hipLaunchKernelGGL(decode_bf16_kernel<D>, grid, dim3(64), 0, st, a);
     }
@@ -177,7 +185,9 @@ int launch_decode_merge_bf16(const DecodeArgs& a, void* stream) {
     return static_cast<int>(hipGetLastError());
 }
 
-int launch_decode_bf16(const DecodeArgs& a, void* stream) {
+int launch_decode_bf16(const DecodeArgs& args, void* stream) {
+    DecodeArgs a = args;
+    a.by_hkv = FastDiv::by(static_cast<uint32_t>(a.Hkv));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.d == 128) return launch_d<128>(a, st);
     if (a.d == 64) return launch_d<64>(a, st);

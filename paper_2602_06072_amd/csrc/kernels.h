@@ -28,25 +28,6 @@ struct AppendArgs {
 int launch_append_bf16(const AppendArgs& a, void* stream);
 int launch_append_f32(const AppendArgs& a, void* stream);
 
-struct DecodeArgs {
-    const void* q; const void* kv_buf; void* out;
-    const int32_t* items; int32_t n_items; int32_t n_wide;   // the first n_wide items have > 16 query rows
-    const int32_t* members; const int32_t* member_slot;
-    const int32_t* req_part_start;
-    const int32_t* req_seg;
-    const int32_t* chain_start; const int32_t* chain;   // per request: (offset, tokens) of its shared segments
-    float* part_o; float* part_lse;
-    int64_t buf_tokens; int32_t n; int Hq; int Hkv; int d; float scale; int out_f32;
-    int32_t grown;                                  // tokens appended to every suffix since the plan was made
-    int32_t max_parts;                              // most partial results of one request
-};
-int launch_decode_bf16(const DecodeArgs& a, void* stream);
-int launch_decode_merge_bf16(const DecodeArgs& a, void* stream);   // the LSE merge alone
-// Device address of the library's fixed scratch array on the current device (looked up once per
-// device); returns a hipError_t as int.
-int static_scratch_address(void** ptr);
-int launch_decode_f32(const DecodeArgs& a, void* stream);
-
 // Division of 0 <= x < 2^31 by a launch constant as a multiplication: x / d = x * mul >> (31 + shift), exact
 // because mul = ceil(2^(31 + shift) / d) with 2^shift >= d.  (A division by a kernel argument is a
 // sequence of some forty dependent instructions that every workgroup runs before it knows its work.)
@@ -63,6 +44,26 @@ struct FastDiv {
     }
 #endif
 };
+
+struct DecodeArgs {
+    const void* q; const void* kv_buf; void* out;
+    const int32_t* items; int32_t n_items; int32_t n_wide;   // the first n_wide items have > 16 query rows
+    const int32_t* members; const int32_t* member_slot;
+    const int32_t* req_part_start;
+    const int32_t* req_seg;
+    const int32_t* chain_start; const int32_t* chain;   // per request: (offset, tokens) of its shared segments
+    float* part_o; float* part_lse;
+    int64_t buf_tokens; int32_t n; int Hq; int Hkv; int d; float scale; int out_f32;
+    int32_t grown;                                  // tokens appended to every suffix since the plan was made
+    int32_t max_parts;                              // most partial results of one request
+    FastDiv by_hkv;                                 // set by the bf16 launches: division by Hkv
+};
+int launch_decode_bf16(const DecodeArgs& a, void* stream);
+int launch_decode_merge_bf16(const DecodeArgs& a, void* stream);   // the LSE merge alone
+// Device address of the library's fixed scratch array on the current device (looked up once per
+// device); returns a hipError_t as int.
+int static_scratch_address(void** ptr);
+int launch_decode_f32(const DecodeArgs& a, void* stream);
 
 struct PrefillArgs {
     const void* q; const void* k; const void* v; void* out;
