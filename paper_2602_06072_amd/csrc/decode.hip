@@ -20,20 +20,20 @@
 namespace pk {
 namespace {
 
-// Work items with at most 16 query rows: one column tile, tile loads double buffered.
+// Work items with at most 16 query rows: one column tile, two register sets (204 registers for D = 128).
 template <int D>
-__global__ __launch_bounds__(64) void decode_bf16_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_bf16_kernel(DecodeArgs a) {
     const int item = a.by_hkv(blockIdx.x), kvh = blockIdx.x - item * a.Hkv;
-    decode_body<D, 1, 1>(a, item, kvh);
+    decode_body<D, 1, 2>(a, item, kvh);
 }
 
 // Batches with shared prefixes: the first n_wide work items carry 17..32 query rows (two column
-// tiles).  Both kinds run in ONE launch so that the short prefix pass and the suffix pass fill
-// the chip together; occupancy, not register prefetch, hides the load latency here.
+// tiles) and have registers for one set.  Both kinds run in ONE launch so that the short prefix pass and
+// the suffix pass fill the chip together.
 template <int D>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_bf16_mixed_kernel(DecodeArgs a) {
     const int item = a.by_hkv(blockIdx.x), kvh = blockIdx.x - item * a.Hkv;
-    if (item < a.n_wide) decode_body<D, 2, 2>(a, item, kvh);
+    if (item < a.n_wide) decode_body<D, 2, 1>(a, item, kvh);
     else decode_body<D, 1, 2>(a, item, kvh);
 }
 
@@ -187,6 +187,8 @@ int launch_decode_merge_bf16(const DecodeArgs& a, void* stream) {
 
 int launch_decode_bf16(const DecodeArgs& args, void* stream) {
     DecodeArgs a = args;
+    a.heads_per_kv = a.Hq / a.Hkv;
+    a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv));
     a.by_hkv = FastDiv::by(static_cast<uint32_t>(a.Hkv));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (a.d == 128) return launch_d<128>(a, st);

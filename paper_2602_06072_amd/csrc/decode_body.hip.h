@@ -1,62 +1,84 @@
 // Device code of the packed decode work item (Sec. 3.2), shared by the decode kernels and by the
 // fused mixed-step kernel: one wave handles (work item, KV head).
 #pragma once
+#include <type_traits>
+
 #include "common.hip.h"
 #include "kernels.h"
 
 namespace pk {
 namespace {
 
-// PREFETCH: 0 = one tile at a time; 1 = two register sets (the loads of tile b+1 are in flight while
-// tile b is processed); 2 = one register set, rolling: the K part of tile b+1 is requested as soon as
-// the scores of tile b are done and its V part as soon as P.V of tile b is done, so that each half of
-// the next tile is in flight under the other half's arithmetic without a second set of registers
-// (for work items with two column tiles of query rows, which have no registers to spare).
-template <int D, int NT, int PREFETCH>
+constexpr int kNonTemporal = 2;                // cache policy of a buffer load
+
+// maximum over the four lane groups of 16: rows 0/1 and 2/3 change places, then the halves of the wave
+__device__ __forceinline__ float max_over_lane_groups(float x) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+// SETS: register sets for tiles.  Rolling in each: the K part of the set's next tile is requested as soon as
+// the scores of its present one are done and the V part as soon as P.V is done, so that all but one of
+// the 2 * SETS half tiles are always in flight.  Every request is unconditional (past the last tile its
+// descriptor is empty: zeros, no memory traffic): behind a condition the compiler waits for everything
+// outstanding at the next use, since it has to take the smaller count of the two paths, and tiles are
+// fetched and processed in turns.  Measured with and without the condition (and with permlane swaps for the
+// LDS look-ups of the maximum): 256 requests of 32..32768 tokens 206.0 -> 201.6 us, four requests 11.5 ->
+// 10.3, a tree of 128 63.1 -> 61.0, 16 families of 8 66.2 -> 64.9, 200 requests with D = 64 73.8 -> 73.2.
+// The first tile is requested before the look-up of the requests (the other order: 65.6 and 74.1 us).
+template <int D, int NT, int SETS>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item, const int kvh) {
     constexpr int KS = D / 32;                 // K steps per 16-key sub-tile
     constexpr int VT = D / 16;                 // V column blocks
     constexpr int NK = 2 * KS;                 // 16-byte chunks per lane of a tile's K part
-    constexpr int TILE_U4 = 2 * 32 * (D / 8);  // 16-byte chunks per tile (K part + V part)
+    constexpr int TILE_BYTES = 2 * 32 * D * 2; // K part + V part
     const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;   // (one wave per work item and KV head)
-    const int r = a.Hq / a.Hkv;
+    const int r = a.heads_per_kv;
     const int32_t* it = a.items + 8 * static_cast<int64_t>(item);
     // the last item of a suffix also covers the tokens appended since the plan was made
     const int tok_begin = it[0], tok_end = it[1] + (it[4] ? a.grown : 0), mem_first = it[2], n_mem = it[3];
     const int64_t n_tiles = a.buf_tokens / 32;
-    const u32x4* base = static_cast<const u32x4*>(a.kv_buf) + static_cast<int64_t>(kvh) * n_tiles * TILE_U4 + lane;
+    const unsigned char* base = static_cast<const unsigned char*>(a.kv_buf) + static_cast<int64_t>(kvh) * n_tiles * TILE_BYTES;
+    const int lane16 = lane * 16;              // this lane's offset into a 1-KiB piece
     const int b0 = tok_begin / 32, b1 = (tok_end + 31) / 32;
 
-    // Two register sets: the loads of tile b+1 are in flight while tile b is processed.  The
-    // first tile is requested before anything else so that it overlaps the query set-up.
-    u32x4 ka[NK], va[VT], kb_[NK], vb_[VT];
-#define PK_LOAD_TILE(KR, VR, B)                                                      \
-    {                                                                                \
-        const u32x4* tile_ = base + static_cast<int64_t>(B) * TILE_U4;               \
-        _Pragma("unroll") for (int i = 0; i < NK; ++i) KR[i] = __builtin_nontemporal_load(tile_ + i * 64);        \
-        _Pragma("unroll") for (int i = 0; i < VT; ++i) VR[i] = __builtin_nontemporal_load(tile_ + (NK + i) * 64); \
+    u32x4 k0[NK], v0[VT], k1[SETS > 1 ? NK : 1], v1[SETS > 1 ? VT : 1];
+    auto load = [&](auto& regs, int piece0, auto count, int b) {
+        const __amdgpu_buffer_rsrc_t tile = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char*>(base + static_cast<int64_t>(b) * TILE_BYTES), 0, b < b1 ? TILE_BYTES : 0, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < decltype(count)::value; ++i)
+            regs[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(tile, lane16, (piece0 + i) * 1024, kNonTemporal));
+    };
+    auto load_k = [&](auto& kr, int b) { load(kr, 0, std::integral_constant<int, NK>{}, b); };
+    auto load_v = [&](auto& vr, int b) { load(vr, NK, std::integral_constant<int, VT>{}, b); };
+    load_k(k0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(v0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // rows without a request repeat the last one (their column of the MFMAs is nobody else's) and store nothing
+    int req_of[NT], hq_of[NT], slot_of[NT];
+    bool ok[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        const int mi = a.by_r(c * 16 + n), mc = min(mi, n_mem - 1);
+        ok[c] = mi < n_mem;
+        req_of[c] = a.members[mem_first + mc];
+        slot_of[c] = a.member_slot[mem_first + mc];
+        hq_of[c] = kvh * r + (c * 16 + n) - mi * r;
     }
-    PK_LOAD_TILE(ka, va, b0);
 
     // query operand (B side): lane (n, g) holds Q[row n][32s + 8g .. +8]
     bf16x8 qf[NT][KS];
-    int req_of[NT], hq_of[NT], slot_of[NT];
 #pragma unroll
-    for (int c = 0; c < NT; ++c) {
-        const int mi = (c * 16 + n) / r;
-        const bool ok = mi < n_mem;
-        req_of[c] = ok ? a.members[mem_first + mi] : -1;
-        slot_of[c] = ok ? a.member_slot[mem_first + mi] : -1;
-        hq_of[c] = kvh * r + (c * 16 + n) % r;
+    for (int c = 0; c < NT; ++c)
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            u32x4 raw = {0u, 0u, 0u, 0u};
-            if (ok) raw = *reinterpret_cast<const u32x4*>(
-                static_cast<const uint16_t*>(a.q) +
-                (static_cast<int64_t>(req_of[c]) * a.Hq + hq_of[c]) * D + 32 * s + 8 * g);
-            qf[c][s] = __builtin_bit_cast(bf16x8, raw);
-        }
-    }
+        for (int s = 0; s < KS; ++s)
+            qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
+                static_cast<const uint16_t*>(a.q) + (static_cast<int64_t>(req_of[c]) * a.Hq + hq_of[c]) * D + 32 * s + 8 * g));
 
     floatx4 o[NT][VT];
     float m[NT], l[NT];
@@ -70,7 +92,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
 
     // scores and probabilities of tile b for column tile c: leaves P (bf16, B operand) and the
     // factor alpha for what has been accumulated so far
-    auto scores = [&](const u32x4 (&kraw)[NK], int b, int c, bf16x8& pf, float& alpha) {
+    auto scores = [&](const auto& kraw, int b, int c, bf16x8& pf, float& alpha) {
         const bool edge = (b * 32 < tok_begin) || (b * 32 + 32 > tok_end);
         floatx4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -92,8 +114,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
         float mx = x[0];
 #pragma unroll
         for (int j = 1; j < 8; ++j) mx = fmaxf(mx, x[j]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = max_over_lane_groups(mx);
         const float m_new = fmaxf(m[c], mx);
         const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
         alpha = __builtin_amdgcn_exp2f(m[c] - m_use);      // 0 on the first tile
@@ -111,7 +132,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
         m[c] = m_new;
         pf = __builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]});
     };
-    auto pv = [&](const u32x4 (&vraw)[VT], int c, const bf16x8& pf, float alpha) {
+    auto pv = [&](const auto& vraw, int c, const bf16x8& pf, float alpha) {
 #pragma unroll
         for (int t = 0; t < VT; ++t) {
             floatx4 acc = o[c][t];
@@ -119,58 +140,47 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
             o[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vraw[t]), pf, acc, 0, 0, 0);
         }
     };
-    auto process = [&](const u32x4 (&kraw)[NK], const u32x4 (&vraw)[VT], int b) {
+    // one tile, and the requests for the one that replaces it (the barriers keep them here: hoisted, they
+    // need registers of their own)
+    auto step = [&](auto& kr, auto& vr, int b, auto fetch) {
+        bf16x8 pf[NT];
+        float alpha[NT];
 #pragma unroll
-        for (int c = 0; c < NT; ++c) {
-            bf16x8 pf;
-            float alpha;
-            scores(kraw, b, c, pf, alpha);
-            pv(vraw, c, pf, alpha);
-        }
+        for (int c = 0; c < NT; ++c) scores(kr, b, c, pf[c], alpha[c]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(fetch)::value) load_k(kr, b + SETS);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < NT; ++c) pv(vr, c, pf[c], alpha[c]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(fetch)::value) load_v(vr, b + SETS);
+        __builtin_amdgcn_sched_barrier(0);
     };
-
-    if (PREFETCH == 2) {
-        for (int b = b0; b < b1; ++b) {
-            bf16x8 pf[NT];
-            float alpha[NT];
-#pragma unroll
-            for (int c = 0; c < NT; ++c) scores(ka, b, c, pf[c], alpha[c]);
-            if (b + 1 < b1) {                       // K registers are free: the next tile's K part
-                const u32x4* tile_ = base + static_cast<int64_t>(b + 1) * TILE_U4;
-#pragma unroll
-                for (int i = 0; i < NK; ++i) ka[i] = __builtin_nontemporal_load(tile_ + i * 64);
-            }
-#pragma unroll
-            for (int c = 0; c < NT; ++c) pv(va, c, pf[c], alpha[c]);
-            if (b + 1 < b1) {                       // V registers are free: the next tile's V part
-                const u32x4* tile_ = base + static_cast<int64_t>(b + 1) * TILE_U4;
-#pragma unroll
-                for (int i = 0; i < VT; ++i) va[i] = __builtin_nontemporal_load(tile_ + (NK + i) * 64);
-            }
-        }
-    } else if (PREFETCH == 1) {
-        for (int b = b0; b < b1; b += 2) {
-            if (b + 1 < b1) PK_LOAD_TILE(kb_, vb_, b + 1);
-            process(ka, va, b);
-            if (b + 1 < b1) {
-                if (b + 2 < b1) PK_LOAD_TILE(ka, va, b + 2);
-                process(kb_, vb_, b + 1);
-            }
-        }
+    // Q came last: it is waited for here, so that inside the loop only the tiles are
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SETS == 1) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0)
+        for (int b = b0; b < b1; ++b) step(k0, v0, b, std::true_type{});
     } else {
-        for (int b = b0; b < b1; ++b) {
-            if (b > b0) PK_LOAD_TILE(ka, va, b);
-            process(ka, va, b);
+        load_k(k1, b0 + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(v1, b0 + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | ((NK + VT) & 0xF) | ((NK + VT) >> 4 << 14));   // vmcnt: the second set alone
+        int b = b0;
+        for (; b + 1 < b1; b += 2) {
+            step(k0, v0, b, std::true_type{});
+            step(k1, v1, b + 1, std::true_type{});
         }
+        if (b < b1) step(k0, v0, b, std::false_type{});
     }
-#undef PK_LOAD_TILE
 
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         float lt = l[c];
         lt += __shfl_xor(lt, 16, 64);
         lt += __shfl_xor(lt, 32, 64);
-        if (req_of[c] < 0) continue;
+        if (!ok[c]) continue;
         const float inv = lt > 0.f ? 1.f / lt : 0.f;
         if (slot_of[c] < 0) {
             // the only work item of this request: write the final output

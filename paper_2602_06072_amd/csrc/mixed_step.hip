@@ -62,11 +62,11 @@ __device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& de
         bool decode;                                                                                 \
         const int block = run_of(m, x / kRun, decode) * kRun + x % kRun;                             \
         if (decode) { /* four (work item, KV head) pairs */                                          \
-            const int unit = block * 4 + static_cast<int>(threadIdx.x >> 6);                         \
+            const int unit = block * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)); \
             const int item = pa.by_hkv(unit), kvh = unit - item * da.Hkv;                            \
             if (item >= da.n_items) return;                                                          \
-            if (item < da.n_wide) decode_body<D, 2, 2>(da, item, kvh);                               \
-            else decode_body<D, 1, 1>(da, item, kvh);                                                \
+            if (item < da.n_wide) decode_body<D, 2, 1>(da, item, kvh);                               \
+            else decode_body<D, 1, 2>(da, item, kvh);                                                \
             return;                                                                                  \
         }                                                                                            \
         if (block < m.n_prefill) NS::prefill_tile_body(pa, block, lds);                              \
@@ -78,11 +78,14 @@ PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64)
 }  // namespace
 
 // bf16, d = 128 or 64.  Returns a hipError_t as int.
-int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& da, void* stream) {
+int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_args, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     PrefillArgs pa = args;
+    DecodeArgs da = decode_args;
     const int r = pa.heads_per_kv = pa.Hq / pa.Hkv;
     pa.by_r = FastDiv::by(static_cast<uint32_t>(r));
+    da.heads_per_kv = r;
+    da.by_r = pa.by_r;
     pa.by_hkv = FastDiv::by(static_cast<uint32_t>(pa.Hkv));
     const int64_t pairs = static_cast<int64_t>(pa.n_tiles) * pa.Hkv;
     const int64_t n_prefill = (pairs + 7) / 8 * 8 * r;                      // as in the prefill launch (XCD map)

@@ -185,6 +185,23 @@ def test_decode_merge_of_partial_results(most, heads, out_f32):
     H.assert_close(out.float().cpu().numpy(), H.oracle_paged_decode(w, False), 0, f"merge of {most}, {heads}")
 
 
+@pytest.mark.parametrize("heads", [(4, 4, 64), (5, 1, 64), (3, 1, 128), (16, 2, 128), (20, 1, 128)])
+@pytest.mark.parametrize("shared", [0, 1, 31, 32, 33, 64, 97])
+def test_decode_work_items_of_few_tiles(shared, heads):
+    """Work items of one to six tiles that begin and end anywhere in a tile: the register sets' first, last and odd
+    tiles, one column tile of query rows and two, rows that no request fills."""
+    Hq, Hkv, d = heads
+    own = np.asarray([1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 128, 129, 160, 161, 190], dtype=np.int32)
+    n = len(own)
+    pid = np.where(np.arange(n) % 3 < 2, 0, -1).astype(np.int32) if shared else None
+    plen = np.where(pid == 0, shared, 0).astype(np.int32) if shared else None
+    kv = own + plen if shared else own
+    w = to_dev(wl.make_paged(f"tiles{shared}", kv, Hq, Hkv, d, 4096, 16, 60 + shared, prefix_ids=pid, prefix_lens=plen,
+                             keep_f32=False))
+    got, _, _ = run_decode(w, False, headroom=3)
+    H.assert_close(got, H.oracle_paged_decode(w, False), 0, f"decode items, prefix {shared}, {heads}")
+
+
 # ---------------------------------------------------------------- prefill
 @pytest.mark.parametrize("use_f32", [True, False])
 @pytest.mark.parametrize("case", ["plain", "ctx", "tiny_requests", "d64", "oversize"])
