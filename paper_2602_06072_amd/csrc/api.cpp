@@ -96,7 +96,7 @@ constexpr size_t kUploadKernelBytes = 256u << 10;
 // A captured upload must find the same bytes at every replay: it is left to the copy command, whose buffer
 // never comes back (its event completes only outside the graph).
 bool upload_by_kernel(size_t bytes, hipStream_t st) {
-    if (bytes > kUploadKernelBytes) return false;
+    if (bytes > kUploadKernelBytes || !launch_upload) return false;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
     return status == hipStreamCaptureStatusNone;

@@ -7,8 +7,8 @@
 namespace pk {
 
 // Copies `bytes` (a multiple of 16) from pinned host memory to device memory, then stores `stamp` to the
-// pinned host word `done`.
-int launch_upload(const void* src, void* dst, int64_t bytes, uint32_t* done, uint32_t stamp, void* stream);
+// pinned host word `done`.  Weak: the host code also links without any kernels (null then), and copies by command.
+__attribute__((weak)) int launch_upload(const void* src, void* dst, int64_t bytes, uint32_t* done, uint32_t stamp, void* stream);
 
 struct ReorgArgs {
     const void* k_pages; const void* v_pages;       // [num_blocks][page][Hkv][d]
