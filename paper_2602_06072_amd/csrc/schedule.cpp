@@ -60,35 +60,39 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
 }
 
 // ---- decode ----------------------------------------------------------------
-void build_decode(const pk_plan& plan, int Hq, int Hkv, int num_cus, Builder& b, DeviceTables& t) {
+void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Builder& b, DeviceTables& t) {
     const int r = Hq / Hkv;
     const int max_members = std::max(1, kDecodeMaxRows / r);
     // split length: about 1500 waves (work items x KV heads) keep enough loads in flight to fill
-    // the memory system (each has 64 KiB outstanding); beyond that, longer items mean fewer
+    // the memory system (each has 32 KiB outstanding); beyond that, longer items mean fewer
     // partial results to write and merge
-    int64_t split = (plan.unique_tokens * Hkv / 1536 + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock;
-    split = std::min<int64_t>(std::max<int64_t>(split, 128), 2048);
+    const int64_t share = plan.unique_tokens * Hkv / 1536;
+    auto whole_blocks = [](int64_t tokens) { return (tokens + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock; };
+    int64_t split = std::min<int64_t>(std::max<int64_t>(whole_blocks(share), 128), 2048);
     {
         // All waves of the launch should be resident at once (a second, partly filled round of
-        // waves is a tail as long as a whole item): 16 waves per CU fit, 8 of the kernel that
-        // also handles 32-row items.  Short suffixes cost an item each whatever the split, so the
-        // items are counted for the candidate and the split is raised until they fit.
-        bool wide = false;
-        for (const Group& g : plan.groups)
-            for (const Node& nd : g.nodes) wide = wide || static_cast<int>(std::min<size_t>(nd.reqs.size(), max_members)) * r > 16;
-        const int64_t capacity = static_cast<int64_t>(wide ? 8 : 16) * num_cus * 9 / 10;
-        auto pieces_of = [&](int64_t len, int64_t sp) { return len <= 0 ? int64_t{0} : ((len + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock + sp - 1) / sp; };
-        auto count_items = [&](int64_t sp) {
+        // waves is a tail as long as a whole item): 8 per CU fit with the registers of head dimension
+        // 128, 16 with those of 64.  Short suffixes cost an item each whatever the split, so the items are
+        // counted for the candidate and the split is raised until they fit -- but not so far that
+        // one wave alone (20 GB/s, half of it with head dimension 64) takes longer than half the launch.
+        // 61 requests of 346..65536 tokens: 2048 tokens (3264 waves) 521 us, 4000 (1776 waves) 483 us,
+        // 8192 486 us.  Batches with too many requests to fit gain from neither (480 rows: 2048 tokens,
+        // 256 requests of 32..32768: 1632 202.8 us, 2048 200.9, 4096 204.7, 8192 224).
+        const int64_t capacity = static_cast<int64_t>(d <= 64 ? 16 : 8) * num_cus * 9 / 10;
+        auto pieces_of = [&](int64_t len, int64_t sp) { return len <= 0 ? int64_t{0} : (whole_blocks(len) + sp - 1) / sp; };
+        auto fits = [&](int64_t sp) {
             int64_t c = 0;
             for (const Group& g : plan.groups) {
                 for (const Node& nd : g.nodes)
                     c += pieces_of(nd.len, sp) * static_cast<int64_t>((nd.reqs.size() + max_members - 1) / max_members);
                 for (const Member& m : g.members) c += std::max<int64_t>(pieces_of(m.lq, sp), plan.headroom > 0 ? 1 : 0);
             }
-            return c;
+            return c * Hkv <= capacity;
         };
-        while (split < 2048 && count_items(split) * Hkv > capacity)
-            split = std::min<int64_t>(2048, (split * 5 / 4 + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock);
+        const int64_t longest = std::min<int64_t>(std::max<int64_t>(whole_blocks(share * 5 / (d <= 64 ? 4 : 2)), split), 8192);
+        int64_t raised = split;
+        while (raised < longest && !fits(raised)) raised = std::min(longest, whole_blocks(raised * 5 / 4));
+        split = raised == split || fits(raised) ? raised : std::min<int64_t>(2048, whole_blocks(split * 5 / 4));
     }
     if (plan.tune_decode_split > 0) split = plan.tune_decode_split;     // pk_plan_tune (profiling sweeps)
     split = (split + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock;
@@ -466,7 +470,7 @@ void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     t.q_start = b.add(std::vector<int32_t>(q_start.begin(), q_start.end()));
     t.kv_start = b.add(std::vector<int32_t>(kv_start.begin(), kv_start.end()));
     build_reorg(plan, b, t);
-    if (plan.decode_only) build_decode(plan, Hq, Hkv, num_cus, b, t);
+    if (plan.decode_only) build_decode(plan, Hq, Hkv, d, num_cus, b, t);
     build_prefill_packed(plan, q_start, kv_start, Hq, num_cus, b, t);
     t.host.resize((t.host.size() + 63) / 64 * 64, 0);
     t.tables_bytes = t.host.size() * sizeof(int32_t);

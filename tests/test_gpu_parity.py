@@ -166,9 +166,9 @@ def test_decode_bf16_output_and_many_members():
 
 @pytest.mark.parametrize("out_f32", [True, False])
 @pytest.mark.parametrize("heads", [(1, 1, 64), (3, 1, 64), (5, 5, 64), (1, 1, 128), (3, 3, 128), (8, 2, 128)])
-@pytest.mark.parametrize("most", [2, 8, 9, 16, 17, 33, 70])
+@pytest.mark.parametrize("most", [2, 8, 9, 16, 17, 33, 64, 65, 70, 150])
 def test_decode_merge_of_partial_results(most, heads, out_f32):
-    """Requests of 1..`most` partial results (work items of 32 tokens): batches of eight, one wave and four; heads
+    """Requests of 1..`most` partial results (work items of 32 tokens): batches of eight; one wave, four and sixteen; heads
     that do not fill the merge's workgroups of 256 columns."""
     Hq, Hkv, d = heads
     kv = np.asarray([32 * most, 1, 32 * most - 31, 32 * (most // 2) + 1, 33], dtype=np.int32)
@@ -200,6 +200,18 @@ def test_decode_work_items_of_few_tiles(shared, heads):
                              keep_f32=False))
     got, _, _ = run_decode(w, False, headroom=3)
     H.assert_close(got, H.oracle_paged_decode(w, False), 0, f"decode items, prefix {shared}, {heads}")
+
+
+@pytest.mark.parametrize("n, d, split", [(900, 128, 160), (1000, 128, 224), (1900, 128, 416), (1900, 64, 320), (3800, 64, 768)])
+def test_decode_split_that_fits_the_chip(n, d, split):
+    """The even share fits; it is raised until it does; one item per request is too many (the share and a quarter);
+    the first and the last again with head dimension 64, where twice as many waves fit."""
+    kv = np.random.default_rng(70 + n).integers(220, 251, size=n).astype(np.int32)
+    w = to_dev(wl.make_paged(f"split{n}", kv, 2, 1, d, 8192, 16, 71, keep_f32=False))
+    got, plan, _ = run_decode(w, False)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert plan.stat(5) == split
+    H.assert_close(got, H.oracle_paged_decode(w, False), 0, f"split of {n} requests")
 
 
 # ---------------------------------------------------------------- prefill
