@@ -123,13 +123,18 @@ __global__ __launch_bounds__(64 * WAVES) void decode_merge_kernel(DecodeArgs a) 
 // output); one column pair per lane, one head per workgroup and the maximum before the sum took
 // four: decode and merge 12.2 -> 11.4 us for four requests, 72.3 -> 69.4 us for that tree.
 constexpr int kOneWaveParts = 2 * kBatch;
+// Few long sequences leave hundreds of partial results to a workgroup: with sixteen waves instead of four, decode
+// and merge of 3 sequences of up to 65536 tokens and one KV head 25.7 -> 18.9 us, of 2 17.2 -> 12.6 us, of one with
+// eight KV heads 22.2 -> 21.1 us.
+constexpr int kFourWaveParts = 2 * 4 * kBatch;
 
 template <int D>
 void launch_merge(const DecodeArgs& a, hipStream_t st) {
     if (a.n > 0 && a.max_parts > 0) {
         const dim3 mgrid(static_cast<unsigned>(a.n), static_cast<unsigned>((a.Hq + 256 / D - 1) / (256 / D)));
         if (a.max_parts <= kOneWaveParts) hipLaunchKernelGGL((decode_merge_kernel<D, 1>), mgrid, dim3(64), 0, st, a);
-        else hipLaunchKernelGGL((decode_merge_kernel<D, 4>), mgrid, dim3(256), 0, st, a);
+        else if (a.max_parts <= kFourWaveParts) hipLaunchKernelGGL((decode_merge_kernel<D, 4>), mgrid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((decode_merge_kernel<D, 16>), mgrid, dim3(1024), 0, st, a);
     }
 }
 
