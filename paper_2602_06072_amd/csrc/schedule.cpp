@@ -98,14 +98,14 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
     split = (split + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock;
     t.dec_split_tokens = static_cast<int32_t>(split);
 
-    struct Item { int64_t a, e; std::vector<int32_t> reqs; bool grows = false; };
+    struct Item { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool grows; };   // (reqs point into the plan)
     std::vector<Item> items;
     // suffix: the segment is a request's private suffix; its last item is marked so that the
     // kernel extends it by the tokens appended into the headroom since the plan was made (an
     // empty suffix with headroom still gets an item for them)
-    auto add_segment = [&](int64_t a, int64_t e, const std::vector<int32_t>& reqs, bool suffix) {
+    auto add_segment = [&](int64_t a, int64_t e, const int32_t* reqs, int32_t n_reqs, bool suffix) {
         if (e <= a) {
-            if (suffix && plan.headroom > 0) { items.push_back({a, a, reqs}); items.back().grows = true; }
+            if (suffix && plan.headroom > 0) items.push_back({a, a, reqs, n_reqs, true});
             return;
         }
         // the fewest pieces of at most `split` tokens, all of (nearly) the same length: a full-length
@@ -114,32 +114,29 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
         const int64_t blocks = (e - a_blk + kDecodeBlock - 1) / kDecodeBlock;
         const int64_t pieces = (blocks * kDecodeBlock + split - 1) / split;
         const int64_t piece = (blocks + pieces - 1) / pieces * kDecodeBlock;
-        for (size_t m0 = 0; m0 < reqs.size(); m0 += max_members) {
-            std::vector<int32_t> chunk(reqs.begin() + m0,
-                                       reqs.begin() + std::min(reqs.size(), m0 + max_members));
-            for (int64_t p0 = a_blk; p0 < e; p0 += piece) {
-                items.push_back({std::max(a, p0), std::min(e, p0 + piece), chunk});
-                items.back().grows = suffix && p0 + piece >= e;
-            }
-        }
+        for (int32_t m0 = 0; m0 < n_reqs; m0 += max_members)
+            for (int64_t p0 = a_blk; p0 < e; p0 += piece)
+                items.push_back({std::max(a, p0), std::min(e, p0 + piece), reqs + m0, std::min(n_reqs - m0, max_members),
+                                 suffix && p0 + piece >= e});
     };
     std::vector<int32_t> req_seg(static_cast<size_t>(plan.n) * 4, 0);
     std::vector<std::vector<int32_t>> chain_of(static_cast<size_t>(plan.n));
+    struct Piece { int32_t off; int32_t node, member; };
+    std::vector<Piece> pieces;
     for (const Group& g : plan.groups) {
         // work items in layout order: a shared segment attends for every request below it
-        struct Piece { int32_t off; int32_t node, member; };
-        std::vector<Piece> pieces;
+        pieces.clear();
         for (size_t k = 0; k < g.nodes.size(); ++k) pieces.push_back({g.nodes[k].off, static_cast<int32_t>(k), -1});
         for (size_t k = 0; k < g.members.size(); ++k) pieces.push_back({g.members[k].suffix_off, -1, static_cast<int32_t>(k)});
         std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.off < y.off; });
         for (const Piece& pc : pieces) {
             if (pc.node >= 0) {
                 const Node& nd = g.nodes[static_cast<size_t>(pc.node)];
-                add_segment(g.buf_base + nd.off, g.buf_base + nd.off + nd.len, nd.reqs, false);
+                add_segment(g.buf_base + nd.off, g.buf_base + nd.off + nd.len, nd.reqs.data(), static_cast<int32_t>(nd.reqs.size()), false);
                 continue;
             }
             const Member& mm = g.members[static_cast<size_t>(pc.member)];
-            add_segment(g.buf_base + mm.suffix_off, g.buf_base + mm.suffix_off + mm.lq, {mm.req}, true);
+            add_segment(g.buf_base + mm.suffix_off, g.buf_base + mm.suffix_off + mm.lq, &mm.req, 1, true);
             int32_t* rs = &req_seg[static_cast<size_t>(mm.req) * 4];
             rs[0] = static_cast<int32_t>(g.buf_base + mm.prefix_off); rs[1] = mm.lp;
             rs[2] = static_cast<int32_t>(g.buf_base + mm.suffix_off); rs[3] = mm.lq;
@@ -158,7 +155,7 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
     }
     // items with more than 16 query rows first (they run the two-column-tile kernel), then
     // the others; inside each class the longest first (stable: deterministic)
-    auto wide = [&](const Item& it) { return static_cast<int>(it.reqs.size()) * r > 16; };
+    auto wide = [&](const Item& it) { return it.n_reqs * r > 16; };
     std::vector<int32_t> order(items.size());
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
@@ -172,7 +169,7 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
     // final output itself (slot -1).
     std::vector<int32_t> n_items_of(static_cast<size_t>(plan.n), 0), start(static_cast<size_t>(plan.n) + 1, 0);
     for (const Item& it : items)
-        for (int32_t rq : it.reqs) ++n_items_of[static_cast<size_t>(rq)];
+        for (int32_t x = 0; x < it.n_reqs; ++x) ++n_items_of[static_cast<size_t>(it.reqs[x])];
     int32_t n_parts = 0;
     for (int32_t i = 0; i < plan.n; ++i) {
         start[static_cast<size_t>(i)] = n_parts;
@@ -181,14 +178,16 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
     start[static_cast<size_t>(plan.n)] = n_parts;
     std::vector<int32_t> next_slot(start.begin(), start.end() - 1);
     std::vector<int32_t> flat, members, member_slot;
+    flat.reserve(items.size() * 8);
     for (int32_t idx : order) {
         const Item& it = items[idx];
         flat.push_back(static_cast<int32_t>(it.a));
         flat.push_back(static_cast<int32_t>(it.e));
         flat.push_back(static_cast<int32_t>(members.size()));
-        flat.push_back(static_cast<int32_t>(it.reqs.size()));
+        flat.push_back(it.n_reqs);
         flat.push_back(it.grows ? 1 : 0); flat.push_back(0); flat.push_back(0); flat.push_back(0);
-        for (int32_t rq : it.reqs) {
+        for (int32_t x = 0; x < it.n_reqs; ++x) {
+            const int32_t rq = it.reqs[x];
             members.push_back(rq);
             member_slot.push_back(n_items_of[static_cast<size_t>(rq)] > 1 ? next_slot[static_cast<size_t>(rq)]++ : -1);
         }
@@ -207,7 +206,7 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
 }
 
 // ---- prefill ---------------------------------------------------------------
-struct QRow { int32_t req, t; };       // packed row -> (request, query position)
+struct RowRun { int32_t begin, count, req, t; };   // tile rows [begin, begin + count) are request req's query rows t, t + 1, ...
 
 // Flat arrays of a schedule under construction (tiles in construction order).
 struct SchedBuild {
@@ -219,32 +218,32 @@ struct SchedBuild {
     int64_t issued = 0;
 };
 
-// Appends one query tile (rows[0..nrows)) and its key-tile list.  all_waves: the padded
+// Appends one query tile (the runs cover rows 0..nrows) and its key-tile list.  all_waves: the padded
 // schedule never lets a wave skip.
 void add_tile(const pk_plan& plan, const std::vector<int64_t>& q_start,
-              const std::vector<int64_t>& kv_start, const QRow* rows, int nrows,
+              const std::vector<int64_t>& kv_start, const std::vector<RowRun>& tile_runs,
               bool all_waves, SchedBuild& sb) {
     constexpr int BM = kPrefillBM, BN = kPrefillBN, WR = 32, NW = BM / WR;
     sb.run_first.push_back(static_cast<int32_t>(sb.runs.size() / 4));
     const size_t kv0 = sb.kv.size();
+    const int nrows = tile_runs.back().begin + tile_runs.back().count;
     int64_t weight = 0;
-    int i = 0;
-    while (i < nrows) {                            // runs of rows of the same request
-        const int32_t rq = rows[i].req;
-        int j = i + 1;
-        while (j < nrows && rows[j].req == rq) ++j;
+    for (const RowRun& run : tile_runs) {
+        const int32_t rq = run.req;
+        const int i = run.begin, j = run.begin + run.count;
         const int64_t ks0 = kv_start[rq];
         const int64_t ctx = plan.kv_lens[rq] - plan.q_lens[rq];
-        const int64_t kend = ks0 + ctx + rows[j - 1].t + 1;              // hi of the run's last row
+        const int64_t hi0 = ks0 + ctx + run.t + 1;                       // hi of the run's first row
+        const int64_t kend = hi0 + run.count - 1;                        // and of its last
         // row x of the run is Q row q_start + t + (x - i) and sees the keys [ks0, ks0 + ctx + t + 1 + (x - i))
-        sb.runs.push_back(i);
-        sb.runs.push_back(static_cast<int32_t>(q_start[rq] + rows[i].t));
-        sb.runs.push_back(static_cast<int32_t>(ks0));
-        sb.runs.push_back(static_cast<int32_t>(ks0 + ctx + rows[i].t + 1));
-        // per wave: its rows inside the run, and whether it holds rows of no other request
+        const int32_t entry[4] = {i, static_cast<int32_t>(q_start[rq] + run.t), static_cast<int32_t>(ks0), static_cast<int32_t>(hi0)};
+        sb.runs.insert(sb.runs.end(), entry, entry + 4);
+        // per wave: its rows inside the run, and whether it holds rows of no other request (waves without rows
+        // of the run take no part in its key tiles)
+        const int w_first = all_waves ? 0 : i / WR, w_end = all_waves ? NW : (j - 1) / WR + 1;
         int wa[NW], wb[NW];
         bool pure[NW];
-        for (int w = 0; w < NW; ++w) {
+        for (int w = w_first; w < w_end; ++w) {
             wa[w] = std::max(i, w * WR);
             wb[w] = std::min(j, (w + 1) * WR);
             pure[w] = i <= w * WR && std::min(nrows, (w + 1) * WR) <= j;
@@ -252,10 +251,10 @@ void add_tile(const pk_plan& plan, const std::vector<int64_t>& q_start,
         for (int64_t ks = ks0; ks < kend; ks += BN) {
             const int64_t ke = std::min(kend, ks + BN);
             int32_t flags = 0;
-            for (int w = 0; w < NW; ++w) {
+            for (int w = w_first; w < w_end; ++w) {
                 int code = 0;
-                if (wa[w] < wb[w] && ks < ks0 + ctx + rows[wb[w] - 1].t + 1) {
-                    const bool below = ke <= ks0 + ctx + rows[wa[w]].t + 1;
+                if (wa[w] < wb[w] && ks < hi0 + (wb[w] - 1 - i)) {
+                    const bool below = ke <= hi0 + (wa[w] - i);
                     code = (pure[w] && below && ke - ks == BN) ? 2 : 1;
                 } else if (all_waves) {
                     code = 1;
@@ -267,7 +266,6 @@ void add_tile(const pk_plan& plan, const std::vector<int64_t>& q_start,
             sb.kv.push_back(static_cast<int32_t>(ks));
             sb.kv.push_back(static_cast<int32_t>(ke - ks) | (flags << 8));
         }
-        i = j;
     }
     sb.issued += weight * WR * BN;
     sb.kv_first.push_back(static_cast<int32_t>(kv0 / 2));
@@ -347,39 +345,36 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     for (int32_t i = 0; i < plan.n; ++i) aligned_tiles += (plan.q_lens[i] + BM - 1) / BM;
     const bool may_share = aligned_tiles * Hq > 2 * static_cast<int64_t>(num_cus);
     SchedBuild sb;
-    std::vector<QRow> rows;
+    std::vector<RowRun> runs;                      // of the tile that is open
+    int32_t filled = 0;                            // its rows
     std::vector<int32_t> tile_req;                 // request of a tile's first row
-    rows.reserve(BM);
+    auto close_tile = [&] {
+        tile_req.push_back(runs[0].req);
+        add_tile(plan, q_start, kv_start, runs, false, sb);
+        runs.clear();
+        filled = 0;
+    };
     for (const Group& g : plan.groups) {
-        rows.clear();
         for (const Member& m : g.members) {
             // A request that does not fit into what is left of the current tile shares it only if
             // that saves the request a tile of its own (its head then rides along with few key
             // tiles); otherwise the tile is closed and the request starts on a fresh one: a shared
             // tile walks the key tiles of both requests one after the other and runs them masked.
             const int32_t lq = plan.q_lens[m.req];
-            const int32_t room = BM - static_cast<int32_t>(rows.size());
-            if (!rows.empty() && (lq > room || !may_share)) {
+            const int32_t room = BM - filled;
+            if (filled > 0 && (lq > room || !may_share)) {
                 const int32_t last = lq % BM == 0 ? BM : lq % BM;   // rows of its last tile when it starts fresh
-                if (room < last || !may_share) {
-                    tile_req.push_back(rows[0].req);
-                    add_tile(plan, q_start, kv_start, rows.data(), static_cast<int>(rows.size()), false, sb);
-                    rows.clear();
-                }
+                if (room < last || !may_share) close_tile();
             }
-            for (int32_t x = 0; x < plan.q_lens[m.req]; ++x) {
-                rows.push_back({m.req, x});
-                if (rows.size() == BM) {
-                    tile_req.push_back(rows[0].req);
-                    add_tile(plan, q_start, kv_start, rows.data(), BM, false, sb);
-                    rows.clear();
-                }
+            for (int32_t x = 0; x < lq;) {
+                const int32_t take = std::min(BM - filled, lq - x);
+                runs.push_back({filled, take, m.req, x});
+                filled += take;
+                x += take;
+                if (filled == BM) close_tile();
             }
         }
-        if (!rows.empty()) {
-            tile_req.push_back(rows[0].req);
-            add_tile(plan, q_start, kv_start, rows.data(), static_cast<int>(rows.size()), false, sb);
-        }
+        if (filled > 0) close_tile();
     }
     std::vector<int32_t> order(sb.n_kv.size());
     std::iota(order.begin(), order.end(), 0);
@@ -416,13 +411,11 @@ void build_prefill_padded(const pk_plan& plan, DeviceTables& t) {
     int32_t max_tiles = 0;
     for (int32_t i = 0; i < plan.n; ++i) max_tiles = std::max(max_tiles, (plan.q_lens[i] + BM - 1) / BM);
     SchedBuild sb;
-    std::vector<QRow> rows;
     for (int32_t i = 0; i < plan.n; ++i) {
         for (int32_t tt = 0; tt < max_tiles; ++tt) {
-            rows.clear();
-            for (int32_t x = tt * BM; x < std::min(plan.q_lens[i], (tt + 1) * BM); ++x) rows.push_back({i, x});
-            if (rows.empty()) add_idle_tile(sb);
-            else add_tile(plan, q_start, kv_start, rows.data(), static_cast<int>(rows.size()), true, sb);
+            const int32_t rows = std::min(plan.q_lens[i] - tt * BM, BM);
+            if (rows <= 0) add_idle_tile(sb);
+            else add_tile(plan, q_start, kv_start, {{0, rows, i, tt * BM}}, true, sb);
         }
     }
     std::vector<int32_t> order(sb.n_kv.size());
