@@ -75,7 +75,8 @@ struct PrefillArgs {
     int Hq; int Hkv; int d; float scale; int out_f32;
     int xcd_swizzle;                                // 1: place the heads of a KV head on one XCD
     int pipeline;                                   // 0: K/V tiles copied straight into LDS; 1: staged through registers
-    int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: Hq / Hkv, divisions by it and by Hkv
+    int64_t n_key_tiles;                            // entries of kvtiles
+    int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: workgroups per (query tile, KV head), divisions by it and by Hkv
 };
 #if defined(__HIPCC__)
 // Row `local` (0..127) of query tile `tile`: its Q row (-1: padding) and its key range [lo, hi).

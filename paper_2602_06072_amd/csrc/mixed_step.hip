@@ -13,6 +13,7 @@
 // two tiles 11.05 ms.  The slots that decode workgroups take cost half a millisecond, streaming 17.9 GB
 // next to the prefill tiles the other one (2.9 ms when nothing else runs).
 #include "decode_body.hip.h"
+#define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
 #include "prefill_body.hip.h"
@@ -23,6 +24,7 @@
 #include "prefill_body.hip.h"
 #undef PK_D
 #undef PK_DNS
+#undef PK_WAVES
 
 namespace pk {
 namespace {

@@ -13,8 +13,9 @@
 //   * copies are requested one tile ahead for V and two for K; one barrier per tile.
 
 // Device code only: included by prefill_pipe.hip (the prefill launch) and by mixed_step.hip (the
-// fused prefill + decode launch).  The includer defines PK_D (the head dimension) and PK_DNS (the
-// namespace this instance goes into) first; the file may be included once per head dimension.
+// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4, or 8 for two
+// query heads of a KV head per workgroup) and PK_DNS (the namespace this instance goes into) first; the
+// file may be included once per combination.
 // With PK_D = 64 a tile is 8 KiB (two 1-KiB copy instructions per wave) and a
 // half tile four MFMAs instead of eight, each followed by two softmax slices instead of one.
 #include <cstdint>
@@ -22,8 +23,8 @@
 #include "common.hip.h"
 #include "kernels.h"
 
-#if !defined(PK_D) || !defined(PK_DNS) || (PK_D != 128 && PK_D != 64)
-#error "define PK_D (128 or 64) and PK_DNS before including prefill_body.hip.h"
+#if !defined(PK_D) || !defined(PK_DNS) || !defined(PK_WAVES) || (PK_D != 128 && PK_D != 64) || (PK_WAVES != 4 && PK_WAVES != 8)
+#error "define PK_D (128 or 64), PK_WAVES (4 or 8) and PK_DNS before including prefill_body.hip.h"
 #endif
 
 namespace pk {
@@ -34,8 +35,10 @@ constexpr int BM = 128, BN = 64, D = PK_D;
 constexpr int ROWB = D * 2;                        // bytes per K/V row in global memory
 constexpr int TILE_BYTES = BN * ROWB;              // 16 KiB (8 KiB for D = 64)
 constexpr int KS = D / 16, DB = D / 32;
-constexpr int PIECES = TILE_BYTES / 4096;          // 1-KiB copy instructions per wave and tile
-constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that one wave fills
+constexpr int WAVES = PK_WAVES;
+constexpr int PIECES = TILE_BYTES / (1024 * WAVES);   // 1-KiB copy instructions per wave and tile
+constexpr int RPW = BN / WAVES, PPS = RPW / 8;        // rows (and copies) of a slab that one wave fills
+constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that take half of a wave's output
 
 // A stage in LDS is one slab per 64 columns: 64 rows of 128 bytes (eight 16-byte chunks).  Whatever
 // the head dimension, four K and four V addresses per lane then reach every operand with constant
@@ -80,14 +83,14 @@ struct WorkUnit {
 // Decodes the workgroup id, loads the row metadata and the Q operand, derives the lane offsets.
 // Returns false for grid padding and for query tiles without key tiles.
 __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[KS]) {
-    // Consecutive workgroup ids go round-robin over the 8 XCDs: the r heads of one (tile, KV head) pair
-    // stay on one XCD and adjacent in time, so that its L2 serves their K/V tiles.
+    // Consecutive workgroup ids go round-robin over the 8 XCDs: the workgroups of one (tile, KV head) pair
+    // (r of them with one head each, or r / 2 with two) stay on one XCD and adjacent in time, so that its L2
+    // serves their K/V tiles.
     const int y = block >> 3, slot = a.by_r(y), p = slot * 8 + (block & 7);
     const int tile = a.by_hkv(p);
     if (tile >= a.n_tiles) return false;
     u.kvh = p - tile * a.Hkv;
-    const int r = a.heads_per_kv;
-    u.head = u.kvh * r + (y - slot * r);
+    const int groups = a.heads_per_kv, pair = y - slot * groups;
     // everything about the tile in one 64-byte scalar load, including the first key rows of its first
     // key tiles: the first K/V copies do not wait for the key-tile list
     typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
@@ -99,10 +102,12 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     const int tid = threadIdx.x;
     u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Wave w of every workgroup runs on SIMD w, and the last rows of a causal tile see more key tiles than
-    // the first: every other set of 256 workgroups (a set is one per compute unit) deals the rows in
-    // reverse, so that the two workgroups of a compute unit load its SIMDs evenly.
-    u.rows = (block >> 8) & 1 ? 3 - u.wave : u.wave;
+    // Wave w of every workgroup runs on SIMD w % 4, and the last rows of a causal tile see more key tiles than
+    // the first: the second head, or every other set of 256 workgroups (a set is one per compute unit), deals
+    // the rows in reverse, so that the two waves of a SIMD get as much together as those of any other.
+    const int w4 = u.wave & 3, second = WAVES > 4 ? u.wave >> 2 : 0;
+    u.head = (u.kvh * groups + pair) * (WAVES / 4) + second;
+    u.rows = (WAVES > 4 ? second : (block >> 8) & 1) ? 3 - w4 : w4;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
     prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + u.n, u.qrow, u.lo, u.hi);
@@ -124,8 +129,8 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     const int r_in = u.lane >> 3, pos = u.lane & 7;    // a copy instruction takes 8 rows of 8 chunks
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) {
-        const int row = 16 * u.wave + 8 * (q & 1) + r_in;
-        off.g[q] = static_cast<int>(row * u.row_bytes + u.kvh * ROWB + (q >> 1) * SLAB_ROWB + ((pos ^ swz(row)) << 4));
+        const int row = RPW * u.wave + 8 * (q % PPS) + r_in;
+        off.g[q] = static_cast<int>(row * u.row_bytes + u.kvh * ROWB + (q / PPS) * SLAB_ROWB + ((pos ^ swz(row)) << 4));
     }
     // Q operand: lane (n, hlf) holds Q[row n][16s + 8hlf .. +8], as it is in memory: the MFMAs
     // deliver raw scores, exact products of the bf16 inputs summed in fp32.  Only requested here;
@@ -225,7 +230,7 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
         RS[3] = 0x00020000u;                                                                 \
     }
 // this wave's piece Q (0..3) of a tile into the stage at byte offset DST
-#define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) >> 1) * SLAB + ((Q) & 1) * 1024, off.g[Q])
+#define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) / PPS) * SLAB + ((Q) % PPS) * 1024, off.g[Q])
 #define PK_COPY_TILE(SRC, KSTART, DST, ENABLED)                                              \
     {                                                                                        \
         PK_TILE_DESC(rs_, SRC, KSTART, ENABLED)                                              \
@@ -520,7 +525,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     const float sc = a.scale * kLog2e;             // raw score -> exponent of two (the API admits only finite scale > 0)
 
     // this wave's 16 rows of a slab, as a scalar
-    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * 16 * SLAB_ROWB);
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * RPW * SLAB_ROWB);
     // window of tile-list entries: e0 = tile j, e1 = tile j+1, e2 = tile j+2 (e3 is fetched for the next turn)
     int e0s, e0i, e1s, e1i, e2s, e2i;
     entry(0, e0s, e0i); entry(1, e1s, e1i); entry(2, e2s, e2i);
@@ -544,12 +549,15 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // compiler's own barrier would also wait for the LDS reads) says that every wave is done with
     // tile j and that V(j+1) and K(j+2) are complete; K(j+1), whose first operands are read during
     // the last MFMAs of tile j, was published a tile earlier.
+    // Two heads per workgroup: the wave of a SIMD that has vector work to do goes first, the one in a phase of
+    // nothing but MFMAs fills in (70B-shaped chunks 11.03 -> 10.87 ms; with four waves 1 % at most).
+#define PK_PRIO(P) if constexpr (WAVES > 4) __builtin_amdgcn_s_setprio(P)
 #define PK_TILE_BEGIN()                                                                       \
     PK_TILE_DESC(rs_k, a.k, e2s, j + 2 < n_kv)                                                 \
     PK_TILE_DESC(rs_v, a.v, e1s, j + 1 < n_kv)
 #define PK_COPY_STEP(I)                                                                       \
     if constexpr ((I) < PIECES) PK_COPY_PIECE(rs_k, k_fill, (I));                              \
-    else PK_COPY_PIECE(rs_v, v_fill, (I) - PIECES);
+    else if constexpr ((I) < 2 * PIECES) PK_COPY_PIECE(rs_v, v_fill, (I) - PIECES);
     // (the next list entry is fetched right before the barrier: scalar loads and LDS reads share a
     // counter and return out of order, so the first wait after the fetch drains the operand ring;
     // here the ring has the whole barrier to land anyway)
@@ -582,9 +590,11 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         const int visible = u.lo <= e0s ? min(u.hi - e0s, e0i & 0xFF) : 0;
         PK_TILE_BEGIN();
         floatx16 s0, s1;
+        PK_PRIO(0);
         PK_EIGHT(s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s0, 0, 0, 0);
                  PK_REFILL(0); PK_COPY_STEP(i));
         HalfSoftmax h0, h1;
+        PK_PRIO(1);
         if (special) {                              // (one branch in the common case)
             if (masked) mask_half(s0, 0, visible, u.hlf);
             if (j == u.n_lead) { asm volatile(""); first_reference(s0, sc, m_ref); }
@@ -605,6 +615,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
             p1[t] = __builtin_bit_cast(bf16x8, u32x4{h1.pw[4 * t], h1.pw[4 * t + 1], h1.pw[4 * t + 2], h1.pw[4 * t + 3]});
         // phase 4; its last refills are the first operands of the next tile
         PK_K_ADDRESSES(k_next)
+        PK_PRIO(0);
         PK_EIGHT(o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p1[i / DB], o[i % DB], 0, 0, 0);
                  PK_ROW_SUM(p1); PK_REFILL(3 * KS));
         PK_TILE_END();
@@ -616,15 +627,16 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); }
         PK_TILE_END();
     }
-    // After the last barrier nobody reads or fills the two stages that would have taken tiles
-    // n_kv and n_kv + 1 (after the final rotation: k_next and v_cur), and a wave's copies only
-    // ever touch its own quarter of a stage: those two quarters stage this wave's output.
+    // After the last barrier nobody fills a stage any more, and what is still being read for a tile after
+    // the last is not used: quarters of two K and V stages per head stage the waves' output.
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
     if (a.out_f32) store_output(a, u, o, lsum[0]);
-    else store_output_bf16(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
+    else store_output_bf16(a, u, o, lsum[0], lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART,
+                           lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
 }
 
 #undef PK_COPY_TILE
+#undef PK_PRIO
 #undef PK_TILE_DESC
 #undef PK_COPY_PIECE
 #undef PK_COPY_STEP

@@ -1,5 +1,6 @@
 // Packed prefill attention, bf16 MFMA, head dimensions 128 and 64 (Sec. 3.1): the launches.  The
 // kernels' device code is in prefill_body.hip.h, included once per head dimension.
+#define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
 #include "prefill_body.hip.h"
@@ -11,8 +12,24 @@
 #undef PK_D
 #undef PK_DNS
 
+#undef PK_WAVES
+#define PK_WAVES 8
+#define PK_D 128
+#define PK_DNS d128x2
+#include "prefill_body.hip.h"
+#undef PK_D
+#undef PK_DNS
+#undef PK_WAVES
+
 namespace pk {
 namespace {
+
+// Two query heads of a KV head per workgroup: they work on the same K/V tiles, which are copied into LDS once
+// for both.
+__global__ __launch_bounds__(512, 2) void prefill_bf16_pair_kernel(PrefillArgs a) {
+    __shared__ __align__(1024) unsigned char lds[5 * d128x2::TILE_BYTES];
+    d128x2::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
+}
 
 __global__ __launch_bounds__(256, 2) void prefill_bf16_dma_kernel(PrefillArgs a) {
     __shared__ __align__(1024) unsigned char lds[5 * d128::TILE_BYTES];
@@ -31,11 +48,27 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     a.heads_per_kv = a.Hq / a.Hkv;
     a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv));
     a.by_hkv = FastDiv::by(static_cast<uint32_t>(a.Hkv));
+    // Copying each K/V tile once for two heads halves the copies (a tile step of two four-wave workgroups on a
+    // compute unit reads 256 KiB of LDS and writes 64; the LDS delivers about 128 bytes a cycle, as many
+    // as the matrix pipes ask for at full rate).  What it costs: nothing runs beside a workgroup's first loads
+    // and last stores, and a chip that is not full has fewer compute units at work.  Four / eight waves:
+    //   32 chunks of a 70B-shaped layer (126 key tiles on average)  11.12 / 10.88 ms
+    //   1 x 4096 rows behind 8192 (160 tiles, 1024 four-wave workgroups)  602 / 582 us
+    //   2 x 3000 behind 3000 with 16 heads (71 tiles, 752 workgroups)     254 / 228 us
+    //   8 x 4096 (32 tiles)  1014 / 1005 us;  32 x 1024 behind 1024 (24 tiles)  803 / 805 us
+    //   16 x 2048 (16 tiles)  573 / 575 us;  64 ragged prompts (10 tiles)  391 / 393 us
+    //   1 x 1024 behind 8192 (136 tiles, 256 workgroups)  158 / 199 us
+    const int64_t alone = static_cast<int64_t>(a.n_tiles) * a.Hq;             // workgroups with one head each
+    const bool two = a.d == 128 && a.heads_per_kv % 2 == 0 && alone >= 512 && a.n_key_tiles >= 32 * static_cast<int64_t>(a.n_tiles);
+    if (two) { a.heads_per_kv /= 2; a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv)); }
     const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
     const int64_t grid = (pairs + 7) / 8 * 8 * a.heads_per_kv;
     if (grid == 0) return 0;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
-    if (a.d == 128)
+    if (two)
+        hipLaunchKernelGGL(prefill_bf16_pair_kernel, dim3(static_cast<unsigned>(grid)), dim3(512), 0,
+                           static_cast<hipStream_t>(stream), a);
+    else if (a.d == 128)
         hipLaunchKernelGGL(prefill_bf16_dma_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
                            static_cast<hipStream_t>(stream), a);
     else if (a.d == 64)

@@ -64,6 +64,28 @@ def test_mixed_step_order_of_workgroups(prefill, rows):
     run_both(p, d, p.token_budget, d.token_budget, torch.bfloat16)
 
 
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("heads, n, lo, hi", [((64, 2), 4, 200, 256), ((64, 4), 24, 20, 90), ((16, 8), 20, 130, 256),
+                                              ((32, 16), 9, 128, 257), ((12, 2), 40, 1, 256)])
+def test_two_heads_per_workgroup(heads, n, lo, hi, out_dtype):
+    """Long key lists, enough workgroups: the prefill call takes two heads per workgroup, the fused step one, with
+    the same arithmetic per query row.  2, 6, 16 and 32 heads per KV head, tiles of one request and of several."""
+    rng = np.random.default_rng(95)
+    ql = rng.integers(lo, hi + 1, size=n).astype(np.int32)
+    kv = ql + rng.integers(2200, 2700, size=n).astype(np.int32)
+    p = wl.make_ragged("pair", kv, ql, heads[0], heads[1], 128, 4096, 96, device=DEV, keep_f32=False)
+    d = wl.small_paged(seed=97, n=5, lo=1, hi=100, Hq=heads[0], Hkv=heads[1], d=128, token_budget=500, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(kv, ql, token_budget=4096)
+    plan.workspace_bytes(heads[0], heads[1], 128, pk.PK_BF16)
+    assert plan.stat(6) * heads[0] >= 512
+    fus_p, _ = run_both(p, d, 4096, 500, out_dtype)
+    req = rng.integers(0, n, size=300)
+    rows = np.stack([req, rng.integers(0, heads[0], size=300), rng.integers(0, ql[req])], axis=1).astype(np.int32)
+    start = np.concatenate([[0], np.cumsum(ql)])
+    got = fus_p.float().cpu().numpy()[start[rows[:, 0]] + rows[:, 2], rows[:, 1]]
+    H.assert_close(got, H.oracle_ragged(p, False, rows=rows), 0, f"two heads per workgroup, {heads}")
+
+
 def test_mixed_step_with_an_empty_half_and_bad_arguments():
     p = wl.small_ragged(seed=82, n=3, lo=5, hi=100, Hq=4, Hkv=2, d=128, token_budget=200, device=DEV, keep_f32=False)
     d = wl.small_paged(seed=83, n=4, lo=1, hi=100, Hq=4, Hkv=2, d=128, token_budget=200, device=DEV, keep_f32=False)
