@@ -78,21 +78,31 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
         // 61 requests of 346..65536 tokens: 2048 tokens (3264 waves) 521 us, 4000 (1776 waves) 483 us,
         // 8192 486 us.  Batches with too many requests to fit gain from neither (480 rows: 2048 tokens,
         // 256 requests of 32..32768: 1632 202.8 us, 2048 200.9, 4096 204.7, 8192 224).
-        const int64_t capacity = static_cast<int64_t>(d <= 64 ? 16 : 8) * num_cus * 9 / 10;
+        bool wide = false;                         // items with more than 16 query rows: fewer registers to spare
+        for (const Group& g : plan.groups)
+            for (const Node& nd : g.nodes) wide = wide || static_cast<int>(std::min<size_t>(nd.reqs.size(), max_members)) * r > 16;
+        const int64_t capacity = static_cast<int64_t>(d <= 64 && !wide ? 16 : 8) * num_cus * 9 / 10;
         auto pieces_of = [&](int64_t len, int64_t sp) { return len <= 0 ? int64_t{0} : (whole_blocks(len) + sp - 1) / sp; };
-        auto fits = [&](int64_t sp) {
+        auto fits = [&](int64_t sp, int64_t waves) {
             int64_t c = 0;
             for (const Group& g : plan.groups) {
                 for (const Node& nd : g.nodes)
                     c += pieces_of(nd.len, sp) * static_cast<int64_t>((nd.reqs.size() + max_members - 1) / max_members);
                 for (const Member& m : g.members) c += std::max<int64_t>(pieces_of(m.lq, sp), plan.headroom > 0 ? 1 : 0);
             }
-            return c * Hkv <= capacity;
+            return c * Hkv <= waves;
         };
         const int64_t longest = std::min<int64_t>(std::max<int64_t>(whole_blocks(share * 5 / (d <= 64 ? 4 : 2)), split), 8192);
-        int64_t raised = split;
-        while (raised < longest && !fits(raised)) raised = std::min(longest, whole_blocks(raised * 5 / 4));
-        split = raised == split || fits(raised) ? raised : std::min<int64_t>(2048, whole_blocks(split * 5 / 4));
+        // from `from` in steps of a quarter up to `most`, until `waves` waves are enough
+        auto raise = [&](int64_t from, int64_t most, int64_t waves) {
+            while (from < most && !fits(from, waves)) from = std::min(most, whole_blocks(from * 5 / 4));
+            return from;
+        };
+        // where not even that fits, the even share and a quarter; and in every case no more partial results
+        // than two rounds of waves leave (the fixed scratch of pk_packed_decode_attn_static holds those)
+        const int64_t two_rounds = raise(split, 2048, static_cast<int64_t>(wide ? 8 : 16) * num_cus * 9 / 10);
+        const int64_t raised = raise(split, longest, capacity);
+        split = std::max(two_rounds, fits(raised, capacity) ? raised : std::min<int64_t>(2048, whole_blocks(split * 5 / 4)));
     }
     if (plan.tune_decode_split > 0) split = plan.tune_decode_split;     // pk_plan_tune (profiling sweeps)
     split = (split + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock;

@@ -202,9 +202,9 @@ def test_decode_work_items_of_few_tiles(shared, heads):
     H.assert_close(got, H.oracle_paged_decode(w, False), 0, f"decode items, prefix {shared}, {heads}")
 
 
-@pytest.mark.parametrize("n, d, split", [(900, 128, 160), (1000, 128, 224), (1900, 128, 416), (1900, 64, 320), (3800, 64, 768)])
+@pytest.mark.parametrize("n, d, split", [(900, 128, 160), (1000, 128, 224), (1900, 128, 416), (1900, 64, 320), (3800, 64, 2048)])
 def test_decode_split_that_fits_the_chip(n, d, split):
-    """The even share fits; it is raised until it does; one item per request is too many (the share and a quarter);
+    """The even share fits; it is raised until it does; one item per request is too many (the share and a quarter, or more for two rounds);
     the first and the last again with head dimension 64, where twice as many waves fit."""
     kv = np.random.default_rng(70 + n).integers(220, 251, size=n).astype(np.int32)
     w = to_dev(wl.make_paged(f"split{n}", kv, 2, 1, d, 8192, 16, 71, keep_f32=False))
