@@ -722,7 +722,7 @@ def main():
                      "unit": "TFLOP/s", "frac": m["prefill_kernel_tflops"] / MFMA_BF16_PEAK_TFLOPS,
                      "traffic": profiled("prefill_cfg5_packed", "total_bytes") if args.seed == 0 else None,
                      "traffic_source": "profiles/bench_hbm_traffic.txt (rocprofv3 counters of an earlier run of this command, not this run)",
-                     "kernel": "prefill_bf16_dma_kernel", "kernel_ms": m["prefill_kernel_ms"],
+                     "kernel": "prefill_bf16_pair_kernel", "kernel_ms": m["prefill_kernel_ms"],
                      "flops_per_launch": m["prefill_flops"]},
         "roofline_decode": {"bound": "hbm", "achieved": m["decode_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": m["decode_gbs"] / HBM_PEAK_GBS,
