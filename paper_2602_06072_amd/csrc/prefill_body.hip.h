@@ -135,12 +135,22 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     // Q operand: lane (n, hlf) holds Q[row n][16s + 8hlf .. +8], as it is in memory: the MFMAs
     // deliver raw scores, exact products of the bf16 inputs summed in fp32.  Only requested here;
     // the first K/V copies follow at once, so that the two round trips to memory overlap.  Lanes without
-    // a query read row 0: their probabilities are 0 whatever the score (kNoRow).
+    // a query read row 0 and are cleared once it is there (clear_absent_rows).
     const uint16_t* qp = static_cast<const uint16_t*>(a.q) +
                          (static_cast<int64_t>(u.qrow < 0 ? 0 : u.qrow) * a.Hq + u.head) * D + 8 * u.hlf;
 #pragma unroll
     for (int s = 0; s < KS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * s));
     return true;
+}
+
+// Zeros for the lanes without a query: row 0, which they have read, is another request's and may hold anything.
+__device__ __forceinline__ void clear_absent_rows(const WorkUnit& u, bf16x8 (&qf)[KS]) {
+    if (__builtin_amdgcn_ballot_w64(u.qrow < 0) == 0) return;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const u32x4 raw = __builtin_bit_cast(u32x4, qf[s]);
+        qf[s] = __builtin_bit_cast(bf16x8, u.qrow < 0 ? u32x4{0u, 0u, 0u, 0u} : raw);
+    }
 }
 
 // o / l to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
@@ -535,6 +545,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     PK_COPY_TILE(a.v, u.ks0, 3 * TILE_BYTES, true);
     PK_WAIT_ALL_COPIES();
     __syncthreads();
+    clear_absent_rows(u, qf);
 
     bf16x8 ring[4];                                 // LDS operands of the next four MFMAs
     const unsigned char* kp[4];
