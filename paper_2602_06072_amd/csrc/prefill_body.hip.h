@@ -270,8 +270,12 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
 //           above the row maximum it was taken from and only has to stay within a few dozen octaves
 //           of the running one (bf16 and fp32 share their exponent range, so a probability of 2^-12
 //           is as exact as one of 1), so it moves rarely ("lazy" rescaling).  kUnset: no key seen
-//           yet (every visible score then asks for the slow path); kNoRow: no query in this lane
-//           (every probability is 0);
+//           yet, or a far reference (every visible score then asks for the slow path); kNoRow: no query
+//           in this lane (every probability is 0);
+//   far     a reference of 2^24 octaves or more (kNear) is a score instead, the row's maximum when it was taken,
+//           and the exponents are formed in two steps, (s - far) * sc - kSlack: the rounding of m_ref is
+//           32 octaves at 2^30, and from 2^31 on it would leave rows without a probability or with infinite
+//           ones.  0: m_ref is the reference;
 //   lsum[0] the row sum, over both halves of the wave.
 // Fast path of a half tile (16 scores per lane): p = exp2(x), pairs rounded to bf16, no maximum, no
 // sum.  The sum of a row is left to the matrix pipe: one v_mfma_f32_16x16x32_bf16 per 16 keys
@@ -296,6 +300,7 @@ struct HalfSoftmax {
 };
 constexpr float kSlack = 12.f;                     // a fresh reference lies this far above the row maximum
 constexpr float kRaiseBy = 8.f;                    // a set reference is only raised by more than this
+constexpr float kNear = 16777216.f;                // below it fp32 rounds a reference by at most half an octave
 constexpr float kUnset = -1e30f, kNoRow = 1e30f;
 constexpr uint32_t kTooLarge = 0x40004000u;        // a bf16 of 2 or more in either half
 
@@ -349,9 +354,10 @@ __device__ __forceinline__ float row_max(const floatx16& s) {      // both lanes
 }
 // A wave's first half tile: nothing has been accumulated, so the rows that see a key here take their
 // reference before the exponentials (on the slow path they would be computed twice and the 64
-// accumulators, all zero, rescaled: 0.4 us of vector work per query tile).
+// accumulators, all zero, rescaled: 0.4 us of vector work per query tile).  Far references are left to the slow path.
 __device__ __forceinline__ void first_reference(const floatx16& s, const float sc, float& m_ref) {
-    m_ref = max2f(m_ref, __builtin_fmaf(row_max(s), sc, kSlack));
+    const float fresh = __builtin_fmaf(row_max(s), sc, kSlack);
+    if (__builtin_fabsf(fresh) < kNear) m_ref = max2f(m_ref, fresh);
 }
 
 // Slow path of a half tile (wave-uniform, rare): s holds the raw scores.  First the scalars: the
@@ -360,18 +366,26 @@ __device__ __forceinline__ void first_reference(const floatx16& s, const float s
 // when there is nothing).  The caller then recomputes the probabilities and rescales, each in a
 // branch of its own that holds nothing but updates in place: written as one block, the paths join
 // with the 64 accumulators in fresh registers, more than the kernel has.
-__device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const float sc, float& m_ref, float& alpha) {
-    const float fresh = __builtin_fmaf(row_max(s), sc, kSlack);     // -inf for a row without a visible key here
-    const float next = fresh > m_ref + kRaiseBy ? fresh : m_ref;
-    alpha = __builtin_amdgcn_exp2f(m_ref - next);
-    m_ref = next;
+// On this path a reference is far * sc + offset_of(m_ref, far), whichever of the two kinds it is.
+__device__ __forceinline__ float offset_of(const float m_ref, const float far) { return far == 0.f ? m_ref : kSlack; }
+__device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const float sc, float& m_ref, float& far, float& alpha) {
+    const float mx = row_max(s);                   // -inf for a row without a visible key here
+    const float far0 = far, offset0 = offset_of(m_ref, far);
+    if (__builtin_fmaf(mx - far, sc, -offset0) > kRaiseBy - kSlack) {
+        const float fresh = __builtin_fmaf(mx, sc, kSlack);
+        const bool near = __builtin_fabsf(fresh) < kNear;
+        m_ref = near ? fresh : kUnset;
+        far = near ? 0.f : mx;
+    }
+    alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(far0 - far, sc, offset0 - offset_of(m_ref, far)));
 }
-__device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, const float sc, const float m_ref) {
+__device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, const float sc, const float m_ref, const float far) {
+    const float offset = offset_of(m_ref, far);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         floatx2 pp;
-        pp[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q], sc, -m_ref));
-        pp[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q + 1], sc, -m_ref));
+        pp[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q] - far, sc, -offset));
+        pp[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q + 1] - far, sc, -offset));
         h.pw[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
     }
 }
@@ -380,8 +394,8 @@ __device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, 
         const bool slow = __builtin_amdgcn_ballot_w64((H.any & kTooLarge) != 0) != 0;          \
         float alpha = 1.f;                                                                     \
         /* the empty asm statements keep the compiler from computing the rare branches always */ \
-        if (slow) { asm volatile(""); softmax_slow_scalars(S, sc, m_ref, alpha); }             \
-        if (slow) { asm volatile(""); softmax_redo(S, H, sc, m_ref); lsum[0] *= alpha; }       \
+        if (slow) { asm volatile(""); softmax_slow_scalars(S, sc, m_ref, far, alpha); }        \
+        if (slow) { asm volatile(""); softmax_redo(S, H, sc, m_ref, far); lsum[0] *= alpha; }  \
         if (slow) {                                                                            \
             _Pragma("unroll") for (int b = 0; b < DB; ++b)                                     \
                 _Pragma("unroll") for (int e = 0; e < 16; ++e) o[b][e] *= alpha;               \
@@ -529,6 +543,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[b][e] = 0.f;
     float m_ref = u.qrow < 0 ? kNoRow : kUnset;    // rows without a query never ask for the slow path
+    float far = 0.f;
     floatx4 lsum = {0.f, 0.f, 0.f, 0.f};
     const bf16x8 ones = row_sum_selector(u.lane);
     const floatx16 zero16 = {};

@@ -145,3 +145,71 @@ def test_prefill_scores_beyond_the_exponent_range(d):
     # bf16 keys of magnitude 20..23 step by 2^-3: many keys share a row; the score error above (|score| up to
     # 3000 nats: 3000 * 128 * 2^-24 = 2.3e-2) moves a probability by that fraction and an output of |v| <= 5 by 5 times it
     assert np.abs(got[lo:hi] - want[lo:hi]).max() <= 2e-2 + 5 * 2.3e-2
+
+
+def check_prefill_launches(w, want, keep, what):
+    """Packed and padded prefill and the prefill half of the fused step against `want`, on the rows `keep`."""
+    dec = wl.small_paged(seed=3, n=3, lo=1, hi=90, Hq=w.Hq, Hkv=w.Hkv, d=w.d, token_budget=500, device=DEV, keep_f32=False)
+    dplan = pk.pack_plan(dec.kv_lens, np.ones_like(dec.kv_lens), None, None, 500)
+    dws = pk.new_workspace(dplan, w.Hq, w.Hkv, w.d, pk.PK_BF16)
+    buf = pk.new_kv_buf(dplan, w.Hkv, w.d, pk.PK_BF16)
+    pk.kv_reorganize(dplan, dec.k_pages, dec.v_pages, torch.from_numpy(dec.block_table).to(DEV), buf, dws)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=w.token_budget)
+    ws = pk.new_workspace(plan, w.Hq, w.Hkv, w.d, pk.PK_BF16)
+    for launch in ("packed", "padded", "mixed"):
+        out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+        if launch == "mixed":
+            dout = torch.full(dec.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+            pk.packed_mixed_step(plan, w.q, w.k, w.v, out, ws, dplan, dec.q, buf, dout, dws, w.scale)
+        else:
+            (pk.padded_prefill_attn if launch == "padded" else pk.packed_prefill_attn)(plan, w.q, w.k, w.v, out, w.scale, ws)
+        torch.cuda.synchronize()
+        H.assert_close(out.cpu().numpy()[keep], want[keep], 0, f"{what} {launch}")
+    return plan
+
+
+def rows_that_rounding_cannot_turn(w, rows):
+    """Of the rows (request, head, t): those whose best key leads every key that is not a copy of it by more than 40
+    nats and twice what fp32 sums can be off by, d * 2^-24 of the sum of |q c k c| each."""
+    k64 = w.k.double().cpu()
+    q0 = np.concatenate([[0], np.cumsum(w.q_lens)])
+    keep = np.zeros(len(rows), dtype=bool)
+    for x, (i, h, t) in enumerate(rows):
+        seen = int(w.kv_lens[i] - w.q_lens[i] + t + 1)
+        kk = k64[int(w.kv_start[i]):int(w.kv_start[i]) + seen, h // (w.Hq // w.Hkv)]
+        qq = w.q[int(q0[i]) + int(t), h].double().cpu()
+        s = kk @ qq
+        best = int(s.argmax())
+        other = ~(kk == kk[best]).all(dim=1)
+        off = 2 * w.d * 2.0 ** -24 * float((kk.abs() @ qq.abs()).max())
+        keep[x] = not bool(other.any()) or float(s[best] - s[other].max()) > off + 40 / w.scale
+    return keep
+
+
+@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128)])
+@pytest.mark.parametrize("size", [3e3, 1e5, 1e6, 1e9])
+def test_prefill_with_large_finite_scores(size, heads):
+    """Scaled scores of 1e7 to 1e19: a reference rounded to fp32 is off by up to many octaves there, more than the
+    exponentials can take.  Copies of a key, in other key tiles too, have the same score and share the row.  Rows where
+    the rounding of the sums decides between two keys are left out (under 1 in 50)."""
+    Hq, Hkv, d = heads
+    two = Hq == 16                                        # enough workgroups and keys for two heads per workgroup
+    kv = np.asarray([4500, 4800] if two else [513, 200, 97, 640], dtype=np.int32)
+    ql = np.asarray([2100, 2050] if two else [513, 60, 97, 300], dtype=np.int32)
+    w = wl.make_ragged("large_scores", kv, ql, Hq, Hkv, d, 4096, 33, DEV, keep_f32=False)
+    w.q.mul_(size)
+    w.k.mul_(size)
+    rng = np.random.default_rng(34)
+    for s, L in zip(w.kv_start, w.kv_lens):
+        a, b = rng.integers(0, int(L), size=(2, int(L) // 3))
+        w.k[int(s) + torch.from_numpy(b).to(DEV)] = w.k[int(s) + torch.from_numpy(a).to(DEV)]
+    req = rng.integers(0, len(ql), size=600)
+    rows = np.stack([req, rng.integers(0, Hq, size=600), rng.integers(0, ql[req])], axis=1).astype(np.int32)
+    keep = rows_that_rounding_cannot_turn(w, rows)
+    assert keep.mean() > 0.98
+    rows = rows[keep]
+    at = (np.concatenate([[0], np.cumsum(ql)])[rows[:, 0]] + rows[:, 2], rows[:, 1])
+    want = np.zeros(tuple(w.q.shape), dtype=np.float32)
+    want[at] = H.oracle_ragged(w, False, rows=rows)
+    plan = check_prefill_launches(w, want, at, f"scores of {size * size:g} {heads}")
+    assert not two or (plan.stat(6) * Hq >= 512 and plan.stat(1) >= 32 * 64 * 128 * plan.stat(6))
