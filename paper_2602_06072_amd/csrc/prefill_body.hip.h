@@ -301,7 +301,7 @@ struct HalfSoftmax {
 constexpr float kSlack = 12.f;                     // a fresh reference lies this far above the row maximum
 constexpr float kRaiseBy = 8.f;                    // a set reference is only raised by more than this
 constexpr float kNear = 16777216.f;                // below it fp32 rounds a reference by at most half an octave
-constexpr float kUnset = -1e30f, kNoRow = 1e30f;
+constexpr float kUnset = -__FLT_MAX__, kNoRow = 1e30f;   // (kUnset lies below every scaled score that fp32 can hold)
 constexpr uint32_t kTooLarge = 0x40004000u;        // a bf16 of 2 or more in either half
 
 // A operand of the row-sum MFMA.  The B operand is P as the 32x32x16 MFMA takes it: lane l holds

@@ -168,6 +168,19 @@ def check_prefill_launches(w, want, keep, what):
     return plan
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_rows_with_every_score_far_below_zero(d):
+    """Scaled scores around -1e31 .. -1e33.  A row's keys repeat 32 factors a 32nd apart: the nearest to zero that it
+    sees stand alone against the rest by far more than any rounding, and equal keys have equal scores."""
+    kv = np.asarray([200, 100, 33, 400], dtype=np.int32)
+    ql = np.asarray([200, 60, 33, 150], dtype=np.int32)
+    w = wl.make_ragged("far_below", kv, ql, 4, 2, d, 1024, 31, DEV, keep_f32=False)
+    w.q.fill_(1e16)
+    f = 2.0 - (torch.arange(w.k.shape[0], device=DEV) * 7 % 32).float() / 32
+    w.k.copy_((-1e15 * f.view(-1, 1, 1)).expand(w.k.shape))
+    check_prefill_launches(w, H.oracle_ragged(w, False), slice(None), f"scores far below zero d={d}")
+
+
 def rows_that_rounding_cannot_turn(w, rows):
     """Of the rows (request, head, t): those whose best key leads every key that is not a copy of it by more than 40
     nats and twice what fp32 sums can be off by, d * 2^-24 of the sum of |q c k c| each."""
