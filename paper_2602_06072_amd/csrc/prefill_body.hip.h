@@ -153,10 +153,17 @@ __device__ __forceinline__ void clear_absent_rows(const WorkUnit& u, bf16x8 (&qf
     }
 }
 
+// 1 / row sum (0 for a row without a visible key, NaN if either lane of the row holds one)
+__device__ __forceinline__ float row_scale(const float l) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    const float twice = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    return twice == 0.f ? 0.f : 2.f / twice;
+}
+
 // o / l to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
 __device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], const float l) {
+    const float inv = row_scale(l);
     if (u.qrow < 0) return;
-    const float inv = l > 0.f ? 1.f / l : 0.f;
     const int64_t obase = (static_cast<int64_t>(u.qrow) * a.Hq + u.head) * D;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
@@ -182,7 +189,7 @@ __device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUni
 __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB],
                                                   const float l, unsigned char* qa, unsigned char* qb) {
     constexpr int CPR = D / 8, RPI = 64 / CPR;     // 16-byte chunks per row; rows per store instruction
-    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const float inv = row_scale(l);
     const int rr = u.n & 15;
     unsigned char* wrow = (u.n < 16 ? qa : qb) + rr * ROWB + 8 * u.hlf;
 #pragma unroll
@@ -276,7 +283,8 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
 //           and the exponents are formed in two steps, (s - far) * sc - kSlack: the rounding of m_ref is
 //           32 octaves at 2^30, and from 2^31 on it would leave rows without a probability or with infinite
 //           ones.  0: m_ref is the reference;
-//   lsum[0] the row sum, over both halves of the wave.
+//   lsum[0] the row sum, over both halves of the wave; NaN once a score that this lane holds has given a
+//           probability that is not a number (a NaN or an infinity in Q or K).
 // Fast path of a half tile (16 scores per lane): p = exp2(x), pairs rounded to bf16, no maximum, no
 // sum.  The sum of a row is left to the matrix pipe: one v_mfma_f32_16x16x32_bf16 per 16 keys
 // whose A operand holds ones where they bring the sum of a query's P into register 0 of both
@@ -379,7 +387,8 @@ __device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const fl
     }
     alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(far0 - far, sc, offset0 - offset_of(m_ref, far)));
 }
-__device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, const float sc, const float m_ref, const float far) {
+__device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, const float sc, const float m_ref, const float far,
+                                             const float alpha, floatx4& lsum) {
     const float offset = offset_of(m_ref, far);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -388,6 +397,16 @@ __device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, 
         pp[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q + 1] - far, sc, -offset));
         h.pw[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
     }
+    // With its reference in place a row's probabilities are below 2, unless one is a NaN.  None may reach the row-sum
+    // MFMA, whose columns hold two queries and keep them apart by a factor of zero: the NaN goes to the lane's row sum
+    // instead, and to no other row.
+    uint32_t any = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) any |= h.pw[q];
+    const bool bad = (any & kTooLarge) != 0;
+    lsum[0] = bad ? __builtin_nanf("") : lsum[0] * alpha;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) h.pw[q] = bad ? 0u : h.pw[q];
 }
 #define PK_SOFTMAX_CHECK(S, H)                                                                 \
     {                                                                                          \
@@ -395,7 +414,7 @@ __device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, 
         float alpha = 1.f;                                                                     \
         /* the empty asm statements keep the compiler from computing the rare branches always */ \
         if (slow) { asm volatile(""); softmax_slow_scalars(S, sc, m_ref, far, alpha); }        \
-        if (slow) { asm volatile(""); softmax_redo(S, H, sc, m_ref, far); lsum[0] *= alpha; }  \
+        if (slow) { asm volatile(""); softmax_redo(S, H, sc, m_ref, far, alpha, lsum); }       \
         if (slow) {                                                                            \
             _Pragma("unroll") for (int b = 0; b < DB; ++b)                                     \
                 _Pragma("unroll") for (int e = 0; e < 16; ++e) o[b][e] *= alpha;               \

@@ -37,3 +37,58 @@ def test_lanes_without_a_query_hold_nobody_elses_row(d):
         assert plan.stat(6) == 6                           # one tile a request, two for the first: nothing shared
         assert torch.equal(got[32:], clean[padded][32:])
         assert torch.isnan(got[0]).all()
+
+
+BAD = {"q_first": ("q", 0, float("nan")), "q_middle": ("q", 77, float("nan")), "q_inf": ("q", 41, float("inf")),
+       "k_nan": ("k", 25, float("nan")), "k_inf": ("k", 60, float("inf")), "k_first": ("k", 0, float("nan"))}
+
+
+@pytest.mark.parametrize("case", list(BAD))
+@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128)])
+@pytest.mark.parametrize("launch", ["packed", "padded", "mixed"])
+def test_nonfinite_values_reach_only_the_rows_that_see_them(launch, heads, case):
+    """Tiles of several requests; one head per workgroup, D = 64, two heads per workgroup.  A NaN makes exactly the
+    rows that see it NaN; what a row that sees an infinity gives is not asked."""
+    Hq, Hkv, d = heads
+    n = 150
+    rng = np.random.default_rng(51)
+    ql = rng.integers(5, 61, size=n).astype(np.int32)
+    ctx = rng.integers(600, 901, size=n) if Hq == 16 else rng.integers(0, 300, size=n)
+    w = wl.make_ragged("isolation", (ql + ctx).astype(np.int32), ql, Hq, Hkv, d, 8192, 52, DEV, keep_f32=False)
+    dec = wl.small_paged(seed=53, n=4, lo=1, hi=90, Hq=Hq, Hkv=Hkv, d=d, token_budget=500, device=DEV, keep_f32=False)
+    dplan = pk.pack_plan(dec.kv_lens, np.ones_like(dec.kv_lens), None, None, 500)
+    dws = pk.new_workspace(dplan, Hq, Hkv, d, pk.PK_BF16)
+    buf = pk.new_kv_buf(dplan, Hkv, d, pk.PK_BF16)
+    pk.kv_reorganize(dplan, dec.k_pages, dec.v_pages, torch.from_numpy(dec.block_table).to(DEV), buf, dws)
+
+    def run(out_dtype):
+        if launch != "mixed":
+            return prefill(w, launch == "padded", out_dtype)[0]
+        plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=w.token_budget)
+        ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
+        out = torch.full(w.q.shape, 7.0, dtype=out_dtype, device=DEV)
+        pk.packed_mixed_step(plan, w.q, w.k, w.v, out, ws, dplan, dec.q, buf, torch.empty_like(dec.q, dtype=out_dtype), dws, w.scale)
+        torch.cuda.synchronize()
+        return out
+
+    plan = prefill(w)[1]
+    assert plan.stat(6) < n                                # requests share tiles
+    assert Hq != 16 or (plan.stat(6) * Hq >= 512 and plan.stat(1) >= 8 * 64 * 128 * plan.stat(6))
+    clean = {t: run(t).float() for t in (torch.float32, torch.bfloat16)}
+    which, req, value = BAD[case]
+    q0 = int(w.q_lens[:req].sum())
+    sees = torch.zeros(w.q.shape[:2], dtype=torch.bool, device=DEV)
+    if which == "q":
+        row = q0 + int(ql[req]) // 2 if req else 0
+        heads_hit = slice(None) if req == 0 else slice(1, 2)
+        w.q[row, heads_hit, 5] = value
+        sees[row, heads_hit] = True
+    else:                                                  # a key half way through the request's own queries
+        t = int(ql[req]) // 2
+        w.k[int(w.kv_start[req]) + int(ctx[req]) + t, Hkv - 1, 3] = value
+        sees[q0 + t: q0 + int(ql[req]), (Hkv - 1) * (Hq // Hkv):] = True
+    for out_dtype, want in clean.items():
+        got = run(out_dtype).float()
+        H.assert_close(got[~sees].cpu().numpy(), want[~sees].cpu().numpy(), 0, f"{case} {launch} {heads}")
+        if np.isnan(value):
+            assert torch.isnan(got[sees]).all()
