@@ -89,9 +89,11 @@ void staging_release(Staging* s, bool recorded) {
     s->busy = false;
 }
 
-// Tables up to this size go through the upload kernel.  A bind and a small kernel, copy command against upload
-// kernel: workspace of 5 KB 16.6 / 12.1 us, 50 KB 24.3 / 12.1, 240 KB 26.5 / 13.7, 810 KB 31.9 / 35.6, 3.6 MB 57.9 / 149.
-constexpr size_t kUploadKernelBytes = 256u << 10;
+// Tables up to this size go through the upload kernel.  In one stream, with a small kernel behind it (copy command /
+// upload kernel, us): 4 KB of tables 15.2 / 14.0, 76 KB 24.9 / 14.6, 129 KB 26.1 / 16.3, 161 KB 26.4 / 19.2, 246 KB
+// 27.9 / 26.0.  On a second stream under a launch that fills the chip: 12 / 7, 21 / 13, 22 / 20, 23 / 23 and, of
+// 202 KB 24 / 28, of 246 KB 24 / 34: the line lies where neither use pays.
+constexpr size_t kUploadKernelBytes = 160u << 10;
 
 // A captured upload must find the same bytes at every replay: it is left to the copy command, whose buffer
 // never comes back (its event completes only outside the graph).

@@ -4,7 +4,7 @@
 // Bound by latency: a copy command in the stream hands the transfer to a copy engine and waits for it
 // on both sides, some 20 us during which the compute units stand still; a kernel starts like any other
 // behind the one before it.  (Re-layout, decode and merge of a new batch of 48 requests: 129 -> 113.5 us a
-// pass; a bind and a small kernel with 5 KB of tables 16.6 -> 12.1 us, with 50 KB 24.3 -> 12.1.)  One workgroup
+// pass; a bind of 76 KB of tables and a small kernel 24.9 -> 14.6.)  One workgroup
 // of 1024 lanes keeps 64 KiB of reads in flight, which is what the link delivers in one round trip, and
 // lets a single barrier say that the whole table has been read.
 #include "common.hip.h"
