@@ -42,7 +42,8 @@ bool shape_ok(int Hq, int Hkv, int d, int dtype, std::string& why) {
 // stream has drained; from pinned memory it is asynchronous, so the planning of the next batch
 // overlaps the kernels of the current one.  Buffers are recycled once the kernel that reads them has
 // stored its stamp behind them, or once the event recorded behind a copy command has completed; the
-// pool only grows while every buffer is still in flight.
+// pool only grows while every buffer is still in flight.  A buffer whose copy has been captured into a graph
+// stays out of the pool: every replay reads it.
 struct Staging {
     void* ptr = nullptr;
     size_t cap = 0;
@@ -92,24 +93,27 @@ void staging_release(Staging* s, bool recorded) {
 // Tables up to this size go through the upload kernel.  In one stream, with a small kernel behind it (copy command /
 // upload kernel, us): 4 KB of tables 15.2 / 14.0, 76 KB 24.9 / 14.6, 129 KB 26.1 / 16.3, 161 KB 26.4 / 19.2, 246 KB
 // 27.9 / 26.0.  On a second stream under a launch that fills the chip: 12 / 7, 21 / 13, 22 / 20, 23 / 23 and, of
-// 202 KB 24 / 28, of 246 KB 24 / 34: the line lies where neither use pays.
+// 202 KB 24 / 28, of 246 KB 24 / 34: up to the line the kernel is the slower one in neither use.
 constexpr size_t kUploadKernelBytes = 160u << 10;
 
-// A captured upload must find the same bytes at every replay: it is left to the copy command, whose buffer
-// never comes back (its event completes only outside the graph).
-bool upload_by_kernel(size_t bytes, hipStream_t st) {
-    if (bytes > kUploadKernelBytes || !launch_upload) return false;
+// (when it cannot be told, the careful answer)
+bool capturing(hipStream_t st) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
-    return status == hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
+    return status != hipStreamCaptureStatusNone;
 }
 
 int copy_tables(void* dst, const void* src, size_t bytes, void* stream, bool may_allocate = true) {
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const bool captured = capturing(st);
+    // (asking an event or allocating would end a capture, unless this thread says that it is not part of it)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = captured && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     Staging* s = staging_acquire(bytes, may_allocate);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (!s) return static_cast<int>(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
     std::memcpy(s->ptr, src, bytes);
-    if (may_allocate && upload_by_kernel(bytes, st)) {      // (the first launch of a kernel may load its code)
+    if (may_allocate && !captured && bytes <= kUploadKernelBytes && launch_upload) {   // (a kernel's first launch may load its code)
         const int e = launch_upload(s->ptr, dst, static_cast<int64_t>(bytes), s->done, s->stamp + 1, stream);
         // on an error the kernel may or may not have been queued: wait, and take the stamp that is there
         if (e != 0) (void)hipStreamSynchronize(st);
@@ -118,6 +122,7 @@ int copy_tables(void* dst, const void* src, size_t bytes, void* stream, bool may
         return e;
     }
     hipError_t e = hipMemcpyAsync(dst, s->ptr, bytes, hipMemcpyHostToDevice, st);
+    if (captured) return static_cast<int>(e);               // the buffer is the graph's from here on: not released
     if (e != hipSuccess) {
         // the copy may or may not have been queued: keep the buffer out of circulation until the stream drains
         (void)hipStreamSynchronize(st);

@@ -56,3 +56,45 @@ def test_static_decode_replays_in_a_captured_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, eager), f"replay {rep}"
+
+
+def test_captured_bind_keeps_its_tables():
+    """A plan_bind inside a capture: every replay uploads the tables of the captured plan again, whatever has gone
+    through the staging buffers since (the workspace is cleared before each replay)."""
+    def prefill(plan, w, ws, out):
+        pk.plan_bind(plan, w.Hq, w.Hkv, w.d, pk.PK_BF16, ws)
+        pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
+
+    w = wl.small_ragged(seed=10, n=30, lo=1, hi=300, Hq=8, Hkv=2, d=64, token_budget=512, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=512)
+    ws = pk.new_workspace(plan, w.Hq, w.Hkv, w.d, pk.PK_BF16)
+    ref = torch.empty_like(w.q)
+    prefill(plan, w, ws, ref)                                  # (a staging buffer and the kernels are there from here on)
+    many = np.full(4000, 3, dtype=np.int32)                    # more tables than the upload kernel takes
+    big = pk.pack_plan(many, many, token_budget=512)
+    big_ws = pk.new_workspace(big, 8, 2, 64, pk.PK_BF16)
+    pk.plan_bind(big, 8, 2, 64, pk.PK_BF16, big_ws)            # (through the copy command: a buffer with an event to ask)
+    torch.cuda.synchronize()
+
+    out = torch.empty_like(ref)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        prefill(plan, w, ws, out)
+    torch.cuda.synchronize()
+    others = []
+    for seed in range(3):
+        o = wl.small_ragged(seed=20 + seed, n=25, lo=1, hi=200, Hq=8, Hkv=2, d=64, token_budget=512, device=DEV, keep_f32=False)
+        op = pk.pack_plan(o.kv_lens, o.q_lens, token_budget=512)
+        others.append((op, o, pk.new_workspace(op, 8, 2, 64, pk.PK_BF16), torch.empty_like(o.q)))
+    for rep in range(4):
+        out.fill_(float("nan"))
+        ws.zero_()
+        for x in others * 10:
+            prefill(*x)
+        pk.plan_bind(big, 8, 2, 64, pk.PK_BF16, big_ws)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), f"replay {rep}"
