@@ -30,8 +30,9 @@ def test_decode_parity_over_the_sizes_of_the_tables(n):
 
 
 def test_many_new_batches_without_a_synchronisation():
-    """More binds in flight than there are staging buffers, all on one workspace; every batch must get its own
-    tables, on either of two streams."""
+    """More binds in flight than there are staging buffers (64), all on one workspace a stream; every batch must get its
+    own tables, on either of two streams.  Matrix products ahead of them keep the streams busy until every buffer is
+    out; the bind after that waits for its stream to drain, and those that follow reuse buffers."""
     rng = np.random.default_rng(310)
     w = wl.small_ragged(seed=311, n=40, lo=1, hi=300, Hq=8, Hkv=2, d=64, token_budget=512, device=DEV, keep_f32=False)
     total = int(w.q_lens.sum())
@@ -58,8 +59,18 @@ def test_many_new_batches_without_a_synchronisation():
         want.append(out)
     got = [torch.full_like(w.q, float("nan")) for _ in batches]
     torch.cuda.synchronize()
+    x = torch.randn(8192, 8192, dtype=torch.bfloat16, device=DEV)
+    y = [torch.mm(x, x) for _ in streams]
+    torch.cuda.synchronize()
+    for st, z in zip(streams, y):
+        with torch.cuda.stream(st):
+            for _ in range(60):
+                torch.mm(x, x, out=z)
+    ahead = [st.record_event() for st in streams]
     plans = []
     for i, lens in enumerate(batches):
+        if i == 64:
+            assert not any(e.query() for e in ahead)       # nothing has been uploaded yet
         with torch.cuda.stream(streams[i % 2]):
             plans.append(run(lens, spaces[i % 2], got[i]))
     torch.cuda.synchronize()
