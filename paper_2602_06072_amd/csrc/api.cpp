@@ -318,7 +318,6 @@ static int prefill_common(pk_plan* plan, const void* q, const void* k, const voi
     if (tkv > INT32_MAX) return fail(PK_EUNSUPPORTED, std::string(who) + ": more than 2^31 KV rows");
     a.total_q_rows = tq; a.total_kv_rows = tkv;
     a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.scale = scale; a.out_f32 = out_dtype == PK_F32;
-    a.xcd_swizzle = 1;             // both schedules: the r heads of a KV head share an XCD (and its L2)
     a.pipeline = plan->tune_prefill_pipeline;
     if (args_out) { *args_out = a; return PK_OK; }
     const int e = dtype == PK_BF16 ? launch_prefill_bf16(a, stream) : launch_prefill_f32(a, stream);

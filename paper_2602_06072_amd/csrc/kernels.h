@@ -73,7 +73,6 @@ struct PrefillArgs {
     const int32_t* q_start; const int32_t* kv_start; int32_t n;
     int64_t total_q_rows; int64_t total_kv_rows;
     int Hq; int Hkv; int d; float scale; int out_f32;
-    int xcd_swizzle;                                // 1: place the heads of a KV head on one XCD
     int pipeline;                                   // 0: K/V tiles copied straight into LDS; 1: staged through registers
     int64_t n_key_tiles;                            // entries of kvtiles
     int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: workgroups per (query tile, KV head), divisions by it and by Hkv

@@ -39,7 +39,7 @@ namespace {
 constexpr int kRun = 256;
 
 struct MixedOrder {
-    int n_prefill, n_decode;            // workgroups of each kind
+    int n_prefill;                      // prefill workgroups
     int cycles, stride;                 // stretch in which both kinds are dealt: cycles x stride runs
     int rest_is_decode;                 // which kind is left behind it
     FastDiv by_stride;
@@ -97,7 +97,7 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     const int64_t grid = (p_runs + d_runs) * kRun;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
     MixedOrder m{};
-    m.n_prefill = static_cast<int>(n_prefill); m.n_decode = static_cast<int>(n_decode);
+    m.n_prefill = static_cast<int>(n_prefill);
     m.cycles = static_cast<int>(p_runs < d_runs ? p_runs : d_runs);
     m.stride = 1 + static_cast<int>(d_runs > 0 && p_runs > d_runs ? p_runs / d_runs : 1);
     m.rest_is_decode = d_runs > p_runs;

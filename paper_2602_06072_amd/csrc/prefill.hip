@@ -49,17 +49,12 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_kernel(PrefillArgs a) {
 
     // ---- work unit ---------------------------------------------------------
     const int r = a.Hq / a.Hkv;
-    int tile, head, kvh;
-    if (a.xcd_swizzle) {
-        // consecutive workgroup ids go round-robin over the 8 XCDs: keep the r heads of one
-        // (tile, KV head) pair on one XCD and adjacent in time so K/V tiles hit in its L2
-        const int x = blockIdx.x, c = x & 7, y = x >> 3, j = y % r, slot = y / r;
-        const int64_t p = static_cast<int64_t>(slot) * 8 + c;
-        if (p >= static_cast<int64_t>(a.n_tiles) * a.Hkv) return;
-        tile = static_cast<int>(p / a.Hkv); kvh = static_cast<int>(p % a.Hkv); head = kvh * r + j;
-    } else {
-        tile = blockIdx.x / a.Hq; head = blockIdx.x % a.Hq; kvh = head / r;
-    }
+    // consecutive workgroup ids go round-robin over the 8 XCDs: keep the r heads of one
+    // (tile, KV head) pair on one XCD and adjacent in time so K/V tiles hit in its L2
+    const int x = blockIdx.x, c = x & 7, y = x >> 3, j = y % r, slot = y / r;
+    const int64_t p = static_cast<int64_t>(slot) * 8 + c;
+    if (p >= static_cast<int64_t>(a.n_tiles) * a.Hkv) return;
+    const int tile = static_cast<int>(p / a.Hkv), kvh = static_cast<int>(p % a.Hkv), head = kvh * r + j;
     const int32_t* desc = a.tiles + 16 * static_cast<int64_t>(tile);     // (16 words per descriptor; this kernel uses the first 8)
     const int kv_first = desc[0], n_kv = desc[1];
     if (n_kv == 0) return;
@@ -298,13 +293,8 @@ int launch_p(const PrefillArgs& a, hipStream_t st) {
         attr_set = true;
     }
     const int r = a.Hq / a.Hkv;
-    int64_t grid;
-    if (a.xcd_swizzle) {
-        const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
-        grid = (pairs + 7) / 8 * 8 * r;
-    } else {
-        grid = static_cast<int64_t>(a.n_tiles) * a.Hq;
-    }
+    const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
+    const int64_t grid = (pairs + 7) / 8 * 8 * r;
     if (grid == 0) return 0;
     hipLaunchKernelGGL(prefill_bf16_kernel<D>, dim3(static_cast<unsigned>(grid)), dim3(256), Smem<D>::TOTAL, st, a);
     return static_cast<int>(hipGetLastError());

@@ -16,7 +16,7 @@
 // fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4, or 8 for two
 // query heads of a KV head per workgroup) and PK_DNS (the namespace this instance goes into) first; the
 // file may be included once per combination.
-// With PK_D = 64 a tile is 8 KiB (two 1-KiB copy instructions per wave) and a
+// With PK_D = 64 a tile is 8 KiB instead of 16 and a
 // half tile four MFMAs instead of eight, each followed by two softmax slices instead of one.
 #include <cstdint>
 
@@ -219,8 +219,8 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
                                       (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * D + 8 * chunk) = v[k];
 }
 
-// Copies of K/V tiles into LDS stages.  A tile is 16 instructions of 1 KiB (four per wave; eight and
-// two for D = 64), each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the end
+// Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
+// them per wave, each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the end
 // of the array arrive as zeros (the descriptor's size is what is left of the array; a tile past
 // the end of the key-tile list gets size 0: zeros, no memory traffic).  The copy is issued from
 // inline assembly on purpose: the compiler makes every later LDS read wait for all copies it
@@ -246,7 +246,7 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
         RS[2] = __builtin_amdgcn_readfirstlane((ENABLED) ? static_cast<uint32_t>(left_ > 0x7FFFFFFFull ? 0x7FFFFFFFull : left_) : 0u); \
         RS[3] = 0x00020000u;                                                                 \
     }
-// this wave's piece Q (0..3) of a tile into the stage at byte offset DST
+// this wave's piece Q (0 .. PIECES - 1) of a tile into the stage at byte offset DST
 #define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) / PPS) * SLAB + ((Q) % PPS) * 1024, off.g[Q])
 #define PK_COPY_TILE(SRC, KSTART, DST, ENABLED)                                              \
     {                                                                                        \
@@ -257,10 +257,10 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
 #define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
 
 // ---------------------------------------------------------------------------------------------
-// Kernel A (default).  Two workgroups per CU (80 KiB of LDS each: three stages for K, two for V).
+// Two workgroups of four waves per CU, three with D = 64, or one of eight; five stages of LDS each, three for K and two for V.
 // A key tile is handled as two halves of 32 keys, each with its own online-softmax step, so that
 // within one wave the matrix pipe and the vector ALU overlap without state that crosses tiles:
-//   phase 1   S0 = K(half 0) Q^T      with the requests for V(j+1), K(j+2)   (8 MFMAs + 8 copies)
+//   phase 1   S0 = K(half 0) Q^T      with the requests for V(j+1), K(j+2)   (8 MFMAs + 2 * PIECES copies)
 //   phase 2   S1 = K(half 1) Q^T      with the softmax of S0       (8 MFMAs + vector work)
 //   phase 3   O += V(half 0)^T P0^T   with the softmax of S1       (8 MFMAs + vector work)
 //   phase 4   O += V(half 1)^T P1^T                                (8 MFMAs)
@@ -589,7 +589,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     int k_cur = 0, k_next = TILE_BYTES, k_fill = 2 * TILE_BYTES;   // K stage read now / next / filled now
     int v_cur = 3 * TILE_BYTES, v_fill = 4 * TILE_BYTES;
     // Tile j: while S0 is computed, V(j+1) and K(j+2) are requested into the stages of V(j-1) and
-    // K(j-1), one 1-KiB piece behind each of the eight MFMAs, where their issue costs nothing.  The
+    // K(j-1), one 1-KiB piece behind each of the first 2 * PIECES MFMAs, where their issue costs nothing.  The
     // barrier at the END of the tile (after this wave's copies have landed: only they matter, the
     // compiler's own barrier would also wait for the LDS reads) says that every wave is done with
     // tile j and that V(j+1) and K(j+2) are complete; K(j+1), whose first operands are read during
