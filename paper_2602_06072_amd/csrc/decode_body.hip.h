@@ -25,8 +25,8 @@ __device__ __forceinline__ float max_over_lane_groups(float x) {
 // descriptor is empty: zeros, no memory traffic): behind a condition the compiler waits for everything
 // outstanding at the next use, since it has to take the smaller count of the two paths, and tiles are
 // fetched and processed in turns.  Measured with and without the condition (and with permlane swaps for the
-// LDS look-ups of the maximum): 256 requests of 32..32768 tokens 206.0 -> 201.6 us, four requests 11.5 ->
-// 10.3, a tree of 128 63.1 -> 61.0, 16 families of 8 66.2 -> 64.9, 200 requests with D = 64 73.8 -> 73.2.
+// LDS look-ups of the maximum): 256 requests of 32..32768 tokens 206.0 -> 201.6 us, four requests 12.1 ->
+// 11.5, a tree of 128 63.1 -> 61.0, 16 families of 8 66.2 -> 64.9, 200 requests with D = 64 73.8 -> 73.2.
 // The first tile is requested before the look-up of the requests (the other order: 65.6 and 74.1 us).
 template <int D, int NT, int SETS>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item, const int kvh) {

@@ -58,6 +58,10 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     //   8 x 4096 (32 tiles)  1014 / 1005 us;  32 x 1024 behind 1024 (24 tiles)  803 / 805 us
     //   16 x 2048 (16 tiles)  573 / 575 us;  64 ragged prompts (10 tiles)  391 / 393 us
     //   1 x 1024 behind 8192 (136 tiles, 256 workgroups)  158 / 199 us
+    // D = 64 stays with four waves: with 151 registers a wave, three such workgroups share a compute unit, of eight waves
+    // only one does (in 128 registers, for two, the body spills and is slower again):
+    //   8 x 4096  604 / 667 us;  16 x 2048  336 / 375 us;  32 x 512 behind 8192 with 64 heads  2342 / 2560 us
+    //   1 x 1024 behind 8192  115 / 149 us;  1 x 4096 behind 8192  378 / 374 us;  2 x 3000 behind 3000 with 16 heads  187 / 165 us
     const int64_t alone = static_cast<int64_t>(a.n_tiles) * a.Hq;             // workgroups with one head each
     const bool two = a.d == 128 && a.heads_per_kv % 2 == 0 && alone >= 512 && a.n_key_tiles >= 32 * static_cast<int64_t>(a.n_tiles);
     if (two) { a.heads_per_kv /= 2; a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv)); }
