@@ -73,7 +73,7 @@ __device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneO
 struct WorkUnit {
     int head, kvh, n_kv, n_lead, n_active, wave, lane, n, hlf;   // this wave computes key tiles [n_lead, n_active)
     int rows;                          // which 32 of the tile's 128 rows this wave has
-    int ks0, ks1;                      // first key rows of the tile's first two key tiles
+    int ks[3], info[3];                // (first key row, info) of the tile's first three key tiles (the last one repeated)
     int qrow, lo, hi;                  // this lane's query row (-1: padding) and its key range [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
@@ -98,7 +98,8 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     u.n_kv = desc[1];
     if (u.n_kv == 0) return false;
     u.kvt = a.kvtiles + 2 * static_cast<int64_t>(desc[0]);
-    u.ks0 = desc[8]; u.ks1 = desc[9];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) { u.ks[x] = desc[8 + x]; u.info[x] = desc[11 + x]; }
     const int tid = threadIdx.x;
     u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -234,25 +235,34 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
                  :: "s"(lds_addr), "v"(voffset), "s"(rsrc)
                  : "memory");                       // M0 has no other user in this file
 }
-// descriptor of the tile that starts at key row KSTART of SRC (a.k or a.v); ENABLED = false: empty
-#define PK_TILE_DESC(RS, SRC, KSTART, ENABLED)                                               \
-    u32x4 RS;                                                                                \
-    {                                                                                        \
-        const uint32_t ks_ = static_cast<uint32_t>(KSTART);       /* row counts fit 31 bits */ \
-        const uint64_t base_ = reinterpret_cast<uint64_t>(SRC) + static_cast<uint64_t>(ks_) * u.row_bytes32; \
-        const uint64_t left_ = static_cast<uint64_t>(u.total_rows32 - ks_) * u.row_bytes32;  \
-        RS[0] = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base_));               \
-        RS[1] = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base_ >> 32) & 0xFFFFu);  /* stride 0: raw buffer */ \
-        RS[2] = __builtin_amdgcn_readfirstlane((ENABLED) ? static_cast<uint32_t>(left_ > 0x7FFFFFFFull ? 0x7FFFFFFFull : left_) : 0u); \
-        RS[3] = 0x00020000u;                                                                 \
-    }
+// Keeps a wave-uniform value in scalar registers (left to itself the compiler does the descriptor arithmetic on the
+// vector ALU, with a 16-cycle multiplication per word).
+__device__ __forceinline__ void scalar(uint32_t& x) { x = __builtin_amdgcn_readfirstlane(x); asm volatile("" : "+s"(x)); }
+__device__ __forceinline__ void scalar(int& x) { x = __builtin_amdgcn_readfirstlane(x); asm volatile("" : "+s"(x)); }
+
+// Byte offset of a K/V row, as two words.
+struct RowOffset { uint32_t lo, hi; };
+__device__ __forceinline__ RowOffset row_offset(const int row, const uint32_t row_bytes) {   // (row counts fit 31 bits)
+    RowOffset r;
+    const int row_s = __builtin_amdgcn_readfirstlane(row);
+    asm("s_mul_i32 %0, %1, %2" : "=s"(r.lo) : "s"(row_s), "s"(row_bytes));
+    asm("s_mul_hi_u32 %0, %1, %2" : "=s"(r.hi) : "s"(row_s), "s"(row_bytes));
+    return r;
+}
+// descriptor of a tile of `rows` valid rows at offset `off` of K or V (rows 0: empty)
+__device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off, const uint32_t rows, const uint32_t row_bytes) {
+    const uint64_t s = reinterpret_cast<uint64_t>(src);
+    uint32_t lo, hi, size;
+    asm("s_add_u32 %0, %2, %4\n\ts_addc_u32 %1, %3, %5\n\ts_and_b32 %1, %1, 0xffff"       // stride 0: raw buffer
+        : "=&s"(lo), "=&s"(hi) : "s"(off.lo), "s"(off.hi), "s"(static_cast<uint32_t>(s)), "s"(static_cast<uint32_t>(s >> 32)) : "scc");
+    const uint32_t rows_s = __builtin_amdgcn_readfirstlane(rows);
+    asm("s_mul_i32 %0, %1, %2" : "=s"(size) : "s"(rows_s), "s"(row_bytes));
+    return u32x4{lo, hi, size, 0x00020000u};
+}
 // this wave's piece Q (0 .. PIECES - 1) of a tile into the stage at byte offset DST
 #define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) / PPS) * SLAB + ((Q) % PPS) * 1024, off.g[Q])
-#define PK_COPY_TILE(SRC, KSTART, DST, ENABLED)                                              \
-    {                                                                                        \
-        PK_TILE_DESC(rs_, SRC, KSTART, ENABLED)                                              \
-        _Pragma("unroll") for (int q = 0; q < PIECES; ++q) PK_COPY_PIECE(rs_, DST, q);       \
-    }
+#define PK_COPY_TILE(RS, DST)                                                                \
+    { _Pragma("unroll") for (int q = 0; q < PIECES; ++q) PK_COPY_PIECE(RS, DST, q); }
 #define PK_WAIT_ALL_COPIES() __builtin_amdgcn_s_waitcnt(0x0F70)      /* vmcnt(0) */
 #define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
 
@@ -549,12 +559,16 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     bf16x8 qf[KS];
     if (!setup(a, block, u, off, qf)) return;
     const int n_kv = u.n_kv;
-    const __attribute__((address_space(4))) int32_t* kvt_c =
-        (const __attribute__((address_space(4))) int32_t*)(u.kvt);
-    auto entry = [&](int j, int& ks, int& info) {   // scalar loads; indices past the end are clamped
-        const int jj = j < n_kv ? j : n_kv - 1;
-        ks = kvt_c[2 * jj]; info = kvt_c[2 * jj + 1];
+    // The key-tile list, 64 entries at a time, one per lane: the loop takes the next entry out with v_readlane.  (A
+    // scalar load shares its counter with the LDS reads and returns out of order: the wait for it drained the
+    // operand ring, on the critical path of every tile.)
+    int cur_s, cur_i, nxt_s, nxt_i;
+    auto load_chunk = [&](int first, int& ks, int& info) {
+        const int2 e = reinterpret_cast<const int2*>(u.kvt)[min(first + u.lane, n_kv - 1)];
+        ks = e.x; info = e.y;
     };
+    load_chunk(0, cur_s, cur_i);
+    load_chunk(64, nxt_s, nxt_i);
 
     floatx16 o[DB];
 #pragma unroll
@@ -570,13 +584,25 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 
     // this wave's 16 rows of a slab, as a scalar
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * RPW * SLAB_ROWB);
-    // window of tile-list entries: e0 = tile j, e1 = tile j+1, e2 = tile j+2 (e3 is fetched for the next turn)
-    int e0s, e0i, e1s, e1i, e2s, e2i;
-    entry(0, e0s, e0i); entry(1, e1s, e1i); entry(2, e2s, e2i);
-    // prologue: K(0), K(1), V(0), from the key rows in the descriptor (the entries above arrive meanwhile)
-    PK_COPY_TILE(a.k, u.ks0, 0, true);
-    PK_COPY_TILE(a.k, u.ks1, TILE_BYTES, 1 < n_kv);
-    PK_COPY_TILE(a.v, u.ks0, 3 * TILE_BYTES, true);
+    // window of tile-list entries: e0 = tile j, e1 = tile j+1, e2 = tile j+2; what the loop copies in tile j is
+    // K(j+2) and V(j+1)
+    int e0s = u.ks[0], e0i = u.info[0], e1i = u.info[1], e1s = u.ks[1], e2s = u.ks[2], e2i = u.info[2];
+    scalar(e0s); scalar(e0i); scalar(e1s); scalar(e1i); scalar(e2s); scalar(e2i);
+    uint32_t row_bytes = u.row_bytes32;
+    scalar(row_bytes);
+    auto valid_rows = [&](int info, int tile) { return tile < n_kv ? static_cast<uint32_t>(info & 0xFF) : 0u; };
+    // prologue: K(0), K(1), V(0), from the descriptor
+    {
+        const u32x4 rk0 = tile_desc(a.k, row_offset(e0s, row_bytes), valid_rows(e0i, 0), row_bytes);
+        PK_COPY_TILE(rk0, 0)
+        const u32x4 rk1 = tile_desc(a.k, row_offset(e1s, row_bytes), valid_rows(e1i, 1), row_bytes);
+        PK_COPY_TILE(rk1, TILE_BYTES)
+        const u32x4 rv0 = tile_desc(a.v, row_offset(e0s, row_bytes), valid_rows(e0i, 0), row_bytes);
+        PK_COPY_TILE(rv0, 3 * TILE_BYTES)
+    }
+    RowOffset off2 = row_offset(e2s, row_bytes);             // of tile j+2
+    u32x4 rs_k = tile_desc(a.k, off2, valid_rows(e2i, 2), row_bytes);
+    u32x4 rs_v = tile_desc(a.v, row_offset(e1s, row_bytes), valid_rows(e1i, 1), row_bytes);
     PK_WAIT_ALL_COPIES();
     __syncthreads();
     clear_absent_rows(u, qf);
@@ -597,31 +623,46 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // Two heads per workgroup: the wave of a SIMD that has vector work to do goes first, the one in a phase of
     // nothing but MFMAs fills in (70B-shaped chunks 11.03 -> 10.87 ms; with four waves 1 % at most).
 #define PK_PRIO(P) if constexpr (WAVES > 4) __builtin_amdgcn_s_setprio(P)
-#define PK_TILE_BEGIN()                                                                       \
-    PK_TILE_DESC(rs_k, a.k, e2s, j + 2 < n_kv)                                                 \
-    PK_TILE_DESC(rs_v, a.v, e1s, j + 1 < n_kv)
 #define PK_COPY_STEP(I)                                                                       \
     if constexpr ((I) < PIECES) PK_COPY_PIECE(rs_k, k_fill, (I));                              \
     else if constexpr ((I) < 2 * PIECES) PK_COPY_PIECE(rs_v, v_fill, (I) - PIECES);
-    // (the next list entry is fetched right before the barrier: scalar loads and LDS reads share a
-    // counter and return out of order, so the first wait after the fetch drains the operand ring;
-    // here the ring has the whole barrier to land anyway)
+    // The next tile's list entry and descriptors, in four steps that stand between the last MFMAs of a tile: done
+    // behind the barrier they keep all waves of the workgroup from the matrix pipe at once.
+#define PK_ADVANCE(I)                                                                         \
+    if constexpr ((I) == 0) {                                                                  \
+        e3s = __builtin_amdgcn_readlane(cur_s, (j + 3) & 63); e3i = __builtin_amdgcn_readlane(cur_i, (j + 3) & 63); \
+        rs_v = tile_desc(a.v, off2, valid_rows(e2i, j + 2), row_bytes);                    \
+    } else if constexpr ((I) == 1) {                                                           \
+        off2 = row_offset(e3s, row_bytes);                                                             \
+    } else if constexpr ((I) == 2) {                                                           \
+        rs_k = tile_desc(a.k, off2, valid_rows(e3i, j + 3), row_bytes);                    \
+    }
+    // entry j + 3 is the first of the next 64
+#define PK_NEXT_CHUNK()                                                                       \
+    if (((j + 3) & 63) == 0) {                                                                 \
+        cur_s = nxt_s; cur_i = nxt_i;                                                          \
+        load_chunk(j + 3 + 64, nxt_s, nxt_i);                                                  \
+    }
 #define PK_TILE_END()                                                                         \
-    int e3s, e3i;                                                                              \
-    entry(j + 3, e3s, e3i);                                                                    \
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");                              \
     e0s = e1s; e0i = e1i; e1s = e2s; e1i = e2i; e2s = e3s; e2i = e3i;                          \
+    scalar(e0s); scalar(e0i); scalar(e1s); scalar(e1i); scalar(e2s); scalar(e2i);              \
     { const int kc = k_cur; k_cur = k_next; k_next = k_fill; k_fill = kc; }                    \
     { const int vc = v_cur; v_cur = v_fill; v_fill = vc; }
+#define PK_SKIP_TILE()                                                                        \
+    {                                                                                          \
+        int e3s, e3i;                                                                          \
+        _Pragma("unroll") for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); } \
+        PK_NEXT_CHUNK()                                                                        \
+        PK_ADVANCE(0) PK_ADVANCE(1) PK_ADVANCE(2)                                              \
+        PK_TILE_END()                                                                          \
+    }
 
     int j = 0;
     // leading tiles that this wave skips: it only takes part in the copies and in the barriers,
     // then picks up its first operands from the stage that is current by then
     for (; j < u.n_lead; ++j) {
-        PK_TILE_BEGIN();
-#pragma unroll
-        for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); }
-        PK_TILE_END();
+        PK_SKIP_TILE()
     }
     if (u.n_lead > 0) {
         PK_K_ADDRESSES(k_cur)
@@ -633,7 +674,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         const bool masked = PK_CODE(e0i) != 2, special = masked || j == u.n_lead;
         // (keys past the tile's valid count are foreign)
         const int visible = u.lo <= e0s ? min(u.hi - e0s, e0i & 0xFF) : 0;
-        PK_TILE_BEGIN();
+        int e3s, e3i;
         floatx16 s0, s1;
         PK_PRIO(0);
         PK_EIGHT(s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s0, 0, 0, 0);
@@ -659,18 +700,16 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         for (int t = 0; t < 2; ++t)
             p1[t] = __builtin_bit_cast(bf16x8, u32x4{h1.pw[4 * t], h1.pw[4 * t + 1], h1.pw[4 * t + 2], h1.pw[4 * t + 3]});
         // phase 4; its last refills are the first operands of the next tile
+        PK_NEXT_CHUNK()
         PK_K_ADDRESSES(k_next)
         PK_PRIO(0);
         PK_EIGHT(o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p1[i / DB], o[i % DB], 0, 0, 0);
-                 PK_ROW_SUM(p1); PK_REFILL(3 * KS));
+                 PK_ROW_SUM(p1); PK_REFILL(3 * KS); PK_ADVANCE(i));
         PK_TILE_END();
     }
     // trailing tiles that this wave skips: it only takes part in the copies and in the barriers
     for (; j < n_kv; ++j) {
-        PK_TILE_BEGIN();
-#pragma unroll
-        for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); }
-        PK_TILE_END();
+        PK_SKIP_TILE()
     }
     // After the last barrier nobody fills a stage any more, and what is still being read for a tile after
     // the last is not used: quarters of two K and V stages per head stage the waves' output.
@@ -682,11 +721,12 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 
 #undef PK_COPY_TILE
 #undef PK_PRIO
-#undef PK_TILE_DESC
 #undef PK_COPY_PIECE
 #undef PK_COPY_STEP
 #undef PK_SOFTMAX_CHECK
-#undef PK_TILE_BEGIN
+#undef PK_ADVANCE
+#undef PK_NEXT_CHUNK
+#undef PK_SKIP_TILE
 #undef PK_TILE_END
 #undef PK_SLICE
 #undef PK_SLICE2

@@ -327,14 +327,15 @@ void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, Builder
         const int32_t* run = sb.runs.data() + 4 * static_cast<size_t>(sb.run_first[idx]);
         desc.push_back(sb.n_rows[idx] | (nr << 16));
         for (int x = 1; x < 4; ++x) desc.push_back(nr > 0 ? run[x] : 0);
-        // words 8..10: the first key rows of the tile's first three key tiles (the last one repeated
-        // if there are fewer), so that the kernel can request its first K/V tiles without waiting for
-        // a look-up in the key-tile list; the rest pads the descriptor to 64 bytes
-        for (int e = 0; e < 3; ++e) {
-            const int32_t ee = sb.n_kv[idx] > 0 ? std::min(e, sb.n_kv[idx] - 1) : 0;
-            desc.push_back(sb.n_kv[idx] > 0 ? sb.kv[2 * (static_cast<size_t>(sb.kv_first[idx]) + ee)] : 0);
-        }
-        for (int x = 11; x < kTileDescWords; ++x) desc.push_back(0);
+        // words 8..10 and 11..13: first key rows and infos of the tile's first three key tiles (the last one
+        // repeated if there are fewer), so that the kernel can request its first K/V tiles without waiting
+        // for a look-up in the key-tile list; the rest pads the descriptor to 64 bytes
+        for (int word = 0; word < 2; ++word)
+            for (int e = 0; e < 3; ++e) {
+                const int32_t ee = std::min(e, sb.n_kv[idx] - 1);
+                desc.push_back(ee >= 0 ? sb.kv[2 * (static_cast<size_t>(sb.kv_first[idx]) + ee) + word] : 0);
+            }
+        for (int x = 14; x < kTileDescWords; ++x) desc.push_back(0);
         more_first.push_back(static_cast<int32_t>(more.size() / 4));
         if (nr > 1) more.insert(more.end(), run + 4, run + 4 * static_cast<size_t>(nr));
         kv.insert(kv.end(), sb.kv.begin() + 2 * sb.kv_first[idx], sb.kv.begin() + 2 * (sb.kv_first[idx] + sb.n_kv[idx]));
