@@ -13,6 +13,7 @@
 // two tiles 11.05 ms.  The slots that decode workgroups take cost half a millisecond, streaming 17.9 GB
 // next to the prefill tiles the other one (2.9 ms when nothing else runs).
 #include "decode_body.hip.h"
+#define PK_HEADS 1
 #define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
@@ -24,6 +25,7 @@
 #include "prefill_body.hip.h"
 #undef PK_D
 #undef PK_DNS
+#undef PK_HEADS
 #undef PK_WAVES
 
 namespace pk {
@@ -57,8 +59,8 @@ __device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& de
 }
 
 // one kernel per head dimension (NS: the namespace of the prefill body, D: the head dimension)
-#define PK_MIXED_STEP_KERNEL(NAME, NS, D)                                                            \
-    __global__ __launch_bounds__(256, 2) void NAME(PrefillArgs pa, DecodeArgs da, MixedOrder m) {     \
+#define PK_MIXED_STEP_KERNEL(NAME, NS, D, WPE)                                                       \
+    __global__ __launch_bounds__(256, WPE) void NAME(PrefillArgs pa, DecodeArgs da, MixedOrder m) {     \
         __shared__ __align__(1024) unsigned char lds[5 * NS::TILE_BYTES];                             \
         const int x = static_cast<int>(blockIdx.x);                                                  \
         bool decode;                                                                                 \
@@ -73,8 +75,8 @@ __device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& de
         }                                                                                            \
         if (block < m.n_prefill) NS::prefill_tile_body(pa, block, lds);                              \
     }
-PK_MIXED_STEP_KERNEL(mixed_step_kernel, d128, 128)
-PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64)
+PK_MIXED_STEP_KERNEL(mixed_step_kernel, d128, 128, 2)
+PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64, 3)
 #undef PK_MIXED_STEP_KERNEL
 
 }  // namespace

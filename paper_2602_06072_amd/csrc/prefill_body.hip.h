@@ -1,30 +1,36 @@
-// Packed prefill attention, bf16 MFMA, head dimension PK_D = 128 or 64 (Sec. 3.1).  Same tables, same
-// arithmetic and same operand scheme as prefill.hip (S^T = K.Q^T, O^T += V^T.P^T with
-// v_mfma_f32_32x32x16_bf16, one wave per 32 query rows, key tiles of 64), but
+// Packed prefill attention, bf16 MFMA, head dimension PK_D = 128 or 64 (Sec. 3.1).  Same tables and
+// arithmetic as prefill.hip (S^T = K.Q^T, O^T += V^T.P^T, one wave per 32 query rows, key tiles of 64), but
 //   * K/V tiles go HBM/L2 -> LDS directly (buffer_load ... lds, 16 bytes per lane, no staging
 //     registers, hardware bounds check) into slabs of 64 columns; the 16-byte chunks of a row are
 //     XOR-swizzled -- the swizzle is applied on the global side of the copy, so that both the K
 //     row reads (ds_read_b128) and the V transpose reads (ds_read_b64_tr_b16) are free of bank
 //     conflicts;
-//   * a key tile is processed as two halves of 32 keys whose softmax steps are interleaved,
-//     slice by slice, with the MFMAs of the neighbouring phase, and the LDS operand reads run
-//     four MFMAs ahead in a ring of registers: matrix pipe, vector ALU and LDS overlap inside
-//     one wave, with no state crossing tiles except the accumulators;
-//   * copies are requested one tile ahead for V and two for K; one barrier per tile.
+//   * a key tile is processed as two halves of 32 keys, in a software pipeline: the softmax of one half is dealt
+//     over the MFMAs that make the scores of the next half but one and those that take the probabilities of the half
+//     before, and the LDS operand reads run four steps ahead in a ring of registers: matrix pipe,
+//     vector ALU and LDS overlap inside one wave;
+//   * the MFMA is v_mfma_f32_16x16x32_bf16.  Under this load the clock is managed by power, and per flop the 32x32x16
+//     form costs more of it (MFMAs alone on random operands: 1.75 PFLOP/s at 1.70 GHz against 2.07 at 2.02).
 
 // Device code only: included by prefill_pipe.hip (the prefill launch) and by mixed_step.hip (the
-// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4, or 8 for two
-// query heads of a KV head per workgroup) and PK_DNS (the namespace this instance goes into) first; the
+// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_HEADS (query heads of a KV
+// head that one wave works on: 1 or 2) and PK_DNS (the namespace this instance goes into) first; the
 // file may be included once per combination.
-// With PK_D = 64 a tile is 8 KiB instead of 16 and a
-// half tile four MFMAs instead of eight, each followed by two softmax slices instead of one.
 #include <cstdint>
 
 #include "common.hip.h"
 #include "kernels.h"
 
-#if !defined(PK_D) || !defined(PK_DNS) || !defined(PK_WAVES) || (PK_D != 128 && PK_D != 64) || (PK_WAVES != 4 && PK_WAVES != 8)
-#error "define PK_D (128 or 64), PK_WAVES (4 or 8) and PK_DNS before including prefill_body.hip.h"
+#if !defined(PK_D) || !defined(PK_DNS) || !defined(PK_HEADS) || !defined(PK_WAVES) || (PK_D != 128 && PK_D != 64) || (PK_HEADS != 1 && PK_HEADS != 2)
+#error "define PK_D (128 or 64), PK_HEADS (1 or 2) and PK_DNS before including prefill_body.hip.h"
+#endif
+
+// Where the output accumulators live.  With two heads and D = 128 one wave has all 512 registers of its SIMD; the
+// accumulation registers take the 144 that only MFMAs touch.
+#if PK_D == 128 && PK_HEADS == 2
+#define PK_OUT(X) "+a"(X)
+#else
+#define PK_OUT(X) "+v"(X)
 #endif
 
 namespace pk {
@@ -34,47 +40,50 @@ namespace PK_DNS {
 constexpr int BM = 128, BN = 64, D = PK_D;
 constexpr int ROWB = D * 2;                        // bytes per K/V row in global memory
 constexpr int TILE_BYTES = BN * ROWB;              // 16 KiB (8 KiB for D = 64)
-constexpr int KS = D / 16, DB = D / 32;
-constexpr int WAVES = PK_WAVES;
+constexpr int KS = D / 32;                         // contraction steps of a score
+constexpr int OPS = D / 16;                        // LDS operands per half tile, of K (two blocks of 16 keys x KS) as of V (blocks of 16 columns)
+constexpr int HEADS = PK_HEADS, NC = 2 * HEADS;    // column blocks of a wave: block c holds rows 16 (c & 1) .. + 15 of head c / 2
+constexpr int WAVES = PK_WAVES;                     // 4, or 8: waves 4 .. 7 work on the next head
 constexpr int PIECES = TILE_BYTES / (1024 * WAVES);   // 1-KiB copy instructions per wave and tile
 constexpr int RPW = BN / WAVES, PPS = RPW / 8;        // rows (and copies) of a slab that one wave fills
-constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that take half of a wave's output
+constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that take half of a wave's output for one head
 
 // A stage in LDS is one slab per 64 columns: 64 rows of 128 bytes (eight 16-byte chunks).  Whatever
-// the head dimension, four K and four V addresses per lane then reach every operand with constant
-// offsets, eight additions to the stage's address per key tile; with rows of 256 bytes it took eight of
-// each and 24 additions, every sixth vector instruction of the loop (70B-shaped chunks 11.02 -> 10.91 ms,
-// 8 long prompts with D = 64, where the addresses are carried over the tile now, 573 -> 565 us).
+// the head dimension, two K and four V addresses per lane then reach every operand with constant
+// offsets, six additions to the stage's address per key tile.
 constexpr int SLAB_ROWB = 128, SLAB = BN * SLAB_ROWB;
 
 typedef bf16x4 __attribute__((address_space(3))) * lds_bf16x4_ptr;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-// Chunk position p of row `row` holds logical chunk p ^ swz(row).  Two 128-byte rows share a line of
-// the 64 banks, so rows of the same parity need eight different values (K row reads of 16
-// consecutive rows), and rows r and r + 2 must differ in bit 2 (the transpose reads take 64 bytes
-// from each of four consecutive rows).
-__device__ __forceinline__ int swz(int row) { const int x = (row >> 1) & 7; return ((x & 1) << 2) | (x >> 1); }
+// Chunk position p of row `row` holds logical chunk p ^ swz(row).  Two 128-byte rows share a line of the 64 banks.  A
+// 16-byte read (K: rows 0 .. 15, lane group g at chunk g) is served in sets of sixteen lanes, of which one takes rows 0 .. 3 and 12 .. 15
+// at an even chunk and rows 4 .. 11 at the odd one next to it: the eight rows of a parity need eight different positions,
+// and those of rows 4 .. 11 pairs 2 i, 2 i + 1.  A transpose read (V) takes 32 bytes, two chunks, from each of eight consecutive
+// rows per 32 lanes: four rows of a parity need different pairs.
+__device__ __forceinline__ int swz(int row) { const int x = (row >> 1) & 7; return (((x & 3) ^ ((x >> 1) & 2)) << 1) | (x >> 2); }
 
 struct LaneOffsets {
-    int k[4];           // K operand read: row n, logical chunk 2 (st & 3) + hlf of a slab
-    int v1[2], v2[2];   // V transpose reads of column block b & 1 of a slab, rows +0..3 and +8..11
+    int k[2];           // K operand read: row n, logical chunk 4 (s & 1) + g of a slab
+    int v[4];           // V transpose reads of column block t & 3 of a slab: rows 4 g .. + 3 (and 16 behind them)
     int g[PIECES];      // global byte offsets of this lane's copy instructions
 };
 
-__device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneOffsets& lo, int kb, int t, int b) {
-    const unsigned char* p = vs + (b >> 1) * SLAB + (32 * kb + 16 * t) * SLAB_ROWB;
-    const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + lo.v1[b & 1]));
-    const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + lo.v2[b & 1]));
-    return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+// A operand of P.V, columns 16 t .. + 15 of V as rows: lane (n, g) holds keys 4 g + j (j < 4) and 16 + 4 g + j - 4 of
+// half tile kb, the order in which the scores of its query leave the S MFMAs.
+__device__ __forceinline__ bf16x4 v_half_operand(const unsigned char* vs, const LaneOffsets& lo, int kb, int t, int half) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(vs + (t >> 2) * SLAB + (32 * kb + 16 * half) * SLAB_ROWB + lo.v[t & 3]));
+}
+__device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneOffsets& lo, int kb, int t) {
+    return __builtin_shufflevector(v_half_operand(vs, lo, kb, t, 0), v_half_operand(vs, lo, kb, t, 1), 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 // What a workgroup works on, and this lane's share of it.
 struct WorkUnit {
-    int head, kvh, n_kv, n_lead, n_active, wave, lane, n, hlf;   // this wave computes key tiles [n_lead, n_active)
+    int head, kvh, n_kv, n_lead, n_active, wave, lane, n, g;   // (first) head; this wave computes key tiles [n_lead, n_active)
     int rows;                          // which 32 of the tile's 128 rows this wave has
     int ks[3], info[3];                // (first key row, info) of the tile's first three key tiles (the last one repeated)
-    int qrow, lo, hi;                  // this lane's query row (-1: padding) and its key range [lo, hi)
+    int qrow[2], lo[2], hi[2];         // this lane's query rows (-1: padding) and their key ranges [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
     uint32_t row_bytes32, total_rows32;  // the same, and the number of K/V rows, as 32-bit scalars
@@ -82,7 +91,7 @@ struct WorkUnit {
 
 // Decodes the workgroup id, loads the row metadata and the Q operand, derives the lane offsets.
 // Returns false for grid padding and for query tiles without key tiles.
-__device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[KS]) {
+__device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[NC][KS]) {
     // Consecutive workgroup ids go round-robin over the 8 XCDs: the workgroups of one (tile, KV head) pair
     // (r of them with one head each, or r / 2 with two) stay on one XCD and adjacent in time, so that its L2
     // serves their K/V tiles.
@@ -101,107 +110,99 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
 #pragma unroll
     for (int x = 0; x < 3; ++x) { u.ks[x] = desc[8 + x]; u.info[x] = desc[11 + x]; }
     const int tid = threadIdx.x;
-    u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
+    u.lane = tid & 63; u.n = u.lane & 15; u.g = u.lane >> 4;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Wave w of every workgroup runs on SIMD w % 4, and the last rows of a causal tile see more key tiles than
-    // the first: the second head, or every other set of 256 workgroups (a set is one per compute unit), deals
-    // the rows in reverse, so that the two waves of a SIMD get as much together as those of any other.
-    const int w4 = u.wave & 3, second = WAVES > 4 ? u.wave >> 2 : 0;
-    u.head = (u.kvh * groups + pair) * (WAVES / 4) + second;
+    // the first: every other set of 256 workgroups (a set is one per compute unit) deals
+    // the rows in reverse, so that the waves of a SIMD get as much together as those of any other.
+    const int w4 = u.wave & 3, second = u.wave >> 2;
+    u.head = ((u.kvh * groups + pair) * (WAVES / 4) + second) * HEADS;
     u.rows = (WAVES > 4 ? second : (block >> 8) & 1) ? 3 - w4 : w4;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
-    prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + u.n, u.qrow, u.lo, u.hi);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+        prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + 16 * c + u.n, u.qrow[c], u.lo[c], u.hi[c]);
     u.row_bytes = static_cast<int64_t>(a.Hkv) * ROWB;
     u.row_bytes32 = static_cast<uint32_t>(a.Hkv) * ROWB;
     u.total_rows32 = static_cast<uint32_t>(a.total_kv_rows);
 
-    const int fl = swz(u.n);
 #pragma unroll
-    for (int st = 0; st < 4; ++st) off.k[st] = u.n * SLAB_ROWB + (((2 * st + u.hlf) ^ fl) << 4);
-    const int i16 = u.lane & 15, gl = (u.lane >> 4) & 1, r4 = i16 >> 2;
-    const int rowl = 4 * u.hlf + r4, byte = (i16 & 1) * 8;
+    for (int s = 0; s < 2; ++s) off.k[s] = u.n * SLAB_ROWB + (((4 * s + u.g) ^ swz(u.n)) << 4);
+    const int row = 4 * u.g + (u.n >> 2);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int c = 4 * b + 2 * gl + ((i16 & 3) >> 1);
-        off.v1[b] = rowl * SLAB_ROWB + ((c ^ swz(rowl)) << 4) + byte;
-        off.v2[b] = (rowl + 8) * SLAB_ROWB + ((c ^ swz(rowl + 8)) << 4) + byte;
-    }
+    for (int t = 0; t < 4; ++t)
+        off.v[t] = row * SLAB_ROWB + (((2 * t + ((u.n & 3) >> 1)) ^ swz(row)) << 4) + (u.n & 1) * 8;
     const int r_in = u.lane >> 3, pos = u.lane & 7;    // a copy instruction takes 8 rows of 8 chunks
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) {
-        const int row = RPW * u.wave + 8 * (q % PPS) + r_in;
-        off.g[q] = static_cast<int>(row * u.row_bytes + u.kvh * ROWB + (q / PPS) * SLAB_ROWB + ((pos ^ swz(row)) << 4));
+        const int crow = RPW * u.wave + 8 * (q % PPS) + r_in;
+        off.g[q] = static_cast<int>(crow * u.row_bytes + u.kvh * ROWB + (q / PPS) * SLAB_ROWB + ((pos ^ swz(crow)) << 4));
     }
-    // Q operand: lane (n, hlf) holds Q[row n][16s + 8hlf .. +8], as it is in memory: the MFMAs
+    // Q operand: lane (n, g) holds Q[row n of block c][32s + 8g .. +8], as it is in memory: the MFMAs
     // deliver raw scores, exact products of the bf16 inputs summed in fp32.  Only requested here;
-    // the first K/V copies follow at once, so that the two round trips to memory overlap.  Lanes without
+    // the first K copies follow at once, so that the two round trips to memory overlap.  Lanes without
     // a query read row 0 and are cleared once it is there (clear_absent_rows).
-    const uint16_t* qp = static_cast<const uint16_t*>(a.q) +
-                         (static_cast<int64_t>(u.qrow < 0 ? 0 : u.qrow) * a.Hq + u.head) * D + 8 * u.hlf;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 16 * s));
+    for (int c = 0; c < NC; ++c) {
+        const int qrow = u.qrow[c & 1];
+        const uint16_t* qp = static_cast<const uint16_t*>(a.q) +
+                             (static_cast<int64_t>(qrow < 0 ? 0 : qrow) * a.Hq + u.head + c / 2) * D + 8 * u.g;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 32 * s));
+    }
     return true;
 }
 
 // Zeros for the lanes without a query: row 0, which they have read, is another request's and may hold anything.
-__device__ __forceinline__ void clear_absent_rows(const WorkUnit& u, bf16x8 (&qf)[KS]) {
-    if (__builtin_amdgcn_ballot_w64(u.qrow < 0) == 0) return;
+__device__ __forceinline__ void clear_absent_rows(const WorkUnit& u, bf16x8 (&qf)[NC][KS]) {
+    if (__builtin_amdgcn_ballot_w64(u.qrow[0] < 0 || u.qrow[1] < 0) == 0) return;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const u32x4 raw = __builtin_bit_cast(u32x4, qf[s]);
-        qf[s] = __builtin_bit_cast(bf16x8, u.qrow < 0 ? u32x4{0u, 0u, 0u, 0u} : raw);
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const u32x4 raw = __builtin_bit_cast(u32x4, qf[c][s]);
+            qf[c][s] = __builtin_bit_cast(bf16x8, u.qrow[c & 1] < 0 ? u32x4{0u, 0u, 0u, 0u} : raw);
+        }
+}
+
+// 1 / row sum (0 for a row without a visible key)
+__device__ __forceinline__ float row_scale(const float l) { return l == 0.f ? 0.f : 1.f / l; }
+
+// o / l of head `h` to global memory; lane (n, g) owns columns 16t + 4g .. +3 of its two query rows.
+__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const int h, const floatx4 (&o)[NC][OPS], const floatx4 (&l)[NC]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float inv = row_scale(l[2 * h + c][0]);
+        if (u.qrow[c] < 0) continue;
+        float* out = static_cast<float*>(a.out) + (static_cast<int64_t>(u.qrow[c]) * a.Hq + u.head + h) * D + 4 * u.g;
+#pragma unroll
+        for (int t = 0; t < OPS; ++t) {
+            const floatx4 x = o[2 * h + c][t];
+            *reinterpret_cast<float4*>(out + 16 * t) = make_float4(x[0] * inv, x[1] * inv, x[2] * inv, x[3] * inv);
+        }
     }
 }
 
-// 1 / row sum (0 for a row without a visible key, NaN if either lane of the row holds one)
-__device__ __forceinline__ float row_scale(const float l) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
-    const float twice = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    return twice == 0.f ? 0.f : 2.f / twice;
-}
-
-// o / l to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
-__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], const float l) {
-    const float inv = row_scale(l);
-    if (u.qrow < 0) return;
-    const int64_t obase = (static_cast<int64_t>(u.qrow) * a.Hq + u.head) * D;
-#pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const int col = 32 * b + 8 * q4 + 4 * u.hlf;
-            const float x0 = o[b][4 * q4] * inv, x1 = o[b][4 * q4 + 1] * inv;
-            const float x2 = o[b][4 * q4 + 2] * inv, x3 = o[b][4 * q4 + 3] * inv;
-            if (a.out_f32) {
-                *reinterpret_cast<float4*>(static_cast<float*>(a.out) + obase + col) = make_float4(x0, x1, x2, x3);
-            } else {
-                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + obase + col) =
-                    make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
-            }
-        }
-}
-
-// bf16 output through LDS, so that every row leaves as whole 16-byte pieces (four rows of 256
-// bytes, or eight of 128, per store instruction) instead of 8-byte pieces of 32 different rows.
-// The wave uses two pieces of LDS of 16 rows each that belong to it alone (rows 0..15 in qa, rows
-// 16..31 in qb); the 16-byte chunks of a row are XOR-swizzled with the row number, which keeps
+// bf16 output of head `h` through LDS, so that every row leaves as whole 16-byte pieces (four rows of 256
+// bytes, or eight of 128, per store instruction) instead of 8-byte pieces of 16 different rows.
+// The wave uses two pieces of LDS of 16 rows each that belong to it alone (block 0 in qa, block 1
+// in qb); the 16-byte chunks of a row are XOR-swizzled with the row number, which keeps
 // both sides off bank conflicts.
-__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB],
-                                                  const float l, unsigned char* qa, unsigned char* qb) {
+__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const int h, const floatx4 (&o)[NC][OPS],
+                                                  const floatx4 (&l)[NC], unsigned char* qa, unsigned char* qb) {
     constexpr int CPR = D / 8, RPI = 64 / CPR;     // 16-byte chunks per row; rows per store instruction
-    const float inv = row_scale(l);
-    const int rr = u.n & 15;
-    unsigned char* wrow = (u.n < 16 ? qa : qb) + rr * ROWB + 8 * u.hlf;
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
+    for (int c = 0; c < 2; ++c) {
+        const float inv = row_scale(l[2 * h + c][0]);
+        unsigned char* wrow = (c ? qb : qa) + u.n * ROWB + 8 * (u.g & 1);
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {       // columns 32b + 8q4 + 4hlf .. +3: chunk 4b + q4, half hlf
-            const float x0 = o[b][4 * q4] * inv, x1 = o[b][4 * q4 + 1] * inv;
-            const float x2 = o[b][4 * q4 + 2] * inv, x3 = o[b][4 * q4 + 3] * inv;
-            *reinterpret_cast<uint2*>(wrow + (((4 * b + q4) ^ (rr & (CPR - 1))) << 4)) =
-                make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+        for (int t = 0; t < OPS; ++t) {            // columns 16t + 4g .. +3: chunk 2t + g / 2, half g & 1
+            const floatx4 x = o[2 * h + c][t];
+            *reinterpret_cast<uint2*>(wrow + (((2 * t + (u.g >> 1)) ^ (u.n & (CPR - 1))) << 4)) =
+                make_uint2(pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv));
         }
+    }
     // all look-ups and reads before the first store: one by one, each would wait for its own LDS round trips
     const int chunk = u.lane & (CPR - 1);
     int q_row[32 / RPI];
@@ -209,15 +210,15 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
 #pragma unroll
     for (int k = 0; k < 32 / RPI; ++k) {
         const int row = RPI * k + u.lane / CPR, r2 = row & 15;
-        q_row[k] = __shfl(u.qrow, row, 64);
-        v[k] = *reinterpret_cast<const u32x4*>((row < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
+        q_row[k] = __shfl(u.qrow[RPI * k / 16], r2, 64);
+        v[k] = *reinterpret_cast<const u32x4*>((RPI * k < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
     }
     asm volatile("" ::: "memory");                 // (the reads stay before the branches below)
 #pragma unroll
     for (int k = 0; k < 32 / RPI; ++k)
         if (q_row[k] >= 0)
             *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) +
-                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * D + 8 * chunk) = v[k];
+                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head + h) * D + 8 * chunk) = v[k];
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
@@ -235,6 +236,12 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
                  :: "s"(lds_addr), "v"(voffset), "s"(rsrc)
                  : "memory");                       // M0 has no other user in this file
 }
+// The same in two parts, for the loop: the LDS address goes into M0 a step before the copy that uses it, and
+// the descriptor was built in the turn before, so that neither needs wait states (four of them cost a lone wave 20 cycles a copy).
+__device__ __forceinline__ void copy_to(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds_addr) : "memory"); }
+__device__ __forceinline__ void copy_16(const u32x4& rsrc, int voffset) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voffset), "s"(rsrc) : "memory");
+}
 // Keeps a wave-uniform value in scalar registers (left to itself the compiler does the descriptor arithmetic on the
 // vector ALU, with a 16-cycle multiplication per word).
 __device__ __forceinline__ void scalar(uint32_t& x) { x = __builtin_amdgcn_readfirstlane(x); asm volatile("" : "+s"(x)); }
@@ -245,19 +252,29 @@ struct RowOffset { uint32_t lo, hi; };
 __device__ __forceinline__ RowOffset row_offset(const int row, const uint32_t row_bytes) {   // (row counts fit 31 bits)
     RowOffset r;
     const int row_s = __builtin_amdgcn_readfirstlane(row);
-    asm("s_mul_i32 %0, %1, %2" : "=s"(r.lo) : "s"(row_s), "s"(row_bytes));
-    asm("s_mul_hi_u32 %0, %1, %2" : "=s"(r.hi) : "s"(row_s), "s"(row_bytes));
+    asm volatile("s_mul_i32 %0, %1, %2" : "=s"(r.lo) : "s"(row_s), "s"(row_bytes));
+    asm volatile("s_mul_hi_u32 %0, %1, %2" : "=s"(r.hi) : "s"(row_s), "s"(row_bytes));
     return r;
 }
-// descriptor of a tile of `rows` valid rows at offset `off` of K or V (rows 0: empty)
-__device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off, const uint32_t rows, const uint32_t row_bytes) {
+// Descriptor of a tile of `rows` valid rows at offset `off` of K or V (rows 0: empty), in two parts.
+__device__ __forceinline__ void desc_base(u32x4& rs, const void* src, const RowOffset off) {
     const uint64_t s = reinterpret_cast<uint64_t>(src);
-    uint32_t lo, hi, size;
-    asm("s_add_u32 %0, %2, %4\n\ts_addc_u32 %1, %3, %5\n\ts_and_b32 %1, %1, 0xffff"       // stride 0: raw buffer
-        : "=&s"(lo), "=&s"(hi) : "s"(off.lo), "s"(off.hi), "s"(static_cast<uint32_t>(s)), "s"(static_cast<uint32_t>(s >> 32)) : "scc");
+    uint32_t lo, hi;
+    asm volatile("s_add_u32 %0, %2, %4\n\ts_addc_u32 %1, %3, %5\n\ts_and_b32 %1, %1, 0xffff"       // stride 0: raw buffer
+                 : "=&s"(lo), "=&s"(hi) : "s"(off.lo), "s"(off.hi), "s"(static_cast<uint32_t>(s)), "s"(static_cast<uint32_t>(s >> 32)) : "scc");
+    rs[0] = lo; rs[1] = hi; rs[3] = 0x00020000u;
+}
+__device__ __forceinline__ void desc_size(u32x4& rs, const uint32_t rows, const uint32_t row_bytes) {
     const uint32_t rows_s = __builtin_amdgcn_readfirstlane(rows);
-    asm("s_mul_i32 %0, %1, %2" : "=s"(size) : "s"(rows_s), "s"(row_bytes));
-    return u32x4{lo, hi, size, 0x00020000u};
+    uint32_t size;
+    asm volatile("s_mul_i32 %0, %1, %2" : "=s"(size) : "s"(rows_s), "s"(row_bytes));
+    rs[2] = size;
+}
+__device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off, const uint32_t rows, const uint32_t row_bytes) {
+    u32x4 rs;
+    desc_base(rs, src, off);
+    desc_size(rs, rows, row_bytes);
+    return rs;
 }
 // this wave's piece Q (0 .. PIECES - 1) of a tile into the stage at byte offset DST
 #define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) / PPS) * SLAB + ((Q) % PPS) * 1024, off.g[Q])
@@ -267,16 +284,7 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 #define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
 
 // ---------------------------------------------------------------------------------------------
-// Two workgroups of four waves per CU, three with D = 64, or one of eight; five stages of LDS each, three for K and two for V.
-// A key tile is handled as two halves of 32 keys, each with its own online-softmax step, so that
-// within one wave the matrix pipe and the vector ALU overlap without state that crosses tiles:
-//   phase 1   S0 = K(half 0) Q^T      with the requests for V(j+1), K(j+2)   (8 MFMAs + 2 * PIECES copies)
-//   phase 2   S1 = K(half 1) Q^T      with the softmax of S0       (8 MFMAs + vector work)
-//   phase 3   O += V(half 0)^T P0^T   with the softmax of S1       (8 MFMAs + vector work)
-//   phase 4   O += V(half 1)^T P1^T                                (8 MFMAs)
-//   barrier   this wave's copies have landed; every wave is done with the tile
-// The LDS operand reads run four MFMAs ahead, in a ring of four operand registers that carries over
-// the tile boundary (the first operands of tile j + 1 are read during the last MFMAs of tile j).
+// Five stages of LDS per workgroup, three for K and two for V.
 // Softmax state of a query row.  The MFMAs work on Q and K as they are in memory, so a raw score is
 // the exact sum of bf16 products in fp32; one fused multiply-add per score turns it into an exponent
 // of two relative to the row's reference: x = sc * s - m_ref, sc = scale * log2 e.  (Folding sc
@@ -293,20 +301,15 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 //           and the exponents are formed in two steps, (s - far) * sc - kSlack: the rounding of m_ref is
 //           32 octaves at 2^30, and from 2^31 on it would leave rows without a probability or with infinite
 //           ones.  0: m_ref is the reference;
-//   lsum[0] the row sum, over both halves of the wave; NaN once a score that this lane holds has given a
-//           probability that is not a number (a NaN or an infinity in Q or K).
-// Fast path of a half tile (16 scores per lane): p = exp2(x), pairs rounded to bf16, no maximum, no
-// sum.  The sum of a row is left to the matrix pipe: one v_mfma_f32_16x16x32_bf16 per 16 keys
-// whose A operand holds ones where they bring the sum of a query's P into register 0 of both
-// lanes that carry it (row_sum_selector).  It sums the ROUNDED probabilities, the numbers that go into P.V: a
+//   lsum[0] the row sum.
+// Fast path of a half tile (8 scores per lane and column block): p = exp2(x), pairs rounded to bf16, no maximum, no
+// sum.  The sum of a row is left to the matrix pipe: one MFMA per half tile and column block whose A operand is all
+// ones.  It sums the ROUNDED probabilities, the numbers that go into P.V: a
 // probability is taken against a reference that may lie far from the row maximum, so even a
 // dominant one is not a round number, and its rounding error (2^-9 relative) has to cancel between
 // numerator and denominator.  (With the unrounded values in the sum a row that one key dominates is
-// off by 1.4e-2, with the rounded ones by 5e-3, measured.)  A v_dot2_f32_bf16 per pair gives the same
-// sum but costs as much as two and a half multiply-adds: in a loop of this kernel's mix (two
-// waves per SIMD) 2.4 ns of 26.6 per 32x32x16 MFMA; the small MFMAs cost under 1.  On the whole kernel:
-// 32 chunks of a 70B-shaped layer 11.85 -> 11.50 ms, 64 ragged prompts 436 -> 416 us, 8 long prompts
-// with D = 64 604 -> 593 us.
+// off by 1.4e-2, with the rounded ones by 5e-3, measured.)  A column of the MFMAs is one query, so a probability that is
+// not a number (a NaN or an infinity in Q or K) reaches the row that sees it and no other.
 // Whether the reference is still good shows in the exponent bits of the packed pairs: if any
 // probability is 2 or more (bit 14 of a bf16) the whole wave redoes the half tile on the slow path below,
 // which finds the maximum, moves the reference and rescales what has been accumulated.  Scores that
@@ -314,24 +317,14 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 // turn comes.
 struct HalfSoftmax {
     uint32_t any;                                  // all packed pairs or'ed together
-    uint32_t pw[8];
+    uint64_t slow;                                 // lanes that ask for the slow path
+    uint32_t pw[4 * NC];                           // pairs of column block c: 4 c .. 4 c + 3
 };
 constexpr float kSlack = 12.f;                     // a fresh reference lies this far above the row maximum
 constexpr float kRaiseBy = 8.f;                    // a set reference is only raised by more than this
 constexpr float kNear = 16777216.f;                // below it fp32 rounds a reference by at most half an octave
 constexpr float kUnset = -__FLT_MAX__, kNoRow = 1e30f;   // (kUnset lies below every scaled score that fp32 can hold)
 constexpr uint32_t kTooLarge = 0x40004000u;        // a bf16 of 2 or more in either half
-
-// A operand of the row-sum MFMA.  The B operand is P as the 32x32x16 MFMA takes it: lane l holds
-// eight keys of query l & 31.  Seen as the operand of a 16x16x32 MFMA its lane group g = l / 16 is
-// column l & 15, contraction block g; queries 0..15 sit in blocks 0 and 2, queries 16..31 in blocks
-// 1 and 3.  Lane l receives rows 4 (l / 16) .. + 3 of its column: row 4 g takes the ones of the
-// blocks with g's parity, the other rows are zero.
-__device__ __forceinline__ bf16x8 row_sum_selector(int lane) {
-    const int row = lane & 15, block = lane >> 4;
-    const uint32_t w = (row & 3) == 0 && ((row >> 2) & 1) == (block & 1) ? 0x3F803F80u : 0u;
-    return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
-}
 
 // max without the canonicalising self-maximum that fmaxf() costs per operand (scores are never NaN;
 // -inf is ordinary here).  Not volatile: the compiler schedules these like any arithmetic.
@@ -346,34 +339,51 @@ __device__ __forceinline__ float max2f(float a, float b) {
     return r;
 }
 
-// Slice C (0..7) of the fast path: pair C of the half tile, in two stages, so that the conversion
-// never waits for its exponentials: stage A (fma, exp) right behind MFMA C, stage B (round, pack)
-// behind MFMA C + 1 (1.4 % on the whole kernel; a third stage between fma and exp: nothing).
-template <int C>
-__device__ __forceinline__ floatx2 slice_a(const floatx16& s, const float sc, const float m_ref) {
-    floatx2 pp;
-    pp[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * C], sc, -m_ref));
-    pp[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * C + 1], sc, -m_ref));
-    return pp;
-}
-template <int C>
-__device__ __forceinline__ void slice_b(const floatx2 pp, HalfSoftmax& h) {
-    h.pw[C] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
-    if constexpr (C == 0) h.any = h.pw[0];
-    else if constexpr (C == 7) h.any |= h.pw[7];
-    else if constexpr ((C & 1) == 0) h.any |= h.pw[C - 1] | h.pw[C];    // one v_or3_b32 every other slice
+// The fast path of a half tile is dealt over the SLOTS MFMAs of a part, what stands behind MFMA `slot` here: an MFMA keeps
+// the matrix pipe for 16 cycles, and a wave that has the next one ready stands there until it is free, so that what follows
+// a run of MFMAs overlaps with the last of them only.  Of a lone wave one instruction behind each MFMA is free, every
+// further one costs four cycles (an exponential and a multiply-add behind the same one: also with two waves).
+// The scores are through SPARE slots before the end and a pair is converted two slots behind its exponentials: neither
+// the conversion nor the branch at the end waits for results.  Score e of a
+// lane is element e & 3 of key block (e >> 2) & 1 of column block e >> 3.
+typedef floatx4 Scores[NC][2];
+struct Pending { float x[8]; };                    // exponents, then exponentials that are not packed yet
+template <int SLOTS, int SPARE>
+__device__ __forceinline__ void softmax_slot(const int slot, const Scores& s, const float sc, const float (&m_ref)[NC], Pending& p, HalfSoftmax& h) {
+    constexpr int SCORES = 8 * NC;
+    static_assert(SPARE == 0 || (SCORES - 1) * (SLOTS - SPARE) / SCORES + 3 < SLOTS, "every pair is packed before the part ends");
+    auto last = [](int at) { return at < SLOTS ? at : SLOTS; };
+#pragma unroll
+    for (int e = 0; e < SCORES; ++e) {
+        const int at = e * (SLOTS - SPARE) / SCORES;
+        if (e % 2 == 1 && last(at + 3) == slot) {
+            const int k = e / 2;
+            asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(h.pw[k]) : "v"(p.x[(e - 1) & 7]), "v"(p.x[e & 7]));
+            if (k == 2) asm volatile("v_or3_b32 %0, %1, %2, %3" : "=v"(h.any) : "v"(h.pw[0]), "v"(h.pw[1]), "v"(h.pw[2]));
+            else if (k > 2 && k % 2 == 0) asm volatile("v_or3_b32 %0, %0, %1, %2" : "+v"(h.any) : "v"(h.pw[k - 1]), "v"(h.pw[k]));
+            else if (k == SCORES / 2 - 1) asm volatile("v_or_b32 %0, %0, %1" : "+v"(h.any) : "v"(h.pw[k]));
+        }
+        if (at == slot)
+            asm volatile("v_fma_f32 %0, %1, %2, -%3\n\tv_exp_f32 %0, %0"
+                         : "=v"(p.x[e & 7]) : "v"(s[e >> 3][(e >> 2) & 1][e & 3]), "s"(sc), "v"(m_ref[e >> 3]));
+    }
+    if (slot == (SPARE > 0 ? SLOTS - 1 : SLOTS)) {
+        h.slow = __builtin_amdgcn_ballot_w64((h.any & kTooLarge) != 0);
+        asm volatile("" : "+s"(h.slow));
+    }
 }
 
-__device__ __forceinline__ float row_max(const floatx16& s) {      // both lanes of a row agree through the swap
-    float mx = max3f(max3f(max3f(max2f(s[0], s[1]), s[2], s[3]), s[4], s[5]), s[6], s[7]);
-    mx = max3f(max3f(max3f(max3f(mx, s[8], s[9]), s[10], s[11]), s[12], s[13]), s[14], s[15]);
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    return max2f(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+__device__ __forceinline__ float row_max(const floatx4 (&s)[2]) {   // the four lanes of a row agree through the swaps
+    float mx = max3f(max3f(max3f(max2f(s[0][0], s[0][1]), s[0][2], s[0][3]), s[1][0], s[1][1]), s[1][2], s[1][3]);
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = max2f(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return max2f(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 // A wave's first half tile: nothing has been accumulated, so the rows that see a key here take their
 // reference before the exponentials (on the slow path they would be computed twice and the 64
 // accumulators, all zero, rescaled: 0.4 us of vector work per query tile).  Far references are left to the slow path.
-__device__ __forceinline__ void first_reference(const floatx16& s, const float sc, float& m_ref) {
+__device__ __forceinline__ void first_reference(const floatx4 (&s)[2], const float sc, float& m_ref) {
     const float fresh = __builtin_fmaf(row_max(s), sc, kSlack);
     if (__builtin_fabsf(fresh) < kNear) m_ref = max2f(m_ref, fresh);
 }
@@ -386,7 +396,7 @@ __device__ __forceinline__ void first_reference(const floatx16& s, const float s
 // with the 64 accumulators in fresh registers, more than the kernel has.
 // On this path a reference is far * sc + offset_of(m_ref, far), whichever of the two kinds it is.
 __device__ __forceinline__ float offset_of(const float m_ref, const float far) { return far == 0.f ? m_ref : kSlack; }
-__device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const float sc, float& m_ref, float& far, float& alpha) {
+__device__ __forceinline__ void softmax_slow_scalars(const floatx4 (&s)[2], const float sc, float& m_ref, float& far, float& alpha) {
     const float mx = row_max(s);                   // -inf for a row without a visible key here
     const float far0 = far, offset0 = offset_of(m_ref, far);
     if (__builtin_fmaf(mx - far, sc, -offset0) > kRaiseBy - kSlack) {
@@ -397,158 +407,164 @@ __device__ __forceinline__ void softmax_slow_scalars(const floatx16& s, const fl
     }
     alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(far0 - far, sc, offset0 - offset_of(m_ref, far)));
 }
-__device__ __forceinline__ void softmax_redo(const floatx16& s, HalfSoftmax& h, const float sc, const float m_ref, const float far,
-                                             const float alpha, floatx4& lsum) {
+__device__ __forceinline__ void softmax_redo(const floatx4 (&s)[2], uint32_t* pw, const float sc, const float m_ref, const float far) {
     const float offset = offset_of(m_ref, far);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        floatx2 pp;
-        pp[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q] - far, sc, -offset));
-        pp[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * q + 1] - far, sc, -offset));
-        h.pw[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
+    for (int k = 0; k < 4; ++k) {
+        const float s0 = s[k >> 1][2 * (k & 1)], s1 = s[k >> 1][2 * (k & 1) + 1];
+        pw[k] = pack_bf16x2(__builtin_amdgcn_exp2f(__builtin_fmaf(s0 - far, sc, -offset)),
+                            __builtin_amdgcn_exp2f(__builtin_fmaf(s1 - far, sc, -offset)));
     }
-    // With its reference in place a row's probabilities are below 2, unless one is a NaN.  None may reach the row-sum
-    // MFMA, whose columns hold two queries and keep them apart by a factor of zero: the NaN goes to the lane's row sum
-    // instead, and to no other row.
-    uint32_t any = 0;
+}
+// (The statements around the products keep them in place: the compiler would otherwise put the rescaled accumulators into fresh
+// registers, more than there are.)
+__device__ __forceinline__ void rescale(floatx4& x, const float alpha) {
+    asm volatile("" : PK_OUT(x));
 #pragma unroll
-    for (int q = 0; q < 8; ++q) any |= h.pw[q];
-    const bool bad = (any & kTooLarge) != 0;
-    lsum[0] = bad ? __builtin_nanf("") : lsum[0] * alpha;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) h.pw[q] = bad ? 0u : h.pw[q];
+    for (int e = 0; e < 4; ++e) x[e] *= alpha;
+    asm volatile("" : PK_OUT(x));
 }
 #define PK_SOFTMAX_CHECK(S, H)                                                                 \
-    {                                                                                          \
-        const bool slow = __builtin_amdgcn_ballot_w64((H.any & kTooLarge) != 0) != 0;          \
-        float alpha = 1.f;                                                                     \
-        /* the empty asm statements keep the compiler from computing the rare branches always */ \
-        if (slow) { asm volatile(""); softmax_slow_scalars(S, sc, m_ref, far, alpha); }        \
-        if (slow) { asm volatile(""); softmax_redo(S, H, sc, m_ref, far, alpha, lsum); }       \
-        if (slow) {                                                                            \
-            _Pragma("unroll") for (int b = 0; b < DB; ++b)                                     \
-                _Pragma("unroll") for (int e = 0; e < 16; ++e) o[b][e] *= alpha;               \
+    if (H.slow != 0) {                                                                         \
+        float alpha[NC];                                                                       \
+        PK_MFMA_RESULTS()                                                                      \
+        _Pragma("unroll") for (int c = 0; c < NC; ++c) softmax_slow_scalars(S[c], sc, m_ref[c], far[c], alpha[c]); \
+        _Pragma("unroll") for (int c = 0; c < NC; ++c) softmax_redo(S[c], H.pw + 4 * c, sc, m_ref[c], far[c]); \
+        _Pragma("unroll") for (int c = 0; c < NC; ++c) {                                       \
+            rescale(lsum[c], alpha[c]);                                                        \
+            _Pragma("unroll") for (int t = 0; t < OPS; ++t) rescale(o[c][t], alpha[c]);        \
         }                                                                                      \
     }
-
-// The compiler is free to move the (side-effect free) softmax arithmetic and the MFMAs of a phase
-// apart again.  Two empty volatile asm statements per slice tie them together: the first makes the
-// slice's inputs depend on the point after MFMA i, the second makes the operand of MFMA i+1 depend
-// on the point after the slice's results.
-template <int C>
-__device__ __forceinline__ void pin_slice_inputs(floatx16& acc, floatx16& s) {
-    // (not after the first MFMA of a chain: tying its fresh result to the statement makes the
-    // compiler copy the sixteen start values into it instead of naming them as the C operand)
-    if constexpr (C == 0) asm volatile("" : "+v"(s));
-    else asm volatile("" : "+v"(acc), "+v"(s));
-}
-template <int C>
-__device__ __forceinline__ void pin_slice_outputs(bf16x8& next_operand, HalfSoftmax& h) {
-    asm volatile("" : "+v"(next_operand), "+v"(h.pw[C]));
-}
 
 // -inf for the keys of half `half` of a tile that a query row may not see.  A key tile lies inside the
 // keys of one request, so a row either sees it from its first key on (up to its causal limit) or, being
 // another request's, not at all: `visible` counts the tile's keys, from the first, that it sees.
-__device__ __forceinline__ void mask_half(floatx16& s, int half, int visible, int hlf) {
-    const int left = visible - 4 * hlf - 32 * half;
+__device__ __forceinline__ void mask_half(Scores& s, int half, const int (&visible)[2], int g) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        if (left <= 8 * (e >> 2) + (e & 3)) s[e] = -INFINITY;
-        asm volatile("" : "+v"(s[e]));   // ties the selects to this place, behind the caller's branch
+    for (int c = 0; c < NC; ++c) {
+        const int left = visible[c & 1] - 4 * g - 32 * half;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (left <= 16 * k + j) s[c][k][j] = -INFINITY;
+            asm volatile("" : "+v"(s[c][k]));   // ties the selects to this place, behind the caller's branch
+        }
     }
 }
 
-// operand x (0..7) of a half tile: K rows of contraction step x; V^T block (t, b) = (x / 4, x % 4)
-__device__ __forceinline__ bf16x8 k_operand(const unsigned char* const (&kp)[4], int half, int x) {
-    return *reinterpret_cast<const bf16x8*>(kp[x & 3] + (x >> 2) * SLAB + half * 32 * SLAB_ROWB);
+// K operand x (0 .. OPS - 1) of a half tile: rows of key block x & 1, contraction step x / 2 (the two chains of
+// scores take turns)
+__device__ __forceinline__ bf16x8 k_operand(const unsigned char* const (&kp)[2], int half, int x) {
+    const int s = x >> 1;
+    return *reinterpret_cast<const bf16x8*>(kp[s & 1] + (s >> 1) * SLAB + (half * 32 + (x & 1) * 16) * SLAB_ROWB);
 }
-__device__ __forceinline__ bf16x8 v_operand_x(const unsigned char* vs, const LaneOffsets& lo, int half, int x) {
-    return v_operand(vs, lo, half, x / DB, x % DB);
+// Order of a part's 2 * OPS steps, one LDS operand and NC MFMAs each: of the scores (operand K) and of P.V (operand V).  Part A
+// starts with four K operands, which can be read before the barrier that publishes the V tile; otherwise the two kinds
+// take turns.
+constexpr int NM = 2 * OPS;
+constexpr int SPARE = D == 128 ? 2 * NC : 4;       // slots of a part behind its last score (at least four: softmax_slot)
+constexpr bool op_is_v(int part, int m) {
+    return part == 0 ? m >= 4 && (m >= NM - 4 || (m - 4) % 2 == 0) : m % 2 == 1;
 }
-// Operand stream of a tile (KS operands per half tile; shown for D = 128): 0..7 K(half 0), 8..15
-// K(half 1), 16..23 V(half 0), 24..31 V(half 1), 32..35 the first K operands of the next tile.
-// MFMA k takes ring[k % 4] and then refills that slot with operand k + 4, so that every LDS read
-// has four MFMAs (and their vector slices) to land.
-template <int K>
-__device__ __forceinline__ bf16x8 stream_operand(const unsigned char* const (&kp)[4], const unsigned char* v_cur,
-                                                 const LaneOffsets& off) {
-    if constexpr (K < 2 * KS) return k_operand(kp, K / KS, K % KS);
-    else if constexpr (K < 4 * KS) return v_operand_x(v_cur, off, (K - 2 * KS) / KS, K % KS);
-    else return k_operand(kp, 0, K - 4 * KS);      // (by then the addresses are those of the next tile)
+constexpr int op_index(int part, int m) {
+    int x = 0;
+    for (int i = 0; i < m; ++i) x += op_is_v(part, i) == op_is_v(part, m);
+    return x;
 }
-// kp: this lane's four K addresses in the stage that is read; they move on to the next stage before
-// phase 4, so that they are computed once per tile
-#define PK_REFILL(K0) ring[i & 3] = stream_operand<(K0) + i + 4>(kp, lds + v_cur, off)
-#define PK_K_ADDRESSES(STAGE) _Pragma("unroll") for (int x = 0; x < 4; ++x) kp[x] = lds + (STAGE) + off.k[x];
-// the row sums of 16 keys, next to the first of the MFMAs that take the same P
-#define PK_ROW_SUM(P) if constexpr (i % DB == 0) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[i / DB], lsum, 0, 0, 0)
-#define PK_SLICE(C, S, H, ACC, BODY)                                                          \
+// piece of PK_ADVANCE behind MFMA c of step m: one each, or one in two, of the last 4 NC MFMAs
+constexpr int advance_at(int m, int c) {
+    const int q = (m - (NM - 4)) * NC + c;
+    return q < 0 || q % (NC / 2) != 0 ? -1 : q / (NC / 2);
+}
+// Operand of step m of part `part` (0: A, 1: B; m >= NM: of the part that follows), or its piece PIECE of two: V operands
+// take two reads, K operands one.  kp: this lane's two K addresses in the stage that is read; by the time the next part
+// A's operands are read they are those of the next stage.
+template <int PART, int M, int PIECE>
+__device__ __forceinline__ void read_operand(bf16x8& op, bf16x4& half, const unsigned char* const (&kp)[2], const unsigned char* v_cur,
+                                             const LaneOffsets& off) {
+    constexpr int part = M < NM ? PART : 1 - PART, m = M < NM ? M : M - NM, x = op_index(part, m);
+    if constexpr (!op_is_v(part, m)) { if constexpr (PIECE == 0) op = k_operand(kp, part, x); }
+    else if constexpr (PIECE == 0) half = v_half_operand(v_cur, off, part, x, 0);
+    else op = __builtin_shufflevector(half, v_half_operand(v_cur, off, part, x, 1), 0, 1, 2, 3, 4, 5, 6, 7);
+}
+#define PK_K_ADDRESSES(STAGE) _Pragma("unroll") for (int x = 0; x < 2; ++x) kp[x] = lds + (STAGE) + off.k[x];
+// The MFMA, in place.  From the builtin the compiler makes the form with a destination of its own, and pays for it with copies
+// of the accumulators wherever two paths join; and it moves the (side-effect free) arithmetic of the softmax and the
+// MFMAs apart again, where the order of volatile statements stays.  What the compiler does not do for a statement is to wait for
+// the result (a vector instruction may read it twelve wait states behind the last MFMA of the chain) and for operands that a
+// vector instruction has written (two wait states).  In the loop other MFMAs are in between; elsewhere
+// PK_MFMA_RESULTS() stands before the first reader and PK_MFMA_OPERANDS() before the MFMA.
+__device__ __forceinline__ void mfma(floatx4& d, const bf16x8& a, const bf16x8& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_out(floatx4& d, const bf16x8& a, const bf16x8& b) {     // (d: output accumulator)
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : PK_OUT(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_first(floatx4& d, const bf16x8& a, const bf16x8& b) {   // d = a.b
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+}
+#define PK_MFMA_OPERANDS() asm volatile("s_nop 1");
+#define PK_MFMA_RESULTS() { asm volatile("s_nop 15"); __builtin_amdgcn_sched_barrier(0); }
+// MFMA c of a step: scores of key block X & 1 / columns 16 X .. + 15 of P.V, and a row sum behind the last of each of the first NC
+template <int X>
+__device__ __forceinline__ void scores_mfma(const int c, Scores& s, const bf16x8& k, const bf16x8 (&qf)[NC][KS]) {
+    if constexpr (X < 2) mfma_first(s[c][X & 1], k, qf[c][X >> 1]);
+    else mfma(s[c][X & 1], k, qf[c][X >> 1]);
+}
+template <int X>
+__device__ __forceinline__ void pv_mfma(const int c, floatx4 (&o)[NC][OPS], floatx4 (&lsum)[NC], const bf16x8& v, const bf16x8 (&p)[NC], const bf16x8& ones) {
+    mfma_out(o[c][X], v, p[c]);
+    if (X < NC && c == NC - 1) mfma_out(lsum[X < NC ? X : 0], ones, p[X < NC ? X : 0]);
+}
+// one step: NC MFMAs (MFMA, in terms of c), each with what stands behind it (SLOT, in terms of c)
+#define PK_SLOT(C, MFMA, ...) if constexpr ((C) < NC) { constexpr int c = C; MFMA; __VA_ARGS__; __builtin_amdgcn_sched_barrier(0); }
+#define PK_SLOTS(MFMA, ...) PK_SLOT(0, MFMA, __VA_ARGS__) PK_SLOT(1, MFMA, __VA_ARGS__) PK_SLOT(2, MFMA, __VA_ARGS__) PK_SLOT(3, MFMA, __VA_ARGS__)
+// M: step of the part; DST: scores in the making; SRC: scores whose softmax is taken, into H; P: probabilities for P.V.  The ring
+// holds operands M .. M + 2, and operand M + 3 replaces that of the step before.
+#define PK_STEP_SLOT(PART, DST, SRC, H, P, EXTRA)                                             \
+    softmax_slot<NM * NC, SPARE>(m * NC + c, SRC, sc, m_ref, pend, H);                         \
+    if constexpr (c == NC - 1) { read_operand<PART, m + 4, 0>(ring[m & 3], ring_half, kp, lds + v_cur, off); read_operand<PART, m + 4, 1>(ring[m & 3], ring_half, kp, lds + v_cur, off); } \
+    EXTRA
+#define PK_STEP(PART, M, DST, SRC, H, P, EXTRA)                                               \
     {                                                                                          \
-        constexpr int i = C;                                                                   \
-        BODY;                                                                                  \
-        pin_slice_inputs<C>(ACC, S);                                                           \
-        if constexpr (C > 0) slice_b<(C > 0 ? C - 1 : 0)>(pend, H);                            \
-        pend = slice_a<C>(S, sc, m_ref);                                                       \
-        asm volatile("" : "+v"(pend));                                                         \
-        pin_slice_outputs<(C > 0 ? C - 1 : 0)>(ring[(C + 1) & 3], H);                          \
+        constexpr int m = M, x = op_index(PART, m);                                            \
+        if constexpr (op_is_v(PART, m)) {                                                      \
+            PK_SLOTS((pv_mfma<x>(c, o, lsum, ring[m & 3], P, ones)), PK_STEP_SLOT(PART, DST, SRC, H, P, EXTRA)) \
+        } else {                                                                               \
+            PK_SLOTS((scores_mfma<x>(c, DST, ring[m & 3], qf)), PK_STEP_SLOT(PART, DST, SRC, H, P, EXTRA)) \
+        }                                                                                      \
     }
+#define PK_FOUR(PART, M, DST, SRC, H, P, EXTRA)                                               \
+    PK_STEP(PART, (M), DST, SRC, H, P, EXTRA) PK_STEP(PART, (M) + 1, DST, SRC, H, P, EXTRA)    \
+    PK_STEP(PART, (M) + 2, DST, SRC, H, P, EXTRA) PK_STEP(PART, (M) + 3, DST, SRC, H, P, EXTRA)
 #if PK_D == 128
-// eight MFMAs (BODY, with accumulator ACC) interleaved with the softmax of the scores S
-#define PK_SLICES(S, H, ACC, BODY)                                                             \
+#define PK_PART(PART, DST, SRC, H, P, EXTRA)                                                  \
     {                                                                                          \
-    floatx2 pend;                                                                              \
-    PK_SLICE(0, S, H, ACC, BODY) PK_SLICE(1, S, H, ACC, BODY) PK_SLICE(2, S, H, ACC, BODY)       \
-    PK_SLICE(3, S, H, ACC, BODY) PK_SLICE(4, S, H, ACC, BODY) PK_SLICE(5, S, H, ACC, BODY)       \
-    PK_SLICE(6, S, H, ACC, BODY) PK_SLICE(7, S, H, ACC, BODY)                                    \
-    slice_b<7>(pend, H);                                                                       \
-    }
-
-#define PK_EIGHT(BODY)                                                                         \
-    {                                                                                          \
-        { constexpr int i = 0; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 1; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 2; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 3; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 4; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 5; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 6; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 7; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
+        Pending pend;                                                                          \
+        PK_FOUR(PART, 0, DST, SRC, H, P, EXTRA) PK_FOUR(PART, 4, DST, SRC, H, P, EXTRA)        \
+        PK_FOUR(PART, 8, DST, SRC, H, P, EXTRA) PK_FOUR(PART, 12, DST, SRC, H, P, EXTRA)       \
     }
 #else
-// D = 64: four MFMAs per half tile, each followed by two of the eight softmax slices
-#define PK_SLICE2(I, S, H, ACC, BODY)                                                          \
+#define PK_PART(PART, DST, SRC, H, P, EXTRA)                                                  \
     {                                                                                          \
-        constexpr int i = I;                                                                   \
-        BODY;                                                                                  \
-        pin_slice_inputs<I>(ACC, S);                                                           \
-        if constexpr ((I) > 0) {                                                               \
-            slice_b<((I) > 0 ? 2 * (I) - 2 : 0)>(pend, H);                                     \
-            slice_b<((I) > 0 ? 2 * (I) - 1 : 1)>(pend2, H);                                    \
-        }                                                                                      \
-        pend = slice_a<2 * (I)>(S, sc, m_ref);                                                 \
-        pend2 = slice_a<2 * (I) + 1>(S, sc, m_ref);                                            \
-        asm volatile("" : "+v"(pend), "+v"(pend2));                                            \
-        pin_slice_outputs<((I) > 0 ? 2 * (I) - 2 : 0)>(ring[((I) + 1) & 3], H);                \
-        pin_slice_outputs<((I) > 0 ? 2 * (I) - 1 : 1)>(ring[((I) + 1) & 3], H);                \
-    }
-#define PK_SLICES(S, H, ACC, BODY)                                                             \
-    {                                                                                          \
-    floatx2 pend, pend2;                                                                       \
-    PK_SLICE2(0, S, H, ACC, BODY) PK_SLICE2(1, S, H, ACC, BODY) PK_SLICE2(2, S, H, ACC, BODY)    \
-    PK_SLICE2(3, S, H, ACC, BODY)                                                              \
-    slice_b<6>(pend, H);                                                                       \
-    slice_b<7>(pend2, H);                                                                      \
-    }
-
-#define PK_EIGHT(BODY)                                                                         \
-    {                                                                                          \
-        { constexpr int i = 0; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 1; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 2; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
-        { constexpr int i = 3; BODY; __builtin_amdgcn_sched_barrier(0); }                      \
+        Pending pend;                                                                          \
+        PK_FOUR(PART, 0, DST, SRC, H, P, EXTRA) PK_FOUR(PART, 4, DST, SRC, H, P, EXTRA)        \
     }
 #endif
+// the OPS steps of one kind at the ends of a wave's tiles, step i
+#define PK_OPS_STEP(I, ...) { constexpr int i = I; __VA_ARGS__; __builtin_amdgcn_sched_barrier(0); }
+#define PK_OPS_FOUR(I, ...) PK_OPS_STEP(I, __VA_ARGS__) PK_OPS_STEP((I) + 1, __VA_ARGS__) PK_OPS_STEP((I) + 2, __VA_ARGS__) PK_OPS_STEP((I) + 3, __VA_ARGS__)
+#if PK_D == 128
+#define PK_OPS_STEPS(...) { PK_OPS_FOUR(0, __VA_ARGS__) PK_OPS_FOUR(4, __VA_ARGS__) }
+#else
+#define PK_OPS_STEPS(...) { PK_OPS_FOUR(0, __VA_ARGS__) }
+#endif
+#define PK_PACK_P(P, H)                                                                       \
+    _Pragma("unroll") for (int c = 0; c < NC; ++c) {                                           \
+        P[c] = __builtin_bit_cast(bf16x8, u32x4{H.pw[4 * c], H.pw[4 * c + 1], H.pw[4 * c + 2], H.pw[4 * c + 3]}); \
+        asm volatile("" : "+v"(P[c]));                                                         \
+    }
 
 // `block`: the workgroup's number in the prefill launch order; `lds`: 5 * TILE_BYTES, 1 KiB aligned
 // (K stages 0..2, V stages 3..4).
@@ -556,184 +572,228 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_ptr)lds));
     WorkUnit u;
     LaneOffsets off;
-    bf16x8 qf[KS];
+    bf16x8 qf[NC][KS];
     if (!setup(a, block, u, off, qf)) return;
     const int n_kv = u.n_kv;
-    // The key-tile list, 64 entries at a time, one per lane: the loop takes the next entry out with v_readlane.  (A
+    // The key-tile list, 64 entries at a time, one per lane: the loop takes entries out with v_readlane.  (A
     // scalar load shares its counter with the LDS reads and returns out of order: the wait for it drained the
-    // operand ring, on the critical path of every tile.)
-    int cur_s, cur_i, nxt_s, nxt_i;
+    // operand ring, on the critical path of every tile.)  Two of them, for the tile whose K is copied
+    // and for the one whose V is copied, two tiles behind: the next 64 entries replace the present ones in place.
+    int lk_s, lk_i, lv_s, lv_i;
     auto load_chunk = [&](int first, int& ks, int& info) {
         const int2 e = reinterpret_cast<const int2*>(u.kvt)[min(first + u.lane, n_kv - 1)];
         ks = e.x; info = e.y;
     };
-    load_chunk(0, cur_s, cur_i);
-    load_chunk(64, nxt_s, nxt_i);
+    load_chunk(0, lk_s, lk_i);
+    lv_s = lk_s; lv_i = lk_i;
 
-    floatx16 o[DB];
+    floatx4 o[NC][OPS], lsum[NC];
+    float m_ref[NC], far[NC];
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
+    for (int c = 0; c < NC; ++c) {
+        m_ref[c] = u.qrow[c & 1] < 0 ? kNoRow : kUnset;   // rows without a query never ask for the slow path
+        far[c] = 0.f;
+        lsum[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 16; ++e) o[b][e] = 0.f;
-    float m_ref = u.qrow < 0 ? kNoRow : kUnset;    // rows without a query never ask for the slow path
-    float far = 0.f;
-    floatx4 lsum = {0.f, 0.f, 0.f, 0.f};
-    const bf16x8 ones = row_sum_selector(u.lane);
-    const floatx16 zero16 = {};
+        for (int t = 0; t < OPS; ++t) o[c][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
+    asm volatile("" : "+v"(ones));                 // (not made again right before its MFMA)
     const float sc = a.scale * kLog2e;             // raw score -> exponent of two (the API admits only finite scale > 0)
 
     // this wave's 16 rows of a slab, as a scalar
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * RPW * SLAB_ROWB);
-    // window of tile-list entries: e0 = tile j, e1 = tile j+1, e2 = tile j+2; what the loop copies in tile j is
-    // K(j+2) and V(j+1)
-    int e0s = u.ks[0], e0i = u.info[0], e1i = u.info[1], e1s = u.ks[1], e2s = u.ks[2], e2i = u.info[2];
-    scalar(e0s); scalar(e0i); scalar(e1s); scalar(e1i); scalar(e2s); scalar(e2i);
     uint32_t row_bytes = u.row_bytes32;
     scalar(row_bytes);
     auto valid_rows = [&](int info, int tile) { return tile < n_kv ? static_cast<uint32_t>(info & 0xFF) : 0u; };
-    // prologue: K(0), K(1), V(0), from the descriptor
+    // prologue: K(0), K(1), from the descriptor; the first turn copies K(2) and V(0)
     {
-        const u32x4 rk0 = tile_desc(a.k, row_offset(e0s, row_bytes), valid_rows(e0i, 0), row_bytes);
+        const u32x4 rk0 = tile_desc(a.k, row_offset(u.ks[0], row_bytes), valid_rows(u.info[0], 0), row_bytes);
         PK_COPY_TILE(rk0, 0)
-        const u32x4 rk1 = tile_desc(a.k, row_offset(e1s, row_bytes), valid_rows(e1i, 1), row_bytes);
+        const u32x4 rk1 = tile_desc(a.k, row_offset(u.ks[1], row_bytes), valid_rows(u.info[1], 1), row_bytes);
         PK_COPY_TILE(rk1, TILE_BYTES)
-        const u32x4 rv0 = tile_desc(a.v, row_offset(e0s, row_bytes), valid_rows(e0i, 0), row_bytes);
-        PK_COPY_TILE(rv0, 3 * TILE_BYTES)
     }
-    RowOffset off2 = row_offset(e2s, row_bytes);             // of tile j+2
-    u32x4 rs_k = tile_desc(a.k, off2, valid_rows(e2i, 2), row_bytes);
-    u32x4 rs_v = tile_desc(a.v, row_offset(e1s, row_bytes), valid_rows(e1i, 1), row_bytes);
-    PK_WAIT_ALL_COPIES();
-    __syncthreads();
+    u32x4 rs_k = tile_desc(a.k, row_offset(u.ks[2], row_bytes), valid_rows(u.info[2], 2), row_bytes);
+    u32x4 rs_v = tile_desc(a.v, row_offset(u.ks[0], row_bytes), valid_rows(u.info[0], 0), row_bytes);
+    int cur_s = u.ks[0], cur_i = 0, nxt_s = u.ks[0], nxt_i = u.info[0];   // list entries of tiles t and t + 1
+    scalar(cur_s); scalar(cur_i); scalar(nxt_s); scalar(nxt_i);
+#define PK_WAIT_AND_MEET() asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : "+v"(lk_s), "+v"(lk_i), "+v"(lv_s), "+v"(lv_i) :: "memory")
+    PK_WAIT_AND_MEET();
     clear_absent_rows(u, qf);
 
-    bf16x8 ring[4];                                 // LDS operands of the next four MFMAs
-    const unsigned char* kp[4];
-    PK_K_ADDRESSES(0)
-#pragma unroll
-    for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
-    int k_cur = 0, k_next = TILE_BYTES, k_fill = 2 * TILE_BYTES;   // K stage read now / next / filled now
-    int v_cur = 3 * TILE_BYTES, v_fill = 4 * TILE_BYTES;
-    // Tile j: while S0 is computed, V(j+1) and K(j+2) are requested into the stages of V(j-1) and
-    // K(j-1), one 1-KiB piece behind each of the first 2 * PIECES MFMAs, where their issue costs nothing.  The
-    // barrier at the END of the tile (after this wave's copies have landed: only they matter, the
-    // compiler's own barrier would also wait for the LDS reads) says that every wave is done with
-    // tile j and that V(j+1) and K(j+2) are complete; K(j+1), whose first operands are read during
-    // the last MFMAs of tile j, was published a tile earlier.
-    // Two heads per workgroup: the wave of a SIMD that has vector work to do goes first, the one in a phase of
-    // nothing but MFMAs fills in (70B-shaped chunks 11.03 -> 10.87 ms; with four waves 1 % at most).
-#define PK_PRIO(P) if constexpr (WAVES > 4) __builtin_amdgcn_s_setprio(P)
-#define PK_COPY_STEP(I)                                                                       \
-    if constexpr ((I) < PIECES) PK_COPY_PIECE(rs_k, k_fill, (I));                              \
-    else if constexpr ((I) < 2 * PIECES) PK_COPY_PIECE(rs_v, v_fill, (I) - PIECES);
-    // The next tile's list entry and descriptors, in four steps that stand between the last MFMAs of a tile: done
+    bf16x8 ring[4];                                 // LDS operands of the next steps
+    bf16x4 ring_half;                               // first half of one that takes two reads
+    const unsigned char* kp[2];
+    int k_cur = 0, k_next = TILE_BYTES, k_fill = 2 * TILE_BYTES;   // K stage read in this turn / in the next / filled now
+    int v_cur = 4 * TILE_BYTES, v_fill = 3 * TILE_BYTES;
+    copy_to(lds_wave + k_fill);
+#define PK_PIECE_AT(Q) (((Q) / PPS) * SLAB + ((Q) % PPS) * 1024)
+    // step I of a turn: copy I, and where copy I + 1 goes (copy 0: set at the end of the turn before)
+#define PK_COPY_STEP(I) PK_COPY_ISSUE(I) PK_COPY_NEXT(I)
+#define PK_COPY_ISSUE(I)                                                                      \
+    if constexpr ((I) < PIECES) copy_16(rs_k, off.g[(I) < PIECES ? (I) : 0]);                  \
+    else if constexpr ((I) < 2 * PIECES) copy_16(rs_v, off.g[(I) < 2 * PIECES ? (I) - PIECES : 0]);
+#define PK_COPY_NEXT(I)                                                                       \
+    if constexpr ((I) + 1 < PIECES) copy_to(lds_wave + k_fill + PK_PIECE_AT((I) + 1));         \
+    else if constexpr ((I) + 1 < 2 * PIECES) copy_to(lds_wave + v_fill + PK_PIECE_AT((I) + 1 - PIECES));
+    // The next turn's list entries and descriptors, in eight pieces that stand behind the last MFMAs of a turn: done
     // behind the barrier they keep all waves of the workgroup from the matrix pipe at once.
 #define PK_ADVANCE(I)                                                                         \
-    if constexpr ((I) == 0) {                                                                  \
-        e3s = __builtin_amdgcn_readlane(cur_s, (j + 3) & 63); e3i = __builtin_amdgcn_readlane(cur_i, (j + 3) & 63); \
-        rs_v = tile_desc(a.v, off2, valid_rows(e2i, j + 2), row_bytes);                    \
-    } else if constexpr ((I) == 1) {                                                           \
-        off2 = row_offset(e3s, row_bytes);                                                             \
-    } else if constexpr ((I) == 2) {                                                           \
-        rs_k = tile_desc(a.k, off2, valid_rows(e3i, j + 3), row_bytes);                    \
-    }
-    // entry j + 3 is the first of the next 64
-#define PK_NEXT_CHUNK()                                                                       \
-    if (((j + 3) & 63) == 0) {                                                                 \
-        cur_s = nxt_s; cur_i = nxt_i;                                                          \
-        load_chunk(j + 3 + 64, nxt_s, nxt_i);                                                  \
-    }
-#define PK_TILE_END()                                                                         \
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");                              \
-    e0s = e1s; e0i = e1i; e1s = e2s; e1i = e2i; e2s = e3s; e2i = e3i;                          \
-    scalar(e0s); scalar(e0i); scalar(e1s); scalar(e1i); scalar(e2s); scalar(e2i);              \
+    if constexpr ((I) == 0) { ek_s = __builtin_amdgcn_readlane(lk_s, (t + 4) & 63); ek_i = __builtin_amdgcn_readlane(lk_i, (t + 4) & 63); } \
+    else if constexpr ((I) == 1) { ev_s = __builtin_amdgcn_readlane(lv_s, (t + 2) & 63); ev_i = __builtin_amdgcn_readlane(lv_i, (t + 2) & 63); } \
+    else if constexpr ((I) == 2) ek_off = row_offset(ek_s, row_bytes);                         \
+    else if constexpr ((I) == 3) desc_base(rs_k, a.k, ek_off);                                 \
+    else if constexpr ((I) == 4) desc_size(rs_k, valid_rows(ek_i, t + 4), row_bytes);          \
+    else if constexpr ((I) == 5) ev_off = row_offset(ev_s, row_bytes);                         \
+    else if constexpr ((I) == 6) desc_base(rs_v, a.v, ev_off);                                 \
+    else if constexpr ((I) == 7) desc_size(rs_v, valid_rows(ev_i, t + 2), row_bytes);
+#define PK_ADVANCE_ALL() PK_ADVANCE(0) PK_ADVANCE(1) PK_ADVANCE(2) PK_ADVANCE(3) PK_ADVANCE(4) PK_ADVANCE(5) PK_ADVANCE(6) PK_ADVANCE(7)
+    // behind the last of 64 entries the next 64 are requested, here for the barrier to wait for
+#define PK_TURN_END()                                                                         \
+    if (((t + 4) & 63) == 63) load_chunk(t + 5, lk_s, lk_i);                                   \
+    if (((t + 2) & 63) == 63) load_chunk(t + 3, lv_s, lv_i);                                   \
+    PK_WAIT_AND_MEET();                                                                        \
+    cur_s = nxt_s; cur_i = nxt_i; nxt_s = ev_s; nxt_i = ev_i;                                  \
+    scalar(cur_s); scalar(cur_i); scalar(nxt_s); scalar(nxt_i);                                \
     { const int kc = k_cur; k_cur = k_next; k_next = k_fill; k_fill = kc; }                    \
-    { const int vc = v_cur; v_cur = v_fill; v_fill = vc; }
-#define PK_SKIP_TILE()                                                                        \
+    { const int vc = v_cur; v_cur = v_fill; v_fill = vc; }                                     \
+    copy_to(lds_wave + k_fill);                                                                \
+    ++t;
+    // a turn in which this wave only takes part in the copies and the barrier
+#define PK_SKIP_TURN()                                                                        \
     {                                                                                          \
-        int e3s, e3i;                                                                          \
+        int ek_s, ek_i, ev_s, ev_i;                                                            \
+        RowOffset ek_off, ev_off;                                                              \
         _Pragma("unroll") for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); } \
-        PK_NEXT_CHUNK()                                                                        \
-        PK_ADVANCE(0) PK_ADVANCE(1) PK_ADVANCE(2)                                              \
-        PK_TILE_END()                                                                          \
+        PK_ADVANCE_ALL()                                                                       \
+        PK_TURN_END()                                                                          \
     }
+    // mask of half `half` of a tile (the keys past its valid count are foreign)
+    auto mask = [&](Scores& s, int half, int ks, int info) {
+        int visible[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) visible[c] = u.lo[c] <= ks ? min(u.hi[c] - ks, info & 0xFF) : 0;
+        mask_half(s, half, visible, u.g);
+    };
 
-    int j = 0;
-    // leading tiles that this wave skips: it only takes part in the copies and in the barriers,
-    // then picks up its first operands from the stage that is current by then
-    for (; j < u.n_lead; ++j) {
-        PK_SKIP_TILE()
-    }
-    if (u.n_lead > 0) {
-        PK_K_ADDRESSES(k_cur)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
-    }
-    for (; j < u.n_active; ++j) {
-        // a tile that this wave could skip inside its active range is computed as a masked one
-        const bool masked = PK_CODE(e0i) != 2, special = masked || j == u.n_lead;
-        // (keys past the tile's valid count are foreign)
-        const int visible = u.lo <= e0s ? min(u.hi - e0s, e0i & 0xFF) : 0;
-        int e3s, e3i;
-        floatx16 s0, s1;
-        PK_PRIO(0);
-        PK_EIGHT(s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s0, 0, 0, 0);
-                 PK_REFILL(0); PK_COPY_STEP(i));
+    // Turn t = -1 .. n_kv - 1: P(t).V(t), the scores of tile t + 1 and the softmax of the halves (t, 1) and (t + 1, 0);
+    // K(t + 3) and V(t + 1) are requested into the stages of K(t) and V(t - 1), one 1-KiB piece behind each of the
+    // first 2 * PIECES steps, where their issue costs nothing.  The barrier at the end of a turn (after this
+    // wave's copies have landed: only they matter, the compiler's own barrier would also wait for the LDS reads) says
+    // that every wave is done with K(t + 1) and V(t) and that K(t + 3) and V(t + 1) are complete; K(t + 2), whose
+    // first operands are read during the last MFMAs of the turn, was published a turn earlier.
+    int t = -1;
+    const bool any_tile = u.n_lead < u.n_active;
+    const int first_turn = any_tile ? u.n_lead - 1 : n_kv;     // (a wave without a tile skips every turn)
+    while (t < first_turn) PK_SKIP_TURN()
+    if (any_tile) {
+        Scores s0, s1;                              // scores of the first and of the second half of a tile
         HalfSoftmax h0, h1;
-        PK_PRIO(1);
-        if (special) {                              // (one branch in the common case)
-            if (masked) mask_half(s0, 0, visible, u.hlf);
-            if (j == u.n_lead) { asm volatile(""); first_reference(s0, sc, m_ref); }
+        bf16x8 p0[NC], p1[NC];
+        bool masked = false;                        // tile t needs its mask
+        {
+            // first turn: the scores of this wave's first tile and the probabilities of its first half
+            int ek_s, ek_i, ev_s, ev_i;
+            RowOffset ek_off, ev_off;
+            PK_K_ADDRESSES(k_cur)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
+            PK_OPS_STEPS(PK_SLOTS(scores_mfma<i>(c, s0, ring[i & 3], qf)) ring[i & 3] = k_operand(kp, (i + 4) / OPS, (i + 4) % OPS); PK_COPY_STEP(i))
+            PK_MFMA_RESULTS()
+            masked = PK_CODE(nxt_i) != 2;
+            if (masked) mask(s0, 0, nxt_s, nxt_i);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) first_reference(s0[c], sc, m_ref[c]);
+            Pending pend;
+            PK_OPS_STEPS(PK_SLOTS(scores_mfma<i>(c, s1, ring[(OPS + i) & 3], qf), softmax_slot<OPS * NC, 0>(i * NC + c, s0, sc, m_ref, pend, h0))
+                         if constexpr (i + 4 < OPS) ring[(OPS + i) & 3] = k_operand(kp, 1, i + 4))
+            PK_ADVANCE_ALL()
+            softmax_slot<OPS * NC, 0>(OPS * NC, s0, sc, m_ref, pend, h0);
+            PK_SOFTMAX_CHECK(s0, h0)
+            PK_PACK_P(p0, h0)
+            PK_K_ADDRESSES(k_next)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
+            PK_TURN_END()
         }
-        PK_SLICES(s0, h0, s1, s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s1, 0, 0, 0);
-                  PK_REFILL(KS));
-        PK_SOFTMAX_CHECK(s0, h0)
-        bf16x8 p0[2], p1[2];
+        for (; t < u.n_active - 1;) {
+            int ek_s, ek_i, ev_s, ev_i;
+            RowOffset ek_off, ev_off;
+            if (masked) mask(s1, 1, cur_s, cur_i);
+            PK_PART(0, s0, s1, h1, p0, if constexpr (c == NC / 2) { PK_COPY_ISSUE(m) } if constexpr (c == NC - 1) { PK_COPY_NEXT(m) })
+            PK_SOFTMAX_CHECK(s1, h1)
+            PK_PACK_P(p1, h1)
+            // (a tile that this wave could skip inside its active range is computed as a masked one)
+            masked = PK_CODE(nxt_i) != 2;
+            if (masked) mask(s0, 0, nxt_s, nxt_i);
+            PK_PART(1, s1, s0, h0, p1, if constexpr (m == NM - 5 && c == NC - 1) { PK_K_ADDRESSES(k_next) }
+                    PK_ADVANCE(advance_at(m, c)))
+            PK_SOFTMAX_CHECK(s0, h0)
+            PK_PACK_P(p0, h0)
+            PK_TURN_END()
+        }
+        {
+            // Last turn: nothing but P.V and the probabilities of the last half.  Of the rows of a causal tile every other
+            // wave's end in the first half of their last key tile: the second half is left out then.
+            int ek_s, ek_i, ev_s, ev_i;
+            RowOffset ek_off, ev_off;
+            const bool both = !masked || __builtin_amdgcn_ballot_w64((u.lo[0] <= cur_s && u.hi[0] - cur_s > 32) || (u.lo[1] <= cur_s && u.hi[1] - cur_s > 32)) != 0;
+            if (masked) mask(s1, 1, cur_s, cur_i);
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-            p0[t] = __builtin_bit_cast(bf16x8, u32x4{h0.pw[4 * t], h0.pw[4 * t + 1], h0.pw[4 * t + 2], h0.pw[4 * t + 3]});
-        if (masked) mask_half(s1, 1, visible, u.hlf);
-        PK_SLICES(s1, h1, o[i % DB], o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p0[i / DB], o[i % DB], 0, 0, 0);
-                  PK_ROW_SUM(p0); PK_REFILL(2 * KS));
-        PK_SOFTMAX_CHECK(s1, h1)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-            p1[t] = __builtin_bit_cast(bf16x8, u32x4{h1.pw[4 * t], h1.pw[4 * t + 1], h1.pw[4 * t + 2], h1.pw[4 * t + 3]});
-        // phase 4; its last refills are the first operands of the next tile
-        PK_NEXT_CHUNK()
-        PK_K_ADDRESSES(k_next)
-        PK_PRIO(0);
-        PK_EIGHT(o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p1[i / DB], o[i % DB], 0, 0, 0);
-                 PK_ROW_SUM(p1); PK_REFILL(3 * KS); PK_ADVANCE(i));
-        PK_TILE_END();
+            for (int x = 0; x < 4; ++x) ring[x] = v_operand(lds + v_cur, off, 0, x);
+            Pending pend;
+            PK_OPS_STEPS(PK_SLOTS((pv_mfma<i>(c, o, lsum, ring[i & 3], p0, ones)), softmax_slot<OPS * NC, 0>(i * NC + c, s1, sc, m_ref, pend, h1))
+                         ring[i & 3] = v_operand(lds + v_cur, off, (i + 4) / OPS, (i + 4) % OPS); PK_COPY_STEP(i))
+            softmax_slot<OPS * NC, 0>(OPS * NC, s1, sc, m_ref, pend, h1);
+            if (both) {
+                PK_SOFTMAX_CHECK(s1, h1)
+                PK_PACK_P(p1, h1)
+                PK_MFMA_OPERANDS()
+                PK_OPS_STEPS(PK_SLOTS((pv_mfma<i>(c, o, lsum, ring[(OPS + i) & 3], p1, ones))) if constexpr (i + 4 < OPS) ring[(OPS + i) & 3] = v_operand(lds + v_cur, off, 1, i + 4))
+                PK_MFMA_RESULTS()
+            }
+            PK_ADVANCE_ALL()
+            PK_TURN_END()
+        }
     }
-    // trailing tiles that this wave skips: it only takes part in the copies and in the barriers
-    for (; j < n_kv; ++j) {
-        PK_SKIP_TILE()
-    }
-    // After the last barrier nobody fills a stage any more, and what is still being read for a tile after
-    // the last is not used: quarters of two K and V stages per head stage the waves' output.
+    while (t < n_kv) PK_SKIP_TURN()
+    // After the last barrier nobody fills or reads a stage any more: quarters of a K and a V stage stage the
+    // waves' output, one head after the other (a wave's LDS accesses are in order).
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
-    if (a.out_f32) store_output(a, u, o, lsum[0]);
-    else store_output_bf16(a, u, o, lsum[0], lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART,
-                           lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
+    PK_MFMA_RESULTS()
+#pragma unroll
+    for (int c = 0; c < NC; ++c) asm volatile("" : PK_OUT(lsum[c]));   // (all four words of a sum are live until here)
+#pragma unroll
+    for (int h = 0; h < HEADS; ++h) {
+        if (a.out_f32) store_output(a, u, h, o, lsum);
+        else store_output_bf16(a, u, h, o, lsum, lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART, lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
+    }
 }
 
 #undef PK_COPY_TILE
-#undef PK_PRIO
 #undef PK_COPY_PIECE
 #undef PK_COPY_STEP
+#undef PK_PIECE_AT
 #undef PK_SOFTMAX_CHECK
+#undef PK_MFMA_RESULTS
+#undef PK_MFMA_OPERANDS
+#undef PK_STEP
+#undef PK_STEP_SLOT
+#undef PK_SLOT
+#undef PK_SLOTS
+#undef PK_FOUR
+#undef PK_OPS_STEP
+#undef PK_OPS_FOUR
+#undef PK_COPY_ISSUE
+#undef PK_COPY_NEXT
+#undef PK_ADVANCE_ALL
+#undef PK_PART
+#undef PK_OPS_STEPS
+#undef PK_PACK_P
+#undef PK_WAIT_AND_MEET
+#undef PK_TURN_END
+#undef PK_SKIP_TURN
 #undef PK_ADVANCE
-#undef PK_NEXT_CHUNK
-#undef PK_SKIP_TILE
-#undef PK_TILE_END
-#undef PK_SLICE
-#undef PK_SLICE2
-#undef PK_SLICES
-#undef PK_EIGHT
-#undef PK_REFILL
-#undef PK_ROW_SUM
 #undef PK_K_ADDRESSES
 #undef PK_WAIT_ALL_COPIES
 #undef PK_CODE
@@ -741,3 +801,4 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 }  // namespace PK_DNS
 }  // namespace
 }  // namespace pk
+#undef PK_OUT

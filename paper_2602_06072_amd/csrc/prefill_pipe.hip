@@ -1,5 +1,6 @@
 // Packed prefill attention, bf16 MFMA, head dimensions 128 and 64 (Sec. 3.1): the launches.  The
 // kernels' device code is in prefill_body.hip.h, included once per head dimension.
+#define PK_HEADS 1
 #define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
@@ -11,7 +12,6 @@
 #include "prefill_body.hip.h"
 #undef PK_D
 #undef PK_DNS
-
 #undef PK_WAVES
 #define PK_WAVES 8
 #define PK_D 128
@@ -20,6 +20,7 @@
 #undef PK_D
 #undef PK_DNS
 #undef PK_WAVES
+#undef PK_HEADS
 
 namespace pk {
 namespace {
@@ -36,7 +37,7 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_dma_kernel(PrefillArgs a)
     d128::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
 }
 
-__global__ __launch_bounds__(256, 2) void prefill_bf16_dma64_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(256, 3) void prefill_bf16_dma64_kernel(PrefillArgs a) {
     __shared__ __align__(1024) unsigned char lds[5 * d64::TILE_BYTES];
     d64::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
 }
