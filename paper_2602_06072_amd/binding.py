@@ -20,6 +20,9 @@ PK_KV_BLOCK = 32
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpackinfer.so")
 _lib = None
+_torch = None                           # the torch module, once lib() has loaded it
+_dtype_codes = {}
+_raw_stream = None                      # handle of a device's current stream, without a Stream object around it
 
 
 class PackInferError(RuntimeError):
@@ -27,7 +30,7 @@ class PackInferError(RuntimeError):
 
 
 def lib():
-    global _lib
+    global _lib, _torch, _raw_stream
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -35,7 +38,7 @@ def lib():
             f"{LIB_PATH} is missing: build it with `python -m paper_2602_06072_amd.build`")
     # PyTorch owns the device memory and the streams: load its HIP runtime first so that the
     # library's libamdhip64 dependency resolves to the same, already initialised, runtime.
-    import torch  # noqa: F401
+    import torch
     L = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, f32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
     ci = ctypes.c_int
@@ -88,6 +91,8 @@ def lib():
     L.pk_plan_stat.argtypes = [vp, ci]
     L.pk_last_error.restype = ctypes.c_char_p
     L.pk_last_error.argtypes = []
+    _torch = torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _lib = L
     return L
 
@@ -121,27 +126,30 @@ def _i32(x) -> Optional[np.ndarray]:
 
 
 def _ptr(a):
-    if a is None:
-        return None
-    if isinstance(a, np.ndarray):
-        return a.ctypes.data
-    return a.data_ptr()                 # torch tensor
+    try:
+        return a.data_ptr()             # torch tensor
+    except AttributeError:
+        return None if a is None else a.ctypes.data
 
 
 def _dtype_code(t):
-    import torch
-    if t.dtype == torch.bfloat16:
-        return PK_BF16
-    if t.dtype == torch.float32:
-        return PK_F32
-    raise PackInferError(f"unsupported dtype {t.dtype}")
+    if not _dtype_codes:
+        import torch
+        _dtype_codes.update({torch.bfloat16: PK_BF16, torch.float32: PK_F32})
+    code = _dtype_codes.get(t.dtype)
+    if code is None:
+        raise PackInferError(f"unsupported dtype {t.dtype}")
+    return code
 
 
+# A call of a small batch is bound by what the host does per call, and half of that was here: torch.cuda.current_stream()
+# alone, which resolves a device argument and builds a Stream object, takes 5 us of the 11 of a decode call.
 def _stream(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and _torch.cuda.is_initialized():
+        return _raw_stream(_torch._C._cuda_getDevice())
+    return _torch.cuda.current_stream().cuda_stream
 
 
 class Plan:
@@ -262,7 +270,7 @@ def new_kv_buf(plan: Plan, Hkv, d, dtype, device="cuda", fill=None):
 
 def plan_bind(plan: Plan, Hq, Hkv, d, dtype, workspace, stream=None):
     rc = lib().pk_plan_bind(plan.handle, Hq, Hkv, d, dtype, _ptr(workspace),
-                            workspace.numel() * workspace.element_size(), _stream(stream))
+                            workspace.nbytes, _stream(stream))
     _check(rc, "pk_plan_bind")
     plan._ws = workspace
 
@@ -273,7 +281,7 @@ def kv_reorganize(plan: Plan, k_pages, v_pages, block_table, kv_buf, workspace, 
     rc = lib().pk_kv_reorganize(
         plan.handle, _ptr(k_pages), _ptr(v_pages), _ptr(block_table), block_table.shape[1],
         page, nb, Hkv, d, _dtype_code(k_pages), _ptr(kv_buf), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream))
+        workspace.nbytes, _stream(stream))
     _check(rc, "pk_kv_reorganize")
     plan._ws = workspace                # the call may have bound the plan to it
 
@@ -284,7 +292,7 @@ def _prefill(fn_name, plan, q, k, v, out, scale, workspace, stream):
     rc = getattr(lib(), fn_name)(
         plan.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(out), float(scale), Hq, Hkv, d,
         _dtype_code(q), _dtype_code(out), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream))
+        workspace.nbytes, _stream(stream))
     _check(rc, fn_name)
     plan._ws = workspace
     return out
@@ -303,7 +311,7 @@ def packed_decode_attn(plan, q, kv_buf, out, scale, Hkv, workspace, stream=None)
     rc = lib().pk_packed_decode_attn(
         plan.handle, _ptr(q), _ptr(kv_buf), _ptr(out), float(scale), Hq, Hkv, d,
         _dtype_code(q), _dtype_code(out), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream))
+        workspace.nbytes, _stream(stream))
     _check(rc, "pk_packed_decode_attn")
     plan._ws = workspace
     return out
@@ -316,9 +324,9 @@ def packed_mixed_step(prefill_plan, q, k, v, out, prefill_workspace,
     Hkv = k.shape[1]
     rc = lib().pk_packed_mixed_step(
         prefill_plan.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(prefill_workspace),
-        prefill_workspace.numel() * prefill_workspace.element_size(),
+        prefill_workspace.nbytes,
         decode_plan.handle, _ptr(decode_q), _ptr(kv_buf), _ptr(decode_out), _ptr(decode_workspace),
-        decode_workspace.numel() * decode_workspace.element_size(),
+        decode_workspace.nbytes,
         float(scale), Hq, Hkv, d, _dtype_code(q), _dtype_code(out), _stream(stream))
     _check(rc, "pk_packed_mixed_step")
     prefill_plan._ws = prefill_workspace
@@ -343,7 +351,7 @@ def packed_decode_attn_grown(plan, q, kv_buf, out, scale, grown, Hkv, workspace,
     rc = lib().pk_packed_decode_attn_grown(
         plan.handle, _ptr(q), _ptr(kv_buf), _ptr(out), float(scale), int(grown), Hq, Hkv, d,
         _dtype_code(q), _dtype_code(out), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream))
+        workspace.nbytes, _stream(stream))
     _check(rc, "pk_packed_decode_attn_grown")
     plan._ws = workspace
     return out
@@ -353,7 +361,7 @@ def kv_append(plan, k_new, v_new, kv_buf, step, workspace, stream=None):
     n, Hkv, d = k_new.shape
     rc = lib().pk_kv_append(
         plan.handle, _ptr(k_new), _ptr(v_new), _ptr(kv_buf), int(step), Hkv, d, _dtype_code(k_new),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
+        _ptr(workspace), workspace.nbytes, _stream(stream))
     _check(rc, "pk_kv_append")
     plan._ws = workspace
     return kv_buf
@@ -405,7 +413,7 @@ def padded_decode_attn(plan, q, k_pages, v_pages, block_table, out, scale, works
         plan.handle, _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
         block_table.shape[1], page, nb, _ptr(out), float(scale), Hq, Hkv, d,
         _dtype_code(q), _dtype_code(out), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream))
+        workspace.nbytes, _stream(stream))
     _check(rc, "pk_padded_decode_attn")
     plan._ws = workspace
     return out
