@@ -372,19 +372,21 @@ int decode_common(const char* who, pk_plan* plan, const void* q, const void* kv_
     int rc = ensure_bound(plan, Hq, Hkv, d, dtype, workspace, workspace_bytes, stream, fixed_scratch);
     if (rc != PK_OK) return rc;
     const DeviceTables& t = plan->tables;
+    const DeviceTables::DecodeSched& s = t.dec;
     DecodeArgs a{};
     a.q = q; a.kv_buf = kv_buf; a.out = out;
-    a.items = tab(plan, t.dec_items); a.n_items = t.n_dec_items; a.n_wide = t.n_dec_wide;
-    a.members = tab(plan, t.dec_members); a.member_slot = tab(plan, t.dec_member_slot);
-    a.req_part_start = tab(plan, t.dec_req_part_start);
+    a.items = tab(plan, s.items); a.n_items = s.n_items; a.n_wide = s.n_wide;
+    a.members = tab(plan, s.members); a.member_slot = tab(plan, s.member_slot);
+    a.req_part_start = tab(plan, s.req_part_start);
     a.req_seg = tab(plan, t.dec_req_seg);
     a.chain_start = tab(plan, t.dec_chain_start); a.chain = tab(plan, t.dec_chain);
     a.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_offset);
-    a.part_lse = a.part_o + static_cast<size_t>(t.n_dec_parts) * Hq * d;
+    a.part_lse = a.part_o + static_cast<size_t>(s.n_parts) * Hq * d;
     a.buf_tokens = plan->buf_tokens; a.n = plan->n;
     a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.scale = scale; a.out_f32 = out_dtype == PK_F32;
     a.grown = grown;
-    a.max_parts = t.dec_max_parts;
+    a.max_parts = s.max_parts;
+    a.arrived = s.group ? const_cast<int32_t*>(tab(plan, s.arrived)) : nullptr;
     if (args_out) { *args_out = a; return PK_OK; }
     const int e = dtype == PK_BF16 ? launch_decode_bf16(a, stream) : launch_decode_f32(a, stream);
     return e ? hip_fail(who, e) : PK_OK;
@@ -576,9 +578,9 @@ extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
                 if (!plan->tables.padded_built && plan->tables.dtype >= 0)
                     build_prefill_padded(*plan, plan->tables);
                 return plan->tables.padded.issued_pairs;
-            case 3: return plan->tables.n_dec_items;
-            case 4: return plan->tables.n_dec_parts;
-            case 5: return plan->tables.dec_split_tokens;
+            case 3: return plan->tables.dec.n_items;
+            case 4: return plan->tables.dec.n_parts;
+            case 5: return plan->tables.dec.split_tokens;
             case 6: return plan->tables.packed.n_tiles;
             case 7:
                 if (!plan->tables.padded_built && plan->tables.dtype >= 0)

@@ -5,7 +5,8 @@
 // (a shared prefix or a private suffix) together with the requests whose
 // queries attend to it: one request for a suffix, all members of the
 // (sub-)family for a prefix -- the prefix is streamed from HBM once and used
-// for every member's rows.  One wave handles (work item, KV head): the query
+// for every member's rows.  One wave handles (work item, KV head) -- or, in batches
+// without shared prefixes, a workgroup that merges in the same launch --: the query
 // rows of up to 32/r requests x r heads sit on the N side of 16x16x32 bf16
 // MFMAs, the buffer tiles are already in MFMA operand order, so every load is
 // a fully coalesced 16-byte-per-lane read straight into the operand
@@ -35,6 +36,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
     const int item = a.by_hkv(blockIdx.x), kvh = blockIdx.x - item * a.Hkv;
     if (item < a.n_wide) decode_body<D, 2, 1>(a, item, kvh);
     else decode_body<D, 1, 2>(a, item, kvh);
+}
+
+// Batches whose items carry up to 16 rows of one request each (DecodeArgs::arrived; the schedule builder's choice): one launch.
+template <int D>
+__global__ __launch_bounds__(64 * kGroupWaves, 2) void decode_bf16_group_kernel(DecodeArgs a) {
+    __shared__ __align__(16) unsigned char lds[kGroupLds<D>];
+    const int item = a.by_hkv(blockIdx.x), kvh = blockIdx.x - item * a.Hkv;
+    decode_group_body<D>(a, item, kvh, lds);
 }
 
 // out[i, h, :] = sum_j exp(lse_j - lse) o_j over the request's partial slots (consecutive).
@@ -148,6 +157,10 @@ int launch_d(const DecodeArgs& a, hipStream_t st) {
         const int64_t waves = static_cast<int64_t>(a.n_items) * a.Hkv;
         if (waves > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
         const dim3 grid(static_cast<unsigned>(waves));
+        if (a.arrived) {
+            hipLaunchKernelGGL(decode_bf16_group_kernel<D>, grid, dim3(64 * kGroupWaves), 0, st, a);
+            return static_cast<int>(hipGetLastError());
+        }
         if (a.n_wide > 0) hipLaunchKernelGGL(decode_bf16_mixed_kernel<D>, grid, dim3(64), 0, st, a);
         else hipLaunchKernelGGL(decode_bf16_kernel<D>, grid, dim3(64), 0, st, a);
     }

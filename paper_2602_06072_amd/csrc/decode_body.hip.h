@@ -1,5 +1,5 @@
 // Device code of the packed decode work item (Sec. 3.2), shared by the decode kernels and by the
-// fused mixed-step kernel: one wave handles (work item, KV head).
+// fused mixed-step kernel: one wave handles (work item, KV head), or the waves of a workgroup together.
 #pragma once
 #include <type_traits>
 
@@ -28,8 +28,19 @@ __device__ __forceinline__ float max_over_lane_groups(float x) {
 // LDS look-ups of the maximum): 256 requests of 32..32768 tokens 206.0 -> 201.6 us, four requests 12.1 ->
 // 11.5, a tree of 128 63.1 -> 61.0, 16 families of 8 66.2 -> 64.9, 200 requests with D = 64 73.8 -> 73.2.
 // The first tile is requested before the look-up of the requests (the other order: 65.6 and 74.1 us).
-template <int D, int NT, int SETS>
-__device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item, const int kvh) {
+//
+// What a wave has of a work item: lane (n, g) holds columns 16 t + 4 g .. + 3 of its query row 16 c + n.
+template <int D, int NT>
+struct ItemRows {
+    int req[NT], hq[NT], slot[NT];             // request, query head and partial slot (-1: the item writes the output)
+    bool ok[NT];                               // a request's row
+    floatx4 o[NT][D / 16];                     // sum of p v, relative to m
+    float m[NT], l[NT];                        // maximum (exp2 domain); this lane group's share of the sum of p
+};
+
+// Tiles first, first + STRIDE, ... of the item
+template <int D, int NT, int SETS, int STRIDE>
+__device__ __forceinline__ void decode_tiles(const DecodeArgs& a, const int item, const int kvh, const int first, ItemRows<D, NT>& rows) {
     constexpr int KS = D / 32;                 // K steps per 16-key sub-tile
     constexpr int VT = D / 16;                 // V column blocks
     constexpr int NK = 2 * KS;                 // 16-byte chunks per lane of a tile's K part
@@ -42,7 +53,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
     const int64_t n_tiles = a.buf_tokens / 32;
     const unsigned char* base = static_cast<const unsigned char*>(a.kv_buf) + static_cast<int64_t>(kvh) * n_tiles * TILE_BYTES;
     const int lane16 = lane * 16;              // this lane's offset into a 1-KiB piece
-    const int b0 = tok_begin / 32, b1 = (tok_end + 31) / 32;
+    const int b0 = tok_begin / 32 + first, b1 = (tok_end + 31) / 32;
 
     u32x4 k0[NK], v0[VT], k1[SETS > 1 ? NK : 1], v1[SETS > 1 ? VT : 1];
     auto load = [&](auto& regs, int piece0, auto count, int b) {
@@ -60,8 +71,8 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
     __builtin_amdgcn_sched_barrier(0);
 
     // rows without a request repeat the last one (their column of the MFMAs is nobody else's) and store nothing
-    int req_of[NT], hq_of[NT], slot_of[NT];
-    bool ok[NT];
+    int (&req_of)[NT] = rows.req, (&hq_of)[NT] = rows.hq, (&slot_of)[NT] = rows.slot;
+    bool (&ok)[NT] = rows.ok;
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         const int mi = a.by_r(c * 16 + n), mc = min(mi, n_mem - 1);
@@ -80,8 +91,8 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
             qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
                 static_cast<const uint16_t*>(a.q) + (static_cast<int64_t>(req_of[c]) * a.Hq + hq_of[c]) * D + 32 * s + 8 * g));
 
-    floatx4 o[NT][VT];
-    float m[NT], l[NT];
+    floatx4 (&o)[NT][VT] = rows.o;
+    float (&m)[NT] = rows.m, (&l)[NT] = rows.l;
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         m[c] = -INFINITY; l[c] = 0.f;
@@ -148,64 +159,194 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
 #pragma unroll
         for (int c = 0; c < NT; ++c) scores(kr, b, c, pf[c], alpha[c]);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(fetch)::value) load_k(kr, b + SETS);
+        if constexpr (decltype(fetch)::value) load_k(kr, b + SETS * STRIDE);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < NT; ++c) pv(vr, c, pf[c], alpha[c]);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(fetch)::value) load_v(vr, b + SETS);
+        if constexpr (decltype(fetch)::value) load_v(vr, b + SETS * STRIDE);
         __builtin_amdgcn_sched_barrier(0);
     };
     // Q came last: it is waited for here, so that inside the loop only the tiles are
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SETS == 1) {
         __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0)
-        for (int b = b0; b < b1; ++b) step(k0, v0, b, std::true_type{});
+        for (int b = b0; b < b1; b += STRIDE) step(k0, v0, b, std::true_type{});
     } else {
-        load_k(k1, b0 + 1);
+        load_k(k1, b0 + STRIDE);
         __builtin_amdgcn_sched_barrier(0);
-        load_v(v1, b0 + 1);
+        load_v(v1, b0 + STRIDE);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0x0F70 | ((NK + VT) & 0xF) | ((NK + VT) >> 4 << 14));   // vmcnt: the second set alone
         int b = b0;
-        for (; b + 1 < b1; b += 2) {
+        for (; b + STRIDE < b1; b += 2 * STRIDE) {
             step(k0, v0, b, std::true_type{});
-            step(k1, v1, b + 1, std::true_type{});
+            step(k1, v1, b + STRIDE, std::true_type{});
         }
         if (b < b1) step(k0, v0, b, std::false_type{});
     }
 
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
-        float lt = l[c];
-        lt += __shfl_xor(lt, 16, 64);
-        lt += __shfl_xor(lt, 32, 64);
-        if (!ok[c]) continue;
-        const float inv = lt > 0.f ? 1.f / lt : 0.f;
-        if (slot_of[c] < 0) {
-            // the only work item of this request: write the final output
-            const int64_t dst = (static_cast<int64_t>(req_of[c]) * a.Hq + hq_of[c]) * D;
+        l[c] += __shfl_xor(l[c], 16, 64);
+        l[c] += __shfl_xor(l[c], 32, 64);
+    }
+}
+
+// Four columns of a row, divided by its sum of probabilities, to the output or to the row's partial result.
+template <int D>
+__device__ __forceinline__ void store_columns(const DecodeArgs& a, const int req, const int hq, const int slot, const int col, const floatx4 x) {
+    if (slot < 0) {
+        const int64_t dst = (static_cast<int64_t>(req) * a.Hq + hq) * D + col;
+        if (a.out_f32)
+            *reinterpret_cast<float4*>(static_cast<float*>(a.out) + dst) = make_float4(x[0], x[1], x[2], x[3]);
+        else
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + dst) = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+        return;
+    }
+    *reinterpret_cast<float4*>(a.part_o + (static_cast<int64_t>(slot) * a.Hq + hq) * D + col) = make_float4(x[0], x[1], x[2], x[3]);
+}
+__device__ __forceinline__ void store_lse(const DecodeArgs& a, const int hq, const int slot, const float m, const float l) {
+    if (slot >= 0) a.part_lse[static_cast<int64_t>(slot) * a.Hq + hq] = l > 0.f ? (m + log2f(l)) * kLn2 : -INFINITY;
+}
+
+// one wave for the whole item
+template <int D, int NT, int SETS>
+__device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item, const int kvh) {
+    ItemRows<D, NT> r;
+    decode_tiles<D, NT, SETS, 1>(a, item, kvh, 0, r);
+    const int g = (threadIdx.x & 63) >> 4;
 #pragma unroll
-            for (int t = 0; t < VT; ++t) {
-                const float x0 = o[c][t][0] * inv, x1 = o[c][t][1] * inv, x2 = o[c][t][2] * inv, x3 = o[c][t][3] * inv;
-                if (a.out_f32)
-                    *reinterpret_cast<float4*>(static_cast<float*>(a.out) + dst + 16 * t + 4 * g) = make_float4(x0, x1, x2, x3);
-                else
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + dst + 16 * t + 4 * g) =
-                        make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+    for (int c = 0; c < NT; ++c) {
+        if (!r.ok[c]) continue;
+        const float inv = r.l[c] > 0.f ? 1.f / r.l[c] : 0.f;
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) store_columns<D>(a, r.req[c], r.hq[c], r.slot[c], 16 * t + 4 * g, r.o[c][t] * inv);
+        if (g == 0) store_lse(a, r.hq[c], r.slot[c], r.m[c], r.l[c]);
+    }
+}
+
+// Partial results that another workgroup of the same launch reads: written through to memory, and read past whatever an L2 has
+// of an earlier launch (relaxed atomics at device scope).
+__device__ __forceinline__ void publish(float* p, const floatx4 x) {
+    uint64_t* q = reinterpret_cast<uint64_t*>(p);
+    __hip_atomic_store(q, __builtin_bit_cast(uint64_t, floatx2{x[0], x[1]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, __builtin_bit_cast(uint64_t, floatx2{x[2], x[3]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ floatx4 read_published(const float* p) {
+    const uint64_t* q = reinterpret_cast<const uint64_t*>(p);
+    const floatx2 a = __builtin_bit_cast(floatx2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const floatx2 b = __builtin_bit_cast(floatx2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return floatx4{a[0], a[1], b[0], b[1]};
+}
+
+// A batch in one launch: a workgroup takes a work item of one request, its waves the item's tiles in turns, and
+// puts their results together in LDS; the workgroup that is the last to finish an item of a (request, KV head) merges
+// the partial results of all of them, in the order of their slots whichever workgroup it is.  Nobody waits for another workgroup.
+// Short batches are bound by latency: a launch, two to four round trips for tables, Q and the first tiles, the tiles, and
+// for split requests a write, a count and a read at the memory side (about 2 us) in place of a second launch (4 to 5 us).
+// Long ones are bound by HBM; there four waves to an item leave fewer items, starts, ends and partial results: 480 rows of up to
+// 65536 tokens 2.86 -> 2.59 ms (6.9 TB/s), 256 requests of 32..32768 201 -> 194 us, one request of 500 tokens 8.9 -> 6.3 us,
+// four of 300..3000 10.2 -> 9.6 us.  With eight waves to an item the one request takes 6.8 us; with
+// batches of 16 partial results in the merge instead of 8 the four take 10.4 us, with 4 9.9.
+// `lds`: kGroupLds<D> bytes; a.arrived: a count per (request, KV head), zero between launches.
+constexpr int kGroupWaves = 4;
+template <int D> constexpr int kGroupLds = kGroupWaves * 16 * (D + 4 + 2) * 4 + 16;
+template <int D>
+__device__ __forceinline__ void decode_group_body(const DecodeArgs& a, const int item, const int kvh, unsigned char* lds) {
+    constexpr int WAVES = kGroupWaves, PITCH = D + 4;          // (16 bytes more: the 16 rows of a lane group on different banks)
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+    float* po = reinterpret_cast<float*>(lds);                 // [WAVES][16][PITCH]
+    float* pm = po + WAVES * 16 * PITCH;                       // [WAVES][16]: maxima, then sums
+    float* pl = pm + WAVES * 16;
+    int* last = reinterpret_cast<int*>(pl + WAVES * 16);
+    {
+        ItemRows<D, 1> r;
+        decode_tiles<D, 1, 2, WAVES>(a, item, kvh, wave, r);
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) *reinterpret_cast<floatx4*>(po + (wave * 16 + n) * PITCH + 16 * t + 4 * g) = r.o[0][t];
+        if (g == 0) { pm[wave * 16 + n] = r.m[0]; pl[wave * 16 + n] = r.l[0]; }
+    }
+    const int mem = a.items[8 * static_cast<int64_t>(item) + 2];
+    const int req = a.members[mem], slot = a.member_slot[mem];
+    __syncthreads();
+    const int heads = a.heads_per_kv, hq0 = kvh * heads;
+    for (int x = threadIdx.x; x < heads * (D / 4); x += 64 * WAVES) {
+        const int row = x / (D / 4), col = 4 * (x % (D / 4));
+        float mx = pm[row];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) mx = fmaxf(mx, pm[w * 16 + row]);
+        const float m_use = mx == -INFINITY ? 0.f : mx;
+        float l = 0.f;
+        floatx4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float f = __builtin_amdgcn_exp2f(pm[w * 16 + row] - m_use);
+            const floatx4 v = *reinterpret_cast<const floatx4*>(po + (w * 16 + row) * PITCH + col);
+            l = fmaf(f, pl[w * 16 + row], l);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(f, v[e], o[e]);
+        }
+        o *= l > 0.f ? 1.f / l : 0.f;
+        if (slot < 0) {
+            store_columns<D>(a, req, hq0 + row, slot, col, o);
+        } else {
+            publish(a.part_o + (static_cast<int64_t>(slot) * a.Hq + hq0 + row) * D + col, o);
+            if (col == 0)
+                __hip_atomic_store(a.part_lse + static_cast<int64_t>(slot) * a.Hq + hq0 + row,
+                                   l > 0.f ? (mx + log2f(l)) * kLn2 : -INFINITY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (slot < 0) return;
+    const int p0 = a.req_part_start[req], p1 = a.req_part_start[req + 1];
+    __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's partial results are in memory
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t* count = a.arrived + static_cast<int64_t>(req) * a.Hkv + kvh;
+        const int before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *last = before == p1 - p0 - 1;
+        if (*last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    }
+    __syncthreads();
+    if (*last == 0) return;
+    // out[req, h, :] = sum_j exp(lse_j - lse) o_j over the request's slots, in batches as in decode_merge_kernel
+    constexpr int BATCH = 8;
+    for (int x = threadIdx.x; x < heads * (D / 4); x += 64 * WAVES) {
+        const int row = x / (D / 4), col = 4 * (x % (D / 4));
+        const float* lse_base = a.part_lse + hq0 + row;
+        const float* o_base = a.part_o + static_cast<int64_t>(hq0 + row) * D + col;
+        float m = -INFINITY, tot = 0.f;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int p = p0; p < p1; p += BATCH) {
+            float lse[BATCH];
+            floatx4 v[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int q = min(p + u, p1 - 1);
+                lse[u] = __hip_atomic_load(lse_base + static_cast<int64_t>(q) * a.Hq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                v[u] = read_published(o_base + static_cast<int64_t>(q) * a.Hq * D);
             }
-            continue;
-        }
-        const int slot = slot_of[c];
-        float* po = a.part_o + (static_cast<int64_t>(slot) * a.Hq + hq_of[c]) * D;
+            float m_new = m;
 #pragma unroll
-        for (int t = 0; t < VT; ++t) {
-            float4 w = make_float4(o[c][t][0] * inv, o[c][t][1] * inv, o[c][t][2] * inv, o[c][t][3] * inv);
-            *reinterpret_cast<float4*>(po + 16 * t + 4 * g) = w;
+            for (int u = 0; u < BATCH; ++u) {
+                if (p + u >= p1) lse[u] = -INFINITY;
+                m_new = fmaxf(m_new, lse[u]);
+            }
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = expf(m - m_use);
+            tot *= alpha;
+            acc *= alpha;
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const float w = expf(lse[u] - m_use);
+                tot += w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, v[u][e], acc[e]);
+            }
+            m = m_new;
         }
-        if (g == 0)
-            a.part_lse[static_cast<int64_t>(slot) * a.Hq + hq_of[c]] =
-                lt > 0.f ? (m[c] + log2f(lt)) * kLn2 : -INFINITY;
+        store_columns<D>(a, req, hq0 + row, -1, col, acc * (tot > 0.f ? 1.f / tot : 0.f));
     }
 }
 

@@ -56,6 +56,7 @@ struct DecodeArgs {
     int64_t buf_tokens; int32_t n; int Hq; int Hkv; int d; float scale; int out_f32;
     int32_t grown;                                  // tokens appended to every suffix since the plan was made
     int32_t max_parts;                              // most partial results of one request
+    int32_t* arrived;                               // not null: a workgroup per (work item, KV head), which counts itself in here ([n][Hkv])
     int heads_per_kv; FastDiv by_r, by_hkv;         // set by the bf16 launches: Hq / Hkv, divisions by it and by Hkv
 };
 int launch_decode_bf16(const DecodeArgs& a, void* stream);

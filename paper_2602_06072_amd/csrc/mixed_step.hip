@@ -4,7 +4,8 @@
 // compute unit they use what the other leaves idle.  The two kernels launched one after the other
 // cannot do that, and launched on two streams they hardly overlap: the prefill workgroups take
 // every register and LDS slot first.  Here the roles are dealt by workgroup number instead: runs of
-// prefill workgroups and runs of decode workgroups (four waves, one (work item, KV head) pair each),
+// prefill workgroups and runs of decode workgroups (four waves: a (work item, KV head) pair each or, as
+// the decode plan has it, one pair together),
 // the decode runs spread evenly over the launch; the prefill workgroups keep their numbers modulo 8,
 // i.e. their XCD, so the heads of a KV head still share an L2.  The LSE merge of the decode partials
 // is a second, short launch.
@@ -58,25 +59,40 @@ __device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& de
     return decode ? c : c * (m.stride - 1) + (r == 0 ? 0 : r - 1);
 }
 
-// one kernel per head dimension (NS: the namespace of the prefill body, D: the head dimension)
-#define PK_MIXED_STEP_KERNEL(NAME, NS, D, WPE)                                                       \
-    __global__ __launch_bounds__(256, WPE) void NAME(PrefillArgs pa, DecodeArgs da, MixedOrder m) {     \
+// one kernel per head dimension and kind of decode workgroup (NS: the namespace of the prefill body, D: the head
+// dimension); the work items and the arithmetic are those of the decode launch
+#define PK_MIXED_STEP_KERNEL(NAME, NS, D, WPE, DECODE)                                                \
+    __global__ __launch_bounds__(256, WPE) void NAME(PrefillArgs pa, DecodeArgs da, MixedOrder m) {   \
         __shared__ __align__(1024) unsigned char lds[5 * NS::TILE_BYTES];                             \
-        const int x = static_cast<int>(blockIdx.x);                                                  \
-        bool decode;                                                                                 \
-        const int block = run_of(m, x / kRun, decode) * kRun + x % kRun;                             \
-        if (decode) { /* four (work item, KV head) pairs */                                          \
-            const int unit = block * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)); \
-            const int item = pa.by_hkv(unit), kvh = unit - item * da.Hkv;                            \
-            if (item >= da.n_items) return;                                                          \
-            if (item < da.n_wide) decode_body<D, 2, 1>(da, item, kvh);                               \
-            else decode_body<D, 1, 2>(da, item, kvh);                                                \
-            return;                                                                                  \
-        }                                                                                            \
-        if (block < m.n_prefill) NS::prefill_tile_body(pa, block, lds);                              \
+        const int x = static_cast<int>(blockIdx.x);                                                   \
+        bool decode;                                                                                  \
+        const int block = run_of(m, x / kRun, decode) * kRun + x % kRun;                              \
+        if (decode) {                                                                                 \
+            DECODE<D>(pa.by_hkv, da, block, lds);                                                     \
+            return;                                                                                   \
+        }                                                                                             \
+        if (block < m.n_prefill) NS::prefill_tile_body(pa, block, lds);                               \
     }
-PK_MIXED_STEP_KERNEL(mixed_step_kernel, d128, 128, 2)
-PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64, 3)
+// four (work item, KV head) pairs, a wave each
+template <int D>
+__device__ __forceinline__ void decode_by_waves(const FastDiv& by_hkv, const DecodeArgs& da, const int block, unsigned char*) {
+    const int unit = block * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int item = by_hkv(unit), kvh = unit - item * da.Hkv;
+    if (item >= da.n_items) return;
+    if (item < da.n_wide) decode_body<D, 2, 1>(da, item, kvh);
+    else decode_body<D, 1, 2>(da, item, kvh);
+}
+// one pair
+template <int D>
+__device__ __forceinline__ void decode_by_workgroup(const FastDiv& by_hkv, const DecodeArgs& da, const int block, unsigned char* lds) {
+    const int item = by_hkv(block), kvh = block - item * da.Hkv;
+    if (item < da.n_items) decode_group_body<D>(da, item, kvh, lds);
+}
+static_assert(kGroupLds<128> <= 5 * d128::TILE_BYTES && kGroupLds<64> <= 5 * d64::TILE_BYTES && kGroupWaves == 4, "decode_by_workgroup");
+PK_MIXED_STEP_KERNEL(mixed_step_kernel, d128, 128, 2, decode_by_waves)
+PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64, 3, decode_by_waves)
+PK_MIXED_STEP_KERNEL(mixed_step_group_kernel, d128, 128, 2, decode_by_workgroup)
+PK_MIXED_STEP_KERNEL(mixed_step64_group_kernel, d64, 64, 3, decode_by_workgroup)
 #undef PK_MIXED_STEP_KERNEL
 
 }  // namespace
@@ -94,7 +110,7 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     const int64_t pairs = static_cast<int64_t>(pa.n_tiles) * pa.Hkv;
     const int64_t n_prefill = (pairs + 7) / 8 * 8 * r;                      // as in the prefill launch (XCD map)
     const int64_t units = static_cast<int64_t>(da.n_items) * da.Hkv;
-    const int64_t n_decode = (units + 3) / 4;
+    const int64_t n_decode = da.arrived ? units : (units + 3) / 4;
     const int64_t p_runs = (n_prefill + kRun - 1) / kRun, d_runs = (n_decode + kRun - 1) / kRun;
     const int64_t grid = (p_runs + d_runs) * kRun;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
@@ -106,14 +122,15 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     m.by_stride = FastDiv::by(static_cast<uint32_t>(m.stride));
     if (pa.d != da.d || (pa.d != 128 && pa.d != 64)) return static_cast<int>(hipErrorInvalidValue);
     if (grid > 0) {
-        if (pa.d == 128)
-            hipLaunchKernelGGL(mixed_step_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, pa, da, m);
-        else
-            hipLaunchKernelGGL(mixed_step64_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, pa, da, m);
+        const dim3 wgs(static_cast<unsigned>(grid));
+        if (pa.d == 128 && da.arrived) hipLaunchKernelGGL(mixed_step_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
+        else if (pa.d == 128) hipLaunchKernelGGL(mixed_step_kernel, wgs, dim3(256), 0, st, pa, da, m);
+        else if (da.arrived) hipLaunchKernelGGL(mixed_step64_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
+        else hipLaunchKernelGGL(mixed_step64_kernel, wgs, dim3(256), 0, st, pa, da, m);
     }
     const int e = static_cast<int>(hipGetLastError());
     if (e != 0) return e;
-    return launch_decode_merge_bf16(da, stream);
+    return da.arrived ? 0 : launch_decode_merge_bf16(da, stream);
 }
 
 }  // namespace pk

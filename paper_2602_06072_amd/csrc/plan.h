@@ -58,20 +58,26 @@ struct DeviceTables {
     TableRef reorg_blk_first;       // [NB] first segment that may overlap tile b
     int32_t n_reorg_seg = 0;
     // decode
-    TableRef dec_items;             // [n_items][8]
-    TableRef dec_members;           // request ids of the work items' rows
-    TableRef dec_member_slot;       // partial slot of each (item, member), -1: the item writes the output
-    TableRef dec_req_part_start;    // [n+1] first slot of each request (slots of a request are consecutive)
+    struct DecodeSched {
+        TableRef items;             // [n_items][8]
+        TableRef members;           // request ids of the work items' rows
+        TableRef member_slot;       // partial slot of each (item, member), -1: the item writes the output
+        TableRef req_part_start;    // [n+1] first slot of each request (slots of a request are consecutive)
+        TableRef arrived;           // group: [n][Hkv] zeros, how many of its items have finished
+        int32_t n_items = 0, n_wide = 0, n_parts = 0, split_tokens = 0;
+        int32_t max_parts = 0;      // most partial results of one request
+        bool group = false;         // a workgroup of several waves per (work item, KV head), not a wave
+        int32_t wave_items = 0, wave_parts = 0;     // group: work items and partial results with a wave each
+    } dec;
     TableRef dec_req_seg;           // [n][4] absolute prefix_off, L_P, suffix_off, L_Q (innermost shared segment)
     TableRef dec_chain_start;       // [n+1] first entry of each request in dec_chain
     TableRef dec_chain;             // (absolute offset, tokens) of a request's shared segments, outermost first
-    int32_t n_dec_items = 0, n_dec_wide = 0, n_dec_parts = 0, dec_split_tokens = 0;
-    int32_t dec_max_parts = 0;      // most partial results of one request
     int32_t pad_split_tokens = 0, pad_n_splits = 0;   // padded decode comparison: uniform splits
     // prefill (packed and padded schedules share one format)
     struct PrefillSched {
-        TableRef tiles;             // [n_tiles][8] kv_first, n_kv, leading / trailing skipped key tiles per wave (4 x 8 bits each),
-                                    // rows | runs << 16, then Q row, lo, hi of tile row 0 (the first run)
+        TableRef tiles;             // [n_tiles][16] kv_first, n_kv, leading / trailing skipped key tiles per wave (4 x 8 bits each),
+                                    // rows | runs << 16, then Q row, lo, hi of tile row 0 (the first run), then k_start and
+                                    // info of the first three key tiles
         TableRef run_first;         // [n_tiles] first entry of the tile's further runs
         TableRef runs;              // (first tile row, its Q row, lo, its hi) of the runs after a tile's first
         TableRef kvtiles;           // [n_kv_total][2] k_start, n | wavemask<<8 | full<<16
@@ -87,7 +93,9 @@ struct DeviceTables {
     size_t partial_offset = 0;      // bytes
     size_t partial_bytes = 0;
     size_t total_bytes = 0;
-    size_t decode_only_bytes = 0;   // tables + the packed decode partials alone (what the static scratch must hold)
+    size_t decode_only_bytes = 0;   // tables + the packed decode partials alone (what the static scratch must hold),
+                                    // dec.group: as they would be with a wave per work item
+    bool group_over_scratch = false;    // those of dec.group do not fit the static scratch, the others would
 };
 
 }  // namespace pk

@@ -8,6 +8,7 @@
 // whether that wave skips it, computes it with the mask, or computes it
 // without any mask.
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 #include "plan.h"
@@ -60,7 +61,75 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
 }
 
 // ---- decode ----------------------------------------------------------------
-void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Builder& b, DeviceTables& t) {
+// Split length for a batch whose (work item, KV head) pairs are served by a workgroup of four waves each, 0 where a wave
+// each is the better choice.  A workgroup streams an item 3 to 4 times as fast as a wave does, so that most requests need no
+// split, and it merges in the same launch what is split.  With waves / with workgroups (us, buffers that repeat; both sides
+// with the better split): one request of 500 tokens 8.9 / 6.3, four of 300..3000 11.5 / 11.3 and 10.8 / 9.5 (two cards), 24 of 1500 26.3 / 23.4, 59 of 428
+// with 28/4 heads 13.3 / 9.3, 480 lognormal around 1000 with 64/8 heads 418 / 391, 200 around 700 with head dimension 64
+// 73.4 / 69.7, 256 of 32..32768 200 / 192, 480 rows up to 65536 2860 / 2590.  Waves stay
+//   - for items with rows of several requests or more than 16 rows (the kernel has one column tile of rows and merges one request);
+//   - for many short requests, where the waves of a workgroup get a tile or two each: 600 of 20..200 tokens with 28/4
+//     heads 29.0 / 34.4, 1000 of 128 with 4/1 heads 10.9 / 14.8, 300 of 200 41.7 / 44.4; 305 around 278 with head
+//     dimension 64 31.8 / 30.4, 591 of 300..400 with 4/1 heads 22.1 / 19.9;
+//   - for requests of at most four tiles, which a wave does not split either: 78 of 8..32 tokens 5.4 / 7.7;
+//   - for short launches with many partial results to a request, which a merge of sixteen waves reads faster: one of
+//     11513 tokens and 32/8 heads (20 partial results) 13.9 / 14.5, of 8799 and 16/2 heads (23) 10.0 / 10.8; one of 16000
+//     and 32/8 heads (23) 16.1 / 15.6, of 32768 (20) 27.9 / 25.1.
+// The split is the one with the least estimated time: bytes at the rate of the whole chip, a start and an end of each workgroup,
+// and the longest item alone for as long as its fair share of the other workgroups' time does not cover it.  The estimate
+// picks within 2 % of the best split on average over 57 batches of 1..1000 requests (10 % at worst).  No split is shorter
+// than the one for waves (`from`): there are never more work items and partial results than with that.  None is longer than
+// 8 MiB of a KV head: beside the prefill tiles of a mixed step a workgroup is slow, and whole sequences of 65536
+// tokens keep the chip when everything else is done (12.52 instead of 12.23 ms for 32 chunks and 480 rows of a 70B-shaped
+// layer; with the limit as fast as with waves).
+int64_t group_split(const pk_plan& plan, int Hkv, int d, int num_cus, int64_t from) {
+    std::vector<int64_t> blocks;
+    int64_t total = 0, longest = 0;
+    auto segment = [&](int64_t len) {
+        const int64_t k = (len + kDecodeBlock - 1) / kDecodeBlock;
+        if (k > 0 || plan.headroom > 0) blocks.push_back(std::max<int64_t>(k, 1));
+        total += k;
+        longest = std::max(longest, k);
+    };
+    for (const Group& g : plan.groups) {
+        for (const Node& nd : g.nodes) {
+            if (nd.reqs.size() > 1) return 0;
+            segment(nd.len);
+        }
+        for (const Member& m : g.members) segment(m.lq);
+    }
+    if (longest <= 4) return 0;
+    // in nanoseconds (a tile of head dimension 64 has half the bytes): a tile at the rate of the whole chip and
+    // of one workgroup, a workgroup's start and end, a merge
+    const double scale = d / 128.0;
+    const double all = 3.2 * scale, alone = 530 * scale, fixed = 6.5 * (1 + scale), merge = 2000;
+    const int64_t slots = static_cast<int64_t>(2 * num_cus / scale);
+    double best = 0;
+    int64_t split = 0, best_wgs = 0, best_parts = 0;
+    for (int64_t sp = std::max<int64_t>(from / kDecodeBlock, static_cast<int64_t>(12 / scale)); ; sp = sp * 5 / 4) {
+        int64_t items = 0, most = 0, parts = 0;
+        for (const int64_t b : blocks) {
+            const int64_t pieces = (b + sp - 1) / sp;
+            items += pieces;
+            parts = std::max(parts, pieces);
+            most = std::max(most, (b + pieces - 1) / pieces);
+        }
+        const double wgs = static_cast<double>(items) * Hkv, work = static_cast<double>(total) * Hkv;
+        const double share = work / std::min(wgs, static_cast<double>(slots)), per_cu = wgs / num_cus;
+        // a compute unit streams no faster with two workgroups than with one: 24 requests of 1500 tokens in 192 workgroups 23.9 us,
+        // in 384 29.1, in 576 30.3; 4 of 65536 in 192 150 us, in 256 160, in 352 175, in 512 165
+        const double uneven = per_cu > 1 ? 0.5 + 0.5 * std::ceil(per_cu) / per_cu : 1.0;
+        const double t = (work * all + wgs * fixed) * std::max(uneven, alone / all / wgs) + std::max(0.0, most - share) * alone +
+                         (items > plan.n ? merge : 0.0);
+        if (split == 0 || t < best) { best = t; split = sp * kDecodeBlock; best_wgs = items * Hkv; best_parts = parts; }
+        if (sp >= longest || sp * scale >= 410) break;       // (the next one could exceed 512 tiles of 16 KiB)
+    }
+    if (best_wgs > 3 * num_cus && total * Hkv < 8 * best_wgs) return 0;
+    if (best_parts > 32 || (best_parts > 16 && best < 15000)) return 0;
+    return split;
+}
+
+void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_group, Builder& b, DeviceTables& t) {
     const int r = Hq / Hkv;
     const int max_members = std::max(1, kDecodeMaxRows / r);
     // split length: about 1500 waves (work items x KV heads) keep enough loads in flight to fill
@@ -108,29 +177,11 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
     }
     if (plan.tune_decode_split > 0) split = plan.tune_decode_split;     // pk_plan_tune (profiling sweeps)
     split = (split + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock;
-    t.dec_split_tokens = static_cast<int32_t>(split);
+    const bool may = may_group && dtype == PK_BF16 && r <= 16 && plan.tune_decode_split == 0;
+    const int64_t by_group = may ? group_split(plan, Hkv, d, num_cus, split) : 0;
 
-    struct Item { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool grows; };   // (reqs point into the plan)
-    std::vector<Item> items;
-    // suffix: the segment is a request's private suffix; its last item is marked so that the
-    // kernel extends it by the tokens appended into the headroom since the plan was made (an
-    // empty suffix with headroom still gets an item for them)
-    auto add_segment = [&](int64_t a, int64_t e, const int32_t* reqs, int32_t n_reqs, bool suffix) {
-        if (e <= a) {
-            if (suffix && plan.headroom > 0) items.push_back({a, a, reqs, n_reqs, true});
-            return;
-        }
-        // the fewest pieces of at most `split` tokens, all of (nearly) the same length: a full-length
-        // piece next to a short remainder would set the pace of the launch for little work
-        const int64_t a_blk = a / kDecodeBlock * kDecodeBlock;
-        const int64_t blocks = (e - a_blk + kDecodeBlock - 1) / kDecodeBlock;
-        const int64_t pieces = (blocks * kDecodeBlock + split - 1) / split;
-        const int64_t piece = (blocks + pieces - 1) / pieces * kDecodeBlock;
-        for (int32_t m0 = 0; m0 < n_reqs; m0 += max_members)
-            for (int64_t p0 = a_blk; p0 < e; p0 += piece)
-                items.push_back({std::max(a, p0), std::min(e, p0 + piece), reqs + m0, std::min(n_reqs - m0, max_members),
-                                 suffix && p0 + piece >= e});
-    };
+    struct Segment { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool suffix; };   // (reqs point into the plan)
+    std::vector<Segment> segments;
     std::vector<int32_t> req_seg(static_cast<size_t>(plan.n) * 4, 0);
     std::vector<std::vector<int32_t>> chain_of(static_cast<size_t>(plan.n));
     struct Piece { int32_t off; int32_t node, member; };
@@ -144,11 +195,11 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
         for (const Piece& pc : pieces) {
             if (pc.node >= 0) {
                 const Node& nd = g.nodes[static_cast<size_t>(pc.node)];
-                add_segment(g.buf_base + nd.off, g.buf_base + nd.off + nd.len, nd.reqs.data(), static_cast<int32_t>(nd.reqs.size()), false);
+                segments.push_back({g.buf_base + nd.off, g.buf_base + nd.off + nd.len, nd.reqs.data(), static_cast<int32_t>(nd.reqs.size()), false});
                 continue;
             }
             const Member& mm = g.members[static_cast<size_t>(pc.member)];
-            add_segment(g.buf_base + mm.suffix_off, g.buf_base + mm.suffix_off + mm.lq, &mm.req, 1, true);
+            segments.push_back({g.buf_base + mm.suffix_off, g.buf_base + mm.suffix_off + mm.lq, &mm.req, 1, true});
             int32_t* rs = &req_seg[static_cast<size_t>(mm.req) * 4];
             rs[0] = static_cast<int32_t>(g.buf_base + mm.prefix_off); rs[1] = mm.lp;
             rs[2] = static_cast<int32_t>(g.buf_base + mm.suffix_off); rs[3] = mm.lq;
@@ -165,6 +216,53 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
         chain.insert(chain.end(), chain_of[static_cast<size_t>(i)].begin(), chain_of[static_cast<size_t>(i)].end());
         chain_start[static_cast<size_t>(i) + 1] = static_cast<int32_t>(chain.size() / 2);
     }
+    t.dec_req_seg = b.add(req_seg);
+    t.dec_chain_start = b.add(chain_start);
+    t.dec_chain = b.add(chain);
+
+    struct Item { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool grows; };
+    // suffix: the segment is a request's private suffix; its last item is marked so that the
+    // kernel extends it by the tokens appended into the headroom since the plan was made (an
+    // empty suffix with headroom still gets an item for them)
+    auto cut = [&](int64_t split) {
+        std::vector<Item> items;
+        for (const auto& [a, e, reqs, n_reqs, suffix] : segments) {
+            if (e <= a) {
+                if (suffix && plan.headroom > 0) items.push_back({a, a, reqs, n_reqs, true});
+                continue;
+            }
+            // the fewest pieces of at most `split` tokens, all of (nearly) the same length: a full-length
+            // piece next to a short remainder would set the pace of the launch for little work
+            const int64_t a_blk = a / kDecodeBlock * kDecodeBlock;
+            const int64_t blocks = (e - a_blk + kDecodeBlock - 1) / kDecodeBlock;
+            const int64_t pieces = (blocks * kDecodeBlock + split - 1) / split;
+            const int64_t piece = (blocks + pieces - 1) / pieces * kDecodeBlock;
+            for (int32_t m0 = 0; m0 < n_reqs; m0 += max_members)
+                for (int64_t p0 = a_blk; p0 < e; p0 += piece)
+                    items.push_back({std::max(a, p0), std::min(e, p0 + piece), reqs + m0, std::min(n_reqs - m0, max_members),
+                                     suffix && p0 + piece >= e});
+        }
+        return items;
+    };
+    auto parts_of = [&](const std::vector<Item>& items, std::vector<int32_t>& n_items_of) {
+        n_items_of.assign(static_cast<size_t>(plan.n), 0);
+        for (const Item& it : items)
+            for (int32_t x = 0; x < it.n_reqs; ++x) ++n_items_of[static_cast<size_t>(it.reqs[x])];
+        int32_t n_parts = 0;
+        for (int32_t c : n_items_of) n_parts += c > 1 ? c : 0;
+        return n_parts;
+    };
+    std::vector<int32_t> n_items_of;
+    DeviceTables::DecodeSched& s = t.dec;
+    if (by_group > 0) {                            // (an item of a wave has one member here)
+        const std::vector<Item> by_waves = cut(split);
+        s.wave_items = static_cast<int32_t>(by_waves.size());
+        s.wave_parts = parts_of(by_waves, n_items_of);
+        split = by_group;
+    }
+    s.split_tokens = static_cast<int32_t>(split);
+    s.group = by_group > 0;
+    const std::vector<Item> items = cut(split);
     // items with more than 16 query rows first (they run the two-column-tile kernel), then
     // the others; inside each class the longest first (stable: deterministic)
     auto wide = [&](const Item& it) { return it.n_reqs * r > 16; };
@@ -174,14 +272,12 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
         if (wide(items[x]) != wide(items[y])) return wide(items[x]);
         return items[x].e - items[x].a > items[y].e - items[y].a;
     });
-    t.n_dec_wide = 0;
-    for (const Item& it : items) t.n_dec_wide += wide(it) ? 1 : 0;
+    for (const Item& it : items) s.n_wide += wide(it) ? 1 : 0;
     // Partial slots: the slots of one request are consecutive (the merge streams them without
     // indirection); a request covered by a single work item gets no slot: that item writes the
     // final output itself (slot -1).
-    std::vector<int32_t> n_items_of(static_cast<size_t>(plan.n), 0), start(static_cast<size_t>(plan.n) + 1, 0);
-    for (const Item& it : items)
-        for (int32_t x = 0; x < it.n_reqs; ++x) ++n_items_of[static_cast<size_t>(it.reqs[x])];
+    std::vector<int32_t> start(static_cast<size_t>(plan.n) + 1, 0);
+    parts_of(items, n_items_of);
     int32_t n_parts = 0;
     for (int32_t i = 0; i < plan.n; ++i) {
         start[static_cast<size_t>(i)] = n_parts;
@@ -204,17 +300,14 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int num_cus, Buil
             member_slot.push_back(n_items_of[static_cast<size_t>(rq)] > 1 ? next_slot[static_cast<size_t>(rq)]++ : -1);
         }
     }
-    t.n_dec_items = static_cast<int32_t>(items.size());
-    t.n_dec_parts = n_parts;
-    t.dec_max_parts = 0;
-    for (int32_t c : n_items_of) t.dec_max_parts = std::max(t.dec_max_parts, c > 1 ? c : 0);
-    t.dec_items = b.add(flat);
-    t.dec_members = b.add(members);
-    t.dec_member_slot = b.add(member_slot);
-    t.dec_req_part_start = b.add(start);
-    t.dec_req_seg = b.add(req_seg);
-    t.dec_chain_start = b.add(chain_start);
-    t.dec_chain = b.add(chain);
+    s.n_items = static_cast<int32_t>(items.size());
+    s.n_parts = n_parts;
+    for (int32_t c : n_items_of) s.max_parts = std::max(s.max_parts, c > 1 ? c : 0);
+    s.items = b.add(flat);
+    s.members = b.add(members);
+    s.member_slot = b.add(member_slot);
+    s.req_part_start = b.add(start);
+    if (s.group) s.arrived = b.add(std::vector<int32_t>(static_cast<size_t>(plan.n) * Hkv, 0));
 }
 
 // ---- prefill ---------------------------------------------------------------
@@ -464,7 +557,8 @@ size_t kv_buf_bytes(const pk_plan& plan, int Hkv, int d, int dtype) {
     return static_cast<size_t>(plan.buf_tokens) * Hkv * d * 2 * elem;
 }
 
-void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, DeviceTables& t) {
+namespace {
+void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_group, DeviceTables& t) {
     t = DeviceTables();
     t.Hq = Hq; t.Hkv = Hkv; t.d = d; t.dtype = dtype;
     Builder b(t.host);
@@ -476,13 +570,23 @@ void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     t.q_start = b.add(std::vector<int32_t>(q_start.begin(), q_start.end()));
     t.kv_start = b.add(std::vector<int32_t>(kv_start.begin(), kv_start.end()));
     build_reorg(plan, b, t);
-    if (plan.decode_only) build_decode(plan, Hq, Hkv, d, num_cus, b, t);
+    if (plan.decode_only) build_decode(plan, Hq, Hkv, d, dtype, num_cus, may_group, b, t);
     build_prefill_packed(plan, q_start, kv_start, Hq, num_cus, b, t);
     t.host.resize((t.host.size() + 63) / 64 * 64, 0);
     t.tables_bytes = t.host.size() * sizeof(int32_t);
     t.partial_offset = t.tables_bytes;
-    t.partial_bytes = static_cast<size_t>(t.n_dec_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
+    t.partial_bytes = static_cast<size_t>(t.dec.n_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
     t.decode_only_bytes = t.partial_offset + t.partial_bytes;
+    if (t.dec.group) {
+        // what the plan would need with a wave per item decides whether it may use the fixed scratch
+        auto aligned = [](size_t words) { return (words + 63) / 64 * 64; };
+        auto words = [&](size_t items) { return aligned(8 * items) + 2 * aligned(items); };     // with their members and slots
+        const size_t by_waves = t.tables_bytes + sizeof(int32_t) * (words(static_cast<size_t>(t.dec.wave_items)) -
+            words(static_cast<size_t>(t.dec.n_items)) - aligned(static_cast<size_t>(plan.n) * Hkv)) +
+            static_cast<size_t>(t.dec.wave_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
+        t.group_over_scratch = t.decode_only_bytes > PK_STATIC_SCRATCH_BYTES && by_waves <= PK_STATIC_SCRATCH_BYTES;
+        t.decode_only_bytes = by_waves;
+    }
     if (plan.decode_only) {
         // the padded comparison kernel keeps (request, split) partials in the same region: the
         // same number of splits for every request, sized by the longest -- at most 64, each a
@@ -498,6 +602,12 @@ void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     }
     t.padded_offset = (t.partial_offset + t.partial_bytes + 255) / 256 * 256;
     t.total_bytes = (t.padded_offset + padded_bound_bytes(plan) + 255) / 256 * 256;
+}
+}  // namespace
+
+void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, DeviceTables& t) {
+    fill_tables(plan, Hq, Hkv, d, dtype, num_cus, true, t);
+    if (t.group_over_scratch) fill_tables(plan, Hq, Hkv, d, dtype, num_cus, false, t);
 }
 
 }  // namespace pk
