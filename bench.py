@@ -727,7 +727,7 @@ def main():
         "roofline_decode": {"bound": "hbm", "achieved": m["decode_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": m["decode_gbs"] / HBM_PEAK_GBS,
                             "traffic": profiled("decode_cfg5", "total_bytes") if args.seed == 0 else None,
-                            "kernel": "decode_bf16_kernel<128> + decode_merge_kernel<128, 4>",
+                            "kernel": "decode_bf16_group_kernel<128>",
                             "kernel_ms": m["decode_ms_incl_merge"], "bytes_per_launch": m["decode_alg_bytes"]},
         "roofline_relayout": {"bound": "hbm", "achieved": m["relayout_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": m["relayout_gbs"] / HBM_PEAK_GBS,

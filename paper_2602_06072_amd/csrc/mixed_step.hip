@@ -9,12 +9,10 @@
 // the decode runs spread evenly over the launch; the prefill workgroups keep their numbers modulo 8,
 // i.e. their XCD, so the heads of a KV head still share an L2.  The LSE merge of the decode partials
 // is a second, short launch.
-// What bounds it (32 chunks of a 70B-shaped layer + 480 decode rows, 12.52 ms): the prefill tiles alone
-// take 11.0 ms; with every decode load served by an L2 the step takes 11.5 ms, with decode items of
-// two tiles 11.05 ms.  The slots that decode workgroups take cost half a millisecond, streaming 17.9 GB
-// next to the prefill tiles the other one (2.9 ms when nothing else runs).
+// What bounds it (32 chunks of a 70B-shaped layer + 480 decode rows, 12.2 ms): the prefill tiles alone take 10.3 ms, the
+// decode alone 2.6; what decode workgroups cost is the slots that they take and 17.9 GB streaming next to
+// prefill tiles, about half of it each.  Eight-wave prefill workgroups here: 12.15 to 12.7 ms.
 #include "decode_body.hip.h"
-#define PK_HEADS 1
 #define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
@@ -26,7 +24,6 @@
 #include "prefill_body.hip.h"
 #undef PK_D
 #undef PK_DNS
-#undef PK_HEADS
 #undef PK_WAVES
 
 namespace pk {
@@ -36,8 +33,8 @@ namespace {
 // its XCD).  `cycles` cycles of one decode run and `stride - 1` prefill runs come first, then what is
 // left of the longer kind.  Spread over the launch, the decode runs load the memory system evenly;
 // alternating one by one until the decode work is gone they saturate it for the first quarter of the
-// launch, and the prefill tiles of that stretch wait: 12.68 -> 12.52 ms for the step above, small steps
-// unchanged.  Runs of 64 measure the same, runs of 8 13.0 ms (workgroups go to the compute units of an XCD
+// launch, and the prefill tiles of that stretch wait (spread 1.3 % faster for the step above, small steps
+// unchanged).  Runs of 64 measure the same, runs of 8 4 % more (workgroups go to the compute units of an XCD
 // one per unit before any unit gets its second: short runs put two of a kind on one unit).
 constexpr int kRun = 256;
 

@@ -13,24 +13,15 @@
 //     form costs more of it (MFMAs alone on random operands: 1.75 PFLOP/s at 1.70 GHz against 2.07 at 2.02).
 
 // Device code only: included by prefill_pipe.hip (the prefill launch) and by mixed_step.hip (the
-// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_HEADS (query heads of a KV
-// head that one wave works on: 1 or 2) and PK_DNS (the namespace this instance goes into) first; the
-// file may be included once per combination.
+// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4, or 8 for two query heads of
+// a KV head) and PK_DNS (the namespace this instance goes into) first; the file may be included once per combination.
 #include <cstdint>
 
 #include "common.hip.h"
 #include "kernels.h"
 
-#if !defined(PK_D) || !defined(PK_DNS) || !defined(PK_HEADS) || !defined(PK_WAVES) || (PK_D != 128 && PK_D != 64) || (PK_HEADS != 1 && PK_HEADS != 2)
-#error "define PK_D (128 or 64), PK_HEADS (1 or 2) and PK_DNS before including prefill_body.hip.h"
-#endif
-
-// Where the output accumulators live.  With two heads and D = 128 one wave has all 512 registers of its SIMD; the
-// accumulation registers take the 144 that only MFMAs touch.
-#if PK_D == 128 && PK_HEADS == 2
-#define PK_OUT(X) "+a"(X)
-#else
-#define PK_OUT(X) "+v"(X)
+#if !defined(PK_D) || !defined(PK_DNS) || !defined(PK_WAVES) || (PK_D != 128 && PK_D != 64) || (PK_WAVES != 4 && PK_WAVES != 8)
+#error "define PK_D (128 or 64), PK_WAVES (4 or 8) and PK_DNS before including prefill_body.hip.h"
 #endif
 
 namespace pk {
@@ -42,7 +33,7 @@ constexpr int ROWB = D * 2;                        // bytes per K/V row in globa
 constexpr int TILE_BYTES = BN * ROWB;              // 16 KiB (8 KiB for D = 64)
 constexpr int KS = D / 32;                         // contraction steps of a score
 constexpr int OPS = D / 16;                        // LDS operands per half tile, of K (two blocks of 16 keys x KS) as of V (blocks of 16 columns)
-constexpr int HEADS = PK_HEADS, NC = 2 * HEADS;    // column blocks of a wave: block c holds rows 16 (c & 1) .. + 15 of head c / 2
+constexpr int NC = 2;                              // column blocks of a wave: block c holds its rows 16 c .. + 15
 constexpr int WAVES = PK_WAVES;                     // 4, or 8: waves 4 .. 7 work on the next head
 constexpr int PIECES = TILE_BYTES / (1024 * WAVES);   // 1-KiB copy instructions per wave and tile
 constexpr int RPW = BN / WAVES, PPS = RPW / 8;        // rows (and copies) of a slab that one wave fills
@@ -116,7 +107,7 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     // the first: every other set of 256 workgroups (a set is one per compute unit) deals
     // the rows in reverse, so that the waves of a SIMD get as much together as those of any other.
     const int w4 = u.wave & 3, second = u.wave >> 2;
-    u.head = ((u.kvh * groups + pair) * (WAVES / 4) + second) * HEADS;
+    u.head = (u.kvh * groups + pair) * (WAVES / 4) + second;
     u.rows = (WAVES > 4 ? second : (block >> 8) & 1) ? 3 - w4 : w4;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
@@ -145,9 +136,9 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     // a query read row 0 and are cleared once it is there (clear_absent_rows).
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const int qrow = u.qrow[c & 1];
+        const int qrow = u.qrow[c];
         const uint16_t* qp = static_cast<const uint16_t*>(a.q) +
-                             (static_cast<int64_t>(qrow < 0 ? 0 : qrow) * a.Hq + u.head + c / 2) * D + 8 * u.g;
+                             (static_cast<int64_t>(qrow < 0 ? 0 : qrow) * a.Hq + u.head) * D + 8 * u.g;
 #pragma unroll
         for (int s = 0; s < KS; ++s) qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 32 * s));
     }
@@ -162,7 +153,7 @@ __device__ __forceinline__ void clear_absent_rows(const WorkUnit& u, bf16x8 (&qf
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const u32x4 raw = __builtin_bit_cast(u32x4, qf[c][s]);
-            qf[c][s] = __builtin_bit_cast(bf16x8, u.qrow[c & 1] < 0 ? u32x4{0u, 0u, 0u, 0u} : raw);
+            qf[c][s] = __builtin_bit_cast(bf16x8, u.qrow[c] < 0 ? u32x4{0u, 0u, 0u, 0u} : raw);
         }
 }
 
@@ -170,15 +161,15 @@ __device__ __forceinline__ void clear_absent_rows(const WorkUnit& u, bf16x8 (&qf
 __device__ __forceinline__ float row_scale(const float l) { return l == 0.f ? 0.f : 1.f / l; }
 
 // o / l of head `h` to global memory; lane (n, g) owns columns 16t + 4g .. +3 of its two query rows.
-__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const int h, const floatx4 (&o)[NC][OPS], const floatx4 (&l)[NC]) {
+__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx4 (&o)[NC][OPS], const floatx4 (&l)[NC]) {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const float inv = row_scale(l[2 * h + c][0]);
+        const float inv = row_scale(l[c][0]);
         if (u.qrow[c] < 0) continue;
-        float* out = static_cast<float*>(a.out) + (static_cast<int64_t>(u.qrow[c]) * a.Hq + u.head + h) * D + 4 * u.g;
+        float* out = static_cast<float*>(a.out) + (static_cast<int64_t>(u.qrow[c]) * a.Hq + u.head) * D + 4 * u.g;
 #pragma unroll
         for (int t = 0; t < OPS; ++t) {
-            const floatx4 x = o[2 * h + c][t];
+            const floatx4 x = o[c][t];
             *reinterpret_cast<float4*>(out + 16 * t) = make_float4(x[0] * inv, x[1] * inv, x[2] * inv, x[3] * inv);
         }
     }
@@ -189,16 +180,16 @@ __device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUni
 // The wave uses two pieces of LDS of 16 rows each that belong to it alone (block 0 in qa, block 1
 // in qb); the 16-byte chunks of a row are XOR-swizzled with the row number, which keeps
 // both sides off bank conflicts.
-__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const int h, const floatx4 (&o)[NC][OPS],
+__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx4 (&o)[NC][OPS],
                                                   const floatx4 (&l)[NC], unsigned char* qa, unsigned char* qb) {
     constexpr int CPR = D / 8, RPI = 64 / CPR;     // 16-byte chunks per row; rows per store instruction
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const float inv = row_scale(l[2 * h + c][0]);
+        const float inv = row_scale(l[c][0]);
         unsigned char* wrow = (c ? qb : qa) + u.n * ROWB + 8 * (u.g & 1);
 #pragma unroll
         for (int t = 0; t < OPS; ++t) {            // columns 16t + 4g .. +3: chunk 2t + g / 2, half g & 1
-            const floatx4 x = o[2 * h + c][t];
+            const floatx4 x = o[c][t];
             *reinterpret_cast<uint2*>(wrow + (((2 * t + (u.g >> 1)) ^ (u.n & (CPR - 1))) << 4)) =
                 make_uint2(pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv));
         }
@@ -218,7 +209,7 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
     for (int k = 0; k < 32 / RPI; ++k)
         if (q_row[k] >= 0)
             *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) +
-                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head + h) * D + 8 * chunk) = v[k];
+                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * D + 8 * chunk) = v[k];
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
@@ -419,10 +410,10 @@ __device__ __forceinline__ void softmax_redo(const floatx4 (&s)[2], uint32_t* pw
 // (The statements around the products keep them in place: the compiler would otherwise put the rescaled accumulators into fresh
 // registers, more than there are.)
 __device__ __forceinline__ void rescale(floatx4& x, const float alpha) {
-    asm volatile("" : PK_OUT(x));
+    asm volatile("" : "+v"(x));
 #pragma unroll
     for (int e = 0; e < 4; ++e) x[e] *= alpha;
-    asm volatile("" : PK_OUT(x));
+    asm volatile("" : "+v"(x));
 }
 #define PK_SOFTMAX_CHECK(S, H)                                                                 \
     if (H.slow != 0) {                                                                         \
@@ -442,7 +433,7 @@ __device__ __forceinline__ void rescale(floatx4& x, const float alpha) {
 __device__ __forceinline__ void mask_half(Scores& s, int half, const int (&visible)[2], int g) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const int left = visible[c & 1] - 4 * g - 32 * half;
+        const int left = visible[c] - 4 * g - 32 * half;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
 #pragma unroll
@@ -499,7 +490,7 @@ __device__ __forceinline__ void mfma(floatx4& d, const bf16x8& a, const bf16x8& 
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
 __device__ __forceinline__ void mfma_out(floatx4& d, const bf16x8& a, const bf16x8& b) {     // (d: output accumulator)
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : PK_OUT(d) : "v"(a), "v"(b));
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
 __device__ __forceinline__ void mfma_first(floatx4& d, const bf16x8& a, const bf16x8& b) {   // d = a.b
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
@@ -519,7 +510,7 @@ __device__ __forceinline__ void pv_mfma(const int c, floatx4 (&o)[NC][OPS], floa
 }
 // one step: NC MFMAs (MFMA, in terms of c), each with what stands behind it (SLOT, in terms of c)
 #define PK_SLOT(C, MFMA, ...) if constexpr ((C) < NC) { constexpr int c = C; MFMA; __VA_ARGS__; __builtin_amdgcn_sched_barrier(0); }
-#define PK_SLOTS(MFMA, ...) PK_SLOT(0, MFMA, __VA_ARGS__) PK_SLOT(1, MFMA, __VA_ARGS__) PK_SLOT(2, MFMA, __VA_ARGS__) PK_SLOT(3, MFMA, __VA_ARGS__)
+#define PK_SLOTS(MFMA, ...) PK_SLOT(0, MFMA, __VA_ARGS__) PK_SLOT(1, MFMA, __VA_ARGS__)
 // M: step of the part; DST: scores in the making; SRC: scores whose softmax is taken, into H; P: probabilities for P.V.  The ring
 // holds operands M .. M + 2, and operand M + 3 replaces that of the step before.
 #define PK_STEP_SLOT(PART, DST, SRC, H, P, EXTRA)                                             \
@@ -591,7 +582,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     float m_ref[NC], far[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        m_ref[c] = u.qrow[c & 1] < 0 ? kNoRow : kUnset;   // rows without a query never ask for the slow path
+        m_ref[c] = u.qrow[c] < 0 ? kNoRow : kUnset;   // rows without a query never ask for the slow path
         far[c] = 0.f;
         lsum[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -758,16 +749,13 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     }
     while (t < n_kv) PK_SKIP_TURN()
     // After the last barrier nobody fills or reads a stage any more: quarters of a K and a V stage stage the
-    // waves' output, one head after the other (a wave's LDS accesses are in order).
+    // waves' output (a wave's LDS accesses are in order).
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
     PK_MFMA_RESULTS()
 #pragma unroll
-    for (int c = 0; c < NC; ++c) asm volatile("" : PK_OUT(lsum[c]));   // (all four words of a sum are live until here)
-#pragma unroll
-    for (int h = 0; h < HEADS; ++h) {
-        if (a.out_f32) store_output(a, u, h, o, lsum);
-        else store_output_bf16(a, u, h, o, lsum, lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART, lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
-    }
+    for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(lsum[c]));   // (all four words of a sum are live until here)
+    if (a.out_f32) store_output(a, u, o, lsum);
+    else store_output_bf16(a, u, o, lsum, lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART, lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
 }
 
 #undef PK_COPY_TILE
@@ -801,4 +789,3 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 }  // namespace PK_DNS
 }  // namespace
 }  // namespace pk
-#undef PK_OUT

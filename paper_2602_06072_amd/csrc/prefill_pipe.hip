@@ -1,6 +1,5 @@
 // Packed prefill attention, bf16 MFMA, head dimensions 128 and 64 (Sec. 3.1): the launches.  The
 // kernels' device code is in prefill_body.hip.h, included once per head dimension.
-#define PK_HEADS 1
 #define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
@@ -20,7 +19,6 @@
 #undef PK_D
 #undef PK_DNS
 #undef PK_WAVES
-#undef PK_HEADS
 
 namespace pk {
 namespace {
@@ -50,19 +48,18 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv));
     a.by_hkv = FastDiv::by(static_cast<uint32_t>(a.Hkv));
     // Copying each K/V tile once for two heads halves the copies (a tile step of two four-wave workgroups on a
-    // compute unit reads 256 KiB of LDS and writes 64; the LDS delivers about 128 bytes a cycle, as many
-    // as the matrix pipes ask for at full rate).  What it costs: nothing runs beside a workgroup's first loads
+    // compute unit reads 256 KiB of LDS and writes 64), and the energy they take.  What it costs: nothing runs beside a workgroup's first loads
     // and last stores, and a chip that is not full has fewer compute units at work.  Four / eight waves:
-    //   32 chunks of a 70B-shaped layer (126 key tiles on average)  11.12 / 10.88 ms
-    //   1 x 4096 rows behind 8192 (160 tiles, 1024 four-wave workgroups)  602 / 582 us
-    //   2 x 3000 behind 3000 with 16 heads (71 tiles, 752 workgroups)     254 / 228 us
-    //   8 x 4096 (32 tiles)  1014 / 1005 us;  32 x 1024 behind 1024 (24 tiles)  803 / 805 us
-    //   16 x 2048 (16 tiles)  573 / 575 us;  64 ragged prompts (10 tiles)  391 / 393 us
-    //   1 x 1024 behind 8192 (136 tiles, 256 workgroups)  158 / 199 us
-    // D = 64 stays with four waves: with 151 registers a wave, three such workgroups share a compute unit, of eight waves
-    // only one does (in 128 registers, for two, the body spills and is slower again):
-    //   8 x 4096  604 / 667 us;  16 x 2048  336 / 375 us;  32 x 512 behind 8192 with 64 heads  2342 / 2560 us
-    //   1 x 1024 behind 8192  115 / 149 us;  1 x 4096 behind 8192  378 / 374 us;  2 x 3000 behind 3000 with 16 heads  187 / 165 us
+    //   32 chunks of a 70B-shaped layer (126 key tiles on average)  10.42 / 10.32 ms
+    //   1 x 4096 rows behind 8192 (160 tiles, 1024 four-wave workgroups)  573 / 549 us
+    //   2 x 3000 behind 3000 with 16 heads (71 tiles, 752 workgroups)     252 / 225 us
+    //   32 x 1024 behind 2048 (40 tiles)  1225 / 1216 us;  8 x 4096 (32 tiles)  979 / 981 us;  32 x 1024 behind 1024 (24 tiles)  782 / 786 us
+    //   16 x 2048 (16 tiles)  561 / 558 us;  64 ragged prompts (10 tiles)  379 / 380 us
+    //   1 x 2048 behind 8192 (144 tiles, 512 workgroups)  271 / 265 us;  1 x 1024 (256 workgroups)  152 / 206 us
+    // D = 64 stays with four waves: with 168 registers a wave, three such workgroups share a compute unit, of eight waves
+    // only one does:
+    //   8 x 4096  575 / 627 us;  16 x 2048  326 / 363 us;  32 x 512 behind 8192 with 64 heads  2205 / 2342 us
+    //   1 x 1024 behind 8192  123 / 149 us;  1 x 4096 behind 8192  363 / 348 us;  2 x 3000 behind 3000 with 16 heads  187 / 164 us
     const int64_t alone = static_cast<int64_t>(a.n_tiles) * a.Hq;             // workgroups with one head each
     const bool two = a.d == 128 && a.heads_per_kv % 2 == 0 && alone >= 512 && a.n_key_tiles >= 32 * static_cast<int64_t>(a.n_tiles);
     if (two) { a.heads_per_kv /= 2; a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv)); }

@@ -1,0 +1,51 @@
+"""The prefill pipeline where its parts begin and end: key lists of one to three tiles (prologue and last turn alone) and around
+64 and 128 entries (the list is read 64 entries at a time), last tiles of which a wave sees one half only, tiles that rows of
+other requests skip at the start and the end of the list; four and eight waves, both head dimensions."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_06072_amd import binding as pk
+from paper_2602_06072_amd import workloads as wl
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+TAILS = {"half": 1, "half_full": 32, "second_half": 33, "full": 64}     # keys of the last tile
+
+
+def check(kv, ql, Hq, Hkv, d, what):
+    w = wl.make_ragged(f"pipe_{what}", np.asarray(kv, np.int32), np.asarray(ql, np.int32), Hq, Hkv, d, 1 << 16, 31, device=DEV,
+                       keep_f32=False)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=1 << 16)
+    ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
+    out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
+    torch.cuda.synchronize()
+    H.assert_close(out.cpu().numpy(), H.oracle_ragged(w, False), 0, what)
+    return plan
+
+
+@pytest.mark.parametrize("tail", TAILS)
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 63, 64, 65, 66, 127, 128, 129])
+@pytest.mark.parametrize("d", [64, 128])
+def test_key_lists(d, tiles, tail):
+    kv = 64 * (tiles - 1) + TAILS[tail]
+    check([kv], [min(kv, 37)], 2, 1, d, f"{tiles} tiles, {tail}, d {d}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_tiles_of_several_requests(d):
+    """Enough tiles that requests share them: a wave skips the key tiles of the requests that it holds no rows of."""
+    check([700, 64, 65, 1300, 33, 31] * 6, [30, 2, 33, 31, 31, 1] * 6, 16, 8, d, f"shared tiles of six, d {d}")
+    n = 90
+    ql = np.random.default_rng(5).integers(1, 60, n)
+    check(ql + np.arange(n) * 7, ql, 16, 8, d, f"shared tiles, d {d}")
+
+
+@pytest.mark.parametrize("tail", TAILS)
+def test_eight_waves(tail):
+    kv = np.asarray([64 * t + TAILS[tail] for t in (31, 40, 62, 63, 64, 65, 33, 34)], dtype=np.int32)
+    ql = np.asarray([1, 31, 32, 33, 64, 96, 127, 128], dtype=np.int32)
+    plan = check(kv, ql, 64, 8, 128, f"eight waves, {tail}")
+    assert plan.stat(6) * 64 >= 512                 # (workgroups of one head each: the eight-wave kernel's limit)
