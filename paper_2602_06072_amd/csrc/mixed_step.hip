@@ -24,6 +24,16 @@
 #include "prefill_body.hip.h"
 #undef PK_D
 #undef PK_DNS
+#define PK_D 128
+#define PK_DNS few128
+#include "prefill_few_body.hip.h"
+#undef PK_D
+#undef PK_DNS
+#define PK_D 64
+#define PK_DNS few64
+#include "prefill_few_body.hip.h"
+#undef PK_D
+#undef PK_DNS
 #undef PK_WAVES
 
 namespace pk {
@@ -88,6 +98,10 @@ __device__ __forceinline__ void decode_by_workgroup(const FastDiv& by_hkv, const
 static_assert(kGroupLds<128> <= 5 * d128::TILE_BYTES && kGroupLds<64> <= 5 * d64::TILE_BYTES && kGroupWaves == 4, "decode_by_workgroup");
 PK_MIXED_STEP_KERNEL(mixed_step_kernel, d128, 128, 2, decode_by_waves)
 PK_MIXED_STEP_KERNEL(mixed_step64_kernel, d64, 64, 3, decode_by_waves)
+PK_MIXED_STEP_KERNEL(mixed_step_few_kernel, few128, 128, 2, decode_by_waves)
+PK_MIXED_STEP_KERNEL(mixed_step64_few_kernel, few64, 64, 2, decode_by_waves)
+PK_MIXED_STEP_KERNEL(mixed_step_few_group_kernel, few128, 128, 2, decode_by_workgroup)
+PK_MIXED_STEP_KERNEL(mixed_step64_few_group_kernel, few64, 64, 2, decode_by_workgroup)
 PK_MIXED_STEP_KERNEL(mixed_step_group_kernel, d128, 128, 2, decode_by_workgroup)
 PK_MIXED_STEP_KERNEL(mixed_step64_group_kernel, d64, 64, 3, decode_by_workgroup)
 #undef PK_MIXED_STEP_KERNEL
@@ -120,7 +134,12 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     if (pa.d != da.d || (pa.d != 128 && pa.d != 64)) return static_cast<int>(hipErrorInvalidValue);
     if (grid > 0) {
         const dim3 wgs(static_cast<unsigned>(grid));
-        if (pa.d == 128 && da.arrived) hipLaunchKernelGGL(mixed_step_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
+        if (few_workgroups(pa)) {
+            if (pa.d == 128 && da.arrived) hipLaunchKernelGGL(mixed_step_few_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
+            else if (pa.d == 128) hipLaunchKernelGGL(mixed_step_few_kernel, wgs, dim3(256), 0, st, pa, da, m);
+            else if (da.arrived) hipLaunchKernelGGL(mixed_step64_few_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
+            else hipLaunchKernelGGL(mixed_step64_few_kernel, wgs, dim3(256), 0, st, pa, da, m);
+        } else if (pa.d == 128 && da.arrived) hipLaunchKernelGGL(mixed_step_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
         else if (pa.d == 128) hipLaunchKernelGGL(mixed_step_kernel, wgs, dim3(256), 0, st, pa, da, m);
         else if (da.arrived) hipLaunchKernelGGL(mixed_step64_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
         else hipLaunchKernelGGL(mixed_step64_kernel, wgs, dim3(256), 0, st, pa, da, m);

@@ -11,6 +11,16 @@
 #include "prefill_body.hip.h"
 #undef PK_D
 #undef PK_DNS
+#define PK_D 128
+#define PK_DNS few128
+#include "prefill_few_body.hip.h"
+#undef PK_D
+#undef PK_DNS
+#define PK_D 64
+#define PK_DNS few64
+#include "prefill_few_body.hip.h"
+#undef PK_D
+#undef PK_DNS
 #undef PK_WAVES
 #define PK_WAVES 8
 #define PK_D 128
@@ -40,6 +50,17 @@ __global__ __launch_bounds__(256, 3) void prefill_bf16_dma64_kernel(PrefillArgs 
     d64::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
 }
 
+// Launches that leave compute units without a workgroup.
+__global__ __launch_bounds__(256, 2) void prefill_bf16_few_kernel(PrefillArgs a) {
+    __shared__ __align__(1024) unsigned char lds[5 * few128::TILE_BYTES];
+    few128::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
+}
+
+__global__ __launch_bounds__(256, 2) void prefill_bf16_few64_kernel(PrefillArgs a) {
+    __shared__ __align__(1024) unsigned char lds[5 * few64::TILE_BYTES];
+    few64::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
+}
+
 }  // namespace
 
 int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
@@ -67,6 +88,12 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     const int64_t grid = (pairs + 7) / 8 * 8 * a.heads_per_kv;
     if (grid == 0) return 0;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
+    if (few_workgroups(a) && (a.d == 128 || a.d == 64)) {
+        const dim3 wgs(static_cast<unsigned>(grid));
+        if (a.d == 128) hipLaunchKernelGGL(prefill_bf16_few_kernel, wgs, dim3(256), 0, static_cast<hipStream_t>(stream), a);
+        else hipLaunchKernelGGL(prefill_bf16_few64_kernel, wgs, dim3(256), 0, static_cast<hipStream_t>(stream), a);
+        return static_cast<int>(hipGetLastError());
+    }
     if (two)
         hipLaunchKernelGGL(prefill_bf16_pair_kernel, dim3(static_cast<unsigned>(grid)), dim3(512), 0,
                            static_cast<hipStream_t>(stream), a);

@@ -1,6 +1,7 @@
 """The prefill pipeline where its parts begin and end: key lists of one to three tiles (prologue and last turn alone) and around
 64 and 128 entries (the list is read 64 entries at a time), last tiles of which a wave sees one half only, tiles that rows of
-other requests skip at the start and the end of the list; four and eight waves, both head dimensions."""
+other requests skip at the start and the end of the list; four and eight waves, both head
+dimensions, launches of few workgroups (with a body of their own) and of more than the chip has units."""
 import numpy as np
 import pytest
 import torch
@@ -32,6 +33,7 @@ def check(kv, ql, Hq, Hkv, d, what):
 def test_key_lists(d, tiles, tail):
     kv = 64 * (tiles - 1) + TAILS[tail]
     check([kv], [min(kv, 37)], 2, 1, d, f"{tiles} tiles, {tail}, d {d}")
+    check([kv] * 5, [min(kv, 3 * n + 1) for n in range(5)], 64, 8, d, f"{tiles} tiles, {tail}, d {d}, a full chip")
 
 
 @pytest.mark.parametrize("d", [64, 128])
