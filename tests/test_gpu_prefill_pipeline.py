@@ -33,7 +33,7 @@ def check(kv, ql, Hq, Hkv, d, what):
 def test_key_lists(d, tiles, tail):
     kv = 64 * (tiles - 1) + TAILS[tail]
     check([kv], [min(kv, 37)], 2, 1, d, f"{tiles} tiles, {tail}, d {d}")
-    check([kv] * 5, [min(kv, 3 * n + 1) for n in range(5)], 64, 8, d, f"{tiles} tiles, {tail}, d {d}, a full chip")
+    check([kv] * 7, [min(kv, 3 * n + 1) for n in range(7)], 64, 8, d, f"{tiles} tiles, {tail}, d {d}, a full chip")
 
 
 @pytest.mark.parametrize("d", [64, 128])
