@@ -395,7 +395,7 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
                           int dtype, int out_dtype,
                           void* workspace, size_t workspace_bytes, void* stream);
 
-/* Counts for the benchmark's work accounting (host).  1..7 refer to the
+/* Counts for the benchmark's work accounting (host).  1..9 refer to the
  * tables of the head shape the plan was last sized or bound for (0 before).
  *   what = 0: unmasked (query,key) pairs per head summed over requests
  *   what = 1: (query,key) pairs issued to the MFMA units by the packed
@@ -404,6 +404,9 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
  *   what = 3: decode work items; 4: split-KV partial slots;
  *   what = 5: tokens per decode split chosen by the schedule builder
  *   what = 6: query tiles of the packed prefill schedule; 7: of the padded
+ *   what = 8: 1 if the packed bf16 prefill (also the prefill half of a mixed
+ *             step) takes the kernels for launches of little work, 0 if the
+ *             software-pipelined ones; 9: same for the padded schedule
  */
 int64_t pk_plan_stat(const pk_plan* plan, int what);
 

@@ -312,6 +312,7 @@ static int prefill_common(pk_plan* plan, const void* q, const void* k, const voi
     a.tiles = tab(plan, s.tiles, base); a.n_tiles = s.n_tiles;
     a.run_first = tab(plan, s.run_first, base); a.runs = tab(plan, s.runs, base);
     a.kvtiles = tab(plan, s.kvtiles, base); a.n_key_tiles = static_cast<int64_t>(s.kvtiles.count / 2);
+    a.light = s.light;
     a.q_start = tab(plan, t.q_start); a.kv_start = tab(plan, t.kv_start); a.n = plan->n;
     int64_t tq = 0, tkv = 0;
     for (int32_t i = 0; i < plan->n; ++i) { tq += plan->q_lens[i]; tkv += plan->kv_lens[i]; }
@@ -586,6 +587,11 @@ extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
                 if (!plan->tables.padded_built && plan->tables.dtype >= 0)
                     build_prefill_padded(*plan, plan->tables);
                 return plan->tables.padded.n_tiles;
+            case 8: return plan->tables.packed.light;
+            case 9:
+                if (!plan->tables.padded_built && plan->tables.dtype >= 0)
+                    build_prefill_padded(*plan, plan->tables);
+                return plan->tables.padded.light;
             default: return 0;
         }
     });

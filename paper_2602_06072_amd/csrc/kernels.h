@@ -76,13 +76,9 @@ struct PrefillArgs {
     int Hq; int Hkv; int d; float scale; int out_f32;
     int pipeline;                                   // 0: K/V tiles copied straight into LDS; 1: staged through registers
     int64_t n_key_tiles;                            // entries of kvtiles
+    int light;                                      // pipeline 0: a launch of little work, prefill_few_body.hip.h
     int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: workgroups per (query tile, KV head), divisions by it and by Hkv
 };
-// Fewer prefill workgroups than the 256 compute units (with head dimension 64 than one and a half per unit): most waves are alone on
-// their SIMD, and prefill_few_body.hip.h is the faster one.  One workgroup per unit, 1 x 1024 rows behind 8192 tokens with 32 heads (the other
-// body / that one): head dimension 128 152.5 / 155.2 us, 64 122.0 / 115.4; 64 x 64 behind 1000 (1088 workgroups) 109.7 / 113.2 and 69.0 / 68.8;
-// head dimension 64, 320 workgroups 41.4 / 40.1, 384 74.3 / 74.0, 512 81.3 / 84.2.
-inline bool few_workgroups(const PrefillArgs& a) { return static_cast<int64_t>(a.n_tiles) * a.Hq < (a.d == 64 ? 384 : 256); }
 #if defined(__HIPCC__)
 // Row `local` (0..127) of query tile `tile`: its Q row (-1: padding) and its key range [lo, hi).
 // d4..d7 are words 4..7 of the tile's descriptor (rows | runs << 16; Q row, lo, hi of tile row 0).

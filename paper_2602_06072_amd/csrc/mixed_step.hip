@@ -134,7 +134,7 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     if (pa.d != da.d || (pa.d != 128 && pa.d != 64)) return static_cast<int>(hipErrorInvalidValue);
     if (grid > 0) {
         const dim3 wgs(static_cast<unsigned>(grid));
-        if (few_workgroups(pa)) {
+        if (pa.light) {
             if (pa.d == 128 && da.arrived) hipLaunchKernelGGL(mixed_step_few_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
             else if (pa.d == 128) hipLaunchKernelGGL(mixed_step_few_kernel, wgs, dim3(256), 0, st, pa, da, m);
             else if (da.arrived) hipLaunchKernelGGL(mixed_step64_few_group_kernel, wgs, dim3(256), 0, st, pa, da, m);

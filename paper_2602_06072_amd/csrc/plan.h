@@ -83,7 +83,9 @@ struct DeviceTables {
         TableRef kvtiles;           // [n_kv_total][2] k_start, n | wavemask<<8 | full<<16
         int32_t n_tiles = 0;
         int64_t issued_pairs = 0;
+        bool light = false;         // a launch of little work: prefill_few_body.hip.h (the schedule builder's choice)
     } packed, padded;
+    int num_cus = 0;                // of the device the schedules are built for
     // padded prefill schedule: built on first use, uploaded behind the partial results
     std::vector<int32_t> host_padded;
     bool padded_built = false, padded_uploaded = false;

@@ -1,10 +1,8 @@
-// Packed prefill attention for launches of fewer workgroups than compute units, bf16 MFMA, head dimension PK_D = 128 or 64
-// (Sec. 3.1).  Tables, arithmetic and copies are those of prefill_body.hip.h, with v_mfma_f32_32x32x16_bf16 and without a
-// software pipeline over half tiles.  A wave that is alone on its SIMD is bound by the instructions it issues, one every five to
-// six cycles, and half as many MFMAs for the same work are what counts (prefill_body.hip.h / this one, us, head dimension 128 and
-// 64): 7 x 57 rows behind 2500 tokens with 32 heads (224 workgroups) 43.9 / 40.4 and 33.1 / 32.4, 1 x 512 behind 8192 (128) 142.4 /
-// 134.3 and 115.1 / 106.5, 1 x 64 behind 8000 with 8 heads (8) 124.5 / 114.0 and 94.0 / 91.8; a mixed step of 7 chunks of 20..80 rows behind
-// up to 5311 tokens 88.1 / 81.5.  On a full chip the clock is managed by power, which the 16x16x32 form uses less of.
+// Packed prefill attention for launches of little work, bf16 MFMA, head dimension PK_D = 128 or 64 (Sec. 3.1).  Tables,
+// arithmetic and copies are those of prefill_body.hip.h, with v_mfma_f32_32x32x16_bf16 and without a software pipeline over
+// half tiles: no first and last turn, and half as many MFMAs for the same work, which is what counts for a wave that is alone on its
+// SIMD, bound by the instructions it issues, one every five to six cycles.  Long launches are bound by power, which the 16x16x32 form uses
+// less of; the schedule builder draws the line (light_launch in schedule.cpp, with both sides measured).
 //   * a key tile is processed as two halves of 32 keys whose softmax steps are interleaved,
 //     slice by slice, with the MFMAs of the neighbouring phase, and the LDS operand reads run
 //     four MFMAs ahead in a ring of registers;

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256, 3) void prefill_bf16_dma64_kernel(PrefillArgs 
     d64::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
 }
 
-// Launches that leave compute units without a workgroup.
+// Launches of little work (PrefillArgs::light).
 __global__ __launch_bounds__(256, 2) void prefill_bf16_few_kernel(PrefillArgs a) {
     __shared__ __align__(1024) unsigned char lds[5 * few128::TILE_BYTES];
     few128::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
@@ -82,19 +82,19 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     //   8 x 4096  575 / 627 us;  16 x 2048  326 / 363 us;  32 x 512 behind 8192 with 64 heads  2205 / 2342 us
     //   1 x 1024 behind 8192  123 / 149 us;  1 x 4096 behind 8192  363 / 348 us;  2 x 3000 behind 3000 with 16 heads  187 / 164 us
     const int64_t alone = static_cast<int64_t>(a.n_tiles) * a.Hq;             // workgroups with one head each
-    const bool two = a.d == 128 && a.heads_per_kv % 2 == 0 && alone >= 512 && a.n_key_tiles >= 32 * static_cast<int64_t>(a.n_tiles);
+    const bool two = !a.light && a.d == 128 && a.heads_per_kv % 2 == 0 && alone >= 512 && a.n_key_tiles >= 32 * static_cast<int64_t>(a.n_tiles);
     if (two) { a.heads_per_kv /= 2; a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv)); }
     const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
     const int64_t grid = (pairs + 7) / 8 * 8 * a.heads_per_kv;
     if (grid == 0) return 0;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
-    if (few_workgroups(a) && (a.d == 128 || a.d == 64)) {
-        const dim3 wgs(static_cast<unsigned>(grid));
-        if (a.d == 128) hipLaunchKernelGGL(prefill_bf16_few_kernel, wgs, dim3(256), 0, static_cast<hipStream_t>(stream), a);
-        else hipLaunchKernelGGL(prefill_bf16_few64_kernel, wgs, dim3(256), 0, static_cast<hipStream_t>(stream), a);
-        return static_cast<int>(hipGetLastError());
-    }
-    if (two)
+    if (a.light && a.d == 128)
+        hipLaunchKernelGGL(prefill_bf16_few_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), a);
+    else if (a.light && a.d == 64)
+        hipLaunchKernelGGL(prefill_bf16_few64_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), a);
+    else if (two)
         hipLaunchKernelGGL(prefill_bf16_pair_kernel, dim3(static_cast<unsigned>(grid)), dim3(512), 0,
                            static_cast<hipStream_t>(stream), a);
     else if (a.d == 128)

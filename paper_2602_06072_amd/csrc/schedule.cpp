@@ -388,7 +388,35 @@ void add_idle_tile(SchedBuild& sb) {               // padded grid slot of a requ
 }
 
 // Writes the tiles in the given order (key-tile lists are re-based accordingly).
-void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, Builder& b,
+// Which of the two bodies a prefill launch takes, one head per workgroup: prefill_few_body.hip.h (true) or prefill_body.hip.h.
+// The pipeline of the latter costs a first and a last turn of every workgroup and more issued instructions, and saves energy:
+// it is the faster one where power holds the clock down, in launches of some 200 us and more, and where a wave has a long list
+// to go through.  So the line is drawn by the total of key tiles times the length of a list, per compute unit.  us, pipeline / other body:
+//   d = 128, lists of about 2 tiles, 64 x 200 tokens and 32 heads 80.7 / 77.0, 256 x 130 and 64 heads 431 / 404, 512 x 300 2015 / 1997;
+//   5 to 10 tiles: 16 x 512 and 32 heads 46.6 / 44.7, 16 x 1024 180.7 / 174.6, twice that (75000 key tiles) 1 % the other way;
+//   17 tiles: 24 x 128 behind 1000 and 32 heads 62.9 / 61.4, 64 x 128 the same; 33 tiles: 14 x 128 behind 2000 65.1 / 65.6,
+//   16 x 128 68.1 / 70.7, 1 x 1024 behind 8192 (256 workgroups of 136 tiles) 152.5 / 155.2;
+//   d = 64, about 2 tiles: 64 x 200 and 64 heads 83.7 / 77.0, 256 x 130 247 / 225, 512 x 300 1144 / 1102; 5 to 9 tiles: 21 x 768 and 32
+//   heads 81.2 / 77.6, 32 x 1024 and 16 heads 105.2 / 101.9; 17 tiles: 24 x 128 behind 1000 and 32 heads 38.3 / 37.9, 64 x 128
+//   93.4 / 90.5, 8 x 2048 (70000) 1 % the other way at 64 heads; 33 tiles: 14 x 128 behind 2000 43.9 / 43.2, 16 x 128 46.3 / 46.1.
+// Over 680 such shapes the choice is within 4 % of the better one, but for prompts of exactly 32 rows, four to a tile (64 x 32
+// 15.1 / 15.7 us, d = 64 17.2 / 18.4), whose waves skip three of the four key tiles in the list, and for 513 to 768 workgroups of more than
+// 32 tiles, of which the eight-wave kernel makes a round and a half (24 x 128 behind 2000 and 32 heads 124 / 106).
+// Below one workgroup per unit (with d = 64 one and a half: three share a unit) the other body is the better one with any list: 7 x 57 rows
+// behind 2500 tokens with 32 heads (224 workgroups) 43.9 / 40.4 and 33.1 / 32.4, 1 x 512 behind 8192 (128) 142.4 / 134.3 and
+// 115.1 / 106.5, 1 x 64 behind 8000 with 8 heads (8) 124.5 / 114.0 and 94.0 / 91.8.
+// The prefill half of a mixed step follows the same line, so that its results are those of the prefill call bit for bit (64 x 200 with 32
+// heads and 32 decode rows of 500 tokens 87.2 / 81.8, 8 x 1024 and 256 of 700 178 / 173; d = 64 98.7 / 94.5).
+bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) {   // tiles: query tiles that have key tiles
+    if (tiles == 0) return true;
+    const int64_t wgs = tiles * Hq;
+    if (d == 64 ? 2 * wgs < 3 * num_cus : wgs < num_cus) return true;
+    if (key_tiles < (d == 64 ? 8 : 5) * tiles) return true;
+    const double list = static_cast<double>(key_tiles) / static_cast<double>(tiles);
+    return static_cast<double>(wgs) * list * list < (d == 64 ? 3500.0 : 2000.0) * num_cus;
+}
+
+void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, const DeviceTables& t, Builder& b,
                 DeviceTables::PrefillSched& s) {
     std::vector<int32_t> desc, more_first, more, kv;
     desc.reserve(order.size() * kTileDescWords);
@@ -435,6 +463,8 @@ void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, Builder
     }
     s.n_tiles = static_cast<int32_t>(order.size());
     s.issued_pairs = sb.issued;
+    const int64_t idle = std::count(sb.n_kv.begin(), sb.n_kv.end(), 0);
+    s.light = light_launch(s.n_tiles - idle, static_cast<int64_t>(kv.size() / 2), t.Hq, t.d, t.num_cus);
     s.tiles = b.add(desc);
     s.run_first = b.add(more_first); s.runs = b.add(more);
     s.kvtiles = b.add(kv);
@@ -500,7 +530,7 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         }
         return sb.weight[x] > sb.weight[y];
     });
-    emit_sched(sb, order, b, t.packed);
+    emit_sched(sb, order, t, b, t.packed);
 }
 
 }  // namespace
@@ -528,7 +558,7 @@ void build_prefill_padded(const pk_plan& plan, DeviceTables& t) {
     std::iota(order.begin(), order.end(), 0);
     t.host_padded.clear();
     Builder b(t.host_padded);
-    emit_sched(sb, order, b, t.padded);
+    emit_sched(sb, order, t, b, t.padded);
     t.host_padded.resize((t.host_padded.size() + 63) / 64 * 64, 0);
     t.padded_built = true;
 }
@@ -561,6 +591,7 @@ namespace {
 void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_group, DeviceTables& t) {
     t = DeviceTables();
     t.Hq = Hq; t.Hkv = Hkv; t.d = d; t.dtype = dtype;
+    t.num_cus = num_cus;
     Builder b(t.host);
     std::vector<int64_t> q_start(static_cast<size_t>(plan.n) + 1, 0), kv_start(static_cast<size_t>(plan.n) + 1, 0);
     for (int32_t i = 0; i < plan.n; ++i) {

@@ -1,0 +1,36 @@
+"""Which of the two prefill bodies a batch takes (host only: the tables of a plan say it).  Measured on batches of both kinds;
+results do not depend on it."""
+import numpy as np
+import pytest
+
+from paper_2602_06072_amd import binding as pk
+
+
+def bound(ql, ctx, Hq, Hkv, d):
+    ql = np.asarray(ql, dtype=np.int32)
+    plan = pk.pack_plan(ql + np.asarray(ctx, dtype=np.int32), ql, token_budget=16384)
+    assert plan.workspace_bytes(Hq, Hkv, d, pk.PK_BF16) > 0
+    return plan
+
+
+# n requests of L rows behind ctx tokens: short key lists on a full chip, launches of little work, few workgroups
+@pytest.mark.parametrize("Hq, Hkv, d, n, L, ctx", [
+    (64, 8, 128, 8, 128, 0), (32, 8, 128, 64, 200, 0), (64, 8, 128, 256, 130, 0), (32, 8, 128, 32, 512, 0), (32, 8, 128, 16, 1024, 0),
+    (64, 8, 64, 64, 200, 0), (64, 8, 64, 512, 300, 0), (32, 8, 64, 21, 768, 0), (32, 8, 64, 14, 128, 2000), (8, 8, 64, 8, 512, 0),
+    (32, 8, 128, 1, 512, 8192), (8, 8, 64, 1, 64, 8000)])
+def test_launches_of_little_work(Hq, Hkv, d, n, L, ctx):
+    assert bound([L] * n, [ctx] * n, Hq, Hkv, d).stat(8) == 1
+
+
+@pytest.mark.parametrize("Hq, Hkv, d, n, L, ctx", [
+    (64, 8, 128, 32, 1024, 8192), (32, 8, 128, 1, 1024, 8192), (32, 8, 128, 16, 2048, 0), (32, 8, 128, 16, 128, 2000),
+    (32, 8, 64, 8, 4096, 0), (32, 8, 64, 1, 4096, 8192), (64, 8, 64, 16, 2048, 0)])
+def test_launches_of_much_work(Hq, Hkv, d, n, L, ctx):
+    assert bound([L] * n, [ctx] * n, Hq, Hkv, d).stat(8) == 0
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_idle_tiles_of_the_padded_schedule_do_not_count(d):
+    """One long prompt among short ones: the padded grid has a tile for every 128 rows of the longest one in every request."""
+    plan = bound([8192] + [100] * 30, [0] * 31, 32, 8, d)
+    assert plan.stat(7) == 31 * 64 and plan.stat(8) == 0 and plan.stat(9) == 0
