@@ -280,8 +280,10 @@ int pk_packed_mixed_step(pk_plan* prefill_plan, const void* q, const void* k, co
  *   - All calls on one GPU share the one array, which keeps the contents of
  *     the last call: calls that overlap in time on one GPU (different
  *     streams, different threads) race and must be ordered by the caller.
- *     Nothing in it has to start at zero: every partial slot is written
- *     before the merge reads it.
+ *     Nothing in it has to be prepared: every partial slot is written before
+ *     the merge reads it, and the counts of finished work items, which have
+ *     to be zero when a launch begins, are zeroed by the upload of a plan's
+ *     tables and left at zero by every launch.
  * Other arguments, results and errors as pk_packed_decode_attn; the outputs
  * are bit-identical to that call's. */
 #define PK_STATIC_SCRATCH_BYTES (16u << 20)

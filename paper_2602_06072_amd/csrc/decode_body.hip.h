@@ -3,6 +3,7 @@
 #pragma once
 #include <type_traits>
 
+#include "arrival.h"
 #include "common.hip.h"
 #include "kernels.h"
 
@@ -227,12 +228,20 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, const int item,
 }
 
 // Partial results that another workgroup of the same launch reads: written through to memory, and read past whatever an L2 has
-// of an earlier launch (relaxed atomics at device scope).
+// of an earlier launch (relaxed atomics at device scope).  The order between them and the count comes from instructions and not from
+// the memory model's: gfx950 counts a device-scope store as done (vmcnt) when it has been written through, so a wave that waits for its
+// stores before the barrier in front of the count has published them; a release would also write back the whole L2.
 __device__ __forceinline__ void publish(float* p, const floatx4 x) {
     uint64_t* q = reinterpret_cast<uint64_t*>(p);
     __hip_atomic_store(q, __builtin_bit_cast(uint64_t, floatx2{x[0], x[1]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(q + 1, __builtin_bit_cast(uint64_t, floatx2{x[2], x[3]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+struct DeviceCount {
+    uint32_t* x;
+    __device__ __forceinline__ uint32_t next(const uint32_t limit) const {
+        return __builtin_amdgcn_atomic_inc32(x, limit, __ATOMIC_RELAXED, "agent");
+    }
+};
 __device__ __forceinline__ floatx4 read_published(const float* p) {
     const uint64_t* q = reinterpret_cast<const uint64_t*>(p);
     const floatx2 a = __builtin_bit_cast(floatx2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -249,7 +258,7 @@ __device__ __forceinline__ floatx4 read_published(const float* p) {
 // 65536 tokens 2.86 -> 2.59 ms (6.9 TB/s), 256 requests of 32..32768 201 -> 194 us, one request of 500 tokens 8.9 -> 6.3 us,
 // four of 300..3000 10.2 -> 9.6 us.  With eight waves to an item the one request takes 6.8 us; with
 // batches of 16 partial results in the merge instead of 8 the four take 10.4 us, with 4 9.9.
-// `lds`: kGroupLds<D> bytes; a.arrived: a count per (request, KV head), zero between launches.
+// `lds`: kGroupLds<D> bytes; a.arrived: a count per (request, KV head), zero between launches (arrival.h).
 constexpr int kGroupWaves = 4;
 template <int D> constexpr int kGroupLds = kGroupWaves * 16 * (D + 4 + 2) * 4 + 16;
 template <int D>
@@ -303,10 +312,8 @@ __device__ __forceinline__ void decode_group_body(const DecodeArgs& a, const int
     __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's partial results are in memory
     __syncthreads();
     if (threadIdx.x == 0) {
-        int32_t* count = a.arrived + static_cast<int64_t>(req) * a.Hkv + kvh;
-        const int before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *last = before == p1 - p0 - 1;
-        if (*last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+        const DeviceCount count{reinterpret_cast<uint32_t*>(a.arrived) + static_cast<int64_t>(req) * a.Hkv + kvh};
+        *last = arrives_last(count, static_cast<uint32_t>(p1 - p0));
     }
     __syncthreads();
     if (*last == 0) return;
