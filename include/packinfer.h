@@ -397,7 +397,7 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
                           int dtype, int out_dtype,
                           void* workspace, size_t workspace_bytes, void* stream);
 
-/* Counts for the benchmark's work accounting (host).  1..9 refer to the
+/* Counts for the benchmark's work accounting (host).  1..10 refer to the
  * tables of the head shape the plan was last sized or bound for (0 before).
  *   what = 0: unmasked (query,key) pairs per head summed over requests
  *   what = 1: (query,key) pairs issued to the MFMA units by the packed
@@ -409,6 +409,8 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
  *   what = 8: 1 if the packed bf16 prefill (also the prefill half of a mixed
  *             step) takes the kernels for launches of little work, 0 if the
  *             software-pipelined ones; 9: same for the padded schedule
+ *   what = 10: waves that share a (decode work item, KV head) pair: 4 (a
+ *             workgroup, which merges in the same launch), 1, or 0 (no items)
  */
 int64_t pk_plan_stat(const pk_plan* plan, int what);
 
@@ -417,7 +419,9 @@ int64_t pk_plan_stat(const pk_plan* plan, int what);
  * the schedule builder for this plan; the next pk_workspace_bytes /
  * pk_plan_bind builds the tables again.  Results never depend on it.
  *   PK_TUNE_DECODE_SPLIT     tokens per split-KV work item (rounded up to
- *                            PK_KV_BLOCK); 0 = the builder's own choice
+ *                            PK_KV_BLOCK); 0 = the builder's own choice.
+ *                            The kernel stays the one that 0 gives (a wave
+ *                            or a workgroup for an item)
  *   PK_TUNE_PREFILL_PIPELINE how the bf16 prefill kernels (packed and padded)
  *                            bring K/V tiles into LDS: 0 = copied straight
  *                            from memory into LDS, three K and two V stages

@@ -592,6 +592,7 @@ extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
                 if (!plan->tables.padded_built && plan->tables.dtype >= 0)
                     build_prefill_padded(*plan, plan->tables);
                 return plan->tables.padded.light;
+            case 10: return plan->tables.dec.n_items == 0 ? 0 : plan->tables.dec.group ? 4 : 1;
             default: return 0;
         }
     });

@@ -175,10 +175,13 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
         const int64_t raised = raise(split, longest, capacity);
         split = std::max(two_rounds, fits(raised, capacity) ? raised : std::min<int64_t>(2048, whole_blocks(split * 5 / 4)));
     }
-    if (plan.tune_decode_split > 0) split = plan.tune_decode_split;     // pk_plan_tune (profiling sweeps)
-    split = (split + kDecodeBlock - 1) / kDecodeBlock * kDecodeBlock;
-    const bool may = may_group && dtype == PK_BF16 && r <= 16 && plan.tune_decode_split == 0;
-    const int64_t by_group = may ? group_split(plan, Hkv, d, num_cus, split) : 0;
+    split = whole_blocks(split);
+    const bool may = may_group && dtype == PK_BF16 && r <= 16;
+    int64_t by_group = may ? group_split(plan, Hkv, d, num_cus, split) : 0;
+    if (plan.tune_decode_split > 0) {              // pk_plan_tune (profiling sweeps): another split for the same kernel
+        split = whole_blocks(plan.tune_decode_split);
+        if (by_group > 0) by_group = split;
+    }
 
     struct Segment { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool suffix; };   // (reqs point into the plan)
     std::vector<Segment> segments;
