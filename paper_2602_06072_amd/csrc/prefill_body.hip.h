@@ -229,6 +229,7 @@ __device__ __forceinline__ void lds_copy_16(const u32x4& rsrc, uint32_t lds_addr
 }
 // The same in two parts, for the loop: the LDS address goes into M0 a step before the copy that uses it, and
 // the descriptor was built in the turn before, so that neither needs wait states (four of them cost a lone wave 20 cycles a copy).
+// That holds as long as no scalar register is spilled: build.py refuses a build in which one is.
 __device__ __forceinline__ void copy_to(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds_addr) : "memory"); }
 __device__ __forceinline__ void copy_16(const u32x4& rsrc, int voffset) {
     asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voffset), "s"(rsrc) : "memory");
