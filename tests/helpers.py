@@ -81,3 +81,13 @@ def oracle_paged_decode(w, use_f32, requests=None):
     qq, kk, vv = opaged.decode_inputs_as_ragged(q, kp, vp, w.block_table, w.kv_lens, w.page_size, idx)
     out, _ = oa.attention_ragged(qq, kk, vv, [1] * len(idx), [int(w.kv_lens[i]) for i in idx], w.scale)
     return out
+
+
+# Requests of one query row behind 16383 tokens.  The prefill launches take one of two bodies by the amount of work
+# (plan.stat(8), of the padded schedule stat(9)): with these at the end of a batch it goes to the software pipeline.
+LONG = 6
+
+
+def with_long_requests(kv, ql):
+    return (np.concatenate([np.asarray(kv, dtype=np.int32), np.full(LONG, 16384, dtype=np.int32)]),
+            np.concatenate([np.asarray(ql, dtype=np.int32), np.ones(LONG, dtype=np.int32)]))

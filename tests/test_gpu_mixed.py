@@ -54,6 +54,32 @@ def test_mixed_step_small(case):
     H.assert_close(fus_d.cpu().numpy(), H.oracle_paged_decode(d, False), 0, f"mixed step {case}: decode half")
 
 
+@pytest.mark.parametrize("waves", [4, 1])
+@pytest.mark.parametrize("light", [1, 0])
+@pytest.mark.parametrize("d", [64, 128])
+def test_mixed_step_kernels(d, light, waves):
+    """Each prefill body beside each kind of decode workgroup; requests of one and of several partial results."""
+    kv, ql = [700, 300, 129, 64, 1000], [90, 300, 1, 64, 40]
+    if not light:
+        kv, ql = H.with_long_requests(kv, ql)
+    p = wl.make_ragged("kernels", np.asarray(kv, np.int32), np.asarray(ql, np.int32), 4 if light else 32, 2, d, 4096, 98, device=DEV,
+                       keep_f32=False)
+    dkv = np.asarray([9000, 40, 3000, 700, 500, 33] * 4, dtype=np.int32)
+    pid = plen = None
+    if waves == 1:                                        # a shared prefix: items of several requests
+        pid, plen = np.zeros_like(dkv), np.full_like(dkv, 32)
+    dec = wl.make_paged("kernels", dkv, p.Hq, p.Hkv, d, 1 << 18, 16, 99, prefix_ids=pid, prefix_lens=plen, device=DEV, keep_f32=False)
+    plan_p = pk.pack_plan(p.kv_lens, p.q_lens, token_budget=4096)
+    plan_d = pk.pack_plan(dec.kv_lens, np.ones_like(dkv), pid, plen, 1 << 18)
+    for plan in (plan_p, plan_d):
+        plan.workspace_bytes(p.Hq, p.Hkv, d, pk.PK_BF16)
+    assert plan_p.stat(8) == light and plan_d.stat(10) == waves and plan_d.stat(4) > 0
+    for out_dtype in (torch.float32, torch.bfloat16):
+        fus_p, fus_d = run_both(p, dec, 4096, 1 << 18, out_dtype)
+        H.assert_close(fus_p.float().cpu().numpy(), H.oracle_ragged(p, False), 0, f"mixed step: prefill half, d {d}")
+        H.assert_close(fus_d.float().cpu().numpy(), H.oracle_paged_decode(dec, False), 0, f"mixed step: decode half, d {d}")
+
+
 @pytest.mark.parametrize("prefill, rows", [(40, 12), (33, 260), (16, 300), (9, 64)])
 def test_mixed_step_order_of_workgroups(prefill, rows):
     """Runs of 256 workgroups: 5 prefill to 1 decode, 5 to 3 (two left over), 2 to 3 (one decode run left over),

@@ -23,18 +23,22 @@ def prefill(w, padded=False, out_dtype=torch.float32):
     return out, plan
 
 
+@pytest.mark.parametrize("light", [1, 0])
 @pytest.mark.parametrize("d", [128, 64])
-def test_lanes_without_a_query_hold_nobody_elses_row(d):
+def test_lanes_without_a_query_hold_nobody_elses_row(d, light):
     """Partly filled waves with unmasked key tiles; the first query row of the batch holds a NaN.  Tiles are not
     shared here, so every row behind the first wave of request 0 is in another wave than that row."""
     ql = np.asarray([200, 17, 45, 100, 9], dtype=np.int32)
     kv = ql + np.asarray([0, 500, 300, 130, 700], dtype=np.int32)
-    w = wl.make_ragged("padding", kv, ql, 4, 2, d, 1024, 21, DEV, keep_f32=False)
+    if not light:
+        kv, ql = H.with_long_requests(kv, ql)
+    w = wl.make_ragged("padding", kv, ql, 4 if light else 32, 2, d, 1024, 21, DEV, keep_f32=False)
     clean = {p: prefill(w, p)[0] for p in (False, True)}
     w.q[0] = float("nan")
     for padded in (False, True):
         got, plan = prefill(w, padded)
-        assert plan.stat(6) == 6                           # one tile a request, two for the first: nothing shared
+        assert plan.stat(6) == len(ql) + 1                 # one tile a request, two for the first: nothing shared
+        assert plan.stat(8) == light and (not padded or plan.stat(9) == light)
         assert torch.equal(got[32:], clean[padded][32:])
         assert torch.isnan(got[0]).all()
 
@@ -44,16 +48,16 @@ BAD = {"q_first": ("q", 0, float("nan")), "q_middle": ("q", 77, float("nan")), "
 
 
 @pytest.mark.parametrize("case", list(BAD))
-@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128)])
+@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128), (12, 4, 128), (16, 2, 64)])
 @pytest.mark.parametrize("launch", ["packed", "padded", "mixed"])
 def test_nonfinite_values_reach_only_the_rows_that_see_them(launch, heads, case):
-    """Tiles of several requests; one head per workgroup, D = 64, two heads per workgroup.  A NaN makes exactly the
-    rows that see it NaN; what a row that sees an infinity gives is not asked."""
+    """Tiles of several requests; one head per workgroup, D = 64, two heads per workgroup, and in the pipeline also one head per
+    workgroup and D = 64.  A NaN makes exactly the rows that see it NaN; what a row that sees an infinity gives is not asked."""
     Hq, Hkv, d = heads
     n = 150
     rng = np.random.default_rng(51)
     ql = rng.integers(5, 61, size=n).astype(np.int32)
-    ctx = rng.integers(600, 901, size=n) if Hq == 16 else rng.integers(0, 300, size=n)
+    ctx = rng.integers(600, 901, size=n) if Hq > 4 else rng.integers(0, 300, size=n)
     w = wl.make_ragged("isolation", (ql + ctx).astype(np.int32), ql, Hq, Hkv, d, 8192, 52, DEV, keep_f32=False)
     dec = wl.small_paged(seed=53, n=4, lo=1, hi=90, Hq=Hq, Hkv=Hkv, d=d, token_budget=500, device=DEV, keep_f32=False)
     dplan = pk.pack_plan(dec.kv_lens, np.ones_like(dec.kv_lens), None, None, 500)
@@ -74,6 +78,8 @@ def test_nonfinite_values_reach_only_the_rows_that_see_them(launch, heads, case)
     plan = prefill(w)[1]
     assert plan.stat(6) < n                                # requests share tiles
     assert Hq != 16 or (plan.stat(6) * Hq >= 512 and plan.stat(1) >= 8 * 64 * 128 * plan.stat(6))
+    # (of the padded schedule, whose lists are not shared, both kinds are light with one head per workgroup)
+    assert plan.stat(8) == int(Hq == 4)
     clean = {t: run(t).float() for t in (torch.float32, torch.bfloat16)}
     which, req, value = BAD[case]
     q0 = int(w.q_lens[:req].sum())

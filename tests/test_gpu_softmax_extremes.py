@@ -46,13 +46,28 @@ def shape_scores(q, k, kv_start, kv_lens, case, rng):
 CASES = ["ramp", "falling", "late_outlier", "first_outlier", "far_below_zero", "jumps"]
 
 
-@pytest.mark.parametrize("d", [128, 64])
+@pytest.fixture
+def sized(request):
+    """(kv, ql) -> a batch for one of the prefill bodies (the pipeline with one or, with D = 128, two heads per workgroup) with its
+    heads; `.light`: what plan.stat(8) says of it."""
+    def batch(kv, ql):
+        if batch.light:
+            return np.asarray(kv, dtype=np.int32), np.asarray(ql, dtype=np.int32), 4, 2
+        return *H.with_long_requests(kv, ql), *((33, 3) if request.param == "four_waves" else (64, 2))
+    batch.light = int(request.param == "light")
+    return batch
+
+
+BODIES = pytest.mark.parametrize("d, sized", [(128, "light"), (128, "four_waves"), (128, "eight_waves"), (64, "light"), (64, "four_waves")],
+                                 indirect=["sized"])
+
+
+@BODIES
 @pytest.mark.parametrize("case", CASES)
-def test_prefill_softmax_extremes(case, d):
+def test_prefill_softmax_extremes(case, d, sized):
     rng = np.random.default_rng(100 * CASES.index(case) + d)
-    kv = np.asarray([700 + 333, 300, 129, 64, 1500], dtype=np.int32)
-    ql = np.asarray([700, 300, 129, 64, 1500], dtype=np.int32)
-    w = wl.make_ragged(f"extreme_{case}", kv, ql, 4, 2, d, 1024, 5, DEV, keep_f32=False)
+    kv, ql, Hq, Hkv = sized([700 + 333, 300, 129, 64, 1500], [700, 300, 129, 64, 1500])
+    w = wl.make_ragged(f"extreme_{case}", kv, ql, Hq, Hkv, d, 1024, 5, DEV, keep_f32=False)
     shape_scores(w.q, w.k, w.kv_start, w.kv_lens, case, rng)
     want = H.oracle_ragged(w, False)
     for padded, pipeline in ((False, 0), (True, 0), (False, 1)):
@@ -62,6 +77,7 @@ def test_prefill_softmax_extremes(case, d):
         out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
         (pk.padded_prefill_attn if padded else pk.packed_prefill_attn)(plan, w.q, w.k, w.v, out, w.scale, ws)
         torch.cuda.synchronize()
+        assert plan.stat(9 if padded else 8) == sized.light
         H.assert_close(out.cpu().numpy(), want, 0, f"prefill {case} d={d} padded={padded} pipeline={pipeline}")
 
 
@@ -117,15 +133,15 @@ def test_decode_softmax_extremes(case):
     H.assert_close(out2.cpu().numpy(), want, 0, f"padded decode {case}")
 
 
-@pytest.mark.parametrize("d", [128, 64])
-def test_prefill_scores_beyond_the_exponent_range(d):
+@BODIES
+def test_prefill_scores_beyond_the_exponent_range(d, sized):
     """Row maxima that jump by more than 127 octaves inside a request (a probability against the old
     reference overflows to infinity in bf16 and fp32) and rows all of whose scores lie thousands of
     nats below zero.  Rows are one-hot or nearly: an error of a score of magnitude S is at most
     S * d * 2^-24 (fp32 sums of exact products), 2e-2 for the largest here, and only keys of equal
     score share a row, so the usual tolerance holds."""
-    kv = np.asarray([513, 200, 97, 1000], dtype=np.int32)
-    w = wl.make_ragged("exponent_range", kv, kv, 4, 2, d, 1024, 9, DEV, keep_f32=False)
+    kv, ql, Hq, Hkv = sized([513, 200, 97, 1000], [513, 200, 97, 1000])
+    w = wl.make_ragged("exponent_range", kv, ql, Hq, Hkv, d, 1024, 9, DEV, keep_f32=False)
     w.q.copy_(w.q.abs())
     s0 = w.kv_start
     for pos, value in ((0, -4.0), (40, 12.0), (64, 30.0), (130, 60.0), (131, -60.0), (300, 100.0)):
@@ -138,6 +154,7 @@ def test_prefill_scores_beyond_the_exponent_range(d):
     out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
     pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
     torch.cuda.synchronize()
+    assert plan.stat(8) == sized.light
     got = out.cpu().numpy()
     lo, hi = int(s0[1]), int(s0[2])                        # scores around -2000 nats there: checked loosely below
     keep = np.r_[0:lo, hi:got.shape[0]]
@@ -147,7 +164,7 @@ def test_prefill_scores_beyond_the_exponent_range(d):
     assert np.abs(got[lo:hi] - want[lo:hi]).max() <= 2e-2 + 5 * 2.3e-2
 
 
-def check_prefill_launches(w, want, keep, what):
+def check_prefill_launches(w, want, keep, what, light):
     """Packed and padded prefill and the prefill half of the fused step against `want`, on the rows `keep`."""
     dec = wl.small_paged(seed=3, n=3, lo=1, hi=90, Hq=w.Hq, Hkv=w.Hkv, d=w.d, token_budget=500, device=DEV, keep_f32=False)
     dplan = pk.pack_plan(dec.kv_lens, np.ones_like(dec.kv_lens), None, None, 500)
@@ -165,20 +182,20 @@ def check_prefill_launches(w, want, keep, what):
             (pk.padded_prefill_attn if launch == "padded" else pk.packed_prefill_attn)(plan, w.q, w.k, w.v, out, w.scale, ws)
         torch.cuda.synchronize()
         H.assert_close(out.cpu().numpy()[keep], want[keep], 0, f"{what} {launch}")
+    assert plan.stat(8) == light and plan.stat(9) == light
     return plan
 
 
-@pytest.mark.parametrize("d", [128, 64])
-def test_prefill_rows_with_every_score_far_below_zero(d):
+@BODIES
+def test_prefill_rows_with_every_score_far_below_zero(d, sized):
     """Scaled scores around -1e31 .. -1e33.  A row's keys repeat 32 factors a 32nd apart: the nearest to zero that it
     sees stand alone against the rest by far more than any rounding, and equal keys have equal scores."""
-    kv = np.asarray([200, 100, 33, 400], dtype=np.int32)
-    ql = np.asarray([200, 60, 33, 150], dtype=np.int32)
-    w = wl.make_ragged("far_below", kv, ql, 4, 2, d, 1024, 31, DEV, keep_f32=False)
+    kv, ql, Hq, Hkv = sized([200, 100, 33, 400], [200, 60, 33, 150])
+    w = wl.make_ragged("far_below", kv, ql, Hq, Hkv, d, 1024, 31, DEV, keep_f32=False)
     w.q.fill_(1e16)
     f = 2.0 - (torch.arange(w.k.shape[0], device=DEV) * 7 % 32).float() / 32
     w.k.copy_((-1e15 * f.view(-1, 1, 1)).expand(w.k.shape))
-    check_prefill_launches(w, H.oracle_ragged(w, False), slice(None), f"scores far below zero d={d}")
+    check_prefill_launches(w, H.oracle_ragged(w, False), slice(None), f"scores far below zero d={d}", sized.light)
 
 
 def rows_that_rounding_cannot_turn(w, rows):
@@ -199,7 +216,7 @@ def rows_that_rounding_cannot_turn(w, rows):
     return keep
 
 
-@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128)])
+@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128), (30, 10, 128), (30, 10, 64)])
 @pytest.mark.parametrize("size", [3e3, 1e5, 1e6, 1e9])
 def test_prefill_with_large_finite_scores(size, heads):
     """Scaled scores of 1e7 to 1e19: a reference rounded to fp32 is off by up to many octaves there, more than the
@@ -209,6 +226,8 @@ def test_prefill_with_large_finite_scores(size, heads):
     two = Hq == 16                                        # enough workgroups and keys for two heads per workgroup
     kv = np.asarray([4500, 4800] if two else [513, 200, 97, 640], dtype=np.int32)
     ql = np.asarray([2100, 2050] if two else [513, 60, 97, 300], dtype=np.int32)
+    if Hq == 30:                                          # the pipeline with one head per workgroup
+        kv, ql = H.with_long_requests(kv, ql)
     w = wl.make_ragged("large_scores", kv, ql, Hq, Hkv, d, 4096, 33, DEV, keep_f32=False)
     w.q.mul_(size)
     w.k.mul_(size)
@@ -224,5 +243,5 @@ def test_prefill_with_large_finite_scores(size, heads):
     at = (np.concatenate([[0], np.cumsum(ql)])[rows[:, 0]] + rows[:, 2], rows[:, 1])
     want = np.zeros(tuple(w.q.shape), dtype=np.float32)
     want[at] = H.oracle_ragged(w, False, rows=rows)
-    plan = check_prefill_launches(w, want, at, f"scores of {size * size:g} {heads}")
+    plan = check_prefill_launches(w, want, at, f"scores of {size * size:g} {heads}", int(Hq == 4))
     assert not two or (plan.stat(6) * Hq >= 512 and plan.stat(1) >= 32 * 64 * 128 * plan.stat(6))
