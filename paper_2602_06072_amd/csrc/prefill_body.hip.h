@@ -77,7 +77,7 @@ struct WorkUnit {
     int qrow[2], lo[2], hi[2];         // this lane's query rows (-1: padding) and their key ranges [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
-    uint32_t row_bytes32, total_rows32;  // the same, and the number of K/V rows, as 32-bit scalars
+    uint32_t row_bytes32;              // the same in 32 bits
 };
 
 // Decodes the workgroup id, loads the row metadata and the Q operand, derives the lane offsets.
@@ -116,7 +116,6 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
         prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + 16 * c + u.n, u.qrow[c], u.lo[c], u.hi[c]);
     u.row_bytes = static_cast<int64_t>(a.Hkv) * ROWB;
     u.row_bytes32 = static_cast<uint32_t>(a.Hkv) * ROWB;
-    u.total_rows32 = static_cast<uint32_t>(a.total_kv_rows);
 
 #pragma unroll
     for (int s = 0; s < 2; ++s) off.k[s] = u.n * SLAB_ROWB + (((4 * s + u.g) ^ swz(u.n)) << 4);
@@ -213,9 +212,9 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
-// them per wave, each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the end
-// of the array arrive as zeros (the descriptor's size is what is left of the array; a tile past
-// the end of the key-tile list gets size 0: zeros, no memory traffic).  The copy is issued from
+// them per wave, each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the
+// tile's valid ones arrive as zeros (they are the descriptor's size; a tile past the end of the
+// key-tile list has none: zeros, no memory traffic).  The copy is issued from
 // inline assembly on purpose: the compiler makes every later LDS read wait for all copies it
 // knows of, also those into another stage, which would serialise the pipeline.  The waits are
 // explicit instead (vmcnt before the barrier that publishes a stage).  Descriptor and LDS address

@@ -9,16 +9,16 @@
 //   * copies are requested one tile ahead for V and two for K; one barrier per tile.
 
 // Device code only: included by prefill_pipe.hip (the prefill launch) and by mixed_step.hip (the
-// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4) and PK_DNS (the
-// namespace this instance goes into) first.  With PK_D = 64 a tile is 8 KiB instead of 16 and a
+// fused prefill + decode launch).  The includer defines PK_D (the head dimension) and PK_DNS (the namespace this
+// instance goes into) first.  With PK_D = 64 a tile is 8 KiB instead of 16 and a
 // half tile four MFMAs instead of eight, each followed by two softmax slices instead of one.
 #include <cstdint>
 
 #include "common.hip.h"
 #include "kernels.h"
 
-#if !defined(PK_D) || !defined(PK_DNS) || !defined(PK_WAVES) || (PK_D != 128 && PK_D != 64) || (PK_WAVES != 4 && PK_WAVES != 8)
-#error "define PK_D (128 or 64), PK_WAVES (4 or 8) and PK_DNS before including prefill_few_body.hip.h"
+#if !defined(PK_D) || !defined(PK_DNS) || (PK_D != 128 && PK_D != 64)
+#error "define PK_D (128 or 64) and PK_DNS before including prefill_few_body.hip.h"
 #endif
 
 namespace pk {
@@ -29,7 +29,7 @@ constexpr int BM = 128, BN = 64, D = PK_D;
 constexpr int ROWB = D * 2;                        // bytes per K/V row in global memory
 constexpr int TILE_BYTES = BN * ROWB;              // 16 KiB (8 KiB for D = 64)
 constexpr int KS = D / 16, DB = D / 32;
-constexpr int WAVES = PK_WAVES;
+constexpr int WAVES = 4;
 constexpr int PIECES = TILE_BYTES / (1024 * WAVES);   // 1-KiB copy instructions per wave and tile
 constexpr int RPW = BN / WAVES, PPS = RPW / 8;        // rows (and copies) of a slab that one wave fills
 constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that take half of a wave's output
@@ -37,8 +37,7 @@ constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that take
 // A stage in LDS is one slab per 64 columns: 64 rows of 128 bytes (eight 16-byte chunks).  Whatever
 // the head dimension, four K and four V addresses per lane then reach every operand with constant
 // offsets, eight additions to the stage's address per key tile; with rows of 256 bytes it took eight of
-// each and 24 additions, every sixth vector instruction of the loop (70B-shaped chunks 11.02 -> 10.91 ms,
-// 8 long prompts with D = 64, where the addresses are carried over the tile now, 573 -> 565 us).
+// each and 24 additions, every sixth vector instruction of the loop.
 constexpr int SLAB_ROWB = 128, SLAB = BN * SLAB_ROWB;
 
 typedef bf16x4 __attribute__((address_space(3))) * lds_bf16x4_ptr;
@@ -71,14 +70,14 @@ struct WorkUnit {
     int qrow, lo, hi;                  // this lane's query row (-1: padding) and its key range [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
-    uint32_t row_bytes32, total_rows32;  // the same, and the number of K/V rows, as 32-bit scalars
+    uint32_t row_bytes32;              // the same in 32 bits
 };
 
 // Decodes the workgroup id, loads the row metadata and the Q operand, derives the lane offsets.
 // Returns false for grid padding and for query tiles without key tiles.
 __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[KS]) {
     // Consecutive workgroup ids go round-robin over the 8 XCDs: the workgroups of one (tile, KV head) pair
-    // (r of them with one head each, or r / 2 with two) stay on one XCD and adjacent in time, so that its L2
+    // (r of them, one per head) stay on one XCD and adjacent in time, so that its L2
     // serves their K/V tiles.
     const int y = block >> 3, slot = a.by_r(y), p = slot * 8 + (block & 7);
     const int tile = a.by_hkv(p);
@@ -98,17 +97,15 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Wave w of every workgroup runs on SIMD w % 4, and the last rows of a causal tile see more key tiles than
-    // the first: the second head, or every other set of 256 workgroups (a set is one per compute unit), deals
-    // the rows in reverse, so that the two waves of a SIMD get as much together as those of any other.
-    const int w4 = u.wave & 3, second = WAVES > 4 ? u.wave >> 2 : 0;
-    u.head = (u.kvh * groups + pair) * (WAVES / 4) + second;
-    u.rows = (WAVES > 4 ? second : (block >> 8) & 1) ? 3 - w4 : w4;
+    // the first: every other set of 256 workgroups (a set is one per compute unit) deals the rows in reverse,
+    // so that the two waves of a SIMD get as much together as those of any other.
+    u.head = u.kvh * groups + pair;
+    u.rows = (block >> 8) & 1 ? 3 - u.wave : u.wave;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
     prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + u.n, u.qrow, u.lo, u.hi);
     u.row_bytes = static_cast<int64_t>(a.Hkv) * ROWB;
     u.row_bytes32 = static_cast<uint32_t>(a.Hkv) * ROWB;
-    u.total_rows32 = static_cast<uint32_t>(a.total_kv_rows);
 
     const int fl = swz(u.n);
 #pragma unroll
@@ -215,9 +212,9 @@ __device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const Wo
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
-// them per wave, each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the end
-// of the array arrive as zeros (the descriptor's size is what is left of the array; a tile past
-// the end of the key-tile list gets size 0: zeros, no memory traffic).  The copy is issued from
+// them per wave, each lane fetching the 16-byte chunk that belongs at its (swizzled) LDS position; rows past the
+// tile's valid ones arrive as zeros (they are the descriptor's size; a tile past the end of the
+// key-tile list has none: zeros, no memory traffic).  The copy is issued from
 // inline assembly on purpose: the compiler makes every later LDS read wait for all copies it
 // knows of, also those into another stage, which would serialise the pipeline.  The waits are
 // explicit instead (vmcnt before the barrier that publishes a stage).  Descriptor and LDS address
@@ -261,7 +258,7 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 #define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
 
 // ---------------------------------------------------------------------------------------------
-// Two workgroups of four waves per CU, three with D = 64, or one of eight; five stages of LDS each, three for K and two for V.
+// Two workgroups per CU, three with D = 64; five stages of LDS each, three for K and two for V.
 // A key tile is handled as two halves of 32 keys, each with its own online-softmax step, so that
 // within one wave the matrix pipe and the vector ALU overlap without state that crosses tiles:
 //   phase 1   S0 = K(half 0) Q^T      with the requests for V(j+1), K(j+2)   (8 MFMAs + 2 * PIECES copies)
@@ -614,9 +611,6 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // compiler's own barrier would also wait for the LDS reads) says that every wave is done with
     // tile j and that V(j+1) and K(j+2) are complete; K(j+1), whose first operands are read during
     // the last MFMAs of tile j, was published a tile earlier.
-    // Two heads per workgroup: the wave of a SIMD that has vector work to do goes first, the one in a phase of
-    // nothing but MFMAs fills in (70B-shaped chunks 11.03 -> 10.87 ms; with four waves 1 % at most).
-#define PK_PRIO(P) if constexpr (WAVES > 4) __builtin_amdgcn_s_setprio(P)
 #define PK_COPY_STEP(I)                                                                       \
     if constexpr ((I) < PIECES) PK_COPY_PIECE(rs_k, k_fill, (I));                              \
     else if constexpr ((I) < 2 * PIECES) PK_COPY_PIECE(rs_v, v_fill, (I) - PIECES);
@@ -670,11 +664,9 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         const int visible = u.lo <= e0s ? min(u.hi - e0s, e0i & 0xFF) : 0;
         int e3s, e3i;
         floatx16 s0, s1;
-        PK_PRIO(0);
         PK_EIGHT(s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], qf[i], i == 0 ? zero16 : s0, 0, 0, 0);
                  PK_REFILL(0); PK_COPY_STEP(i));
         HalfSoftmax h0, h1;
-        PK_PRIO(1);
         if (special) {                              // (one branch in the common case)
             if (masked) mask_half(s0, 0, visible, u.hlf);
             if (j == u.n_lead) { asm volatile(""); first_reference(s0, sc, m_ref); }
@@ -696,7 +688,6 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         // phase 4; its last refills are the first operands of the next tile
         PK_NEXT_CHUNK()
         PK_K_ADDRESSES(k_next)
-        PK_PRIO(0);
         PK_EIGHT(o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i & 3], p1[i / DB], o[i % DB], 0, 0, 0);
                  PK_ROW_SUM(p1); PK_REFILL(3 * KS); PK_ADVANCE(i));
         PK_TILE_END();
@@ -706,15 +697,13 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         PK_SKIP_TILE()
     }
     // After the last barrier nobody fills a stage any more, and what is still being read for a tile after
-    // the last is not used: quarters of two K and V stages per head stage the waves' output.
+    // the last is not used: quarters of a K and a V stage stage the waves' output.
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
     if (a.out_f32) store_output(a, u, o, lsum[0]);
-    else store_output_bf16(a, u, o, lsum[0], lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART,
-                           lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
+    else store_output_bf16(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
 }
 
 #undef PK_COPY_TILE
-#undef PK_PRIO
 #undef PK_COPY_PIECE
 #undef PK_COPY_STEP
 #undef PK_SOFTMAX_CHECK
