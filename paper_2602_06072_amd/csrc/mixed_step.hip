@@ -44,8 +44,8 @@ namespace {
 // left of the longer kind.  Spread over the launch, the decode runs load the memory system evenly;
 // alternating one by one until the decode work is gone they saturate it for the first quarter of the
 // launch, and the prefill tiles of that stretch wait (spread 1.3 % faster for the step above, small steps
-// unchanged).  Runs of 64 measure the same, runs of 8 4 % more (workgroups go to the compute units of an XCD
-// one per unit before any unit gets its second: short runs put two of a kind on one unit).
+// unchanged).  Runs of 128 measure the same (12.26 ms, of 256 12.30), runs of 64 0.7 % more, runs of 8 9 % (workgroups go
+// to the compute units of an XCD one per unit before any unit gets its second: short runs put two of a kind on one unit).
 constexpr int kRun = 256;
 
 struct MixedOrder {
