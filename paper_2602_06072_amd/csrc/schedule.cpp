@@ -74,7 +74,10 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
 //   - for requests of at most four tiles, which a wave does not split either: 78 of 8..32 tokens 5.4 / 7.7;
 //   - for short launches with many partial results to a request, which a merge of sixteen waves reads faster: one of
 //     11513 tokens and 32/8 heads (20 partial results) 13.9 / 14.5, of 8799 and 16/2 heads (23) 10.0 / 10.8; one of 16000
-//     and 32/8 heads (23) 16.1 / 15.6, of 32768 (20) 27.9 / 25.1.
+//     and 32/8 heads (23) 16.1 / 15.6, of 32768 (20) 27.9 / 25.1.  Merged rows count as well: one workgroup reads the partial results of all
+//     query heads of a KV head.  One of 4000 tokens (11 partial results): 32/8 heads 9.3 / 9.9 and 8/2 heads 9.3 / 8.1, 64/8 9.5 / 10.4, 64/4
+//     9.7 / 11.2, 32/2 9.2 / 11.2; two of 3000 and 2500 (8): 16/2 9.4 / 8.5, 32/2 9.0 / 9.0, 64/4 9.0 / 9.8; one of 1500 (4) 64/8 9.4 / 8.8, 64/4 9.0 / 9.8,
+//     16/1 9.6 / 8.4; eight of 3000 (5) 64/4 14.3 / 13.1.  (From a captured graph, where a second launch costs 2 us less, waves are ahead from two partial results on.)
 // The split is the one with the least estimated time: bytes at the rate of the whole chip, a start and an end of each workgroup,
 // and the longest item alone for as long as its fair share of the other workgroups' time does not cover it.  The estimate
 // picks within 2 % of the best split on average over 57 batches of 1..1000 requests (10 % at worst).  No split is shorter
@@ -82,7 +85,7 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
 // 8 MiB of a KV head: beside the prefill tiles of a mixed step a workgroup is slow, and whole sequences of 65536
 // tokens keep the chip when everything else is done (12.52 instead of 12.23 ms for 32 chunks and 480 rows of a 70B-shaped
 // layer; with the limit as fast as with waves).
-int64_t group_split(const pk_plan& plan, int Hkv, int d, int num_cus, int64_t from) {
+int64_t group_split(const pk_plan& plan, int r, int Hkv, int d, int num_cus, int64_t from) {
     std::vector<int64_t> blocks;
     int64_t total = 0, longest = 0;
     auto segment = [&](int64_t len) {
@@ -125,7 +128,7 @@ int64_t group_split(const pk_plan& plan, int Hkv, int d, int num_cus, int64_t fr
         if (sp >= longest || sp * scale >= 410) break;       // (the next one could exceed 512 tiles of 16 KiB)
     }
     if (best_wgs > 3 * num_cus && total * Hkv < 8 * best_wgs) return 0;
-    if (best_parts > 32 || (best_parts > 16 && best < 15000)) return 0;
+    if (best_parts > 32 || (best_parts > 16 && best < 15000) || (best_parts * r > 64 && best < 12500)) return 0;
     return split;
 }
 
@@ -177,7 +180,7 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     }
     split = whole_blocks(split);
     const bool may = may_group && dtype == PK_BF16 && r <= 16;
-    int64_t by_group = may ? group_split(plan, Hkv, d, num_cus, split) : 0;
+    int64_t by_group = may ? group_split(plan, r, Hkv, d, num_cus, split) : 0;
     if (plan.tune_decode_split > 0) {              // pk_plan_tune (profiling sweeps): another split for the same kernel
         split = whole_blocks(plan.tune_decode_split);
         if (by_group > 0) by_group = split;

@@ -24,7 +24,9 @@ def test_decode_by_workgroups(case, heads, out_f32):
     kv = np.asarray([1, 31, 32, 33, 95, 96, 97, 127, 128, 129, 160, 161, 190, 255, 257], dtype=np.int32)
     pid = plen = None
     if case != "tiles":
-        kv = np.asarray([2 * unit, 5, 8 * unit, unit + 1, 9 * unit - 31, 16 * unit, unit], dtype=np.int32)
+        # (short batches with more than 64 merged rows per KV head stay with waves: at most four of sixteen here, more in the test below)
+        most = 16 if Hq // Hkv < 16 else 4
+        kv = np.asarray([2 * unit, 5, most // 2 * unit, unit + 1, (most // 2 + 1) * unit - 31, most * unit, unit], dtype=np.int32)
         if case == "parts_reversed":
             kv = np.ascontiguousarray(kv[::-1])
         if case == "private_prefix":                # shared segments of one request each
@@ -36,7 +38,7 @@ def test_decode_by_workgroups(case, heads, out_f32):
     buf = pk.new_kv_buf(plan, Hkv, d, pk.PK_BF16, fill=0x7F)
     pk.kv_reorganize(plan, w.k_pages, w.v_pages, torch.from_numpy(w.block_table).to(DEV), buf, ws)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert plan.stat(5) >= unit and (plan.stat(4) >= 37) == (case != "tiles")   # (a wave each would have 128)
+        assert plan.stat(5) >= unit and (plan.stat(4) >= (37 if Hq // Hkv < 16 else 13)) == (case != "tiles")   # (a wave each would have 128)
     waves = plan.stat(10)
     assert waves == 4
     want = H.oracle_paged_decode(w, False)
@@ -73,6 +75,26 @@ def batch(kv, seed):
     assert plan.stat(10) == 4 and plan.stat(4) > 0
     H.assert_close(ref.cpu().numpy(), H.oracle_paged_decode(w, False), 0, f"batch {seed}")
     return w, plan, ws, buf, ref
+
+
+def test_many_partial_results_of_sixteen_rows():
+    """Sixteen query heads of a KV head and as many as 17 partial results: three batches of the merge, two passes of the workgroup."""
+    kv = np.asarray([40000, 9000, 33000, 5, 20000, 768], dtype=np.int32)
+    w = wl.make_paged("sixteen", kv, 64, 4, 128, 32768, 16, 65, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(kv, np.ones_like(kv), None, None, 32768)
+    ws = pk.new_workspace(plan, 64, 4, 128, pk.PK_BF16)
+    buf = pk.new_kv_buf(plan, 4, 128, pk.PK_BF16)
+    pk.kv_reorganize(plan, w.k_pages, w.v_pages, torch.from_numpy(w.block_table).to(DEV), buf, ws)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert plan.stat(10) == 4 and -(-40000 // plan.stat(5)) > 16
+    got = []
+    for _ in range(2):
+        out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+        pk.packed_decode_attn(plan, w.q, buf, out, w.scale, 4, ws)
+        torch.cuda.synchronize()
+        got.append(out)
+    H.assert_close(got[0].cpu().numpy(), H.oracle_paged_decode(w, False), 0, "many partial results of sixteen rows")
+    assert torch.equal(got[0], got[1])
 
 
 def test_merge_through_the_fixed_scratch_and_in_replays():

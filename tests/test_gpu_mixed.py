@@ -62,7 +62,7 @@ def test_mixed_step_kernels(d, light, waves):
     kv, ql = [700, 300, 129, 64, 1000], [90, 300, 1, 64, 40]
     if not light:
         kv, ql = H.with_long_requests(kv, ql)
-    p = wl.make_ragged("kernels", np.asarray(kv, np.int32), np.asarray(ql, np.int32), 4 if light else 32, 2, d, 4096, 98, device=DEV,
+    p = wl.make_ragged("kernels", np.asarray(kv, np.int32), np.asarray(ql, np.int32), 4 if light else 32, 2 if light else 8, d, 4096, 98, device=DEV,
                        keep_f32=False)
     dkv = np.asarray([9000, 40, 3000, 700, 500, 33] * 4, dtype=np.int32)
     pid = plen = None
