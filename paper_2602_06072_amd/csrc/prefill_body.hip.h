@@ -332,8 +332,13 @@ __device__ __forceinline__ float max2f(float a, float b) {
 
 // The fast path of a half tile is dealt over the SLOTS MFMAs of a part, what stands behind MFMA `slot` here: an MFMA keeps
 // the matrix pipe for 16 cycles, and a wave that has the next one ready stands there until it is free, so that what follows
-// a run of MFMAs overlaps with the last of them only.  Of a lone wave one instruction behind each MFMA is free, every
-// further one costs four cycles (an exponential and a multiply-add behind the same one: also with two waves).
+// a run of MFMAs overlaps with the last of them only.  Of the vector ALU an MFMA takes 8 cycles, an exponential 8 and anything else
+// 4, and a lone wave issues one instruction in 8.  Cycles for an MFMA and what stands behind it, one wave / two waves on a SIMD: alone 16.2 /
+// 16.1, one multiply-add 16.3 / 16.1, an exponential 16.7 / 16.3, multiply-add and exponential of the same score 24.3 / 21.1, the exponential of
+// one score and the multiply-add of the next 20.9 / 20.5; with a conversion behind every other MFMA 26.3 / 23.3 in the first order, 22.5 /
+// 22.2 in the second.  So the exponential of a score stands a slot behind its multiply-add, and in front of the next one's, and the
+// combination of the packed pairs a slot behind the conversion (one order / the other: 64 ragged prompts 383.0 / 377.2 us, 32 chunks of a 70B-shaped layer
+// 10.58 / 10.49 ms, 8 x 2048 with head dimension 64 163.2 / 162.2 us, other shapes equal).
 // The scores are through SPARE slots before the end and a pair is converted two slots behind its exponentials: neither
 // the conversion nor the branch at the end waits for results.  Score e of a
 // lane is element e & 3 of key block (e >> 2) & 1 of column block e >> 3.
@@ -344,20 +349,23 @@ __device__ __forceinline__ void softmax_slot(const int slot, const Scores& s, co
     constexpr int SCORES = 8 * NC;
     static_assert(SPARE == 0 || (SCORES - 1) * (SLOTS - SPARE) / SCORES + 3 < SLOTS, "every pair is packed before the part ends");
     auto last = [](int at) { return at < SLOTS ? at : SLOTS; };
+    auto begin = [](int e) { return e * (SLOTS - SPARE) / SCORES; };
 #pragma unroll
-    for (int e = 0; e < SCORES; ++e) {
-        const int at = e * (SLOTS - SPARE) / SCORES;
-        if (e % 2 == 1 && last(at + 3) == slot) {
-            const int k = e / 2;
-            asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(h.pw[k]) : "v"(p.x[(e - 1) & 7]), "v"(p.x[e & 7]));
-            if (k == 2) asm volatile("v_or3_b32 %0, %1, %2, %3" : "=v"(h.any) : "v"(h.pw[0]), "v"(h.pw[1]), "v"(h.pw[2]));
-            else if (k > 2 && k % 2 == 0) asm volatile("v_or3_b32 %0, %0, %1, %2" : "+v"(h.any) : "v"(h.pw[k - 1]), "v"(h.pw[k]));
-            else if (k == SCORES / 2 - 1) asm volatile("v_or_b32 %0, %0, %1" : "+v"(h.any) : "v"(h.pw[k]));
-        }
-        if (at == slot)
-            asm volatile("v_fma_f32 %0, %1, %2, -%3\n\tv_exp_f32 %0, %0"
-                         : "=v"(p.x[e & 7]) : "v"(s[e >> 3][(e >> 2) & 1][e & 3]), "s"(sc), "v"(m_ref[e >> 3]));
+    for (int e = 0; e < SCORES; ++e)
+        if (last(begin(e) + 1) == slot) asm volatile("v_exp_f32 %0, %0" : "+v"(p.x[e & 7]));
+#pragma unroll
+    for (int k = 0; k < SCORES / 2; ++k) {
+        if (last(begin(2 * k + 1) + 3) == slot)
+            asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(h.pw[k]) : "v"(p.x[(2 * k) & 7]), "v"(p.x[(2 * k + 1) & 7]));
+        if (last(begin(2 * k + 1) + 4) != slot) continue;
+        if (k == 2) asm volatile("v_or3_b32 %0, %1, %2, %3" : "=v"(h.any) : "v"(h.pw[0]), "v"(h.pw[1]), "v"(h.pw[2]));
+        else if (k > 2 && k % 2 == 0) asm volatile("v_or3_b32 %0, %0, %1, %2" : "+v"(h.any) : "v"(h.pw[k - 1]), "v"(h.pw[k]));
+        else if (k == SCORES / 2 - 1) asm volatile("v_or_b32 %0, %0, %1" : "+v"(h.any) : "v"(h.pw[k]));
     }
+#pragma unroll
+    for (int e = 0; e < SCORES; ++e)
+        if (begin(e) == slot)
+            asm volatile("v_fma_f32 %0, %1, %2, -%3" : "=v"(p.x[e & 7]) : "v"(s[e >> 3][(e >> 2) & 1][e & 3]), "s"(sc), "v"(m_ref[e >> 3]));
     if (slot == (SPARE > 0 ? SLOTS - 1 : SLOTS)) {
         h.slow = __builtin_amdgcn_ballot_w64((h.any & kTooLarge) != 0);
         asm volatile("" : "+s"(h.slow));
