@@ -37,7 +37,6 @@ constexpr int NC = 2;                              // column blocks of a wave: b
 constexpr int WAVES = PK_WAVES;                     // 4, or 8: waves 4 .. 7 work on the next head
 constexpr int PIECES = TILE_BYTES / (1024 * WAVES);   // 1-KiB copy instructions per wave and tile
 constexpr int RPW = BN / WAVES, PPS = RPW / 8;        // rows (and copies) of a slab that one wave fills
-constexpr int WAVE_PART = TILE_BYTES / 4;          // bytes of a stage that take half of a wave's output for one head
 
 // A stage in LDS is one slab per 64 columns: 64 rows of 128 bytes (eight 16-byte chunks).  Whatever
 // the head dimension, two K and four V addresses per lane then reach every operand with constant
@@ -174,41 +173,30 @@ __device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUni
     }
 }
 
-// bf16 output of head `h` through LDS, so that every row leaves as whole 16-byte pieces (four rows of 256
-// bytes, or eight of 128, per store instruction) instead of 8-byte pieces of 16 different rows.
-// The wave uses two pieces of LDS of 16 rows each that belong to it alone (block 0 in qa, block 1
-// in qb); the 16-byte chunks of a row are XOR-swizzled with the row number, which keeps
-// both sides off bank conflicts.
-__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx4 (&o)[NC][OPS],
-                                                  const floatx4 (&l)[NC], unsigned char* qa, unsigned char* qb) {
-    constexpr int CPR = D / 8, RPI = 64 / CPR;     // 16-byte chunks per row; rows per store instruction
+// The same in bf16.  Of two neighbouring blocks of 16 columns the lane groups 1 and 3 give away the first and the groups 0 and 2 the
+// second: every lane then has 16 contiguous bytes, a store instruction writes 64 from each of 16 rows, and nothing
+// goes through LDS (there the rows leave whole, but the round trip, a look-up of every row and the branches around eight stores
+// take 3200 cycles of a workgroup, this 1200: 64 ragged prompts 377.2 -> 373.3 us, 8 x 2048 286.9 -> 283.7, with head dimension 64
+// 162.2 -> 160.8, 1 x 4096 with 64 heads 241.3 -> 236.9; short lists in launches of 70 us the same).
+__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx4 (&o)[NC][OPS], const floatx4 (&l)[NC]) {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const float inv = row_scale(l[c][0]);
-        unsigned char* wrow = (c ? qb : qa) + u.n * ROWB + 8 * (u.g & 1);
+        if (u.qrow[c] < 0) continue;
+        uint16_t* out = static_cast<uint16_t*>(a.out) + (static_cast<int64_t>(u.qrow[c]) * a.Hq + u.head) * D + 16 * (u.g & 1) + 8 * (u.g >> 1);
 #pragma unroll
-        for (int t = 0; t < OPS; ++t) {            // columns 16t + 4g .. +3: chunk 2t + g / 2, half g & 1
-            const floatx4 x = o[c][t];
-            *reinterpret_cast<uint2*>(wrow + (((2 * t + (u.g >> 1)) ^ (u.n & (CPR - 1))) << 4)) =
-                make_uint2(pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv));
+        for (int t = 0; t < OPS; t += 2) {
+            uint32_t w[2][2];                          // [block t, t + 1][columns 4g, 4g + 1 / + 2, + 3]
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const floatx4 x = o[c][t + b];
+                w[b][0] = pack_bf16x2(x[0] * inv, x[1] * inv); w[b][1] = pack_bf16x2(x[2] * inv, x[3] * inv);
+            }
+            const auto p0 = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+            const auto p1 = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+            *reinterpret_cast<u32x4*>(out + 16 * t) = u32x4{p0[0], p1[0], p0[1], p1[1]};
         }
     }
-    // all look-ups and reads before the first store: one by one, each would wait for its own LDS round trips
-    const int chunk = u.lane & (CPR - 1);
-    int q_row[32 / RPI];
-    u32x4 v[32 / RPI];
-#pragma unroll
-    for (int k = 0; k < 32 / RPI; ++k) {
-        const int row = RPI * k + u.lane / CPR, r2 = row & 15;
-        q_row[k] = __shfl(u.qrow[RPI * k / 16], r2, 64);
-        v[k] = *reinterpret_cast<const u32x4*>((RPI * k < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
-    }
-    asm volatile("" ::: "memory");                 // (the reads stay before the branches below)
-#pragma unroll
-    for (int k = 0; k < 32 / RPI; ++k)
-        if (q_row[k] >= 0)
-            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) +
-                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * D + 8 * chunk) = v[k];
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
@@ -271,7 +259,6 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 #define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) / PPS) * SLAB + ((Q) % PPS) * 1024, off.g[Q])
 #define PK_COPY_TILE(RS, DST)                                                                \
     { _Pragma("unroll") for (int q = 0; q < PIECES; ++q) PK_COPY_PIECE(RS, DST, q); }
-#define PK_WAIT_ALL_COPIES() __builtin_amdgcn_s_waitcnt(0x0F70)      /* vmcnt(0) */
 #define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
 
 // ---------------------------------------------------------------------------------------------
@@ -683,7 +670,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // first operands are read during the last MFMAs of the turn, was published a turn earlier.
     int t = -1;
     const bool any_tile = u.n_lead < u.n_active;
-    const int first_turn = any_tile ? u.n_lead - 1 : n_kv;     // (a wave without a tile skips every turn)
+    const int first_turn = any_tile ? u.n_lead - 1 : -1;
     while (t < first_turn) PK_SKIP_TURN()
     if (any_tile) {
         Scores s0, s1;                              // scores of the first and of the second half of a tile
@@ -732,38 +719,39 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
             PK_TURN_END()
         }
         {
-            // Last turn: nothing but P.V and the probabilities of the last half.  Of the rows of a causal tile every other
-            // wave's end in the first half of their last key tile: the second half is left out then.
-            int ek_s, ek_i, ev_s, ev_i;
-            RowOffset ek_off, ev_off;
+            // Last turn: nothing but P.V and the probabilities of the last half, and no copies if it is the workgroup's last (nothing may
+            // be on its way into LDS when that ends).  Of the rows of a causal tile every other wave's end in the first half of
+            // their last key tile: the second half is left out then.
+            if (t + 1 < n_kv) { _Pragma("unroll") for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); } }
             const bool both = !masked || __builtin_amdgcn_ballot_w64((u.lo[0] <= cur_s && u.hi[0] - cur_s > 32) || (u.lo[1] <= cur_s && u.hi[1] - cur_s > 32)) != 0;
             if (masked) mask(s1, 1, cur_s, cur_i);
 #pragma unroll
             for (int x = 0; x < 4; ++x) ring[x] = v_operand(lds + v_cur, off, 0, x);
             Pending pend;
             PK_OPS_STEPS(PK_SLOTS((pv_mfma<i>(c, o, lsum, ring[i & 3], p0, ones)), softmax_slot<OPS * NC, 0>(i * NC + c, s1, sc, m_ref, pend, h1))
-                         ring[i & 3] = v_operand(lds + v_cur, off, (i + 4) / OPS, (i + 4) % OPS); PK_COPY_STEP(i))
+                         ring[i & 3] = v_operand(lds + v_cur, off, (i + 4) / OPS, (i + 4) % OPS))
             softmax_slot<OPS * NC, 0>(OPS * NC, s1, sc, m_ref, pend, h1);
             if (both) {
                 PK_SOFTMAX_CHECK(s1, h1)
                 PK_PACK_P(p1, h1)
                 PK_MFMA_OPERANDS()
                 PK_OPS_STEPS(PK_SLOTS((pv_mfma<i>(c, o, lsum, ring[(OPS + i) & 3], p1, ones))) if constexpr (i + 4 < OPS) ring[(OPS + i) & 3] = v_operand(lds + v_cur, off, 1, i + 4))
-                PK_MFMA_RESULTS()
             }
-            PK_ADVANCE_ALL()
-            PK_TURN_END()
         }
     }
-    while (t < n_kv) PK_SKIP_TURN()
-    // After the last barrier nobody fills or reads a stage any more: quarters of a K and a V stage stage the
-    // waves' output (a wave's LDS accesses are in order).
-    PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
     PK_MFMA_RESULTS()
 #pragma unroll
     for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(lsum[c]));   // (all four words of a sum are live until here)
     if (a.out_f32) store_output(a, u, o, lsum);
-    else store_output_bf16(a, u, o, lsum, lds + (u.wave < 4 ? k_next : k_fill) + (u.wave & 3) * WAVE_PART, lds + (u.wave < 4 ? v_cur : v_fill) + (u.wave & 3) * WAVE_PART);
+    else store_output_bf16(a, u, o, lsum);
+    // The turns that are left for the other waves (the barrier at the end of the last one has nothing to wait for).
+    if (any_tile && t < n_kv - 1) {
+        int ek_s, ek_i, ev_s, ev_i;
+        RowOffset ek_off, ev_off;
+        PK_ADVANCE_ALL()
+        PK_TURN_END()
+    }
+    while (t < n_kv - 1) PK_SKIP_TURN()
 }
 
 #undef PK_COPY_TILE
@@ -791,7 +779,6 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #undef PK_SKIP_TURN
 #undef PK_ADVANCE
 #undef PK_K_ADDRESSES
-#undef PK_WAIT_ALL_COPIES
 #undef PK_CODE
 
 }  // namespace PK_DNS
