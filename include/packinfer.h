@@ -405,7 +405,9 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
  *   what = 2: same for the padded prefill schedule
  *   what = 3: decode work items; 4: split-KV partial slots;
  *   what = 5: tokens per decode split chosen by the schedule builder
- *   what = 6: query tiles of the packed prefill schedule; 7: of the padded
+ *   what = 6: query tiles of the packed prefill schedule, of 128 rows (with
+ *             an even number of heads per KV head the launch has tiles of 32
+ *             or 64 rows and several heads instead); 7: of the padded
  *   what = 8: 1 if the packed bf16 prefill (also the prefill half of a mixed
  *             step) takes the kernels for launches of little work, 0 if the
  *             software-pipelined ones; 9: same for the padded schedule

@@ -311,8 +311,8 @@ static int prefill_common(pk_plan* plan, const void* q, const void* k, const voi
     a.q = q; a.k = k; a.v = v; a.out = out;
     a.tiles = tab(plan, s.tiles, base); a.n_tiles = s.n_tiles;
     a.run_first = tab(plan, s.run_first, base); a.runs = tab(plan, s.runs, base);
-    a.kvtiles = tab(plan, s.kvtiles, base); a.n_key_tiles = static_cast<int64_t>(s.kvtiles.count / 2);
-    a.light = s.light;
+    a.kvtiles = tab(plan, s.kvtiles, base);
+    a.light = s.light; a.eight = s.eight; a.row_shift = s.row_shift;
     a.q_start = tab(plan, t.q_start); a.kv_start = tab(plan, t.kv_start); a.n = plan->n;
     int64_t tq = 0, tkv = 0;
     for (int32_t i = 0; i < plan->n; ++i) { tq += plan->q_lens[i]; tkv += plan->kv_lens[i]; }
@@ -582,7 +582,7 @@ extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
             case 3: return plan->tables.dec.n_items;
             case 4: return plan->tables.dec.n_parts;
             case 5: return plan->tables.dec.split_tokens;
-            case 6: return plan->tables.packed.n_tiles;
+            case 6: return plan->tables.packed.n_query_tiles;
             case 7:
                 if (!plan->tables.padded_built && plan->tables.dtype >= 0)
                     build_prefill_padded(*plan, plan->tables);

@@ -75,7 +75,8 @@ struct PrefillArgs {
     int64_t total_q_rows; int64_t total_kv_rows;
     int Hq; int Hkv; int d; float scale; int out_f32;
     int pipeline;                                   // 0: K/V tiles copied straight into LDS; 1: staged through registers
-    int64_t n_key_tiles;                            // entries of kvtiles
+    int eight;                                      // pipeline 0: workgroups of eight waves
+    int row_shift;                                  // a query tile has 32 << row_shift rows; a workgroup's waves take them 32 at a time, for as many heads as there are waves
     int light;                                      // pipeline 0: a launch of little work, prefill_few_body.hip.h
     int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: workgroups per (query tile, KV head), divisions by it and by Hkv
 };

@@ -113,10 +113,10 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     hipStream_t st = static_cast<hipStream_t>(stream);
     PrefillArgs pa = args;
     DecodeArgs da = decode_args;
-    const int r = pa.heads_per_kv = pa.Hq / pa.Hkv;
+    da.heads_per_kv = pa.Hq / pa.Hkv;
+    da.by_r = FastDiv::by(static_cast<uint32_t>(da.heads_per_kv));
+    const int r = pa.heads_per_kv = da.heads_per_kv >> (2 - pa.row_shift);  // workgroups per (query tile, KV head)
     pa.by_r = FastDiv::by(static_cast<uint32_t>(r));
-    da.heads_per_kv = r;
-    da.by_r = pa.by_r;
     pa.by_hkv = FastDiv::by(static_cast<uint32_t>(pa.Hkv));
     const int64_t pairs = static_cast<int64_t>(pa.n_tiles) * pa.Hkv;
     const int64_t n_prefill = (pairs + 7) / 8 * 8 * r;                      // as in the prefill launch (XCD map)

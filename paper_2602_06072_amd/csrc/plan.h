@@ -75,14 +75,19 @@ struct DeviceTables {
     int32_t pad_split_tokens = 0, pad_n_splits = 0;   // padded decode comparison: uniform splits
     // prefill (packed and padded schedules share one format)
     struct PrefillSched {
-        TableRef tiles;             // [n_tiles][16] kv_first, n_kv, leading / trailing skipped key tiles per wave (4 x 8 bits each),
+        TableRef tiles;             // [n_tiles][16] kv_first, n_kv, leading / trailing skipped key tiles per 32 rows (4 x 8 bits each),
                                     // rows | runs << 16, then Q row, lo, hi of tile row 0 (the first run), then k_start and
-                                    // info of the first three key tiles
+                                    // info of the first three key tiles, then the end of the keys that the tile sees (INT32_MAX: the
+                                    // list says it)
         TableRef run_first;         // [n_tiles] first entry of the tile's further runs
         TableRef runs;              // (first tile row, its Q row, lo, its hi) of the runs after a tile's first
-        TableRef kvtiles;           // [n_kv_total][2] k_start, n | wavemask<<8 | full<<16
+        TableRef kvtiles;           // [n_kv_total][2] k_start, n | codes << 8 (2 bits per 32 rows: 0 skip, 1 masked, 2 unmasked); with
+                                    // row_shift < 2 a list per request, which its query tiles share (all codes 2)
         int32_t n_tiles = 0;
         int64_t issued_pairs = 0;
+        int32_t n_query_tiles = 0;  // packed: of 128 rows, whatever row_shift is
+        int row_shift = 2;          // rows of a query tile: 32 << row_shift
+        bool eight = false;         // workgroups of eight waves, twice the heads (the prefill launch, d = 128)
         bool light = false;         // a launch of little work: prefill_few_body.hip.h (the schedule builder's choice)
     } packed, padded;
     int num_cus = 0;                // of the device the schedules are built for

@@ -48,20 +48,21 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_kernel(PrefillArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
 
     // ---- work unit ---------------------------------------------------------
-    const int r = a.Hq / a.Hkv;
-    // consecutive workgroup ids go round-robin over the 8 XCDs: keep the r heads of one
+    const int mates = 4 >> a.row_shift, r = a.Hq / a.Hkv / mates;    // heads per workgroup, workgroups per (tile, KV head)
+    // consecutive workgroup ids go round-robin over the 8 XCDs: keep the heads of one
     // (tile, KV head) pair on one XCD and adjacent in time so K/V tiles hit in its L2
     const int x = blockIdx.x, c = x & 7, y = x >> 3, j = y % r, slot = y / r;
     const int64_t p = static_cast<int64_t>(slot) * 8 + c;
     if (p >= static_cast<int64_t>(a.n_tiles) * a.Hkv) return;
-    const int tile = static_cast<int>(p / a.Hkv), kvh = static_cast<int>(p % a.Hkv), head = kvh * r + j;
+    const int tile = static_cast<int>(p / a.Hkv), kvh = static_cast<int>(p % a.Hkv);
     const int32_t* desc = a.tiles + 16 * static_cast<int64_t>(tile);     // (16 words per descriptor; this kernel uses the first 8)
     const int kv_first = desc[0], n_kv = desc[1];
     if (n_kv == 0) return;
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, hlf = lane >> 5;
     int qrow, lo, hi;
-    prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], wave * 32 + n, qrow, lo, hi);
+    const int part = wave & ((1 << a.row_shift) - 1), head = (kvh * r + j) * mates + (wave >> a.row_shift);
+    prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], part * 32 + n, qrow, lo, hi);
 
     // ---- Q operand: lane (n, hlf) holds Q[row n][16s + 8hlf .. +8] ----------
     bf16x8 qf[KS];
@@ -126,7 +127,8 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_kernel(PrefillArgs a) {
     // barrier are not scalarised by the compiler and their latency would sit in every iteration,
     // so they run through a window: e0 / e1 hold tiles j, j+1 and the entry of j+2 is in flight.
     const int32_t* kvt = a.kvtiles + 2 * static_cast<int64_t>(kv_first);
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int part_u = __builtin_amdgcn_readfirstlane(part);
+    const int full = a.row_shift < 2 ? __builtin_amdgcn_readfirstlane(hi) : 0x7FFFFFFF;   // keys that all rows of the wave see (row_shift 2: the list says)
     auto entry_load = [&](int j) -> int2 {
         return *reinterpret_cast<const int2*>(kvt + 2 * (j < n_kv ? j : n_kv - 1));
     };
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_kernel(PrefillArgs a) {
         if (j + 1 < n_kv) PK_GLOAD(e1s);
         const int2 e2 = entry_load(j + 2);
         const int32_t k_start = e0s, info = e0i;
-        const int code = (info >> (8 + 2 * wave_u)) & 3;     // 0 skip, 1 masked, 2 unmasked
+        const int code = k_start + BN > full ? 1 : (info >> (8 + 2 * part_u)) & 3;     // 0 skip, 1 masked, 2 unmasked
         if (code != 0) {
             const unsigned char* ks = smem + stage * SM::STAGE;
             const unsigned char* vs = ks + SM::K_BYTES;
@@ -292,7 +294,7 @@ int launch_p(const PrefillArgs& a, hipStream_t st) {
         if (e != hipSuccess) return static_cast<int>(e);
         attr_set = true;
     }
-    const int r = a.Hq / a.Hkv;
+    const int r = a.Hq / a.Hkv >> (2 - a.row_shift);
     const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
     const int64_t grid = (pairs + 7) / 8 * 8 * r;
     if (grid == 0) return 0;

@@ -70,11 +70,12 @@ __device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneO
 
 // What a workgroup works on, and this lane's share of it.
 struct WorkUnit {
-    int head, kvh, n_kv, n_lead, n_active, wave, lane, n, g;   // (first) head; this wave computes key tiles [n_lead, n_active)
-    int rows;                          // which 32 of the tile's 128 rows this wave has
+    int head, kvh, n_kv, n_lead, n_active, wave, lane, n, g;   // this wave's head; it computes key tiles [n_lead, n_active)
+    int rows;                          // which 32 of the tile's rows this wave has
     int ks[3], info[3];                // (first key row, info) of the tile's first three key tiles (the last one repeated)
     int qrow[2], lo[2], hi[2];         // this lane's query rows (-1: padding) and their key ranges [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
+    int k_end, full;                   // keys from k_end on are not the tile's; up to `full` all of this wave's rows see them (row_shift < 2)
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
     uint32_t row_bytes32;              // the same in 32 bits
 };
@@ -83,13 +84,13 @@ struct WorkUnit {
 // Returns false for grid padding and for query tiles without key tiles.
 __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[NC][KS]) {
     // Consecutive workgroup ids go round-robin over the 8 XCDs: the workgroups of one (tile, KV head) pair
-    // (r of them with one head each, or r / 2 with two) stay on one XCD and adjacent in time, so that its L2
+    // (heads_per_kv of them, each with its share of the KV head's query heads) stay on one XCD and adjacent in time, so that its L2
     // serves their K/V tiles.
     const int y = block >> 3, slot = a.by_r(y), p = slot * 8 + (block & 7);
     const int tile = a.by_hkv(p);
     if (tile >= a.n_tiles) return false;
     u.kvh = p - tile * a.Hkv;
-    const int groups = a.heads_per_kv, pair = y - slot * groups;
+    const int groups = a.heads_per_kv, group = y - slot * groups;
     // everything about the tile in one 64-byte scalar load, including the first key rows of its first
     // key tiles: the first K/V copies do not wait for the key-tile list
     typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
@@ -99,20 +100,22 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     u.kvt = a.kvtiles + 2 * static_cast<int64_t>(desc[0]);
 #pragma unroll
     for (int x = 0; x < 3; ++x) { u.ks[x] = desc[8 + x]; u.info[x] = desc[11 + x]; }
+    u.k_end = desc[14];
     const int tid = threadIdx.x;
     u.lane = tid & 63; u.n = u.lane & 15; u.g = u.lane >> 4;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Wave w of every workgroup runs on SIMD w % 4, and the last rows of a causal tile see more key tiles than
     // the first: every other set of 256 workgroups (a set is one per compute unit) deals
     // the rows in reverse, so that the waves of a SIMD get as much together as those of any other.
-    const int w4 = u.wave & 3, second = u.wave >> 2;
-    u.head = (u.kvh * groups + pair) * (WAVES / 4) + second;
-    u.rows = (WAVES > 4 ? second : (block >> 8) & 1) ? 3 - w4 : w4;
+    const int part = u.wave & ((1 << a.row_shift) - 1), mate = u.wave >> a.row_shift;
+    u.head = ((u.kvh * groups + group) << ((WAVES == 8 ? 3 : 2) - a.row_shift)) + mate;
+    u.rows = (WAVES > 4 ? mate & 1 : (block >> 8) & 1) ? (1 << a.row_shift) - 1 - part : part;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
 #pragma unroll
     for (int c = 0; c < 2; ++c)
         prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + 16 * c + u.n, u.qrow[c], u.lo[c], u.hi[c]);
+    u.full = a.row_shift < 2 ? __builtin_amdgcn_readfirstlane(u.hi[0]) : 0x7FFFFFFF;   // (the first row's; what one row sees, those behind it do)
     u.row_bytes = static_cast<int64_t>(a.Hkv) * ROWB;
     u.row_bytes32 = static_cast<uint32_t>(a.Hkv) * ROWB;
 
@@ -259,7 +262,13 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 #define PK_COPY_PIECE(RS, DST, Q) lds_copy_16(RS, lds_wave + (DST) + ((Q) / PPS) * SLAB + ((Q) % PPS) * 1024, off.g[Q])
 #define PK_COPY_TILE(RS, DST)                                                                \
     { _Pragma("unroll") for (int q = 0; q < PIECES; ++q) PK_COPY_PIECE(RS, DST, q); }
-#define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
+// What the loop needs of a list entry: how many keys there are to copy (none for an entry past the list) and, in bit 8, whether this
+// wave has to mask the tile.  Codes of the list: 0 skip, 1 masked, 2 unmasked.
+__device__ __forceinline__ int entry_info(const WorkUnit& u, const int ks, const int info, const int index) {
+    const int keys = index < u.n_kv ? min(info & 0xFF, u.k_end - ks) : 0;
+    const bool masked = ((info >> (8 + 2 * u.rows)) & 3) != 2 || ks + BN > u.full;
+    return keys | (masked ? 0x100 : 0);
+}
 
 // ---------------------------------------------------------------------------------------------
 // Five stages of LDS per workgroup, three for K and two for V.
@@ -563,15 +572,12 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     const int n_kv = u.n_kv;
     // The key-tile list, 64 entries at a time, one per lane: the loop takes entries out with v_readlane.  (A
     // scalar load shares its counter with the LDS reads and returns out of order: the wait for it drained the
-    // operand ring, on the critical path of every tile.)  Two of them, for the tile whose K is copied
-    // and for the one whose V is copied, two tiles behind: the next 64 entries replace the present ones in place.
-    int lk_s, lk_i, lv_s, lv_i;
-    auto load_chunk = [&](int first, int& ks, int& info) {
-        const int2 e = reinterpret_cast<const int2*>(u.kvt)[min(first + u.lane, n_kv - 1)];
-        ks = e.x; info = e.y;
-    };
-    load_chunk(0, lk_s, lk_i);
-    lv_s = lk_s; lv_i = lk_i;
+    // operand ring, on the critical path of every tile.)  The next 64 are on their way.
+    int list_s, list_i;
+    int2 next_list = {0, 0};
+    auto load_chunk = [&](int first) { return reinterpret_cast<const int2*>(u.kvt)[min(first + u.lane, n_kv - 1)]; };
+    const int2 first_list = load_chunk(0);
+    if (n_kv > 64) next_list = load_chunk(64);
 
     floatx4 o[NC][OPS], lsum[NC];
     float m_ref[NC], far[NC];
@@ -591,20 +597,25 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * RPW * SLAB_ROWB);
     uint32_t row_bytes = u.row_bytes32;
     scalar(row_bytes);
-    auto valid_rows = [&](int info, int tile) { return tile < n_kv ? static_cast<uint32_t>(info & 0xFF) : 0u; };
+#pragma unroll
+    for (int x = 0; x < 3; ++x) u.info[x] = entry_info(u, u.ks[x], u.info[x], x);
+    auto keys_of = [](int info) { return static_cast<uint32_t>(info & 0xFF); };
     // prologue: K(0), K(1), from the descriptor; the first turn copies K(2) and V(0)
     {
-        const u32x4 rk0 = tile_desc(a.k, row_offset(u.ks[0], row_bytes), valid_rows(u.info[0], 0), row_bytes);
+        const u32x4 rk0 = tile_desc(a.k, row_offset(u.ks[0], row_bytes), keys_of(u.info[0]), row_bytes);
         PK_COPY_TILE(rk0, 0)
-        const u32x4 rk1 = tile_desc(a.k, row_offset(u.ks[1], row_bytes), valid_rows(u.info[1], 1), row_bytes);
+        const u32x4 rk1 = tile_desc(a.k, row_offset(u.ks[1], row_bytes), keys_of(u.info[1]), row_bytes);
         PK_COPY_TILE(rk1, TILE_BYTES)
     }
-    u32x4 rs_k = tile_desc(a.k, row_offset(u.ks[2], row_bytes), valid_rows(u.info[2], 2), row_bytes);
-    u32x4 rs_v = tile_desc(a.v, row_offset(u.ks[0], row_bytes), valid_rows(u.info[0], 0), row_bytes);
-    int cur_s = u.ks[0], cur_i = 0, nxt_s = u.ks[0], nxt_i = u.info[0];   // list entries of tiles t and t + 1
-    scalar(cur_s); scalar(cur_i); scalar(nxt_s); scalar(nxt_i);
-#define PK_WAIT_AND_MEET() asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : "+v"(lk_s), "+v"(lk_i), "+v"(lv_s), "+v"(lv_i) :: "memory")
+    u32x4 rs_k = tile_desc(a.k, row_offset(u.ks[2], row_bytes), keys_of(u.info[2]), row_bytes);
+    u32x4 rs_v = tile_desc(a.v, row_offset(u.ks[0], row_bytes), keys_of(u.info[0]), row_bytes);
+    int es[4] = {u.ks[0], u.ks[0], u.ks[1], u.ks[2]}, ei[4] = {0, u.info[0], u.info[1], u.info[2]};   // list entries of tiles t .. t + 3
+    int &cur_s = es[0], &cur_i = ei[0], &nxt_s = es[1], &nxt_i = ei[1];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) { scalar(es[x]); scalar(ei[x]); }
+#define PK_WAIT_AND_MEET() asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory")
     PK_WAIT_AND_MEET();
+    list_s = first_list.x; list_i = entry_info(u, first_list.x, first_list.y, u.lane);
     clear_absent_rows(u, qf);
 
     bf16x8 ring[4];                                 // LDS operands of the next steps
@@ -622,25 +633,29 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #define PK_COPY_NEXT(I)                                                                       \
     if constexpr ((I) + 1 < PIECES) copy_to(lds_wave + k_fill + PK_PIECE_AT((I) + 1));         \
     else if constexpr ((I) + 1 < 2 * PIECES) copy_to(lds_wave + v_fill + PK_PIECE_AT((I) + 1 - PIECES));
-    // The next turn's list entries and descriptors, in eight pieces that stand behind the last MFMAs of a turn: done
+    // The list entry of tile t + 4 and the next turn's descriptors, in eight pieces that stand behind the last MFMAs of a turn: done
     // behind the barrier they keep all waves of the workgroup from the matrix pipe at once.
 #define PK_ADVANCE(I)                                                                         \
-    if constexpr ((I) == 0) { ek_s = __builtin_amdgcn_readlane(lk_s, (t + 4) & 63); ek_i = __builtin_amdgcn_readlane(lk_i, (t + 4) & 63); } \
-    else if constexpr ((I) == 1) { ev_s = __builtin_amdgcn_readlane(lv_s, (t + 2) & 63); ev_i = __builtin_amdgcn_readlane(lv_i, (t + 2) & 63); } \
+    if constexpr ((I) == 0) ek_s = __builtin_amdgcn_readlane(list_s, (t + 4) & 63);            \
+    else if constexpr ((I) == 1) ek_i = __builtin_amdgcn_readlane(list_i, (t + 4) & 63);       \
     else if constexpr ((I) == 2) ek_off = row_offset(ek_s, row_bytes);                         \
     else if constexpr ((I) == 3) desc_base(rs_k, a.k, ek_off);                                 \
-    else if constexpr ((I) == 4) desc_size(rs_k, valid_rows(ek_i, t + 4), row_bytes);          \
-    else if constexpr ((I) == 5) ev_off = row_offset(ev_s, row_bytes);                         \
+    else if constexpr ((I) == 4) desc_size(rs_k, keys_of(ek_i), row_bytes);          \
+    else if constexpr ((I) == 5) ev_off = row_offset(es[2], row_bytes);                         \
     else if constexpr ((I) == 6) desc_base(rs_v, a.v, ev_off);                                 \
-    else if constexpr ((I) == 7) desc_size(rs_v, valid_rows(ev_i, t + 2), row_bytes);
+    else if constexpr ((I) == 7) desc_size(rs_v, keys_of(ei[2]), row_bytes);
 #define PK_ADVANCE_ALL() PK_ADVANCE(0) PK_ADVANCE(1) PK_ADVANCE(2) PK_ADVANCE(3) PK_ADVANCE(4) PK_ADVANCE(5) PK_ADVANCE(6) PK_ADVANCE(7)
-    // behind the last of 64 entries the next 64 are requested, here for the barrier to wait for
+    // behind the last of 64 entries come the next 64, which were requested 64 turns ago (and nothing is on its way behind the barrier: taking
+    // them waits for nothing)
 #define PK_TURN_END()                                                                         \
-    if (((t + 4) & 63) == 63) load_chunk(t + 5, lk_s, lk_i);                                   \
-    if (((t + 2) & 63) == 63) load_chunk(t + 3, lv_s, lv_i);                                   \
     PK_WAIT_AND_MEET();                                                                        \
-    cur_s = nxt_s; cur_i = nxt_i; nxt_s = ev_s; nxt_i = ev_i;                                  \
-    scalar(cur_s); scalar(cur_i); scalar(nxt_s); scalar(nxt_i);                                \
+    if (((t + 4) & 63) == 63) {                                                                \
+        list_s = next_list.x; list_i = entry_info(u, next_list.x, next_list.y, t + 5 + u.lane); \
+        next_list = load_chunk(t + 5 + 64);                                                    \
+    }                                                                                          \
+    _Pragma("unroll") for (int x = 0; x < 3; ++x) { es[x] = es[x + 1]; ei[x] = ei[x + 1]; }   \
+    es[3] = ek_s; ei[3] = ek_i;                                                                \
+    _Pragma("unroll") for (int x = 0; x < 4; ++x) { scalar(es[x]); scalar(ei[x]); }            \
     { const int kc = k_cur; k_cur = k_next; k_next = k_fill; k_fill = kc; }                    \
     { const int vc = v_cur; v_cur = v_fill; v_fill = vc; }                                     \
     copy_to(lds_wave + k_fill);                                                                \
@@ -648,7 +663,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // a turn in which this wave only takes part in the copies and the barrier
 #define PK_SKIP_TURN()                                                                        \
     {                                                                                          \
-        int ek_s, ek_i, ev_s, ev_i;                                                            \
+        int ek_s, ek_i;                                                            \
         RowOffset ek_off, ev_off;                                                              \
         _Pragma("unroll") for (int q = 0; q < PIECES; ++q) { PK_COPY_PIECE(rs_k, k_fill, q); PK_COPY_PIECE(rs_v, v_fill, q); } \
         PK_ADVANCE_ALL()                                                                       \
@@ -679,14 +694,14 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
         bool masked = false;                        // tile t needs its mask
         {
             // first turn: the scores of this wave's first tile and the probabilities of its first half
-            int ek_s, ek_i, ev_s, ev_i;
+            int ek_s, ek_i;
             RowOffset ek_off, ev_off;
             PK_K_ADDRESSES(k_cur)
 #pragma unroll
             for (int x = 0; x < 4; ++x) ring[x] = k_operand(kp, 0, x);
             PK_OPS_STEPS(PK_SLOTS(scores_mfma<i>(c, s0, ring[i & 3], qf)) ring[i & 3] = k_operand(kp, (i + 4) / OPS, (i + 4) % OPS); PK_COPY_STEP(i))
             PK_MFMA_RESULTS()
-            masked = PK_CODE(nxt_i) != 2;
+            masked = (nxt_i & 0x100) != 0;
             if (masked) mask(s0, 0, nxt_s, nxt_i);
 #pragma unroll
             for (int c = 0; c < NC; ++c) first_reference(s0[c], sc, m_ref[c]);
@@ -703,14 +718,14 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
             PK_TURN_END()
         }
         for (; t < u.n_active - 1;) {
-            int ek_s, ek_i, ev_s, ev_i;
+            int ek_s, ek_i;
             RowOffset ek_off, ev_off;
             if (masked) mask(s1, 1, cur_s, cur_i);
             PK_PART(0, s0, s1, h1, p0, if constexpr (c == NC / 2) { PK_COPY_ISSUE(m) } if constexpr (c == NC - 1) { PK_COPY_NEXT(m) })
             PK_SOFTMAX_CHECK(s1, h1)
             PK_PACK_P(p1, h1)
             // (a tile that this wave could skip inside its active range is computed as a masked one)
-            masked = PK_CODE(nxt_i) != 2;
+            masked = (nxt_i & 0x100) != 0;
             if (masked) mask(s0, 0, nxt_s, nxt_i);
             PK_PART(1, s1, s0, h0, p1, if constexpr (m == NM - 5 && c == NC - 1) { PK_K_ADDRESSES(k_next) }
                     PK_ADVANCE(advance_at(m, c)))
@@ -746,7 +761,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     else store_output_bf16(a, u, o, lsum);
     // The turns that are left for the other waves (the barrier at the end of the last one has nothing to wait for).
     if (any_tile && t < n_kv - 1) {
-        int ek_s, ek_i, ev_s, ev_i;
+        int ek_s, ek_i;
         RowOffset ek_off, ev_off;
         PK_ADVANCE_ALL()
         PK_TURN_END()
@@ -779,7 +794,6 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #undef PK_SKIP_TURN
 #undef PK_ADVANCE
 #undef PK_K_ADDRESSES
-#undef PK_CODE
 
 }  // namespace PK_DNS
 }  // namespace

@@ -65,10 +65,11 @@ __device__ __forceinline__ bf16x8 v_operand(const unsigned char* vs, const LaneO
 // What a workgroup works on, and this lane's share of it.
 struct WorkUnit {
     int head, kvh, n_kv, n_lead, n_active, wave, lane, n, hlf;   // this wave computes key tiles [n_lead, n_active)
-    int rows;                          // which 32 of the tile's 128 rows this wave has
+    int rows;                          // which 32 of the tile's rows this wave has
     int ks[3], info[3];                // (first key row, info) of the tile's first three key tiles (the last one repeated)
     int qrow, lo, hi;                  // this lane's query row (-1: padding) and its key range [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
+    int k_end, full;                   // keys from k_end on are not the tile's; up to `full` all of this wave's rows see them (row_shift < 2)
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
     uint32_t row_bytes32;              // the same in 32 bits
 };
@@ -77,13 +78,13 @@ struct WorkUnit {
 // Returns false for grid padding and for query tiles without key tiles.
 __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, WorkUnit& u, LaneOffsets& off, bf16x8 (&qf)[KS]) {
     // Consecutive workgroup ids go round-robin over the 8 XCDs: the workgroups of one (tile, KV head) pair
-    // (r of them, one per head) stay on one XCD and adjacent in time, so that its L2
+    // (heads_per_kv of them, each with its share of the KV head's query heads) stay on one XCD and adjacent in time, so that its L2
     // serves their K/V tiles.
     const int y = block >> 3, slot = a.by_r(y), p = slot * 8 + (block & 7);
     const int tile = a.by_hkv(p);
     if (tile >= a.n_tiles) return false;
     u.kvh = p - tile * a.Hkv;
-    const int groups = a.heads_per_kv, pair = y - slot * groups;
+    const int groups = a.heads_per_kv, group = y - slot * groups;
     // everything about the tile in one 64-byte scalar load, including the first key rows of its first
     // key tiles: the first K/V copies do not wait for the key-tile list
     typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
@@ -93,17 +94,20 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     u.kvt = a.kvtiles + 2 * static_cast<int64_t>(desc[0]);
 #pragma unroll
     for (int x = 0; x < 3; ++x) { u.ks[x] = desc[8 + x]; u.info[x] = desc[11 + x]; }
+    u.k_end = desc[14];
     const int tid = threadIdx.x;
     u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Wave w of every workgroup runs on SIMD w % 4, and the last rows of a causal tile see more key tiles than
     // the first: every other set of 256 workgroups (a set is one per compute unit) deals the rows in reverse,
     // so that the two waves of a SIMD get as much together as those of any other.
-    u.head = u.kvh * groups + pair;
-    u.rows = (block >> 8) & 1 ? 3 - u.wave : u.wave;
+    const int part = u.wave & ((1 << a.row_shift) - 1), mate = u.wave >> a.row_shift;
+    u.head = ((u.kvh * groups + group) << (2 - a.row_shift)) + mate;
+    u.rows = (block >> 8) & 1 ? (1 << a.row_shift) - 1 - part : part;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
     prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + u.n, u.qrow, u.lo, u.hi);
+    u.full = a.row_shift < 2 ? __builtin_amdgcn_readfirstlane(u.hi) : 0x7FFFFFFF;      // (the first row's; what one row sees, those behind it do)
     u.row_bytes = static_cast<int64_t>(a.Hkv) * ROWB;
     u.row_bytes32 = static_cast<uint32_t>(a.Hkv) * ROWB;
 
@@ -255,7 +259,13 @@ __device__ __forceinline__ u32x4 tile_desc(const void* src, const RowOffset off,
 #define PK_COPY_TILE(RS, DST)                                                                \
     { _Pragma("unroll") for (int q = 0; q < PIECES; ++q) PK_COPY_PIECE(RS, DST, q); }
 #define PK_WAIT_ALL_COPIES() __builtin_amdgcn_s_waitcnt(0x0F70)      /* vmcnt(0) */
-#define PK_CODE(INFO) (((INFO) >> (8 + 2 * u.rows)) & 3)          /* 0 skip, 1 masked, 2 unmasked */
+// What the loop needs of a list entry: how many keys there are to copy (none for an entry past the list) and, in bit 8, whether this
+// wave has to mask the tile.  Codes of the list: 0 skip, 1 masked, 2 unmasked.
+__device__ __forceinline__ int entry_info(const WorkUnit& u, const int ks, const int info, const int index) {
+    const int keys = index < u.n_kv ? min(info & 0xFF, u.k_end - ks) : 0;
+    const bool masked = ((info >> (8 + 2 * u.rows)) & 3) != 2 || ks + BN > u.full;
+    return keys | (masked ? 0x100 : 0);
+}
 
 // ---------------------------------------------------------------------------------------------
 // Two workgroups per CU, three with D = 64; five stages of LDS each, three for K and two for V.
@@ -577,25 +587,28 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + u.wave * RPW * SLAB_ROWB);
     // window of tile-list entries: e0 = tile j, e1 = tile j+1, e2 = tile j+2; what the loop copies in tile j is
     // K(j+2) and V(j+1)
+#pragma unroll
+    for (int x = 0; x < 3; ++x) u.info[x] = entry_info(u, u.ks[x], u.info[x], x);
     int e0s = u.ks[0], e0i = u.info[0], e1i = u.info[1], e1s = u.ks[1], e2s = u.ks[2], e2i = u.info[2];
     scalar(e0s); scalar(e0i); scalar(e1s); scalar(e1i); scalar(e2s); scalar(e2i);
     uint32_t row_bytes = u.row_bytes32;
     scalar(row_bytes);
-    auto valid_rows = [&](int info, int tile) { return tile < n_kv ? static_cast<uint32_t>(info & 0xFF) : 0u; };
+    auto keys_of = [](int info) { return static_cast<uint32_t>(info & 0xFF); };
     // prologue: K(0), K(1), V(0), from the descriptor
     {
-        const u32x4 rk0 = tile_desc(a.k, row_offset(e0s, row_bytes), valid_rows(e0i, 0), row_bytes);
+        const u32x4 rk0 = tile_desc(a.k, row_offset(e0s, row_bytes), keys_of(e0i), row_bytes);
         PK_COPY_TILE(rk0, 0)
-        const u32x4 rk1 = tile_desc(a.k, row_offset(e1s, row_bytes), valid_rows(e1i, 1), row_bytes);
+        const u32x4 rk1 = tile_desc(a.k, row_offset(e1s, row_bytes), keys_of(e1i), row_bytes);
         PK_COPY_TILE(rk1, TILE_BYTES)
-        const u32x4 rv0 = tile_desc(a.v, row_offset(e0s, row_bytes), valid_rows(e0i, 0), row_bytes);
+        const u32x4 rv0 = tile_desc(a.v, row_offset(e0s, row_bytes), keys_of(e0i), row_bytes);
         PK_COPY_TILE(rv0, 3 * TILE_BYTES)
     }
     RowOffset off2 = row_offset(e2s, row_bytes);             // of tile j+2
-    u32x4 rs_k = tile_desc(a.k, off2, valid_rows(e2i, 2), row_bytes);
-    u32x4 rs_v = tile_desc(a.v, row_offset(e1s, row_bytes), valid_rows(e1i, 1), row_bytes);
+    u32x4 rs_k = tile_desc(a.k, off2, keys_of(e2i), row_bytes);
+    u32x4 rs_v = tile_desc(a.v, row_offset(e1s, row_bytes), keys_of(e1i), row_bytes);
     PK_WAIT_ALL_COPIES();
     __syncthreads();
+    cur_i = entry_info(u, cur_s, cur_i, u.lane);
     clear_absent_rows(u, qf);
 
     bf16x8 ring[4];                                 // LDS operands of the next four MFMAs
@@ -619,16 +632,16 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #define PK_ADVANCE(I)                                                                         \
     if constexpr ((I) == 0) {                                                                  \
         e3s = __builtin_amdgcn_readlane(cur_s, (j + 3) & 63); e3i = __builtin_amdgcn_readlane(cur_i, (j + 3) & 63); \
-        rs_v = tile_desc(a.v, off2, valid_rows(e2i, j + 2), row_bytes);                    \
+        rs_v = tile_desc(a.v, off2, keys_of(e2i), row_bytes);                    \
     } else if constexpr ((I) == 1) {                                                           \
         off2 = row_offset(e3s, row_bytes);                                                             \
     } else if constexpr ((I) == 2) {                                                           \
-        rs_k = tile_desc(a.k, off2, valid_rows(e3i, j + 3), row_bytes);                    \
+        rs_k = tile_desc(a.k, off2, keys_of(e3i), row_bytes);                    \
     }
     // entry j + 3 is the first of the next 64
 #define PK_NEXT_CHUNK()                                                                       \
     if (((j + 3) & 63) == 0) {                                                                 \
-        cur_s = nxt_s; cur_i = nxt_i;                                                          \
+        cur_s = nxt_s; cur_i = entry_info(u, nxt_s, nxt_i, j + 3 + u.lane);                    \
         load_chunk(j + 3 + 64, nxt_s, nxt_i);                                                  \
     }
 #define PK_TILE_END()                                                                         \
@@ -659,7 +672,7 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     }
     for (; j < u.n_active; ++j) {
         // a tile that this wave could skip inside its active range is computed as a masked one
-        const bool masked = PK_CODE(e0i) != 2, special = masked || j == u.n_lead;
+        const bool masked = (e0i & 0x100) != 0, special = masked || j == u.n_lead;
         // (keys past the tile's valid count are foreign)
         const int visible = u.lo <= e0s ? min(u.hi - e0s, e0i & 0xFF) : 0;
         int e3s, e3i;
@@ -719,7 +732,6 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
 #undef PK_ROW_SUM
 #undef PK_K_ADDRESSES
 #undef PK_WAIT_ALL_COPIES
-#undef PK_CODE
 
 }  // namespace PK_DNS
 }  // namespace

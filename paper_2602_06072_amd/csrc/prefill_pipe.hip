@@ -66,7 +66,6 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_few64_kernel(PrefillArgs 
 int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     PrefillArgs a = args;
     a.heads_per_kv = a.Hq / a.Hkv;
-    a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv));
     a.by_hkv = FastDiv::by(static_cast<uint32_t>(a.Hkv));
     // Copying each K/V tile once for two heads halves the copies (a tile step of two four-wave workgroups on a
     // compute unit reads 256 KiB of LDS and writes 64), and the energy they take.  What it costs: nothing runs beside a workgroup's first loads
@@ -81,9 +80,10 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     // only one does:
     //   8 x 4096  575 / 627 us;  16 x 2048  326 / 363 us;  32 x 512 behind 8192 with 64 heads  2205 / 2342 us
     //   1 x 1024 behind 8192  123 / 149 us;  1 x 4096 behind 8192  363 / 348 us;  2 x 3000 behind 3000 with 16 heads  187 / 164 us
-    const int64_t alone = static_cast<int64_t>(a.n_tiles) * a.Hq;             // workgroups with one head each
-    const bool two = !a.light && a.d == 128 && a.heads_per_kv % 2 == 0 && alone >= 512 && a.n_key_tiles >= 32 * static_cast<int64_t>(a.n_tiles);
-    if (two) { a.heads_per_kv /= 2; a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv)); }
+    const int mates = (a.eight ? 8 : 4) >> a.row_shift;     // heads of a workgroup
+    if (a.heads_per_kv % mates != 0) return static_cast<int>(hipErrorInvalidValue);
+    a.heads_per_kv /= mates;
+    a.by_r = FastDiv::by(static_cast<uint32_t>(a.heads_per_kv));
     const int64_t pairs = static_cast<int64_t>(a.n_tiles) * a.Hkv;
     const int64_t grid = (pairs + 7) / 8 * 8 * a.heads_per_kv;
     if (grid == 0) return 0;
@@ -94,7 +94,7 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     else if (a.light && a.d == 64)
         hipLaunchKernelGGL(prefill_bf16_few64_kernel, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
                            static_cast<hipStream_t>(stream), a);
-    else if (two)
+    else if (a.eight)
         hipLaunchKernelGGL(prefill_bf16_pair_kernel, dim3(static_cast<unsigned>(grid)), dim3(512), 0,
                            static_cast<hipStream_t>(stream), a);
     else if (a.d == 128)

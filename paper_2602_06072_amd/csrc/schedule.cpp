@@ -6,7 +6,9 @@
 // and may span requests; a tile lists only the key tiles that hold at least
 // one unmasked pair for it, and each key tile says per wave (32 query rows)
 // whether that wave skips it, computes it with the mask, or computes it
-// without any mask.
+// without any mask.  With an even number of query heads per KV head the rows
+// of several heads of one request are packed into a workgroup instead
+// (emit_head_tiles).
 #include <algorithm>
 #include <cmath>
 #include <numeric>
@@ -393,8 +395,8 @@ void add_idle_tile(SchedBuild& sb) {               // padded grid slot of a requ
     sb.n_kv.push_back(0); sb.n_rows.push_back(0); sb.weight.push_back(0);
 }
 
-// Writes the tiles in the given order (key-tile lists are re-based accordingly).
-// Which of the two bodies a prefill launch takes, one head per workgroup: prefill_few_body.hip.h (true) or prefill_body.hip.h.
+// Which of the two bodies a prefill launch takes: prefill_few_body.hip.h (true) or prefill_body.hip.h; tiles: query tiles of 128 rows that
+// have key tiles, whatever tiles the launch has.
 // The pipeline of the latter costs a first and a last turn of every workgroup and more issued instructions, and saves energy:
 // it is the faster one where power holds the clock down, in launches of some 200 us and more, and where a wave has a long list
 // to go through.  So the line is drawn by the total of key tiles times the length of a list, per compute unit.  us, pipeline / other body:
@@ -413,7 +415,7 @@ void add_idle_tile(SchedBuild& sb) {               // padded grid slot of a requ
 // 115.1 / 106.5, 1 x 64 behind 8000 with 8 heads (8) 124.5 / 114.0 and 94.0 / 91.8.
 // The prefill half of a mixed step follows the same line, so that its results are those of the prefill call bit for bit (64 x 200 with 32
 // heads and 32 decode rows of 500 tokens 87.2 / 81.8, 8 x 1024 and 256 of 700 178 / 173; d = 64 98.7 / 94.5).
-bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) {   // tiles: query tiles that have key tiles
+bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) {
     if (tiles == 0) return true;
     const int64_t wgs = tiles * Hq;
     if (d == 64 ? 2 * wgs < 3 * num_cus : wgs < num_cus) return true;
@@ -422,8 +424,13 @@ bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) 
     return static_cast<double>(wgs) * list * list < (d == 64 ? 3500.0 : 2000.0) * num_cus;
 }
 
-void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, const DeviceTables& t, Builder& b,
-                DeviceTables::PrefillSched& s) {
+// The eight-wave kernel (twice the heads per workgroup) for such a launch: prefill_pipe.hip has both sides' figures (tiles as above).
+bool eight_waves(int64_t tiles, int64_t key_tiles, int Hq, int Hkv, int d) {
+    return d == 128 && Hq / Hkv % 2 == 0 && tiles * Hq >= 512 && key_tiles >= 32 * tiles;
+}
+
+// Writes the tiles in the given order (key-tile lists are re-based accordingly).
+void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, Builder& b, DeviceTables::PrefillSched& s) {
     std::vector<int32_t> desc, more_first, more, kv;
     desc.reserve(order.size() * kTileDescWords);
     more_first.reserve(order.size());
@@ -456,23 +463,87 @@ void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, const D
         for (int x = 1; x < 4; ++x) desc.push_back(nr > 0 ? run[x] : 0);
         // words 8..10 and 11..13: first key rows and infos of the tile's first three key tiles (the last one
         // repeated if there are fewer), so that the kernel can request its first K/V tiles without waiting
-        // for a look-up in the key-tile list; the rest pads the descriptor to 64 bytes
+        // for a look-up in the key-tile list
         for (int word = 0; word < 2; ++word)
             for (int e = 0; e < 3; ++e) {
                 const int32_t ee = std::min(e, sb.n_kv[idx] - 1);
                 desc.push_back(ee >= 0 ? sb.kv[2 * (static_cast<size_t>(sb.kv_first[idx]) + ee) + word] : 0);
             }
-        for (int x = 14; x < kTileDescWords; ++x) desc.push_back(0);
+        desc.push_back(INT32_MAX); desc.push_back(0);
         more_first.push_back(static_cast<int32_t>(more.size() / 4));
         if (nr > 1) more.insert(more.end(), run + 4, run + 4 * static_cast<size_t>(nr));
         kv.insert(kv.end(), sb.kv.begin() + 2 * sb.kv_first[idx], sb.kv.begin() + 2 * (sb.kv_first[idx] + sb.n_kv[idx]));
     }
-    s.n_tiles = static_cast<int32_t>(order.size());
+    s.n_tiles = s.n_query_tiles = static_cast<int32_t>(order.size());
     s.issued_pairs = sb.issued;
-    const int64_t idle = std::count(sb.n_kv.begin(), sb.n_kv.end(), 0);
-    s.light = light_launch(s.n_tiles - idle, static_cast<int64_t>(kv.size() / 2), t.Hq, t.d, t.num_cus);
     s.tiles = b.add(desc);
     s.run_first = b.add(more_first); s.runs = b.add(more);
+    s.kvtiles = b.add(kv);
+}
+
+// Query tiles of one request each and of 32 or 64 rows: the waves of a workgroup take its rows for several heads of a KV head (four waves: four
+// heads or two), all on the same K/V tiles.  With 128 rows and one head a workgroup goes through the key tiles of all its rows while those of most
+// waves are but a part of them: waves 0 and 1 do not see the last key tile of a causal tile, and where a tile holds several requests
+// one wave or two work at a time.  (Rounds of a workgroup through a key tile, 128 rows / this: 64 ragged prompts 87000 / 77600, 44 chunks of
+// 42 rows behind 320 with 64/8 heads 17700 / 7500, chunks of 512..2048 behind up to 16384 3.10 / 2.97 million.)  us, 128 rows / this:
+//   64 ragged prompts, 32/8 heads 372.7 / 347.7;  44 x 42 behind 320, 64/8 66.5 / 44.7;  128 x 30, 32/8 28.5 / 18.6;  3 x 700 behind 600 51.2 / 42.6;
+//   64 x 200, 64/8 153.8 / 131.9;  32 chunks of a 70B-shaped layer 10.61 / 10.33 ms;  8 x 2048, 64/8 544 / 537;  d = 64, 32/8:
+//   256 x 64 behind 100 61.5 / 45.8;  64 x 200 39.7 / 34.3;  8 x 2048 159.0 / 159.1;  64 rows and two heads: 64 x 60, 16/8 12.3 / 10.2,
+//   8 x 2048, 12/2 132 / 124, 40 x 200 behind 100 (a last tile of 8 rows) 16/8 34.0 / 34.9, 12/2 26.5 / 28.2.
+// The key tiles of a request are a list that its query tiles share (a tile sees the first n of them and the keys up to `k_end`).
+void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, const std::vector<int64_t>& kv_start, int row_shift,
+                     Builder& b, DeviceTables::PrefillSched& s) {
+    constexpr int BN = kPrefillBN;
+    const int32_t rows = 32 << row_shift;
+    auto tiles_to = [](int64_t keys) { return static_cast<int32_t>((keys + BN - 1) / BN); };
+    std::vector<int32_t> requests;
+    for (const Group& g : plan.groups)
+        for (const Member& m : g.members) requests.push_back(m.req);
+    std::stable_sort(requests.begin(), requests.end(), [&](int32_t x, int32_t y) {
+        const int32_t nx = tiles_to(plan.kv_lens[x]), ny = tiles_to(plan.kv_lens[y]);
+        return nx != ny ? nx > ny : x < y;
+    });
+    struct Tile { int32_t req, t0, n, n_kv, list; };   // rows [t0, t0 + n) of request req
+    std::vector<Tile> tiles;
+    std::vector<int32_t> kv;
+    int64_t n_tiles = 0, n_entries = 0;
+    for (int32_t rq : requests) { n_tiles += (plan.q_lens[rq] + rows - 1) / rows; n_entries += tiles_to(plan.kv_lens[rq]); }
+    tiles.reserve(static_cast<size_t>(n_tiles));
+    kv.reserve(static_cast<size_t>(n_entries) * 2);
+    for (int32_t rq : requests) {
+        const int64_t ctx = plan.kv_lens[rq] - plan.q_lens[rq];
+        const int32_t list = static_cast<int32_t>(kv.size() / 2);
+        for (int64_t x = 0; x < plan.kv_lens[rq]; x += BN) {
+            kv.push_back(static_cast<int32_t>(kv_start[rq] + x));
+            kv.push_back(static_cast<int32_t>(std::min<int64_t>(BN, plan.kv_lens[rq] - x)) | 0xAA << 8);
+        }
+        for (int32_t tile = (plan.q_lens[rq] + rows - 1) / rows - 1; tile >= 0; --tile) {
+            const int32_t t0 = tile * rows, n = std::min(rows, plan.q_lens[rq] - t0);
+            tiles.push_back({rq, t0, n, tiles_to(ctx + t0 + n), list});
+        }
+    }
+    std::vector<int32_t> desc;
+    desc.reserve(tiles.size() * kTileDescWords);
+    int64_t weight = 0;
+    for (const Tile& x : tiles) {
+        const int64_t ctx = plan.kv_lens[x.req] - plan.q_lens[x.req], ks0 = kv_start[x.req];
+        int32_t trailing = 0;
+        for (int w = 0; w < 4; ++w) {
+            const int32_t own = 32 * w < x.n ? tiles_to(ctx + x.t0 + std::min(x.n, 32 * (w + 1))) : 0;
+            trailing |= std::min(x.n_kv - own, 255) << (8 * w);
+            weight += own;
+        }
+        const int32_t entry[8] = {x.list, x.n_kv, 0, trailing, x.n | 1 << 16, static_cast<int32_t>(q_start[x.req] + x.t0),
+                                  static_cast<int32_t>(ks0), static_cast<int32_t>(ks0 + ctx + x.t0 + 1)};
+        desc.insert(desc.end(), entry, entry + 8);
+        for (int word = 0; word < 2; ++word)
+            for (int e = 0; e < 3; ++e) desc.push_back(kv[2 * (static_cast<size_t>(x.list) + std::min(e, x.n_kv - 1)) + word]);
+        desc.push_back(static_cast<int32_t>(ks0 + ctx + x.t0 + x.n)); desc.push_back(0);
+    }
+    s.row_shift = row_shift;
+    s.n_tiles = static_cast<int32_t>(n_tiles);
+    s.issued_pairs = weight * 32 * BN;
+    s.tiles = b.add(desc);
     s.kvtiles = b.add(kv);
 }
 
@@ -486,14 +557,11 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     int64_t aligned_tiles = 0;
     for (int32_t i = 0; i < plan.n; ++i) aligned_tiles += (plan.q_lens[i] + BM - 1) / BM;
     const bool may_share = aligned_tiles * Hq > 2 * static_cast<int64_t>(num_cus);
-    SchedBuild sb;
-    std::vector<RowRun> runs;                      // of the tile that is open
-    int32_t filled = 0;                            // its rows
-    std::vector<int32_t> tile_req;                 // request of a tile's first row
+    std::vector<RowRun> runs;                      // of all tiles
+    std::vector<size_t> tile_end;                  // where each tile's end
+    int32_t filled = 0;                            // rows of the tile that is open
     auto close_tile = [&] {
-        tile_req.push_back(runs[0].req);
-        add_tile(plan, q_start, kv_start, runs, false, sb);
-        runs.clear();
+        tile_end.push_back(runs.size());
         filled = 0;
     };
     for (const Group& g : plan.groups) {
@@ -518,15 +586,35 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         }
         if (filled > 0) close_tile();
     }
+    // what the choice of the kernel goes by
+    const int64_t n_tiles = static_cast<int64_t>(tile_end.size());
+    int64_t key_tiles = 0;
+    for (const RowRun& run : runs)
+        key_tiles += (plan.kv_lens[run.req] - plan.q_lens[run.req] + run.t + run.count + kPrefillBN - 1) / kPrefillBN;
+    DeviceTables::PrefillSched& s = t.packed;
+    s.light = light_launch(n_tiles, key_tiles, Hq, t.d, num_cus);
+    s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d);
+    const int r = Hq / t.Hkv, waves = s.eight ? 8 : 4;
+    if (!plan.decode_only && t.dtype == PK_BF16 && (r % waves == 0 || r % (waves / 2) == 0)) {
+        emit_head_tiles(plan, q_start, kv_start, r % waves == 0 ? 0 : 1, b, s);
+        s.n_query_tiles = static_cast<int32_t>(n_tiles);
+        return;
+    }
+    SchedBuild sb;
+    std::vector<int32_t> tile_req;                 // request of a tile's first row
+    for (size_t x = 0, run = 0; x < tile_end.size(); run = tile_end[x++]) {
+        tile_req.push_back(runs[run].req);
+        add_tile(plan, q_start, kv_start, std::vector<RowRun>(runs.begin() + run, runs.begin() + tile_end[x]), false, sb);
+    }
     std::vector<int32_t> order(sb.n_kv.size());
     std::iota(order.begin(), order.end(), 0);
+    std::vector<int64_t> req_weight(static_cast<size_t>(plan.n), 0);
+    for (size_t x = 0; x < tile_req.size(); ++x)
+        req_weight[static_cast<size_t>(tile_req[x])] = std::max(req_weight[static_cast<size_t>(tile_req[x])], sb.weight[x]);
     // Launch order: request by request (the request whose heaviest tile is heaviest first), and
     // inside a request the heaviest tile first.  Workgroups that run at the same time on one XCD
     // then stream the same K/V rows, which keeps them in that XCD's L2; the many short tiles at
     // the end of the list even out the tail.
-    std::vector<int64_t> req_weight(static_cast<size_t>(plan.n), 0);
-    for (size_t x = 0; x < tile_req.size(); ++x)
-        req_weight[static_cast<size_t>(tile_req[x])] = std::max(req_weight[static_cast<size_t>(tile_req[x])], sb.weight[x]);
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
         const int32_t rx = tile_req[static_cast<size_t>(x)], ry = tile_req[static_cast<size_t>(y)];
         if (rx != ry) {
@@ -536,7 +624,7 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         }
         return sb.weight[x] > sb.weight[y];
     });
-    emit_sched(sb, order, t, b, t.packed);
+    emit_sched(sb, order, b, s);
 }
 
 }  // namespace
@@ -564,7 +652,10 @@ void build_prefill_padded(const pk_plan& plan, DeviceTables& t) {
     std::iota(order.begin(), order.end(), 0);
     t.host_padded.clear();
     Builder b(t.host_padded);
-    emit_sched(sb, order, t, b, t.padded);
+    emit_sched(sb, order, b, t.padded);
+    const int64_t key_tiles = std::accumulate(sb.n_kv.begin(), sb.n_kv.end(), int64_t{0});
+    t.padded.light = light_launch(t.padded.n_tiles - std::count(sb.n_kv.begin(), sb.n_kv.end(), 0), key_tiles, t.Hq, t.d, t.num_cus);
+    t.padded.eight = !t.padded.light && eight_waves(t.padded.n_tiles, key_tiles, t.Hq, t.Hkv, t.d);
     t.host_padded.resize((t.host_padded.size() + 63) / 64 * 64, 0);
     t.padded_built = true;
 }

@@ -1,0 +1,77 @@
+"""Query tiles of 32 or 64 rows whose workgroups take several heads of a KV head (even numbers of heads per KV head), and tiles of 128
+rows and one head, of one request or of several (odd numbers), against the padded schedule, which has 128 rows, one head and one request to a tile
+whatever the heads: a row's arithmetic does not depend on its tile, so the results are the same bits.  Rows and contexts around the edges of
+tiles, lists around 64 and 128 entries (they are read 64 at a time), both bodies, four and eight waves, both outputs."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_06072_amd import binding as pk
+from paper_2602_06072_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+EDGES = [1, 2, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 257]
+
+
+def compare(ql, ctx, Hq, Hkv, d, what, light, out=torch.bfloat16):
+    ql = np.asarray(ql, dtype=np.int32)
+    kv = ql + np.asarray(ctx, dtype=np.int32)
+    w = wl.make_ragged(what, kv, ql, Hq, Hkv, d, 1 << 14, 77, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=1 << 14)
+    ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
+    got = torch.full(w.q.shape, float("nan"), dtype=out, device=DEV)
+    want = torch.full(w.q.shape, float("nan"), dtype=out, device=DEV)
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, got, w.scale, ws)
+    pk.padded_prefill_attn(plan, w.q, w.k, w.v, want, w.scale, ws)
+    torch.cuda.synchronize()
+    assert light is None or plan.stat(8) == light, what
+    assert torch.isfinite(want).all() and torch.equal(got, want), what
+    return plan
+
+
+# heads per KV head: 1, 2, 3, 4, 5, 6, 8, 12, 16
+@pytest.mark.parametrize("Hq, Hkv", [(2, 2), (4, 2), (3, 1), (8, 2), (5, 1), (6, 1), (16, 2), (12, 1), (16, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_edges_in_launches_of_little_work(d, Hq, Hkv):
+    rng = np.random.default_rng(Hq)
+    ctx = rng.permutation([0, 0, 1, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 500])
+    compare(EDGES, ctx, Hq, Hkv, d, f"edges {Hq}/{Hkv} d {d}", 1)
+    # many requests of few rows: the tiles of 128 rows hold several
+    ql = rng.integers(1, 70, 200)
+    plan = compare(ql, rng.integers(0, 200, 200), Hq, Hkv, d, f"short ones {Hq}/{Hkv} d {d}", 1, torch.float32)
+    assert Hq < 5 or plan.stat(6) < 200
+
+
+@pytest.mark.parametrize("Hq, Hkv", [(16, 16), (16, 8), (24, 8), (32, 8), (30, 5), (64, 8), (48, 4), (64, 4)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_edges_in_launches_of_much_work(d, Hq, Hkv):
+    ctx = [0, 63, 64, 65, 4000, 4031, 4032, 4033, 4095, 8063, 8064, 8130, 8191, 8256]
+    reps = 2 if Hq >= 32 else 3
+    compare(EDGES * reps, ctx * reps, Hq, Hkv, d, f"long lists {Hq}/{Hkv} d {d}", 0, torch.float32 if Hq == 32 else torch.bfloat16)
+
+
+# 512 workgroups and lists of 32 tiles: eight waves, for 2 x 128, 4 x 64 or 8 x 32 rows and heads
+@pytest.mark.parametrize("Hq, Hkv", [(32, 16), (32, 8), (48, 8), (64, 8)])
+def test_edges_with_eight_waves(Hq, Hkv):
+    ql = EDGES + [128] * 6
+    ctx = [2048 + 64 * n + n % 3 for n in range(len(ql))]
+    plan = compare(ql, ctx, Hq, Hkv, 128, f"eight waves {Hq}/{Hkv}", 0)
+    assert plan.stat(6) * Hq >= 512 and plan.stat(1) >= 32 * 64 * 128 * plan.stat(6) // 2
+
+
+@pytest.mark.parametrize("Hq, Hkv, d", [(8, 2, 128), (8, 2, 64), (4, 2, 128), (3, 1, 64)])
+def test_tuned_pipeline_and_back(Hq, Hkv, d):
+    """The register-staged kernel works on the same tables: the pipeline may change between two calls on a bound plan."""
+    ql, kv = np.asarray([40, 300, 7, 64], np.int32), np.asarray([400, 300, 9, 129], np.int32)
+    w = wl.make_ragged("tuned", kv, ql, Hq, Hkv, d, 1 << 14, 3, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(kv, ql, token_budget=1 << 14)
+    ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
+    outs = []
+    for pipeline in (0, 1, 0):
+        plan.tune(pk.TUNE_PREFILL_PIPELINE, pipeline)
+        outs.append(torch.full_like(w.q, float("nan")))
+        pk.packed_prefill_attn(plan, w.q, w.k, w.v, outs[-1], w.scale, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[2])
+    assert (outs[0].float() - outs[1].float()).abs().max() <= 4e-2      # (each within 2e-2 of the reference)
