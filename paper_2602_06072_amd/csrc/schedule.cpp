@@ -408,8 +408,8 @@ void add_idle_tile(SchedBuild& sb) {               // padded grid slot of a requ
 //   heads 81.2 / 77.6, 32 x 1024 and 16 heads 105.2 / 101.9; 17 tiles: 24 x 128 behind 1000 and 32 heads 38.3 / 37.9, 64 x 128
 //   93.4 / 90.5, 8 x 2048 (70000) 1 % the other way at 64 heads; 33 tiles: 14 x 128 behind 2000 43.9 / 43.2, 16 x 128 46.3 / 46.1.
 // Over 680 such shapes the choice is within 4 % of the better one, but for prompts of exactly 32 rows, four to a tile (64 x 32
-// 15.1 / 15.7 us, d = 64 17.2 / 18.4), whose waves skip three of the four key tiles in the list, and for 513 to 768 workgroups of more than
-// 32 tiles, of which the eight-wave kernel makes a round and a half (24 x 128 behind 2000 and 32 heads 124 / 106).
+// 15.1 / 15.7 us, d = 64 17.2 / 18.4), whose waves skip three of the four key tiles in the list.  (With query tiles of several heads, 170
+// shapes: 0.9 % more than the better one on average, 5 % at most but for three; the best line there would take 0.6 %.)
 // Below one workgroup per unit (with d = 64 one and a half: three share a unit) the other body is the better one with any list: 7 x 57 rows
 // behind 2500 tokens with 32 heads (224 workgroups) 43.9 / 40.4 and 33.1 / 32.4, 1 x 512 behind 8192 (128) 142.4 / 134.3 and
 // 115.1 / 106.5, 1 x 64 behind 8000 with 8 heads (8) 124.5 / 114.0 and 94.0 / 91.8.
@@ -424,9 +424,40 @@ bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) 
     return static_cast<double>(wgs) * list * list < (d == 64 ? 3500.0 : 2000.0) * num_cus;
 }
 
-// The eight-wave kernel (twice the heads per workgroup) for such a launch: prefill_pipe.hip has both sides' figures (tiles as above).
+// Rows of a query tile (32 << shift) where `waves` waves of a workgroup may take them for several of the r heads of a KV head (emit_head_tiles).
+int head_tile_shift(int r, int waves) { return r % waves == 0 ? 0 : r % (waves / 2) == 0 ? 1 : 2; }
+
+// The eight-wave kernel (twice the heads per workgroup) may be taken for such a launch: prefill_pipe.hip has both sides' figures (tiles as above).
 bool eight_waves(int64_t tiles, int64_t key_tiles, int Hq, int Hkv, int d) {
     return d == 128 && Hq / Hkv % 2 == 0 && tiles * Hq >= 512 && key_tiles >= 32 * tiles;
+}
+
+// Whether it is ahead on query tiles of several heads.  It runs in rounds of a workgroup per compute unit, with a first and a last turn that nothing covers
+// (6 below, in halves of a key tile), and takes 3.5 % less for a key tile; of the four-wave workgroups two share a unit, one that is alone takes 0.7 of
+// the time, and with fewer than eight heads to a KV head (four, two) their tiles have half the rows.  So what counts are the rounds and how long
+// lists are.  Eight / four waves, us:
+//   64/8 heads: 1 x 4096 behind 8192 1083 / 1119, 16 x 2048 behind 8000 0.979 of the time, 32 chunks behind up to 16384 (140 key tiles on average) 0.992, 8 x 4096
+//   2023 / 1967, 32 x 1024 behind 2048 2436 / 2408, 4 x 300 behind 6000 (320 workgroups / 640) 295 / 255;
+//   32/8: 2 x 1024 behind 8192 (256 / 512) 240 / 251, 16 chunks 2860 / 2798, 4 x 8192 1886 / 1860;  48/8: 4 x 300 behind 6000 (288 / 480) 295 / 175;
+//   16/2: 2 x 1024 behind 8192 (128 / 256) 201 / 155, 1 x 4096 behind 8192 305 / 297.
+// Over 120 launches of more than 32 key tiles a list this choice takes 0.4 % more than the faster one of the two, 6 % at worst (16 x 256 behind 4000, 16/8); four
+// waves everywhere 0.7 %, eight everywhere 3 %, and up to 70 %.
+bool ahead_with_eight(const pk_plan& plan, int64_t tiles, int64_t key_tiles, int Hq, int Hkv, int num_cus) {
+    const int r = Hq / Hkv;
+    auto workgroups = [&](int waves) {
+        const int shift = head_tile_shift(r, waves);
+        int64_t n = 0;
+        for (const int32_t q : plan.q_lens) n += (q + (32 << shift) - 1) >> (5 + shift);
+        return n * Hkv * ((r << shift) / waves);
+    };
+    const int64_t four = workgroups(4), eight = workgroups(8), slots = 2 * num_cus, rest = four % slots;
+    const double list = static_cast<double>(key_tiles) / static_cast<double>(tiles);
+    double rounds4 = static_cast<double>(four) / num_cus, rounds8 = static_cast<double>(eight) / num_cus;
+    if (four <= 16 * slots) {                      // (more rounds than that run into one another)
+        rounds4 = 2.0 * static_cast<double>(four / slots) + (rest == 0 ? 0.0 : rest <= num_cus ? 1.4 : 2.0);
+        rounds8 = std::ceil(rounds8);
+    }
+    return rounds8 * (1.93 * list + 6) < 0.985 * rounds4 * (list + 0.5);
 }
 
 // Writes the tiles in the given order (key-tile lists are re-based accordingly).
@@ -607,10 +638,10 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         key_tiles += (plan.kv_lens[run.req] - plan.q_lens[run.req] + run.t + run.count + kPrefillBN - 1) / kPrefillBN;
     DeviceTables::PrefillSched& s = t.packed;
     s.light = light_launch(n_tiles, key_tiles, Hq, t.d, num_cus);
-    s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d);
-    const int r = Hq / t.Hkv, waves = s.eight ? 8 : 4;
-    if (!plan.decode_only && t.dtype == PK_BF16 && (r % waves == 0 || r % (waves / 2) == 0)) {
-        emit_head_tiles(plan, q_start, kv_start, r % waves == 0 ? 0 : 1, b, s);
+    s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d) && ahead_with_eight(plan, n_tiles, key_tiles, Hq, t.Hkv, num_cus);
+    const int row_shift = head_tile_shift(Hq / t.Hkv, s.eight ? 8 : 4);
+    if (!plan.decode_only && t.dtype == PK_BF16 && row_shift < 2) {
+        emit_head_tiles(plan, q_start, kv_start, row_shift, b, s);
         s.n_query_tiles = static_cast<int32_t>(n_tiles);
         return;
     }

@@ -8,6 +8,7 @@ import torch
 
 from paper_2602_06072_amd import binding as pk
 from paper_2602_06072_amd import workloads as wl
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -58,6 +59,32 @@ def test_edges_with_eight_waves(Hq, Hkv):
     ctx = [2048 + 64 * n + n % 3 for n in range(len(ql))]
     plan = compare(ql, ctx, Hq, Hkv, 128, f"eight waves {Hq}/{Hkv}", 0)
     assert plan.stat(6) * Hq >= 512 and plan.stat(1) >= 32 * 64 * 128 * plan.stat(6) // 2
+
+
+# Rounds of eight-wave workgroups that are full, and lists of some 190 key tiles: 256 (2 x 240 with six heads per KV head) such
+# workgroups, 512 of four waves, of which two share a compute unit.  The mixed step works on the same tables with four waves.
+@pytest.mark.parametrize("Hq, Hkv, n", [(64, 8, 8), (32, 8, 16), (32, 16, 16), (48, 8, 20)])
+def test_long_lists_with_eight_waves(Hq, Hkv, n):
+    ql = ([128, 127, 97, 113, 128, 98, 126, 100] * 3)[:n]
+    ctx = [12000 + 64 * (x % 5) + x % 3 for x in range(n)]
+    compare(ql, ctx, Hq, Hkv, 128, f"eight waves, long lists {Hq}/{Hkv}", 0, torch.float32 if n == 8 else torch.bfloat16)
+    w = wl.make_ragged("long lists", np.asarray(ql, np.int32) + np.asarray(ctx, np.int32), np.asarray(ql, np.int32), Hq, Hkv, 128, 1 << 14, 78, device=DEV,
+                       keep_f32=False)
+    d = wl.small_paged(seed=79, n=3, lo=1, hi=100, Hq=Hq, Hkv=Hkv, d=128, token_budget=500, device=DEV, keep_f32=False)
+    plan, plan_d = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=1 << 14), pk.pack_plan(d.kv_lens, np.ones_like(d.kv_lens), None, None, 500)
+    ws, ws_d = pk.new_workspace(plan, Hq, Hkv, 128, pk.PK_BF16), pk.new_workspace(plan_d, Hq, Hkv, 128, pk.PK_BF16)
+    buf = pk.new_kv_buf(plan_d, Hkv, 128, pk.PK_BF16)
+    pk.kv_reorganize(plan_d, d.k_pages, d.v_pages, torch.from_numpy(d.block_table).to(DEV), buf, ws_d)
+    alone, fused = torch.full_like(w.q, float("nan")), torch.full_like(w.q, float("nan"))
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, alone, w.scale, ws)
+    pk.packed_mixed_step(plan, w.q, w.k, w.v, fused, ws, plan_d, d.q, buf, torch.empty_like(d.q), ws_d, w.scale)
+    torch.cuda.synchronize()
+    assert torch.isfinite(alone.float()).all() and torch.equal(alone, fused)
+    rng = np.random.default_rng(80)
+    req = rng.integers(0, n, size=100)
+    rows = np.stack([req, rng.integers(0, Hq, size=100), rng.integers(0, w.q_lens[req])], axis=1).astype(np.int32)
+    at = (np.concatenate([[0], np.cumsum(ql)])[rows[:, 0]] + rows[:, 2], rows[:, 1])
+    H.assert_close(alone.float().cpu().numpy()[at], H.oracle_ragged(w, False, rows=rows), 0, f"eight waves, long lists {Hq}/{Hkv}")
 
 
 @pytest.mark.parametrize("Hq, Hkv, d", [(8, 2, 128), (8, 2, 64), (4, 2, 128), (3, 1, 64)])
