@@ -524,6 +524,24 @@ int halvings(int64_t list, int64_t longest) {
     return h;
 }
 
+// With fewer than eight KV heads (one, two or four) neighbours in the launch order go to eight, four or two XCDs, and each reads the K/V rows of their request into its own
+// L2.  So that four of them stay together, sets of four in a row are dealt over those XCDs, in one order and in the reverse one in turns: the tiles of a
+// request come heaviest first, and with a fixed order the same XCD would get the heavier ones every time (8 x 4096 with 8/1 heads 244 -> 259 us).
+// us before / now, 16 x 1024: 16/2 87.0 / 81.9, 8/1 46.8 / 42.6, 16/4 85.2 / 83.1, d = 64 16/2 48.4 / 45.6;  64 x 200 16/4 38.4 / 35.4, 16/2 35.2 / 33.3;  128 x 256 behind 7000 4/1
+// 532 / 433, 8/1 855 / 818, 32/2 3220 / 3170;  8 x 4096 4/1 138 / 126, 8/1 253 / 241;  16 x 256 behind 4000 8/1 77.4 / 74.8;  16 chunks behind up to 16384 the same.  Over
+// 96 shapes with one to four KV heads 1.7 % on average (sets of 2, 8 and 16: 1.2, 1.7, 1.2 %), 2.2 % slower at worst (64 ragged prompts 16/2 179.7 / 183.6).
+template <class Tile>
+void deal_over_xcds(std::vector<Tile>& tiles, int Hkv) {
+    if (Hkv >= 8 || 8 % Hkv != 0) return;
+    const size_t xcds = static_cast<size_t>(8 / Hkv), run = 4, block = xcds * run;
+    const std::vector<Tile> from(tiles);
+    for (size_t b0 = 0; b0 + block <= tiles.size(); b0 += block)
+        for (size_t x = 0; x < block; ++x) {
+            const size_t set = b0 / block % 2 == 0 ? x % xcds : xcds - 1 - x % xcds;
+            tiles[b0 + x] = from[b0 + set * run + x / xcds];
+        }
+}
+
 // Query tiles of one request each and of 32 or 64 rows: the waves of a workgroup take its rows for several heads of a KV head (four waves: four
 // heads or two), all on the same K/V tiles.  With 128 rows and one head a workgroup goes through the key tiles of all its rows while those of most
 // waves are but a part of them: waves 0 and 1 do not see the last key tile of a causal tile, and where a tile holds several requests
@@ -534,7 +552,7 @@ int halvings(int64_t list, int64_t longest) {
 //   256 x 64 behind 100 61.5 / 45.8;  64 x 200 39.7 / 34.3;  8 x 2048 159.0 / 159.1;  64 rows and two heads: 64 x 60, 16/8 12.3 / 10.2,
 //   8 x 2048, 12/2 132 / 124, 40 x 200 behind 100 (a last tile of 8 rows) 16/8 34.0 / 34.9, 12/2 26.5 / 28.2.
 // The key tiles of a request are a list that its query tiles share (a tile sees the first n of them and the keys up to `k_end`).
-void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, const std::vector<int64_t>& kv_start, int row_shift,
+void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, const std::vector<int64_t>& kv_start, int Hkv, int row_shift,
                      Builder& b, DeviceTables::PrefillSched& s) {
     constexpr int BN = kPrefillBN;
     const int32_t rows = 32 << row_shift;
@@ -567,6 +585,7 @@ void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, c
     }
     const int32_t longest = tiles.empty() ? 0 : tiles_to(plan.kv_lens[requests[0]]);
     std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile& x, const Tile& y) { return halvings(x.n_kv, longest) < halvings(y.n_kv, longest); });
+    deal_over_xcds(tiles, Hkv);
     std::vector<int32_t> desc;
     desc.reserve(tiles.size() * kTileDescWords);
     int64_t weight = 0;
@@ -641,7 +660,7 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d) && ahead_with_eight(plan, n_tiles, key_tiles, Hq, t.Hkv, num_cus);
     const int row_shift = head_tile_shift(Hq / t.Hkv, s.eight ? 8 : 4);
     if (!plan.decode_only && t.dtype == PK_BF16 && row_shift < 2) {
-        emit_head_tiles(plan, q_start, kv_start, row_shift, b, s);
+        emit_head_tiles(plan, q_start, kv_start, t.Hkv, row_shift, b, s);
         s.n_query_tiles = static_cast<int32_t>(n_tiles);
         return;
     }
