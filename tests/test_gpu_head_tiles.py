@@ -44,6 +44,15 @@ def test_edges_in_launches_of_little_work(d, Hq, Hkv):
     assert Hq < 5 or plan.stat(6) < 200
 
 
+# the same rows, more or fewer of them than a tile of 128 rows and head for every compute unit: with several heads to a workgroup, and without
+@pytest.mark.parametrize("Hq, Hkv", [(4, 2), (4, 1), (8, 2), (6, 1), (16, 2)])
+@pytest.mark.parametrize("reps", [1, 4])
+@pytest.mark.parametrize("d", [64, 128])
+def test_edges_on_both_sides_of_a_full_chip(d, reps, Hq, Hkv):
+    ctx = np.arange(len(EDGES) * reps) * 37 % 200
+    compare(EDGES * reps, ctx, Hq, Hkv, d, f"edges x {reps} {Hq}/{Hkv} d {d}", 1, torch.float32 if Hq == 6 else torch.bfloat16)
+
+
 @pytest.mark.parametrize("Hq, Hkv", [(16, 16), (16, 8), (24, 8), (32, 8), (30, 5), (64, 8), (48, 4), (64, 4)])
 @pytest.mark.parametrize("d", [64, 128])
 def test_edges_in_launches_of_much_work(d, Hq, Hkv):
