@@ -329,19 +329,26 @@ struct SchedBuild {
     std::vector<int32_t> kv_first, n_kv, n_rows;  // per tile
     std::vector<int64_t> weight;                  // active (wave, key tile) pairs per tile
     int64_t issued = 0;
+    void reserve(size_t tiles, size_t n, size_t key_tiles) {
+        runs.reserve(4 * n);
+        kv.reserve(2 * key_tiles);
+        for (std::vector<int32_t>* v : {&run_first, &n_runs, &kv_first, &n_kv, &n_rows}) v->reserve(tiles);
+        weight.reserve(tiles);
+    }
 };
 
 // Appends one query tile (the runs cover rows 0..nrows) and its key-tile list.  all_waves: the padded
 // schedule never lets a wave skip.
 void add_tile(const pk_plan& plan, const std::vector<int64_t>& q_start,
-              const std::vector<int64_t>& kv_start, const std::vector<RowRun>& tile_runs,
+              const std::vector<int64_t>& kv_start, const RowRun* tile_runs, const RowRun* tile_runs_end,
               bool all_waves, SchedBuild& sb) {
     constexpr int BM = kPrefillBM, BN = kPrefillBN, WR = 32, NW = BM / WR;
     sb.run_first.push_back(static_cast<int32_t>(sb.runs.size() / 4));
     const size_t kv0 = sb.kv.size();
-    const int nrows = tile_runs.back().begin + tile_runs.back().count;
+    const int nrows = tile_runs_end[-1].begin + tile_runs_end[-1].count;
     int64_t weight = 0;
-    for (const RowRun& run : tile_runs) {
+    for (const RowRun* x = tile_runs; x < tile_runs_end; ++x) {
+        const RowRun& run = *x;
         const int32_t rq = run.req;
         const int i = run.begin, j = run.begin + run.count;
         const int64_t ks0 = kv_start[rq];
@@ -671,20 +678,23 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         return;
     }
     SchedBuild sb;
+    sb.reserve(tile_end.size(), runs.size(), static_cast<size_t>(key_tiles));
     std::vector<int32_t> tile_req;                 // request of a tile's first row
+    tile_req.reserve(tile_end.size());
     for (size_t x = 0, run = 0; x < tile_end.size(); run = tile_end[x++]) {
         tile_req.push_back(runs[run].req);
-        add_tile(plan, q_start, kv_start, std::vector<RowRun>(runs.begin() + run, runs.begin() + tile_end[x]), false, sb);
+        add_tile(plan, q_start, kv_start, runs.data() + run, runs.data() + tile_end[x], false, sb);
     }
     std::vector<int32_t> order(sb.n_kv.size());
     std::iota(order.begin(), order.end(), 0);
     std::vector<int64_t> req_weight(static_cast<size_t>(plan.n), 0);
     for (size_t x = 0; x < tile_req.size(); ++x)
         req_weight[static_cast<size_t>(tile_req[x])] = std::max(req_weight[static_cast<size_t>(tile_req[x])], sb.weight[x]);
-    const int64_t longest = sb.n_kv.empty() ? 0 : *std::max_element(sb.n_kv.begin(), sb.n_kv.end());
+    const int32_t longest = sb.n_kv.empty() ? 0 : *std::max_element(sb.n_kv.begin(), sb.n_kv.end());
+    std::vector<int> half(order.size());
+    for (size_t x = 0; x < half.size(); ++x) half[x] = halvings(sb.n_kv[x], longest);
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        const int hx = halvings(sb.n_kv[x], longest), hy = halvings(sb.n_kv[y], longest);
-        if (hx != hy) return hx < hy;
+        if (half[x] != half[y]) return half[x] < half[y];
         const int32_t rx = tile_req[static_cast<size_t>(x)], ry = tile_req[static_cast<size_t>(y)];
         if (rx != ry) {
             if (req_weight[static_cast<size_t>(rx)] != req_weight[static_cast<size_t>(ry)])
@@ -713,8 +723,9 @@ void build_prefill_padded(const pk_plan& plan, DeviceTables& t) {
     for (int32_t i = 0; i < plan.n; ++i) {
         for (int32_t tt = 0; tt < max_tiles; ++tt) {
             const int32_t rows = std::min(plan.q_lens[i] - tt * BM, BM);
+            const RowRun run = {0, rows, i, tt * BM};
             if (rows <= 0) add_idle_tile(sb);
-            else add_tile(plan, q_start, kv_start, {{0, rows, i, tt * BM}}, true, sb);
+            else add_tile(plan, q_start, kv_start, &run, &run + 1, true, sb);
         }
     }
     std::vector<int32_t> order(sb.n_kv.size());
