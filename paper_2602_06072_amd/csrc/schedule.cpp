@@ -30,6 +30,14 @@ struct Builder {
         host.insert(host.end(), v.begin(), v.end());
         return r;
     }
+    // Room for a table that the caller fills by index (the pointer is good until the next table).
+    int32_t* room(size_t count, TableRef& r) {
+        host.resize((host.size() + 63) / 64 * 64, 0);
+        r.offset = host.size() * sizeof(int32_t);
+        r.count = count;
+        host.resize(host.size() + count);
+        return host.data() + (host.size() - count);
+    }
 };
 
 // ---- re-layout -------------------------------------------------------------
@@ -42,7 +50,8 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
         for (const Member& m : g.members)
             if (m.lq > 0) segs.push_back({g.buf_base + m.suffix_off, m.lq, m.req, m.shared});
     }
-    std::sort(segs.begin(), segs.end(), [](const Seg& x, const Seg& y) { return x.dst0 < y.dst0; });
+    auto before = [](const Seg& x, const Seg& y) { return x.dst0 < y.dst0; };
+    if (!std::is_sorted(segs.begin(), segs.end(), before)) std::sort(segs.begin(), segs.end(), before);   // (without shared segments they are)
     std::vector<int32_t> flat;
     flat.reserve(segs.size() * 4);
     for (const Seg& s : segs) {
@@ -319,6 +328,9 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
 }
 
 // ---- prefill ---------------------------------------------------------------
+// Key tiles of so many keys (fewer than 2^31, and up to a query tile more).
+int32_t key_tiles_to(int64_t keys) { return static_cast<int32_t>((static_cast<uint32_t>(keys) + kPrefillBN - 1) / kPrefillBN); }
+
 struct RowRun { int32_t begin, count, req, t; };   // tile rows [begin, begin + count) are request req's query rows t, t + 1, ...
 
 // Flat arrays of a schedule under construction (tiles in construction order).
@@ -530,6 +542,7 @@ int halvings(int64_t list, int64_t longest) {
     while (list > 0 && list << (h + 1) <= longest) ++h;
     return h;
 }
+constexpr int kHalvings = 32;                      // (a list has less than 2^31 key tiles)
 
 // With fewer than eight KV heads (one, two or four) neighbours in the launch order go to eight, four or two XCDs, and each reads the K/V rows of their request into its own
 // L2.  So that four of them stay together, sets of four in a row are dealt over those XCDs, in one order and in the reverse one in turns: the tiles of a
@@ -537,17 +550,19 @@ int halvings(int64_t list, int64_t longest) {
 // us before / now, 16 x 1024: 16/2 87.0 / 81.9, 8/1 46.8 / 42.6, 16/4 85.2 / 83.1, d = 64 16/2 48.4 / 45.6;  64 x 200 16/4 38.4 / 35.4, 16/2 35.2 / 33.3;  128 x 256 behind 7000 4/1
 // 532 / 433, 8/1 855 / 818, 32/2 3220 / 3170;  8 x 4096 4/1 138 / 126, 8/1 253 / 241;  16 x 256 behind 4000 8/1 77.4 / 74.8;  16 chunks behind up to 16384 the same.  Over
 // 96 shapes with one to four KV heads 1.7 % on average (sets of 2, 8 and 16: 1.2, 1.7, 1.2 %), 2.2 % slower at worst (64 ragged prompts 16/2 179.7 / 183.6).
-template <class Tile>
-void deal_over_xcds(std::vector<Tile>& tiles, int Hkv) {
-    if (Hkv >= 8 || 8 % Hkv != 0) return;
-    const size_t xcds = static_cast<size_t>(8 / Hkv), run = 4, block = xcds * run;
-    const std::vector<Tile> from(tiles);
-    for (size_t b0 = 0; b0 + block <= tiles.size(); b0 += block)
-        for (size_t x = 0; x < block; ++x) {
-            const size_t set = b0 / block % 2 == 0 ? x % xcds : xcds - 1 - x % xcds;
-            tiles[b0 + x] = from[b0 + set * run + x / xcds];
-        }
-}
+struct DealOverXcds {
+    int shift;                                     // 1 << shift sets to a block, one for each XCD of a KV head (0: tiles stay as they come)
+    size_t whole;                                  // tiles in whole blocks
+    DealOverXcds(size_t n, int Hkv) {
+        shift = Hkv == 1 ? 3 : Hkv == 2 ? 2 : Hkv == 4 ? 1 : 0;
+        whole = n >> (2 + shift) << (2 + shift);
+    }
+    size_t operator()(size_t x) const {            // where tile x in launch order goes
+        if (shift == 0 || x >= whole) return x;
+        const size_t block = x >> (2 + shift), sets = (size_t{1} << shift) - 1, set = x >> 2 & sets;
+        return block << (2 + shift) | (x & 3) << shift | (block & 1 ? sets - set : set);
+    }
+};
 
 // Query tiles of one request each and of 32 or 64 rows: the waves of a workgroup take its rows for several heads of a KV head (four waves: four
 // heads or two), all on the same K/V tiles.  With 128 rows and one head a workgroup goes through the key tiles of all its rows while those of most
@@ -559,63 +574,75 @@ void deal_over_xcds(std::vector<Tile>& tiles, int Hkv) {
 //   256 x 64 behind 100 61.5 / 45.8;  64 x 200 39.7 / 34.3;  8 x 2048 159.0 / 159.1;  64 rows and two heads: 64 x 60, 16/8 12.3 / 10.2,
 //   8 x 2048, 12/2 132 / 124, 40 x 200 behind 100 (a last tile of 8 rows) 16/8 34.0 / 34.9, 12/2 26.5 / 28.2.
 // The key tiles of a request are a list that its query tiles share (a tile sees the first n of them and the keys up to `k_end`).
+// A descriptor goes straight to its place in the launch order, which a count of the classes of lists gives: sorted as a list of tiles by those classes, and
+// written entry by entry, the tables of many short prompts took twice as long as those of 128 rows and one head.  Host time of all tables, us, that way / this /
+// 128 rows: 64 x 256 34.4 / 12.2 / 17.7, 512 x 16 59.6 / 24.8 / 28.7, 64 ragged prompts 83.7 / 20.3 / 51.4, chunks of a 70B-shaped layer 88 / 40 / 500.
 void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, const std::vector<int64_t>& kv_start, int Hkv, int row_shift,
                      Builder& b, DeviceTables::PrefillSched& s) {
     constexpr int BN = kPrefillBN;
     const int32_t rows = 32 << row_shift;
-    auto tiles_to = [](int64_t keys) { return static_cast<int32_t>((keys + BN - 1) / BN); };
-    std::vector<int32_t> requests;
-    for (const Group& g : plan.groups)
-        for (const Member& m : g.members) requests.push_back(m.req);
-    std::stable_sort(requests.begin(), requests.end(), [&](int32_t x, int32_t y) {
-        const int32_t nx = tiles_to(plan.kv_lens[x]), ny = tiles_to(plan.kv_lens[y]);
-        return nx != ny ? nx > ny : x < y;
-    });
-    struct Tile { int32_t req, t0, n, n_kv, list; };   // rows [t0, t0 + n) of request req
-    std::vector<Tile> tiles;
-    std::vector<int32_t> kv;
-    int64_t n_tiles = 0, n_entries = 0;
-    for (int32_t rq : requests) { n_tiles += (plan.q_lens[rq] + rows - 1) / rows; n_entries += tiles_to(plan.kv_lens[rq]); }
-    tiles.reserve(static_cast<size_t>(n_tiles));
-    kv.reserve(static_cast<size_t>(n_entries) * 2);
-    for (int32_t rq : requests) {
-        const int64_t ctx = plan.kv_lens[rq] - plan.q_lens[rq];
-        const int32_t list = static_cast<int32_t>(kv.size() / 2);
-        for (int64_t x = 0; x < plan.kv_lens[rq]; x += BN) {
-            kv.push_back(static_cast<int32_t>(kv_start[rq] + x));
-            kv.push_back(static_cast<int32_t>(std::min<int64_t>(BN, plan.kv_lens[rq] - x)) | 0xAA << 8);
-        }
-        for (int32_t tile = (plan.q_lens[rq] + rows - 1) / rows - 1; tile >= 0; --tile) {
-            const int32_t t0 = tile * rows, n = std::min(rows, plan.q_lens[rq] - t0);
-            tiles.push_back({rq, t0, n, tiles_to(ctx + t0 + n), list});
-        }
+    // requests by the length of their list, the longest first, and by number among equals
+    std::vector<uint64_t> requests(static_cast<size_t>(plan.n));
+    size_t n_tiles = 0, n_entries = 0;
+    for (int32_t rq = 0; rq < plan.n; ++rq) {
+        const int32_t list = key_tiles_to(plan.kv_lens[rq]);
+        requests[static_cast<size_t>(rq)] = static_cast<uint64_t>(INT32_MAX - list) << 32 | static_cast<uint32_t>(rq);
+        n_tiles += static_cast<size_t>((plan.q_lens[rq] + rows - 1) / rows);
+        n_entries += static_cast<size_t>(list);
     }
-    const int32_t longest = tiles.empty() ? 0 : tiles_to(plan.kv_lens[requests[0]]);
-    std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile& x, const Tile& y) { return halvings(x.n_kv, longest) < halvings(y.n_kv, longest); });
-    deal_over_xcds(tiles, Hkv);
-    std::vector<int32_t> desc;
-    desc.reserve(tiles.size() * kTileDescWords);
-    int64_t weight = 0;
-    for (const Tile& x : tiles) {
-        const int64_t ctx = plan.kv_lens[x.req] - plan.q_lens[x.req], ks0 = kv_start[x.req];
-        int32_t trailing = 0;
-        for (int w = 0; w < 4; ++w) {
-            const int32_t own = 32 * w < x.n ? tiles_to(ctx + x.t0 + std::min(x.n, 32 * (w + 1))) : 0;
-            trailing |= std::min(x.n_kv - own, 255) << (8 * w);
-            weight += own;
+    std::sort(requests.begin(), requests.end());
+    const int32_t longest = plan.n > 0 ? INT32_MAX - static_cast<int32_t>(requests[0] >> 32) : 0;
+    // Where the tiles of each class of lists begin.  Inside a request lists get shorter tile by tile, and the class changes but a few times.
+    auto each_tile = [&](int32_t rq, auto&& visit) {   // the heaviest tile first
+        const int32_t lq = plan.q_lens[rq], ctx = plan.kv_lens[rq] - lq;
+        int h = 0;
+        for (int32_t t0 = (lq - 1) & -rows; t0 >= 0; t0 -= rows) {
+            const int32_t n = std::min(rows, lq - t0), n_kv = key_tiles_to(ctx + t0 + n);
+            while (static_cast<int64_t>(n_kv) << (h + 1) <= longest) ++h;
+            visit(t0, n, n_kv, h);
         }
-        const int32_t entry[8] = {x.list, x.n_kv, 0, trailing, x.n | 1 << 16, static_cast<int32_t>(q_start[x.req] + x.t0),
-                                  static_cast<int32_t>(ks0), static_cast<int32_t>(ks0 + ctx + x.t0 + 1)};
-        desc.insert(desc.end(), entry, entry + 8);
-        for (int word = 0; word < 2; ++word)
-            for (int e = 0; e < 3; ++e) desc.push_back(kv[2 * (static_cast<size_t>(x.list) + std::min(e, x.n_kv - 1)) + word]);
-        desc.push_back(static_cast<int32_t>(ks0 + ctx + x.t0 + x.n)); desc.push_back(0);
+    };
+    size_t next[kHalvings + 1] = {};
+    for (const uint64_t key : requests)
+        each_tile(static_cast<int32_t>(key & 0xFFFFFFFFu), [&](int32_t, int32_t, int32_t, int h) { ++next[h + 1]; });
+    for (int h = 0; h < kHalvings; ++h) next[h + 1] += next[h];
+    int32_t* desc = b.room(n_tiles * kTileDescWords, s.tiles);
+    std::vector<int32_t> first_entry(static_cast<size_t>(plan.n));
+    const DealOverXcds deal(n_tiles, Hkv);
+    int64_t weight = 0;
+    int32_t list = 0;
+    for (const uint64_t key : requests) {
+        const int32_t rq = static_cast<int32_t>(key & 0xFFFFFFFFu), kv = plan.kv_lens[rq];
+        const int64_t ctx = kv - plan.q_lens[rq], ks0 = kv_start[rq];
+        first_entry[static_cast<size_t>(rq)] = list;
+        // (first key row, info) of the request's key tile e
+        auto ks_of = [&](int32_t e) { return static_cast<int32_t>(ks0 + static_cast<int64_t>(e) * BN); };
+        auto info_of = [&](int32_t e) { return static_cast<int32_t>(std::min<int64_t>(BN, kv - static_cast<int64_t>(e) * BN)) | 0xAA << 8; };
+        each_tile(rq, [&](int32_t t0, int32_t n, int32_t n_kv, int h) {
+            int32_t trailing = 0;
+            for (int w = 0; w < 4; ++w) {
+                const int32_t own = 32 * w >= n ? 0 : 32 * (w + 1) >= n ? n_kv : key_tiles_to(ctx + t0 + 32 * (w + 1));
+                trailing |= std::min(n_kv - own, 255) << (8 * w);
+                weight += own;
+            }
+            const int32_t e1 = std::min(1, n_kv - 1), e2 = std::min(2, n_kv - 1), hi = static_cast<int32_t>(ks0 + ctx + t0 + 1);
+            const int32_t entry[kTileDescWords] = {list, n_kv, 0, trailing, n | 1 << 16, static_cast<int32_t>(q_start[rq] + t0), static_cast<int32_t>(ks0), hi,
+                                                   ks_of(0), ks_of(e1), ks_of(e2), info_of(0), info_of(e1), info_of(e2), hi + n - 1, 0};
+            std::copy(entry, entry + kTileDescWords, desc + deal(next[h]++) * kTileDescWords);
+        });
+        list += key_tiles_to(kv);
+    }
+    int32_t* entries = b.room(n_entries * 2, s.kvtiles);
+    for (int32_t rq = 0; rq < plan.n; ++rq) {
+        int32_t* e = entries + 2 * static_cast<size_t>(first_entry[static_cast<size_t>(rq)]);
+        for (int64_t x = 0; x < plan.kv_lens[rq]; x += BN, e += 2) {
+            e[0] = static_cast<int32_t>(kv_start[rq] + x);
+            e[1] = static_cast<int32_t>(std::min<int64_t>(BN, plan.kv_lens[rq] - x)) | 0xAA << 8;
+        }
     }
     s.row_shift = row_shift;
     s.n_tiles = static_cast<int32_t>(n_tiles);
     s.issued_pairs = weight * 32 * BN;
-    s.tiles = b.add(desc);
-    s.kvtiles = b.add(kv);
 }
 
 // packed: tiles over each group's packed row stream, heaviest tile first
@@ -628,25 +655,63 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     int64_t aligned_tiles = 0;
     for (int32_t i = 0; i < plan.n; ++i) aligned_tiles += (plan.q_lens[i] + BM - 1) / BM;
     const bool may_share = aligned_tiles * Hq > 2 * static_cast<int64_t>(num_cus);
-    std::vector<RowRun> runs;                      // of all tiles
-    std::vector<size_t> tile_end;                  // where each tile's end
+    // A request that does not fit into what is left of the current tile shares it only if
+    // that saves the request a tile of its own (its head then rides along with few key
+    // tiles); otherwise the tile is closed and the request starts on a fresh one: a shared
+    // tile walks the key tiles of both requests one after the other and runs them masked.
+    auto starts_fresh = [&](int32_t filled, int32_t lq) {
+        return filled > 0 && (!may_share || BM - filled < (lq - 1) % BM + 1);      // (rows of its last tile when it starts fresh)
+    };
+    // What the choice of the kernel goes by: the tiles and their key tiles (a full tile has two more of them than the one before it).
+    int64_t n_tiles = 0, key_tiles = 0, total_rows = 0;
+    for (const Group& g : plan.groups) {
+        int32_t filled = 0;                        // rows of the tile that is open
+        for (const Member& m : g.members) {
+            const int32_t lq = plan.q_lens[m.req];
+            const int64_t ctx = plan.kv_lens[m.req] - lq;
+            if (starts_fresh(filled, lq)) { ++n_tiles; filled = 0; }
+            const int32_t head = std::min(BM - filled, lq);
+            key_tiles += key_tiles_to(ctx + head);
+            total_rows += lq;
+            filled += head;
+            if (filled < BM) continue;
+            const int32_t full = (lq - head) / BM, rest = lq - head - full * BM;
+            key_tiles += full * static_cast<int64_t>(key_tiles_to(ctx + head + BM)) + static_cast<int64_t>(full) * (full - 1) + (rest > 0 ? key_tiles_to(ctx + lq) : 0);
+            n_tiles += 1 + full;
+            filled = rest;
+        }
+        if (filled > 0) ++n_tiles;
+    }
+    DeviceTables::PrefillSched& s = t.packed;
+    s.light = light_launch(n_tiles, key_tiles, Hq, t.d, num_cus);
+    s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d) && ahead_with_eight(plan, n_tiles, key_tiles, Hq, t.Hkv, num_cus);
+    const int row_shift = head_tile_shift(Hq / t.Hkv, s.eight ? 8 : 4);
+    // Where every tile of 128 rows and head has a compute unit of its own and a fifth of its rows or more are empty, fewer waves share a unit's LDS with
+    // those tiles than with several heads to a workgroup (128 rows / several heads, us: 1 x 64 behind 8000 with 16 heads 113 / 121, d = 64 89 / 97; 7 x 57 behind 2500
+    // with 16 heads 40.0 / 42.5, 32 heads 40.4 / 42.6, 64 heads (448 workgroups) 58.3 / 45.9; 3 x 200 behind 300 with 32 heads 12.6 / 13.1, 64 heads (384) 18.6 / 19.0; full tiles the
+    // other way: 1 x 1000 16/2 20.2 / 19.8, 2 x 128 behind 4000 66.3 / 65.3).
+    const bool spread = aligned_tiles * Hq <= num_cus && 5 * total_rows <= 4 * BM * aligned_tiles;
+    if (!plan.decode_only && t.dtype == PK_BF16 && row_shift < 2 && !spread) {
+        emit_head_tiles(plan, q_start, kv_start, t.Hkv, row_shift, b, s);
+        s.n_query_tiles = static_cast<int32_t>(n_tiles);
+        return;
+    }
+    SchedBuild sb;
+    sb.reserve(static_cast<size_t>(n_tiles), static_cast<size_t>(plan.n + n_tiles), static_cast<size_t>(key_tiles));
+    std::vector<RowRun> runs;                      // of the tile that is open
+    std::vector<int32_t> tile_req;                 // request of a tile's first row
+    tile_req.reserve(static_cast<size_t>(n_tiles));
     int32_t filled = 0;                            // rows of the tile that is open
     auto close_tile = [&] {
-        tile_end.push_back(runs.size());
+        tile_req.push_back(runs[0].req);
+        add_tile(plan, q_start, kv_start, runs.data(), runs.data() + runs.size(), false, sb);
+        runs.clear();
         filled = 0;
     };
     for (const Group& g : plan.groups) {
         for (const Member& m : g.members) {
-            // A request that does not fit into what is left of the current tile shares it only if
-            // that saves the request a tile of its own (its head then rides along with few key
-            // tiles); otherwise the tile is closed and the request starts on a fresh one: a shared
-            // tile walks the key tiles of both requests one after the other and runs them masked.
             const int32_t lq = plan.q_lens[m.req];
-            const int32_t room = BM - filled;
-            if (filled > 0 && (lq > room || !may_share)) {
-                const int32_t last = lq % BM == 0 ? BM : lq % BM;   // rows of its last tile when it starts fresh
-                if (room < last || !may_share) close_tile();
-            }
+            if (starts_fresh(filled, lq)) close_tile();
             for (int32_t x = 0; x < lq;) {
                 const int32_t take = std::min(BM - filled, lq - x);
                 runs.push_back({filled, take, m.req, x});
@@ -657,44 +722,12 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         }
         if (filled > 0) close_tile();
     }
-    // what the choice of the kernel goes by
-    const int64_t n_tiles = static_cast<int64_t>(tile_end.size());
-    int64_t key_tiles = 0;
-    for (const RowRun& run : runs)
-        key_tiles += (plan.kv_lens[run.req] - plan.q_lens[run.req] + run.t + run.count + kPrefillBN - 1) / kPrefillBN;
-    DeviceTables::PrefillSched& s = t.packed;
-    s.light = light_launch(n_tiles, key_tiles, Hq, t.d, num_cus);
-    s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d) && ahead_with_eight(plan, n_tiles, key_tiles, Hq, t.Hkv, num_cus);
-    const int row_shift = head_tile_shift(Hq / t.Hkv, s.eight ? 8 : 4);
-    // Where every tile of 128 rows and head has a compute unit of its own and a fifth of its rows or more are empty, fewer waves share a unit's LDS with
-    // those tiles than with several heads to a workgroup (128 rows / several heads, us: 1 x 64 behind 8000 with 16 heads 113 / 121, d = 64 89 / 97; 7 x 57 behind 2500
-    // with 16 heads 40.0 / 42.5, 32 heads 40.4 / 42.6, 64 heads (448 workgroups) 58.3 / 45.9; 3 x 200 behind 300 with 32 heads 12.6 / 13.1, 64 heads (384) 18.6 / 19.0; full tiles the
-    // other way: 1 x 1000 16/2 20.2 / 19.8, 2 x 128 behind 4000 66.3 / 65.3).
-    const int64_t total_rows = std::accumulate(plan.q_lens.begin(), plan.q_lens.end(), int64_t{0});
-    const bool spread = aligned_tiles * Hq <= num_cus && 5 * total_rows <= 4 * BM * aligned_tiles;
-    if (!plan.decode_only && t.dtype == PK_BF16 && row_shift < 2 && !spread) {
-        emit_head_tiles(plan, q_start, kv_start, t.Hkv, row_shift, b, s);
-        s.n_query_tiles = static_cast<int32_t>(n_tiles);
-        return;
-    }
-    SchedBuild sb;
-    sb.reserve(tile_end.size(), runs.size(), static_cast<size_t>(key_tiles));
-    std::vector<int32_t> tile_req;                 // request of a tile's first row
-    tile_req.reserve(tile_end.size());
-    for (size_t x = 0, run = 0; x < tile_end.size(); run = tile_end[x++]) {
-        tile_req.push_back(runs[run].req);
-        add_tile(plan, q_start, kv_start, runs.data() + run, runs.data() + tile_end[x], false, sb);
-    }
     std::vector<int32_t> order(sb.n_kv.size());
     std::iota(order.begin(), order.end(), 0);
     std::vector<int64_t> req_weight(static_cast<size_t>(plan.n), 0);
     for (size_t x = 0; x < tile_req.size(); ++x)
         req_weight[static_cast<size_t>(tile_req[x])] = std::max(req_weight[static_cast<size_t>(tile_req[x])], sb.weight[x]);
-    const int32_t longest = sb.n_kv.empty() ? 0 : *std::max_element(sb.n_kv.begin(), sb.n_kv.end());
-    std::vector<int> half(order.size());
-    for (size_t x = 0; x < half.size(); ++x) half[x] = halvings(sb.n_kv[x], longest);
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        if (half[x] != half[y]) return half[x] < half[y];
         const int32_t rx = tile_req[static_cast<size_t>(x)], ry = tile_req[static_cast<size_t>(y)];
         if (rx != ry) {
             if (req_weight[static_cast<size_t>(rx)] != req_weight[static_cast<size_t>(ry)])
@@ -703,6 +736,12 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
         }
         return sb.weight[x] > sb.weight[y];
     });
+    const int32_t longest = sb.n_kv.empty() ? 0 : *std::max_element(sb.n_kv.begin(), sb.n_kv.end());
+    size_t next[kHalvings + 1] = {};
+    for (const int32_t x : order) ++next[halvings(sb.n_kv[x], longest) + 1];
+    for (int h = 0; h < kHalvings; ++h) next[h + 1] += next[h];
+    const std::vector<int32_t> by_request(order);
+    for (const int32_t x : by_request) order[next[halvings(sb.n_kv[x], longest)]++] = x;
     emit_sched(sb, order, b, s);
 }
 

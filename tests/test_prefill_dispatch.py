@@ -1,9 +1,12 @@
 """Which of the two prefill bodies a batch takes (host only: the tables of a plan say it).  Measured on batches of both kinds;
-results do not depend on it."""
+results do not depend on it.  And what building the tables costs."""
+import time
+
 import numpy as np
 import pytest
 
 from paper_2602_06072_amd import binding as pk
+from paper_2602_06072_amd import workloads as wl
 
 
 def bound(ql, ctx, Hq, Hkv, d):
@@ -34,3 +37,18 @@ def test_idle_tiles_of_the_padded_schedule_do_not_count(d):
     """One long prompt among short ones: the padded grid has a tile for every 128 rows of the longest one in every request."""
     plan = bound([8192] + [100] * 30, [0] * 31, 32, 8, d)
     assert plan.stat(7) == 31 * 64 and plan.stat(8) == 0 and plan.stat(9) == 0
+
+
+# many short prompts: a query tile per request where the waves of a workgroup take several heads, tiles of 128 rows and one head otherwise
+@pytest.mark.parametrize("ql", [[16] * 512, [256] * 64, wl.config2_lengths(0)], ids=["512 x 16", "64 x 256", "64 ragged"])
+def test_tables_of_tiles_of_several_heads_are_no_slower_to_build(ql):
+    """The best of 40 runs each in turn: a fifth beyond the tables of one head per KV head, which do not have such tiles."""
+    ql = np.asarray(ql, dtype=np.int32)
+    best = {}
+    for _ in range(40):
+        for heads in ((32, 8), (8, 1), (16, 16)):
+            plan = pk.pack_plan(ql, ql, token_budget=16384)
+            begin = time.perf_counter()
+            plan.workspace_bytes(*heads, 128, pk.PK_BF16)
+            best[heads] = min(best.get(heads, 1.0), time.perf_counter() - begin)
+    assert max(best[32, 8], best[8, 1]) <= 1.2 * best[16, 16], best
