@@ -536,13 +536,27 @@ void emit_sched(const SchedBuild& sb, const std::vector<int32_t>& order, Builder
 // workgroups that run at the same time on one XCD then stream the same K/V rows, which keeps them in that XCD's L2.
 // Request by request alone / in this order, us: 16 x 512 tokens, 32/8 heads 56.6 / 53.2, 16/8 35.2 / 31.9, 16/1 35.0 / 30.4, with d = 64 16/8
 // 22.5 / 18.8, 8/8 13.6 / 12.5; 8 x 2048 16/8 144 / 133, 12/2 124 / 113, 16/1 146 / 134, d = 64 8/8 61.1 / 46.8; 24 x 1000 16/16
-// 147.5 / 139.8; 28 x 560 64/8 231.6 / 228.0; long lists and many rounds of workgroups the same; 64 ragged prompts 347.7 / 351.1.
+// 147.5 / 139.8; 28 x 560 64/8 231.6 / 228.0; long lists and many rounds of workgroups the same; 64 ragged prompts 347.7 / 351.1.  (Where ends_by_request says
+// so, request by request alone.)
 int halvings(int64_t list, int64_t longest) {
     int h = 0;
     while (list > 0 && list << (h + 1) <= longest) ++h;
     return h;
 }
 constexpr int kHalvings = 32;                      // (a list has less than 2^31 key tiles)
+
+// Whether query tiles of one head stay request by request.  With one query head per KV head no workgroup but those of the request's other tiles reads a tile's K/V rows,
+// and what the order above puts apart is read from memory again; all that it has to give is a shorter end.  So the one is weighed against the other, in launches of some
+// rounds.  read_again: key tiles of the first tile of every further class of a request, ends_by: of the longest list among the last tiles that fill the
+// chip, beyond those in the other order, both as parts of all (of what a slot goes through).  us, by the halvings of lists / request by request:
+//   64 x 200, 16/16 heads 48.4 / 46.5;  32 x 512 32/32 151 / 132;  73 x 380 32/32 221 / 203;  28 of 139..478 32/32 66.0 / 60.3;  64 ragged prompts 32/32 408 / 394;  143 x 205
+//   32/32 261 / 208;  99 x 178 behind up to 1278 32/32 489 / 372;  the other way 16 x 512 16/16 35.8 / 37.7, 24 x 1000 137.7 / 149.6, 3 x 1000 (0.7 rounds) 23.2 / 25.4.
+// Over 577 such launches of 0.4 to 27 rounds this takes 0.6 % more than the faster order, up to 9 % (12 % once), the halvings 2.5 %, up to 32 %, request by request 1.7 %, up to 26 %.
+// With head dimension 64 (half the bytes; 166 launches) the halvings take 0.3 % more than the faster order, 6 % at worst (64 x 200 16/16 27.7 / 25.8 us), request by request
+// 5 %; with three, five and seven heads per KV head (199) 0.3 and 4.4 %.
+bool stays_by_request(double rounds, double ends_by, double read_again, int r, int d) {
+    return r == 1 && d == 128 && rounds > 2.5 && ends_by < 0.7 * read_again;
+}
 
 // With fewer than eight KV heads (one, two or four) neighbours in the launch order go to eight, four or two XCDs, and each reads the K/V rows of their request into its own
 // L2.  So that four of them stay together, sets of four in a row are dealt over those XCDs, in one order and in the reverse one in turns: the tiles of a
@@ -741,7 +755,24 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     for (const int32_t x : order) ++next[halvings(sb.n_kv[x], longest) + 1];
     for (int h = 0; h < kHalvings; ++h) next[h + 1] += next[h];
     const std::vector<int32_t> by_request(order);
-    for (const int32_t x : by_request) order[next[halvings(sb.n_kv[x], longest)]++] = x;
+    double read_again = 0;
+    int32_t before = -1;                           // the tile before, and its class
+    int before_h = 0;
+    for (const int32_t x : by_request) {
+        const int h = halvings(sb.n_kv[x], longest);
+        if (before >= 0 && tile_req[static_cast<size_t>(x)] == tile_req[static_cast<size_t>(before)] && h != before_h) read_again += sb.n_kv[x];
+        order[next[h]++] = before = x;
+        before_h = h;
+    }
+    const int slots = 2 * num_cus;                 // workgroups at a time
+    auto end_of = [&](const std::vector<int32_t>& o) {
+        const size_t last = std::min(o.size(), static_cast<size_t>(std::max(1, slots / Hq)));
+        int32_t list = 0;
+        for (size_t x = o.size() - last; x < o.size(); ++x) list = std::max(list, sb.n_kv[o[x]]);
+        return list;
+    };
+    const double rounds = static_cast<double>(n_tiles) * Hq / slots, work = std::max(1.0, static_cast<double>(key_tiles));
+    if (stays_by_request(rounds, (end_of(by_request) - end_of(order)) * slots / (work * Hq), read_again / work, Hq / t.Hkv, t.d)) order = by_request;
     emit_sched(sb, order, b, s);
 }
 
