@@ -700,11 +700,16 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     s.light = light_launch(n_tiles, key_tiles, Hq, t.d, num_cus);
     s.eight = !s.light && eight_waves(n_tiles, key_tiles, Hq, t.Hkv, t.d) && ahead_with_eight(plan, n_tiles, key_tiles, Hq, t.Hkv, num_cus);
     const int row_shift = head_tile_shift(Hq / t.Hkv, s.eight ? 8 : 4);
-    // Where every tile of 128 rows and head has a compute unit of its own and a fifth of its rows or more are empty, fewer waves share a unit's LDS with
-    // those tiles than with several heads to a workgroup (128 rows / several heads, us: 1 x 64 behind 8000 with 16 heads 113 / 121, d = 64 89 / 97; 7 x 57 behind 2500
-    // with 16 heads 40.0 / 42.5, 32 heads 40.4 / 42.6, 64 heads (448 workgroups) 58.3 / 45.9; 3 x 200 behind 300 with 32 heads 12.6 / 13.1, 64 heads (384) 18.6 / 19.0; full tiles the
-    // other way: 1 x 1000 16/2 20.2 / 19.8, 2 x 128 behind 4000 66.3 / 65.3).
-    const bool spread = aligned_tiles * Hq <= num_cus && 5 * total_rows <= 4 * BM * aligned_tiles;
+    // Where every tile of 128 rows and head has a compute unit of its own, and waves of the tile with the longest list (at least one) or a fifth of all rows are empty, fewer
+    // waves share a unit's LDS with those tiles than with several heads to a workgroup.  128 rows / several heads, us: 1 x 64 behind 8000 with 16 heads 113 / 121, d = 64 89 / 97; 7 x 57 behind
+    // 2500 with 16 heads 40.0 / 42.5, 32 heads 40.4 / 42.6, 64 heads (448 workgroups) 58.3 / 45.9; 3 x 200 behind 300 with 32 heads 12.6 / 13.1, 64 heads (384) 18.6 / 19.0; 2 of 382
+    // and 407, 8/2 10.6 / 11.2; 4 of 315..554, 8/2 12.7 / 13.5; 2 x 440, 16/8 and d = 64 8.5 / 9.0; 6 x 211 behind up to 1161, 8/1 25.2 / 25.9; with a full tile the other way: 1 x 1000
+    // 16/2 20.2 / 19.8, 2 x 128 behind 4000 66.3 / 65.3, 5 of 173..358 (last tile 102 rows) 8/4 10.6 / 10.4.
+    bool spread = aligned_tiles * Hq <= num_cus;
+    if (spread) {
+        const int32_t rq = static_cast<int32_t>(std::max_element(plan.kv_lens.begin(), plan.kv_lens.end()) - plan.kv_lens.begin());
+        spread = (plan.q_lens[rq] - 1) % BM < BM - 32 || 5 * total_rows <= 4 * BM * aligned_tiles;
+    }
     if (!plan.decode_only && t.dtype == PK_BF16 && row_shift < 2 && !spread) {
         emit_head_tiles(plan, q_start, kv_start, t.Hkv, row_shift, b, s);
         s.n_query_tiles = static_cast<int32_t>(n_tiles);
