@@ -705,7 +705,7 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     // 2500 with 16 heads 40.0 / 42.5, 32 heads 40.4 / 42.6, 64 heads (448 workgroups) 58.3 / 45.9; 3 x 200 behind 300 with 32 heads 12.6 / 13.1, 64 heads (384) 18.6 / 19.0; 2 of 382
     // and 407, 8/2 10.6 / 11.2; 4 of 315..554, 8/2 12.7 / 13.5; 2 x 440, 16/8 and d = 64 8.5 / 9.0; 6 x 211 behind up to 1161, 8/1 25.2 / 25.9; with a full tile the other way: 1 x 1000
     // 16/2 20.2 / 19.8, 2 x 128 behind 4000 66.3 / 65.3, 5 of 173..358 (last tile 102 rows) 8/4 10.6 / 10.4.
-    bool spread = aligned_tiles * Hq <= num_cus;
+    bool spread = plan.n > 0 && aligned_tiles * Hq <= num_cus;
     if (spread) {
         const int32_t rq = static_cast<int32_t>(std::max_element(plan.kv_lens.begin(), plan.kv_lens.end()) - plan.kv_lens.begin());
         spread = (plan.q_lens[rq] - 1) % BM < BM - 32 || 5 * total_rows <= 4 * BM * aligned_tiles;
