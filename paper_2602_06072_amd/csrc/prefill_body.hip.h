@@ -343,7 +343,7 @@ struct Pending { float x[8]; };                    // exponents, then exponentia
 template <int SLOTS, int SPARE>
 __device__ __forceinline__ void softmax_slot(const int slot, const Scores& s, const float sc, const float (&m_ref)[NC], Pending& p, HalfSoftmax& h) {
     constexpr int SCORES = 8 * NC;
-    static_assert(SPARE == 0 || (SCORES - 1) * (SLOTS - SPARE) / SCORES + 3 < SLOTS, "every pair is packed before the part ends");
+    static_assert(SPARE == 0 || (SCORES - 1) * (SLOTS - SPARE) / SCORES + 4 < SLOTS, "every pair is packed and combined before the check behind the last slot");
     auto last = [](int at) { return at < SLOTS ? at : SLOTS; };
     auto begin = [](int e) { return e * (SLOTS - SPARE) / SCORES; };
 #pragma unroll

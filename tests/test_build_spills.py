@@ -1,4 +1,8 @@
-"""The build refuses kernels that spill scalar registers where the inline assembly relies on none."""
+"""What the build refuses: kernels that spill scalar registers where the inline assembly relies on none, softmax slots that would end behind the check of their results."""
+import os
+import shutil
+import subprocess
+
 import pytest
 
 from paper_2602_06072_amd import build
@@ -30,3 +34,21 @@ def test_kernels_with_such_copies_are_checked(monkeypatch, tmp_path):
     with pytest.raises(RuntimeError, match="scalar registers spill"):
         build._compile("prefill_pipe.hip")
     assert real(seen[0]) == [] and "prefill_bf16_pair_kernel" in seen[0]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("spare, builds", [(4, True), (3, False)])
+def test_softmax_slots_leave_room_for_the_check(tmp_path, spare, builds):
+    """With a spare slot less the last pair of head dimension 64 would be combined behind the branch that looks for large probabilities."""
+    for name in os.listdir(build.CSRC):
+        if name.endswith((".h", ".hip")):
+            shutil.copy(os.path.join(build.CSRC, name), tmp_path)
+    header = tmp_path / "prefill_body.hip.h"
+    text = header.read_text()
+    line = "constexpr int SPARE = D == 128 ? 2 * NC : 4;"
+    assert line in text
+    header.write_text(text.replace(line, line.replace(": 4;", f": {spare};")))
+    run = subprocess.run(["hipcc", *build.HIP_FLAGS, "-fsyntax-only", "--offload-device-only", str(tmp_path / "prefill_pipe.hip")],
+                         capture_output=True, text=True)
+    assert (run.returncode == 0) == builds, run.stderr[-2000:]
+    assert builds or "packed and combined before the check" in run.stderr
