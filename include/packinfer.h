@@ -397,7 +397,7 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
                           int dtype, int out_dtype,
                           void* workspace, size_t workspace_bytes, void* stream);
 
-/* Counts for the benchmark's work accounting (host).  1..10 refer to the
+/* Counts for the benchmark's work accounting (host).  1..12 refer to the
  * tables of the head shape the plan was last sized or bound for (0 before).
  *   what = 0: unmasked (query,key) pairs per head summed over requests
  *   what = 1: (query,key) pairs issued to the MFMA units by the packed
@@ -405,14 +405,17 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
  *   what = 2: same for the padded prefill schedule
  *   what = 3: decode work items; 4: split-KV partial slots;
  *   what = 5: tokens per decode split chosen by the schedule builder
- *   what = 6: query tiles of the packed prefill schedule, of 128 rows (with
- *             an even number of heads per KV head the launch has tiles of 32
- *             or 64 rows and several heads instead); 7: of the padded
+ *   what = 6: query tiles of the packed prefill schedule, counted in tiles of
+ *             128 rows whatever tiles the launch has (12); 7: of the padded
  *   what = 8: 1 if the packed bf16 prefill (also the prefill half of a mixed
  *             step) takes the kernels for launches of little work, 0 if the
  *             software-pipelined ones; 9: same for the padded schedule
  *   what = 10: waves that share a (decode work item, KV head) pair: 4 (a
  *             workgroup, which merges in the same launch), 1, or 0 (no items)
+ *   what = 11: waves of a workgroup of the packed bf16 prefill: 8 or 4 (the
+ *             prefill half of a mixed step always has 4; 0: no bf16 tables)
+ *   what = 12: query rows of its tiles: 128, or 64 or 32 (a request's alone)
+ *             which the workgroup's waves take for several heads
  */
 int64_t pk_plan_stat(const pk_plan* plan, int what);
 

@@ -593,6 +593,8 @@ extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
                     build_prefill_padded(*plan, plan->tables);
                 return plan->tables.padded.light;
             case 10: return plan->tables.dec.n_items == 0 ? 0 : plan->tables.dec.group ? 4 : 1;
+            case 11: return plan->tables.dtype == PK_BF16 ? (plan->tables.packed.eight ? 8 : 4) : 0;
+            case 12: return plan->tables.dtype == PK_BF16 ? 32 << plan->tables.packed.row_shift : 0;
             default: return 0;
         }
     });

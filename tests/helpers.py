@@ -6,6 +6,7 @@ import torch
 
 from oracle import attention as oa
 from oracle import paged as opaged
+from paper_2602_06072_amd import binding as pk
 
 
 def bf16_bits(t: torch.Tensor) -> np.ndarray:
@@ -91,3 +92,16 @@ LONG = 6
 def with_long_requests(kv, ql):
     return (np.concatenate([np.asarray(kv, dtype=np.int32), np.full(LONG, 16384, dtype=np.int32)]),
             np.concatenate([np.asarray(ql, dtype=np.int32), np.ones(LONG, dtype=np.int32)]))
+
+
+def with_eight_waves(kv, ql, Hq, Hkv, token_budget, rows=1, tokens=16384, most=80):
+    """The batch with requests of `rows` query rows and `tokens` tokens at its end, as many as it takes for the packed prefill with head dimension 128 to run
+    with eight waves to a workgroup (plan.stat(11): long lists on average, and rounds of such workgroups that are full)."""
+    for extra in range(most):
+        kv_all = np.concatenate([np.asarray(kv, dtype=np.int32), np.full(extra, tokens, dtype=np.int32)])
+        ql_all = np.concatenate([np.asarray(ql, dtype=np.int32), np.full(extra, rows, dtype=np.int32)])
+        plan = pk.pack_plan(kv_all, ql_all, token_budget=token_budget)
+        plan.workspace_bytes(Hq, Hkv, 128, pk.PK_BF16)
+        if plan.stat(11) == 8:
+            return kv_all, ql_all
+    raise AssertionError(f"no batch of up to {most} long requests runs with eight waves")

@@ -15,11 +15,11 @@ DEV = "cuda"
 EDGES = [1, 2, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 257]
 
 
-def compare(ql, ctx, Hq, Hkv, d, what, light, out=torch.bfloat16):
+def compare(ql, ctx, Hq, Hkv, d, what, light, out=torch.bfloat16, budget=1 << 14):
     ql = np.asarray(ql, dtype=np.int32)
     kv = ql + np.asarray(ctx, dtype=np.int32)
-    w = wl.make_ragged(what, kv, ql, Hq, Hkv, d, 1 << 14, 77, device=DEV, keep_f32=False)
-    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=1 << 14)
+    w = wl.make_ragged(what, kv, ql, Hq, Hkv, d, budget, 77, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=budget)
     ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
     got = torch.full(w.q.shape, float("nan"), dtype=out, device=DEV)
     want = torch.full(w.q.shape, float("nan"), dtype=out, device=DEV)
@@ -61,13 +61,22 @@ def test_edges_in_launches_of_much_work(d, Hq, Hkv):
     compare(EDGES * reps, ctx * reps, Hq, Hkv, d, f"long lists {Hq}/{Hkv} d {d}", 0, torch.float32 if Hq == 32 else torch.bfloat16)
 
 
-# 512 workgroups and lists of 32 tiles: eight waves, for 2 x 128, 4 x 64 or 8 x 32 rows and heads
-@pytest.mark.parametrize("Hq, Hkv", [(32, 16), (32, 8), (48, 8), (64, 8)])
-def test_edges_with_eight_waves(Hq, Hkv):
-    ql = EDGES + [128] * 6
-    ctx = [2048 + 64 * n + n % 3 for n in range(len(ql))]
-    plan = compare(ql, ctx, Hq, Hkv, 128, f"eight waves {Hq}/{Hkv}", 0)
-    assert plan.stat(6) * Hq >= 512 and plan.stat(1) >= 32 * 64 * 128 * plan.stat(6) // 2
+# Eight waves, for 2 x 128, 4 x 64 or 8 x 32 heads and rows (tiles of 64 rows of which the second half is empty among them): short lists in a batch that
+# is long on average.
+@pytest.mark.parametrize("Hq, Hkv, rows", [(8, 4, 128), (8, 2, 64), (12, 2, 128), (16, 2, 32)])
+def test_edges_with_eight_waves(Hq, Hkv, rows):
+    kv, ql = H.with_eight_waves([x + 63 * n for n, x in enumerate(EDGES)], EDGES, Hq, Hkv, 1 << 14, rows=128)
+    plan = compare(ql, kv - ql, Hq, Hkv, 128, f"eight waves {Hq}/{Hkv}", 0)
+    assert plan.stat(11) == 8 and plan.stat(12) == rows
+
+
+@pytest.mark.parametrize("out", [torch.bfloat16, torch.float32])
+def test_tiles_of_several_requests_with_eight_waves(out):
+    """Two heads of 128 rows with six heads per KV head: the rows of a wave may be of two requests."""
+    ql = np.random.default_rng(81).integers(1, 70, 30)
+    kv, ql = H.with_eight_waves(ql + np.arange(30) * 37, ql, 12, 2, 1 << 18, rows=128)
+    plan = compare(ql, kv - ql, 12, 2, 128, "eight waves, shared tiles", 0, out, 1 << 18)
+    assert plan.stat(11) == 8 and plan.stat(12) == 128 and plan.stat(6) < len(ql) - 10
 
 
 # Rounds of eight-wave workgroups that are full, and lists of some 190 key tiles: 256 (2 x 240 with six heads per KV head) such
@@ -76,7 +85,8 @@ def test_edges_with_eight_waves(Hq, Hkv):
 def test_long_lists_with_eight_waves(Hq, Hkv, n):
     ql = ([128, 127, 97, 113, 128, 98, 126, 100] * 3)[:n]
     ctx = [12000 + 64 * (x % 5) + x % 3 for x in range(n)]
-    compare(ql, ctx, Hq, Hkv, 128, f"eight waves, long lists {Hq}/{Hkv}", 0, torch.float32 if n == 8 else torch.bfloat16)
+    plan = compare(ql, ctx, Hq, Hkv, 128, f"eight waves, long lists {Hq}/{Hkv}", 0, torch.float32 if n == 8 else torch.bfloat16)
+    assert plan.stat(11) == 8
     w = wl.make_ragged("long lists", np.asarray(ql, np.int32) + np.asarray(ctx, np.int32), np.asarray(ql, np.int32), Hq, Hkv, 128, 1 << 14, 78, device=DEV,
                        keep_f32=False)
     d = wl.small_paged(seed=79, n=3, lo=1, hi=100, Hq=Hq, Hkv=Hkv, d=128, token_budget=500, device=DEV, keep_f32=False)

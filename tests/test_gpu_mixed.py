@@ -91,25 +91,27 @@ def test_mixed_step_order_of_workgroups(prefill, rows):
 
 
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("heads, n, lo, hi", [((64, 2), 4, 200, 256), ((64, 4), 24, 20, 90), ((16, 8), 20, 130, 256),
-                                              ((32, 16), 9, 128, 257), ((12, 2), 40, 1, 256)])
-def test_two_heads_per_workgroup(heads, n, lo, hi, out_dtype):
-    """Long key lists, enough workgroups: the prefill call takes two heads per workgroup, the fused step one, with
+@pytest.mark.parametrize("heads, n, lo, hi", [((64, 2), 4, 200, 256), ((64, 4), 24, 20, 90), ((8, 4), 20, 130, 256),
+                                              ((32, 16), 9, 128, 257), ((12, 2), 30, 1, 256)])
+def test_eight_waves_to_a_workgroup(heads, n, lo, hi, out_dtype):
+    """Long key lists, full rounds: the prefill call has eight waves to a workgroup, the fused step four on the same query tiles, with
     the same arithmetic per query row.  2, 6, 16 and 32 heads per KV head, tiles of one request and of several."""
     rng = np.random.default_rng(95)
     ql = rng.integers(lo, hi + 1, size=n).astype(np.int32)
     kv = ql + rng.integers(2200, 2700, size=n).astype(np.int32)
-    p = wl.make_ragged("pair", kv, ql, heads[0], heads[1], 128, 4096, 96, device=DEV, keep_f32=False)
+    kv, ql = H.with_eight_waves(kv, ql, *heads, 1 << 17, rows=128)
+    p = wl.make_ragged("pair", kv, ql, heads[0], heads[1], 128, 1 << 17, 96, device=DEV, keep_f32=False)
     d = wl.small_paged(seed=97, n=5, lo=1, hi=100, Hq=heads[0], Hkv=heads[1], d=128, token_budget=500, device=DEV, keep_f32=False)
-    plan = pk.pack_plan(kv, ql, token_budget=4096)
+    plan = pk.pack_plan(kv, ql, token_budget=1 << 17)
     plan.workspace_bytes(heads[0], heads[1], 128, pk.PK_BF16)
-    assert plan.stat(6) * heads[0] >= 512
-    fus_p, _ = run_both(p, d, 4096, 500, out_dtype)
-    req = rng.integers(0, n, size=300)
+    assert plan.stat(11) == 8 and plan.stat(12) == (32 if heads[0] // heads[1] >= 16 else 128)
+    assert heads != (12, 2) or plan.stat(6) < sum((x + 127) // 128 for x in ql)       # some tiles are shared
+    fus_p, _ = run_both(p, d, 1 << 17, 500, out_dtype)
+    req = rng.integers(0, len(ql), size=300)
     rows = np.stack([req, rng.integers(0, heads[0], size=300), rng.integers(0, ql[req])], axis=1).astype(np.int32)
     start = np.concatenate([[0], np.cumsum(ql)])
     got = fus_p.float().cpu().numpy()[start[rows[:, 0]] + rows[:, 2], rows[:, 1]]
-    H.assert_close(got, H.oracle_ragged(p, False, rows=rows), 0, f"two heads per workgroup, {heads}")
+    H.assert_close(got, H.oracle_ragged(p, False, rows=rows), 0, f"eight waves, {heads}")
 
 
 def test_mixed_step_with_an_empty_half_and_bad_arguments():

@@ -48,17 +48,21 @@ BAD = {"q_first": ("q", 0, float("nan")), "q_middle": ("q", 77, float("nan")), "
 
 
 @pytest.mark.parametrize("case", list(BAD))
-@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128), (12, 4, 128), (16, 2, 64)])
+@pytest.mark.parametrize("heads", [(4, 2, 128), (4, 2, 64), (16, 2, 128), (12, 2, 128), (12, 4, 128), (16, 2, 64)])
 @pytest.mark.parametrize("launch", ["packed", "padded", "mixed"])
 def test_nonfinite_values_reach_only_the_rows_that_see_them(launch, heads, case):
-    """Tiles of several requests; one head per workgroup, D = 64, two heads per workgroup, and in the pipeline also one head per
-    workgroup and D = 64.  A NaN makes exactly the rows that see it NaN; what a row that sees an infinity gives is not asked."""
+    """Both bodies and head dimensions, several heads of a request to a workgroup and (three heads per KV head, and six with eight waves) tiles
+    of several requests; eight waves with 16/2 and 12/2 heads.  A NaN makes exactly the rows that see it NaN; what a row that sees an infinity gives is not asked."""
     Hq, Hkv, d = heads
-    n = 150
+    waves = 8 if heads in ((16, 2, 128), (12, 2, 128)) else 4
+    n, budget = (150, 8192) if waves == 4 else (40, 8192) if Hq == 16 else (30, 1 << 18)
     rng = np.random.default_rng(51)
     ql = rng.integers(5, 61, size=n).astype(np.int32)
     ctx = rng.integers(600, 901, size=n) if Hq > 4 else rng.integers(0, 300, size=n)
-    w = wl.make_ragged("isolation", (ql + ctx).astype(np.int32), ql, Hq, Hkv, d, 8192, 52, DEV, keep_f32=False)
+    kv = (ql + ctx).astype(np.int32)
+    if waves == 8:
+        kv, ql = H.with_eight_waves(kv, ql, Hq, Hkv, budget, rows=1 if Hq == 16 else 128)
+    w = wl.make_ragged("isolation", kv, ql, Hq, Hkv, d, budget, 52, DEV, keep_f32=False)
     dec = wl.small_paged(seed=53, n=4, lo=1, hi=90, Hq=Hq, Hkv=Hkv, d=d, token_budget=500, device=DEV, keep_f32=False)
     dplan = pk.pack_plan(dec.kv_lens, np.ones_like(dec.kv_lens), None, None, 500)
     dws = pk.new_workspace(dplan, Hq, Hkv, d, pk.PK_BF16)
@@ -76,12 +80,13 @@ def test_nonfinite_values_reach_only_the_rows_that_see_them(launch, heads, case)
         return out
 
     plan = prefill(w)[1]
-    assert plan.stat(6) < n                                # requests share tiles
-    assert Hq != 16 or (plan.stat(6) * Hq >= 512 and plan.stat(1) >= 8 * 64 * 128 * plan.stat(6))
+    assert plan.stat(11) == waves and (plan.stat(12) < 128 or plan.stat(6) < len(ql))     # tiles of 128 rows: shared by requests
+    assert plan.stat(12) == {1: 32, 2: 64, 3: 128, 6: 128, 8: 32}[Hq // Hkv]
     # (of the padded schedule, whose lists are not shared, both kinds are light with one head per workgroup)
     assert plan.stat(8) == int(Hq == 4)
     clean = {t: run(t).float() for t in (torch.float32, torch.bfloat16)}
     which, req, value = BAD[case]
+    req %= n
     q0 = int(w.q_lens[:req].sum())
     sees = torch.zeros(w.q.shape[:2], dtype=torch.bool, device=DEV)
     if which == "q":

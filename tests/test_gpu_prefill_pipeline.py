@@ -15,10 +15,10 @@ DEV = "cuda"
 TAILS = {"half": 1, "half_full": 32, "second_half": 33, "full": 64}     # keys of the last tile
 
 
-def check(kv, ql, Hq, Hkv, d, what, light, rows=None):
-    w = wl.make_ragged(f"pipe_{what}", np.asarray(kv, np.int32), np.asarray(ql, np.int32), Hq, Hkv, d, 1 << 16, 31, device=DEV,
+def check(kv, ql, Hq, Hkv, d, what, light, rows=None, budget=1 << 16):
+    w = wl.make_ragged(f"pipe_{what}", np.asarray(kv, np.int32), np.asarray(ql, np.int32), Hq, Hkv, d, budget, 31, device=DEV,
                        keep_f32=False)
-    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=1 << 16)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=budget)
     ws = pk.new_workspace(plan, Hq, Hkv, d, pk.PK_BF16)
     out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
     pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
@@ -69,7 +69,9 @@ def test_tiles_of_several_requests(d):
 
 @pytest.mark.parametrize("tail", TAILS)
 def test_eight_waves(tail):
-    kv = np.asarray([64 * t + TAILS[tail] for t in (31, 40, 62, 63, 64, 65, 33, 34)], dtype=np.int32)
-    ql = np.asarray([1, 31, 32, 33, 64, 96, 127, 128], dtype=np.int32)
-    plan = check(kv, ql, 64, 8, 128, f"eight waves, {tail}", 0)
-    assert plan.stat(6) * 64 >= 512                 # (workgroups of one head each: the eight-wave kernel's limit)
+    """Lists of one to four tiles and around 64 and 128 entries, in a batch that is long on average."""
+    kv = np.asarray([64 * t + TAILS[tail] for t in (0, 1, 2, 3, 30, 62, 63, 64, 65, 126, 127, 128)], dtype=np.int32)
+    ql = np.minimum(kv, [1, 31, 32, 33, 64, 96, 127, 128, 17, 65, 97, 40])
+    kv, ql = H.with_eight_waves(kv, ql, 16, 2, 1 << 14)
+    plan = check(kv, ql, 16, 2, 128, f"eight waves, {tail}", 0, budget=1 << 14)
+    assert plan.stat(11) == 8

@@ -48,13 +48,14 @@ CASES = ["ramp", "falling", "late_outlier", "first_outlier", "far_below_zero", "
 
 @pytest.fixture
 def sized(request):
-    """(kv, ql) -> a batch for one of the prefill bodies (the pipeline with one or, with D = 128, two heads per workgroup) with its
-    heads; `.light`: what plan.stat(8) says of it."""
+    """(kv, ql) -> a batch for one of the prefill bodies (the pipeline with four waves to a workgroup or, with D = 128, eight) with its
+    heads; `.light` and `.waves`: what plan.stat(8) and plan.stat(11) say of it."""
     def batch(kv, ql):
         if batch.light:
             return np.asarray(kv, dtype=np.int32), np.asarray(ql, dtype=np.int32), 4, 2
-        return *H.with_long_requests(kv, ql), *((33, 3) if request.param == "four_waves" else (64, 2))
+        return (*H.with_long_requests(kv, ql), 33, 3) if batch.waves == 4 else (*H.with_eight_waves(kv, ql, 16, 2, 1024), 16, 2)
     batch.light = int(request.param == "light")
+    batch.waves = 8 if request.param == "eight_waves" else 4
     return batch
 
 
@@ -77,7 +78,7 @@ def test_prefill_softmax_extremes(case, d, sized):
         out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
         (pk.padded_prefill_attn if padded else pk.packed_prefill_attn)(plan, w.q, w.k, w.v, out, w.scale, ws)
         torch.cuda.synchronize()
-        assert plan.stat(9 if padded else 8) == sized.light
+        assert plan.stat(9 if padded else 8) == sized.light and plan.stat(11) == sized.waves
         H.assert_close(out.cpu().numpy(), want, 0, f"prefill {case} d={d} padded={padded} pipeline={pipeline}")
 
 
@@ -154,7 +155,7 @@ def test_prefill_scores_beyond_the_exponent_range(d, sized):
     out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
     pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
     torch.cuda.synchronize()
-    assert plan.stat(8) == sized.light
+    assert plan.stat(8) == sized.light and plan.stat(11) == sized.waves
     got = out.cpu().numpy()
     lo, hi = int(s0[1]), int(s0[2])                        # scores around -2000 nats there: checked loosely below
     keep = np.r_[0:lo, hi:got.shape[0]]
@@ -195,7 +196,8 @@ def test_prefill_rows_with_every_score_far_below_zero(d, sized):
     w.q.fill_(1e16)
     f = 2.0 - (torch.arange(w.k.shape[0], device=DEV) * 7 % 32).float() / 32
     w.k.copy_((-1e15 * f.view(-1, 1, 1)).expand(w.k.shape))
-    check_prefill_launches(w, H.oracle_ragged(w, False), slice(None), f"scores far below zero d={d}", sized.light)
+    plan = check_prefill_launches(w, H.oracle_ragged(w, False), slice(None), f"scores far below zero d={d}", sized.light)
+    assert plan.stat(11) == sized.waves
 
 
 def rows_that_rounding_cannot_turn(w, rows):
@@ -223,11 +225,12 @@ def test_prefill_with_large_finite_scores(size, heads):
     exponentials can take.  Copies of a key, in other key tiles too, have the same score and share the row.  Rows where
     the rounding of the sums decides between two keys are left out (under 1 in 50)."""
     Hq, Hkv, d = heads
-    two = Hq == 16                                        # enough workgroups and keys for two heads per workgroup
-    kv = np.asarray([4500, 4800] if two else [513, 200, 97, 640], dtype=np.int32)
-    ql = np.asarray([2100, 2050] if two else [513, 60, 97, 300], dtype=np.int32)
+    kv = np.asarray([513, 200, 97, 640], dtype=np.int32)
+    ql = np.asarray([513, 60, 97, 300], dtype=np.int32)
     if Hq == 30:                                          # the pipeline with one head per workgroup
         kv, ql = H.with_long_requests(kv, ql)
+    elif Hq == 16:                                        # and with eight waves
+        kv, ql = H.with_eight_waves(kv, ql, Hq, Hkv, 4096)
     w = wl.make_ragged("large_scores", kv, ql, Hq, Hkv, d, 4096, 33, DEV, keep_f32=False)
     w.q.mul_(size)
     w.k.mul_(size)
@@ -235,7 +238,7 @@ def test_prefill_with_large_finite_scores(size, heads):
     for s, L in zip(w.kv_start, w.kv_lens):
         a, b = rng.integers(0, int(L), size=(2, int(L) // 3))
         w.k[int(s) + torch.from_numpy(b).to(DEV)] = w.k[int(s) + torch.from_numpy(a).to(DEV)]
-    req = rng.integers(0, len(ql), size=600)
+    req = np.where(rng.random(600) < 0.1, rng.integers(0, len(ql), size=600), rng.integers(0, 4, size=600))
     rows = np.stack([req, rng.integers(0, Hq, size=600), rng.integers(0, ql[req])], axis=1).astype(np.int32)
     keep = rows_that_rounding_cannot_turn(w, rows)
     assert keep.mean() > 0.98
@@ -244,4 +247,4 @@ def test_prefill_with_large_finite_scores(size, heads):
     want = np.zeros(tuple(w.q.shape), dtype=np.float32)
     want[at] = H.oracle_ragged(w, False, rows=rows)
     plan = check_prefill_launches(w, want, at, f"scores of {size * size:g} {heads}", int(Hq == 4))
-    assert not two or (plan.stat(6) * Hq >= 512 and plan.stat(1) >= 32 * 64 * 128 * plan.stat(6))
+    assert plan.stat(11) == (8 if Hq == 16 else 4)

@@ -52,3 +52,15 @@ def test_tables_of_tiles_of_several_heads_are_no_slower_to_build(ql):
             plan.workspace_bytes(*heads, 128, pk.PK_BF16)
             best[heads] = min(best.get(heads, 1.0), time.perf_counter() - begin)
     assert max(best[32, 8], best[8, 1]) <= 1.2 * best[16, 16], best
+
+
+# waves of a workgroup, query rows of a tile: chunks of a 70B-shaped layer, lists too short for eight waves, two, four, six and eight heads per KV head, odd numbers
+@pytest.mark.parametrize("ql, ctx, Hq, Hkv, d, waves, rows", [
+    (*wl.config5_structure(0)[:2], 64, 8, 128, 8, 32), (*wl.config5_structure(0)[:2], 64, 8, 64, 4, 32), (wl.config2_lengths(0), [0] * 64, 32, 8, 128, 4, 32),
+    ([128] * 16, [12000] * 16, 32, 8, 128, 8, 64), ([128] * 16, [12000] * 16, 32, 16, 128, 8, 128), ([128] * 20, [12000] * 20, 48, 8, 128, 8, 128),
+    ([128] * 16, [6000] * 16, 32, 8, 128, 4, 32), ([200] * 64, [0] * 64, 16, 8, 128, 4, 64), ([200] * 64, [0] * 64, 24, 8, 128, 4, 128), ([200] * 64, [0] * 64, 8, 8, 128, 4, 128)])
+def test_waves_and_rows_of_a_workgroup(ql, ctx, Hq, Hkv, d, waves, rows):
+    plan = bound(ql, ctx, Hq, Hkv, d)
+    assert (plan.stat(11), plan.stat(12)) == (waves, rows)
+    plan.workspace_bytes(Hq, Hkv, d, pk.PK_F32)
+    assert (plan.stat(11), plan.stat(12)) == (0, 0)
