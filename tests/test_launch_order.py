@@ -73,8 +73,9 @@ def test_launches_end_with_short_lists(tiles_of, ql, heads):
 # with a compute unit for every tile of 128 rows and head: tiles of 128 rows where the one with the longest list has a wave without rows, several heads to a workgroup where it is full
 @pytest.mark.parametrize("ql, ctx, heads, shift", [([382, 407], 0, (8, 2, 128), 2), ([315, 400, 554, 490], 0, (8, 2, 128), 2), ([440] * 2, 0, (16, 8, 64), 2), ([211] * 6, 1161, (8, 1, 128), 2),
                                                    ([608], 0, (16, 2, 128), 2), ([609], 0, (16, 2, 128), 0), ([1000], 0, (16, 2, 128), 0), ([128] * 2, 4000, (32, 8, 128), 0),
-                                                   ([505] * 3, 0, (8, 4, 128), 1), ([57] * 7, 2500, (32, 8, 128), 2), ([128] + [20] * 12, [1000] + [0] * 12, (16, 8, 128), 2)])
+                                                   ([505] * 3, 0, (8, 4, 128), 1), ([461, 852, 403], 0, (16, 2, 128), 2), ([57] * 7, 2500, (32, 8, 128), 2), ([128] + [20] * 12, [1000] + [0] * 12, (16, 8, 128), 2)])
 def test_rows_of_a_tile_in_launches_that_leave_units_idle(tiles_of, ql, ctx, heads, shift):
-    assert tiles_of(ql, ctx, heads)[0] == shift
+    found, tiles = tiles_of(ql, ctx, heads)
+    assert found == shift and (shift < 2 or is_by_request(tiles))            # (all workgroups start at once: nothing to end earlier)
     if np.size(ctx) == 1 and shift == 2:
         assert tiles_of(list(ql) * 24, ctx, heads)[0] == {1: 2, 2: 1}.get(heads[0] // heads[1], 0)          # (more of the same fill the chip)
