@@ -431,8 +431,8 @@ int64_t pk_plan_stat(const pk_plan* plan, int what);
  *                            bring K/V tiles into LDS: 0 = copied straight
  *                            from memory into LDS, three K and two V stages
  *                            (default); 1 = staged through registers, two
- *                            stages with padded rows.  Same tile shape (128
- *                            query rows x 64 keys), same arithmetic.
+ *                            stages with padded rows.  Same query tiles and
+ *                            key tiles of 64, same arithmetic.
  *                            (pk_packed_mixed_step always runs pipeline 0.)
  * Errors: PK_EINVAL (NULL plan, unknown knob, value out of range). */
 #define PK_TUNE_DECODE_SPLIT 0

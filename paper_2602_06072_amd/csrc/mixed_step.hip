@@ -9,9 +9,11 @@
 // the decode runs spread evenly over the launch; the prefill workgroups keep their numbers modulo 8,
 // i.e. their XCD, so the heads of a KV head still share an L2.  The LSE merge of the decode partials
 // is a second, short launch.
-// What bounds it (32 chunks of a 70B-shaped layer + 480 decode rows, 12.2 ms): the prefill tiles alone take 10.3 ms, the
+// What bounds it (32 chunks of a 70B-shaped layer + 480 decode rows, 11.5 to 12.4 ms on different cards): the prefill tiles alone take 9.6 to 10.6 ms, the
 // decode alone 2.6; what decode workgroups cost is the slots that they take and 17.9 GB streaming next to
-// prefill tiles, about half of it each.  Eight-wave prefill workgroups here: 12.15 to 12.7 ms.
+// prefill tiles, about half of it each.  Eight-wave prefill workgroups here, with 128 rows to a tile: 12.15 to 12.7 against 12.2 ms.
+// The query tiles are the prefill call's, also where that has eight waves and with fewer than eight heads per KV head twice the rows: 8 chunks with 32/8 heads
+// and 200 decode rows 2136 us with tiles of 64 rows and two heads, 2129 with 32 and four; 16 x 128 rows behind some 9000 tokens 512 and 515.
 #include "decode_body.hip.h"
 #define PK_WAVES 4
 #define PK_D 128

@@ -15,7 +15,7 @@
 // the math of tile j.  MFMA-bound: 4*D flops per (query, key) pair.
 // This register-staged kernel is the second pipeline (pk_plan_tune, PK_TUNE_PREFILL_PIPELINE = 1);
 // by default both head dimensions run the direct-to-LDS kernels of prefill_pipe.hip (same tables,
-// same tile shape, same arithmetic).
+// same query tiles, same arithmetic).
 
 #include <mutex>
 

@@ -13,7 +13,7 @@
 //     form costs more of it (MFMAs alone on random operands: 1.75 PFLOP/s at 1.70 GHz against 2.07 at 2.02).
 
 // Device code only: included by prefill_pipe.hip (the prefill launch) and by mixed_step.hip (the
-// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4, or 8 for two query heads of
+// fused prefill + decode launch).  The includer defines PK_D (the head dimension), PK_WAVES (4, or 8 for twice the query heads of
 // a KV head) and PK_DNS (the namespace this instance goes into) first; the file may be included once per combination.
 #include <cstdint>
 
@@ -34,7 +34,7 @@ constexpr int TILE_BYTES = BN * ROWB;              // 16 KiB (8 KiB for D = 64)
 constexpr int KS = D / 32;                         // contraction steps of a score
 constexpr int OPS = D / 16;                        // LDS operands per half tile, of K (two blocks of 16 keys x KS) as of V (blocks of 16 columns)
 constexpr int NC = 2;                              // column blocks of a wave: block c holds its rows 16 c .. + 15
-constexpr int WAVES = PK_WAVES;                     // 4, or 8: waves 4 .. 7 work on the next head
+constexpr int WAVES = PK_WAVES;                     // 4, or 8: twice the heads on the same K/V tiles
 constexpr int PIECES = TILE_BYTES / (1024 * WAVES);   // 1-KiB copy instructions per wave and tile
 constexpr int RPW = BN / WAVES, PPS = RPW / 8;        // rows (and copies) of a slab that one wave fills
 

@@ -71,7 +71,7 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     // compute unit reads 256 KiB of LDS and writes 64), and the energy they take.  What it costs: nothing runs beside a workgroup's first loads
     // and last stores, and a chip that is not full has fewer compute units at work.  Four / eight waves with 128 rows and one head / two (the
     // padded launch; on query tiles of several heads ahead_with_eight in schedule.cpp weighs the two):
-    //   32 chunks of a 70B-shaped layer (126 key tiles on average)  10.42 / 10.32 ms
+    //   32 chunks of a 70B-shaped layer (140 key tiles on average)  10.42 / 10.32 ms
     //   1 x 4096 rows behind 8192 (160 tiles, 1024 four-wave workgroups)  573 / 549 us
     //   2 x 3000 behind 3000 with 16 heads (71 tiles, 752 workgroups)     252 / 225 us
     //   32 x 1024 behind 2048 (40 tiles)  1225 / 1216 us;  8 x 4096 (32 tiles)  979 / 981 us;  32 x 1024 behind 1024 (24 tiles)  782 / 786 us

@@ -6,9 +6,10 @@
 // and may span requests; a tile lists only the key tiles that hold at least
 // one unmasked pair for it, and each key tile says per wave (32 query rows)
 // whether that wave skips it, computes it with the mask, or computes it
-// without any mask.  With an even number of query heads per KV head the rows
-// of several heads of one request are packed into a workgroup instead
-// (emit_head_tiles).
+// without any mask.  With an even number of query heads per KV head a
+// workgroup takes the rows of several heads of one request instead
+// (emit_head_tiles), but for launches that leave units idle and for eight
+// waves with two or six heads per KV head.
 #include <algorithm>
 #include <cmath>
 #include <numeric>
@@ -446,7 +447,8 @@ bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) 
 // Rows of a query tile (32 << shift) where `waves` waves of a workgroup may take them for several of the r heads of a KV head (emit_head_tiles).
 int head_tile_shift(int r, int waves) { return r % waves == 0 ? 0 : r % (waves / 2) == 0 ? 1 : 2; }
 
-// The eight-wave kernel (twice the heads per workgroup) may be taken for such a launch: prefill_pipe.hip has both sides' figures (tiles as above).
+// The eight-wave kernel (twice the heads per workgroup) may be taken for such a launch: prefill_pipe.hip has both sides' figures (tiles as above).  The padded launch goes
+// by this alone; the packed one is held to longer lists by ahead_with_eight, which its rounds, at most half as many, cannot satisfy below 126 key tiles.
 bool eight_waves(int64_t tiles, int64_t key_tiles, int Hq, int Hkv, int d) {
     return d == 128 && Hq / Hkv % 2 == 0 && tiles * Hq >= 512 && key_tiles >= 32 * tiles;
 }
@@ -459,8 +461,9 @@ bool eight_waves(int64_t tiles, int64_t key_tiles, int Hq, int Hkv, int d) {
 //   2023 / 1967, 32 x 1024 behind 2048 2436 / 2408, 4 x 300 behind 6000 (320 workgroups / 640) 295 / 255;
 //   32/8: 2 x 1024 behind 8192 (256 / 512) 240 / 251, 16 chunks 2860 / 2798, 4 x 8192 1886 / 1860;  48/8: 4 x 300 behind 6000 (288 / 480) 295 / 175;
 //   16/2: 2 x 1024 behind 8192 (128 / 256) 201 / 155, 1 x 4096 behind 8192 305 / 297.
-// Over 120 launches of more than 32 key tiles a list this choice takes 0.4 % more than the faster one of the two, 6 % at worst (16 x 256 behind 4000, 16/8); four
-// waves everywhere 0.7 %, eight everywhere 3 %, and up to 70 %.
+// Over 120 launches of more than 32 key tiles a list this choice takes 0.4 % more than the faster one of the two; four
+// waves everywhere 0.7 %, eight everywhere 3 %, and up to 70 %.  Over 90 launches in which it takes eight waves they are 1.8 % ahead of four, between 11 % ahead and 10 % behind (36 x 149 behind
+// some 10000, 8/2 296 / 268; 16 x 128 behind some 9000, 32/8 316 / 286), and never behind 128 rows and two heads to a workgroup.
 bool ahead_with_eight(const pk_plan& plan, int64_t tiles, int64_t key_tiles, int Hq, int Hkv, int num_cus) {
     const int r = Hq / Hkv;
     auto workgroups = [&](int waves) {
