@@ -10,6 +10,7 @@
 #include <iostream>
 #include <sstream>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/packinfer.h"
@@ -72,7 +73,7 @@ int main(int argc, char** argv) {
                     (void)pk_plan_stat(plan, 6); (void)pk_plan_stat(plan, 7);
                     CHECK(pk_kv_buf_bytes(plan, 2, d, PK_BF16) == static_cast<size_t>(pk_plan_buf_tokens(plan)) * 2 * d * 4, "kv_buf bytes");
                 }
-                (void)pk_workspace_bytes(plan, 32, 1, 128, PK_BF16);
+                for (const auto& heads : {std::pair<int, int>{32, 1}, {16, 16}, {64, 8}, {12, 2}, {28, 4}, {8, 4}}) (void)pk_workspace_bytes(plan, heads.first, heads.second, 128, PK_BF16);
                 (void)pk_workspace_bytes(plan, 3, 1, 96, PK_F32);
                 CHECK(pk_plan_tune(plan, PK_TUNE_DECODE_SPLIT, 64) == PK_OK, "tune");
                 (void)pk_workspace_bytes(plan, 8, 2, 128, PK_BF16);

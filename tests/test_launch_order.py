@@ -79,3 +79,18 @@ def test_rows_of_a_tile_in_launches_that_leave_units_idle(tiles_of, ql, ctx, hea
     assert found == shift and (shift < 2 or is_by_request(tiles))            # (all workgroups start at once: nothing to end earlier)
     if np.size(ctx) == 1 and shift == 2:
         assert tiles_of(list(ql) * 24, ctx, heads)[0] == {1: 2, 2: 1}.get(heads[0] // heads[1], 0)          # (more of the same fill the chip)
+
+
+@pytest.mark.parametrize("heads", [(8, 1, 128), (16, 2, 64), (16, 4, 128), (32, 8, 128), (8, 4, 64), (16, 8, 128), (6, 1, 128)])
+def test_tiles_of_several_heads_cover_every_row_once(tiles_of, heads):
+    """Every row of every request in one tile of 32 or 64 rows, which sees the keys up to its last row's; sets of four tiles dealt over the XCDs leave none out."""
+    rng = np.random.default_rng(heads[0])
+    for _ in range(12):
+        n = int(rng.integers(1, 60))
+        ql, ctx = rng.integers(1, int(rng.choice([40, 300, 2500])), size=n), rng.integers(0, int(rng.choice([1, 100, 5000])), size=n)
+        shift, tiles = tiles_of(ql, ctx, heads)
+        if shift == 2:
+            continue                               # (a launch that leaves units idle)
+        want = {(i, t, min(32 << shift, int(ql[i]) - t)) for i in range(n) for t in range(0, int(ql[i]), 32 << shift)}
+        assert sorted(t[:3] for t in tiles) == sorted(want)
+        assert all(n_kv == (int(ctx[i]) + t + rows + 63) // 64 for i, t, rows, n_kv in tiles)
