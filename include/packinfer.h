@@ -248,7 +248,10 @@ int pk_packed_decode_attn(pk_plan* plan, const void* q, const void* kv_buf,
  * the HBM-bound decode work runs beside the matrix-bound prefill work on the
  * same compute units; the LSE merge of the decode partials follows as a
  * second launch.  Results are those of pk_packed_prefill_attn and
- * pk_packed_decode_attn (same arithmetic per tile and per work item).
+ * pk_packed_decode_attn (same arithmetic per tile and per work item; where the
+ * prefill call cuts long key-tile lists into pieces, pk_plan_stat 13, and the
+ * decode half outlasts the whole lists, they stay whole here, and the prefill
+ * results are that call's but for rounding).
  *   prefill half: prefill_plan, q, k, v, out, prefill_workspace (as for
  *                 pk_packed_prefill_attn)
  *   decode half:  decode_plan (q_lens == 1), decode_q, kv_buf (written by
@@ -397,7 +400,7 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
                           int dtype, int out_dtype,
                           void* workspace, size_t workspace_bytes, void* stream);
 
-/* Counts for the benchmark's work accounting (host).  1..12 refer to the
+/* Counts for the benchmark's work accounting (host).  1..13 refer to the
  * tables of the head shape the plan was last sized or bound for (0 before).
  *   what = 0: unmasked (query,key) pairs per head summed over requests
  *   what = 1: (query,key) pairs issued to the MFMA units by the packed
@@ -416,6 +419,8 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
  *             prefill half of a mixed step always has 4; 0: no bf16 tables)
  *   what = 12: query rows of its tiles: 128, or 64 or 32 (a request's alone)
  *             which the workgroup's waves take for several heads
+ *   what = 13: pieces that the packed prefill works on where it cuts long
+ *             key-tile lists (few workgroups), 0 where it does not
  */
 int64_t pk_plan_stat(const pk_plan* plan, int what);
 

@@ -282,11 +282,11 @@ extern "C" int pk_kv_reorganize(pk_plan* plan, const void* k_pages, const void* 
     });
 }
 
-// args_out != nullptr: validate, bind and fill the kernel arguments, but launch nothing (the fused step)
+// args_out != nullptr: validate, bind and fill the kernel arguments, but launch nothing (the fused step, whose decode half takes some beside_us)
 static int prefill_common(pk_plan* plan, const void* q, const void* k, const void* v, void* out,
                           float scale, int Hq, int Hkv, int d, int dtype, int out_dtype,
                           void* workspace, size_t workspace_bytes, void* stream, bool padded,
-                          PrefillArgs* args_out = nullptr, const char* who_override = nullptr) {
+                          PrefillArgs* args_out = nullptr, const char* who_override = nullptr, double beside_us = 0) {
     const char* who = who_override ? who_override : padded ? "pk_padded_prefill_attn" : "pk_packed_prefill_attn";
     std::string why;
     if (!plan) return fail(PK_EINVAL, std::string(who) + ": plan is NULL");
@@ -320,6 +320,16 @@ static int prefill_common(pk_plan* plan, const void* q, const void* k, const voi
     a.total_q_rows = tq; a.total_kv_rows = tkv;
     a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.scale = scale; a.out_f32 = out_dtype == PK_F32;
     a.pipeline = plan->tune_prefill_pipeline;
+    // Beside a decode half that goes on for as long, whole lists cost a mixed step nothing, and what pieces write and read, and their second launch, does (whole / pieces:
+    // 1 x 405 rows behind 2368 with 16/16 heads beside 47 rows of 85 us 93 / 101 us, 1 x 579 behind 1140 with 8/8 and d = 64 beside 45 us 49 / 55).  Beside a short one both
+    // halves are over before that matters (1 x 1353 with 8/2 beside 25 us 31.7 / 31.8).
+    const bool hidden = args_out && beside_us >= 25 && beside_us + 8 >= s.whole_us;
+    const bool pieces = !hidden && (args_out || plan->tune_prefill_pipeline == 0);       // (the register-staged kernel takes whole lists)
+    if (s.n_merges > 0 && pieces) {
+        a.tiles = tab(plan, s.pieces); a.n_tiles = s.n_pieces; a.kvtiles = tab(plan, s.piece_kvtiles); a.row_shift = s.piece_shift;
+        a.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_offset);
+        a.merges = tab(plan, s.merges); a.n_merges = s.n_merges;
+    }
     if (args_out) { *args_out = a; return PK_OK; }
     const int e = dtype == PK_BF16 ? launch_prefill_bf16(a, stream) : launch_prefill_f32(a, stream);
     return e ? hip_fail(who, e) : PK_OK;
@@ -436,8 +446,9 @@ extern "C" int pk_packed_mixed_step(pk_plan* prefill_plan, const void* q, const 
                                   prefill_workspace_bytes, stream, false, nullptr, who);
         PrefillArgs pa{};
         DecodeArgs da{};
+        const double decode_us = static_cast<double>(decode_plan->unique_tokens) * Hkv * d * 4 / 6.2e6;        // (its K/V rows at 6.2 TB/s)
         int rc = prefill_common(prefill_plan, q, k, v, out, scale, Hq, Hkv, d, dtype, out_dtype, prefill_workspace,
-                                prefill_workspace_bytes, stream, false, &pa, who);
+                                prefill_workspace_bytes, stream, false, &pa, who, decode_us);
         if (rc != PK_OK) return rc;
         rc = decode_common(who, decode_plan, decode_q, kv_buf, decode_out, scale, 0, Hq, Hkv, d, dtype, out_dtype,
                            decode_workspace, decode_workspace_bytes, stream, false, &da);
@@ -595,6 +606,7 @@ extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
             case 10: return plan->tables.dec.n_items == 0 ? 0 : plan->tables.dec.group ? 4 : 1;
             case 11: return plan->tables.dtype == PK_BF16 ? (plan->tables.packed.eight ? 8 : 4) : 0;
             case 12: return plan->tables.dtype == PK_BF16 ? 32 << plan->tables.packed.row_shift : 0;
+            case 13: return plan->tables.packed.n_pieces;
             default: return 0;
         }
     });

@@ -41,4 +41,8 @@ __device__ __forceinline__ float wave_sum(float x) {
     return x;
 }
 
+// Cache policy of a buffer store: through the L2 to memory, not left in it until it is evicted or the launch is over.  Beside work that streams at the rate of the memory
+// a line evicted later, alone, costs it many times its own time (64 workgroups' 4.4 MB beside 1.15 GB of reads: 13 us).
+constexpr int kWriteThrough = 16;
+
 }  // namespace pk

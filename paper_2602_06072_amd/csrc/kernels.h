@@ -78,6 +78,9 @@ struct PrefillArgs {
     int eight;                                      // pipeline 0: workgroups of eight waves
     int row_shift;                                  // a query tile has 32 << row_shift rows; a workgroup's waves take them 32 at a time, for as many heads as there are waves
     int light;                                      // pipeline 0: a launch of little work, prefill_few_body.hip.h
+    // lists cut into pieces (light launches): `tiles` are the pieces then, and what they leave in `part` is put together by a second launch
+    float* part;
+    const int32_t* merges; int32_t n_merges;        // [n_merges][4] first slot, pieces, Q row of tile row 0, rows of a tile whose list is cut
     int heads_per_kv; FastDiv by_r, by_hkv;         // set by the launches of pipeline 0: workgroups per (query tile, KV head), divisions by it and by Hkv
 };
 #if defined(__HIPCC__)
@@ -104,6 +107,7 @@ __device__ __forceinline__ void prefill_tile_row(const PrefillArgs& a, int tile,
 #endif
 int launch_prefill_bf16(const PrefillArgs& a, void* stream);
 int launch_prefill_f32(const PrefillArgs& a, void* stream);
+int launch_prefill_merge_bf16(const PrefillArgs& a, void* stream);   // nothing where no list is cut; heads_per_kv and the divisions set
 // prefill tiles and decode work items of one step in one launch (bf16, d = 128), then the LSE merge
 int launch_mixed_step_bf16(const PrefillArgs& pa, const DecodeArgs& da, void* stream);
 

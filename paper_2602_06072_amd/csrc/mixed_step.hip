@@ -146,7 +146,8 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
         else if (da.arrived) hipLaunchKernelGGL(mixed_step64_group_kernel, wgs, dim3(256), 0, st, pa, da, m);
         else hipLaunchKernelGGL(mixed_step64_kernel, wgs, dim3(256), 0, st, pa, da, m);
     }
-    const int e = static_cast<int>(hipGetLastError());
+    int e = static_cast<int>(hipGetLastError());
+    if (e == 0) e = launch_prefill_merge_bf16(pa, stream);
     if (e != 0) return e;
     return da.arrived ? 0 : launch_decode_merge_bf16(da, stream);
 }

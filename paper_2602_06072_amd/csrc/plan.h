@@ -83,6 +83,12 @@ struct DeviceTables {
         TableRef runs;              // (first tile row, its Q row, lo, its hi) of the runs after a tile's first
         TableRef kvtiles;           // [n_kv_total][2] k_start, n | codes << 8 (2 bits per 32 rows: 0 skip, 1 masked, 2 unmasked); with
                                     // row_shift < 2 a list per request, which its query tiles share (all codes 2)
+        // lists cut into pieces (split_lists): what the launch works on instead of `tiles`
+        TableRef pieces;            // [n_pieces][16] descriptors of the pieces, and in the last word the slot of their partial results + 1 (0: a whole list)
+        TableRef merges;            // [n_merges][4] first slot, pieces, Q row of tile row 0, rows of every tile whose list is cut
+        TableRef piece_kvtiles;     // their key-tile lists
+        int32_t n_pieces = 0, n_merges = 0, piece_shift = 2;      // (piece_shift: their row_shift)
+        double whole_us = 0, pieces_us = 0;                       // estimates of the launch with whole lists and in pieces
         int32_t n_tiles = 0;
         int64_t issued_pairs = 0;
         int32_t n_query_tiles = 0;  // packed: of 128 rows, whatever row_shift is
@@ -99,6 +105,7 @@ struct DeviceTables {
     size_t tables_bytes = 0;
     size_t partial_offset = 0;      // bytes
     size_t partial_bytes = 0;
+    size_t prefill_part_bytes = 0;  // of them, partial results of pieces of key-tile lists
     size_t total_bytes = 0;
     size_t decode_only_bytes = 0;   // tables + the packed decode partials alone (what the static scratch must hold),
                                     // dec.group: as they would be with a wave per work item

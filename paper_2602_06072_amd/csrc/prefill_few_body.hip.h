@@ -70,6 +70,8 @@ struct WorkUnit {
     int qrow, lo, hi;                  // this lane's query row (-1: padding) and its key range [lo, hi)
     const int32_t* kvt;                // key-tile list of the query tile: (first key row, info) pairs
     int k_end, full;                   // keys from k_end on are not the tile's; up to `full` all of this wave's rows see them (row_shift < 2)
+    int slot;                          // of this piece of a cut list (-1: the list is whole)
+    int64_t record;                    // slot >= 0: where this wave's partial results go (PartialRecord)
     int64_t row_bytes;                 // bytes between consecutive K/V rows in global memory
     uint32_t row_bytes32;              // the same in 32 bits
 };
@@ -95,6 +97,7 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
 #pragma unroll
     for (int x = 0; x < 3; ++x) { u.ks[x] = desc[8 + x]; u.info[x] = desc[11 + x]; }
     u.k_end = desc[14];
+    u.slot = desc[15] - 1;
     const int tid = threadIdx.x;
     u.lane = tid & 63; u.n = u.lane & 31; u.hlf = u.lane >> 5;
     u.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -104,6 +107,7 @@ __device__ __forceinline__ bool setup(const PrefillArgs& a, const int block, Wor
     const int part = u.wave & ((1 << a.row_shift) - 1), mate = u.wave >> a.row_shift;
     u.head = ((u.kvh * groups + group) << (2 - a.row_shift)) + mate;
     u.rows = (block >> 8) & 1 ? (1 << a.row_shift) - 1 - part : part;
+    u.record = ((static_cast<int64_t>(u.slot) * a.Hkv + u.kvh) * groups + group) * WAVES + (mate << a.row_shift) + u.rows;
     u.n_active = u.n_kv - ((desc[3] >> (8 * u.rows)) & 0xFF);
     u.n_lead = min((desc[2] >> (8 * u.rows)) & 0xFF, u.n_active);
     prefill_tile_row(a, tile, desc[4], desc[5], desc[6], desc[7], u.rows * 32 + u.n, u.qrow, u.lo, u.hi);
@@ -154,6 +158,28 @@ __device__ __forceinline__ float row_scale(const float l) {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
     const float twice = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     return twice == 0.f ? 0.f : 2.f / twice;
+}
+
+// What a piece of a cut list leaves of the 32 rows and one head of a wave: its accumulators as they lie in the registers, and of every row the sum and the
+// two words of its reference.  prefill_merge puts the pieces of a list together.
+struct PartialRecord {
+    floatx4 o[DB][4][64];
+    floatx4 row[64];                               // row sum, m_ref, far
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t record_of(PartialRecord* p) {
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, static_cast<int>(sizeof(PartialRecord)), 0x00020000);
+}
+__device__ __forceinline__ void store_partial(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], const float l, const float m_ref, const float far) {
+    if (__builtin_amdgcn_ballot_w64(u.qrow >= 0) == 0) return;
+    const __amdgpu_buffer_rsrc_t rec = record_of(reinterpret_cast<PartialRecord*>(a.part) + u.record);
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const floatx4 x = {o[b][4 * q4], o[b][4 * q4 + 1], o[b][4 * q4 + 2], o[b][4 * q4 + 3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rec, 16 * u.lane, (4 * b + q4) * 1024, kWriteThrough);
+        }
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, floatx4{l, m_ref, far, 0.f}), rec, 16 * u.lane, 4 * DB * 1024, kWriteThrough);
 }
 
 // o / l to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
@@ -551,6 +577,69 @@ __device__ __forceinline__ bf16x8 stream_operand(const unsigned char* const (&kp
     }
 #endif
 
+// The rows of a tile whose list was cut: the partial results of its pieces, each weighted by its reference against the largest of them, in the order of
+// their slots.  A workgroup has the 32 rows and one head of a wave of prefill_tile_body, wave b of it the columns 32 b .. + 31: `unit` counts (list, KV head,
+// workgroup of the KV head, wave).  A reference is a score times sc and an offset (offset_of), so that those of far rows are subtracted before they are scaled.
+// Bound by latency, two round trips to memory for every four pieces and 4 to 7 us with the launch.  (In the first launch instead, by the workgroup that finishes the last
+// piece of a list: one workgroup then reads 68 KiB a piece, in a mixed step 3 x 90 rows behind some 9000 tokens with 4/1 heads 27.8 -> 43.3 us.)
+__device__ __forceinline__ void prefill_merge(const PrefillArgs& a, const int unit) {
+    constexpr int BATCH = 4;                       // pieces whose accumulators are requested together
+    const int wid = unit & 3, x = unit >> 2, p = a.by_r(x), group = x - p * a.heads_per_kv, entry = a.by_hkv(p), kvh = p - entry * a.Hkv;
+    const int32_t* e = a.merges + 4 * static_cast<int64_t>(entry);
+    const int slot0 = e[0], pieces = e[1], q0 = e[2], n_rows = e[3];
+    const int lane = threadIdx.x & 63, b = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)), n = lane & 31, hlf = lane >> 5;
+    const int row = (wid & ((1 << a.row_shift) - 1)) * 32 + n;
+    if (row - n >= n_rows) return;
+    const int64_t stride = static_cast<int64_t>(a.Hkv) * a.heads_per_kv * WAVES;
+    const PartialRecord* rec = reinterpret_cast<const PartialRecord*>(a.part) + ((static_cast<int64_t>(slot0) * a.Hkv + kvh) * a.heads_per_kv + group) * WAVES + wid;
+    const float sc = a.scale * kLog2e;
+    auto beyond = [&](const float m1, const float far1, const float m0, const float far0) {    // reference 1 minus reference 0, in octaves
+        return __builtin_fmaf(far1 - far0, sc, offset_of(m1, far1) - offset_of(m0, far0));
+    };
+    float m = kUnset, far = 0.f;
+    bool any = false;
+    for (int s = 0; s < pieces; s += 2 * BATCH) {  // the reference farthest up
+        floatx4 r[2 * BATCH];
+#pragma unroll
+        for (int y = 0; y < 2 * BATCH; ++y) r[y] = rec[min(s + y, pieces - 1) * stride].row[lane];
+#pragma unroll
+        for (int y = 0; y < 2 * BATCH; ++y)        // (a piece that a row sees nothing of has none; the last one repeated changes nothing)
+            if (r[y][0] != 0.f && (!any || beyond(r[y][1], r[y][2], m, far) > 0.f)) { m = r[y][1]; far = r[y][2]; any = true; }
+    }
+    float l = 0.f;
+    floatx4 o[4] = {};
+    for (int s = 0; s < pieces; s += BATCH) {
+        floatx4 r[BATCH], v[BATCH][4];
+#pragma unroll
+        for (int y = 0; y < BATCH; ++y) {
+            const PartialRecord& t = rec[min(s + y, pieces - 1) * stride];
+            r[y] = t.row[lane];
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) v[y][q4] = t.o[b][q4][lane];
+        }
+#pragma unroll
+        for (int y = 0; y < BATCH; ++y) {
+            const float w = s + y < pieces && r[y][0] != 0.f ? __builtin_amdgcn_exp2f(beyond(r[y][1], r[y][2], m, far)) : 0.f;
+            l = __builtin_fmaf(w, r[y][0], l);
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[q4][c] = __builtin_fmaf(w, v[y][q4][c], o[q4][c]);
+        }
+    }
+    const float inv = row_scale(l);
+    if (row >= n_rows) return;
+    const int head = ((kvh * a.heads_per_kv + group) << (2 - a.row_shift)) + (wid >> a.row_shift);
+    const int64_t obase = (static_cast<int64_t>(q0 + row) * a.Hq + head) * D;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        const int col = 32 * b + 8 * q4 + 4 * hlf;
+        const floatx4 y = o[q4] * inv;
+        if (a.out_f32) *reinterpret_cast<float4*>(static_cast<float*>(a.out) + obase + col) = make_float4(y[0], y[1], y[2], y[3]);
+        else *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + obase + col) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+    }
+}
+
 // `block`: the workgroup's number in the prefill launch order; `lds`: 5 * TILE_BYTES, 1 KiB aligned
 // (K stages 0..2, V stages 3..4).
 __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const int block, unsigned char* lds) {
@@ -712,7 +801,8 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // After the last barrier nobody fills a stage any more, and what is still being read for a tile after
     // the last is not used: quarters of a K and a V stage stage the waves' output.
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
-    if (a.out_f32) store_output(a, u, o, lsum[0]);
+    if (u.slot >= 0) store_partial(a, u, o, lsum[0], m_ref, far);
+    else if (a.out_f32) store_output(a, u, o, lsum[0]);
     else store_output_bf16(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
 }
 

@@ -61,7 +61,22 @@ __global__ __launch_bounds__(256, 2) void prefill_bf16_few64_kernel(PrefillArgs 
     few64::prefill_tile_body(a, static_cast<int>(blockIdx.x), lds);
 }
 
+// Behind a launch of few workgroups whose lists are cut into pieces.
+__global__ __launch_bounds__(64 * few128::DB) void prefill_merge_kernel(PrefillArgs a) { few128::prefill_merge(a, static_cast<int>(blockIdx.x)); }
+__global__ __launch_bounds__(64 * few64::DB) void prefill_merge64_kernel(PrefillArgs a) { few64::prefill_merge(a, static_cast<int>(blockIdx.x)); }
+
 }  // namespace
+
+int launch_prefill_merge_bf16(const PrefillArgs& a, void* stream) {
+    const int64_t grid = static_cast<int64_t>(a.n_merges) * a.Hkv * a.heads_per_kv * 4;
+    if (grid == 0) return 0;
+    if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
+    if (a.d == 128)
+        hipLaunchKernelGGL(prefill_merge_kernel, dim3(static_cast<unsigned>(grid)), dim3(64 * few128::DB), 0, static_cast<hipStream_t>(stream), a);
+    else
+        hipLaunchKernelGGL(prefill_merge64_kernel, dim3(static_cast<unsigned>(grid)), dim3(64 * few64::DB), 0, static_cast<hipStream_t>(stream), a);
+    return static_cast<int>(hipGetLastError());
+}
 
 int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
     PrefillArgs a = args;
@@ -106,7 +121,8 @@ int launch_prefill_bf16_pipe(const PrefillArgs& args, void* stream) {
                            static_cast<hipStream_t>(stream), a);
     else
         return static_cast<int>(hipErrorInvalidValue);
-    return static_cast<int>(hipGetLastError());
+    const int e = static_cast<int>(hipGetLastError());
+    return e != 0 ? e : launch_prefill_merge_bf16(a, stream);
 }
 
 }  // namespace pk

@@ -662,6 +662,111 @@ void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, c
     s.issued_pairs = weight * 32 * BN;
 }
 
+// Launches whose time is that of a few workgroups with long lists (a chunk or a handful of rows behind a long context, few heads): the lists are cut into
+// pieces of (nearly) the same length, a workgroup each, and a second launch puts the pieces together (prefill_merge).  A key tile takes a workgroup 0.87 us
+// whether it has a compute unit to itself or shares it, so that a launch takes as long as its longest list or, if that is more, as all lists dealt over the units; pieces cost
+// a launch, a start each, and 17 KiB per 32 rows and head (9 with d = 64) that are written and read.  us, whole lists / pieces of the length that ListSplit
+// finds best, d = 128: 1 x 64 rows behind 8000 with 8/8 heads (8 workgroups of 126 key tiles) 113 / 22; 32/8 heads 1 x 16 behind 16000 217 / 29, behind 2000 30.7 / 14.9,
+// 1 x 128 behind 8192 127 / 30, 1 x 512 behind 8192 134 / 83, 4 x 100 behind 3000 52.0 / 38.5; 4/1 heads 8 of 68..112 behind up to 4600 71 / 21, 1 x 4096 64.7 / 35.3;
+// 8/2 heads 1 x 1105 20.6 / 19.0; d = 64: 1 x 64 behind 8000 with 8/8 88.8 / 17.7.  Of 800 launches (1 to 40 requests, up to 20000 keys, eleven head
+// shapes) 173 get pieces, twice as fast on average; one of them lost (1 x 1124 with 12/2 heads 21.1 / 21.7).
+struct ListSplit {
+    int d, num_cus;
+    double tile() const { return d == 64 ? 0.66 : 0.87; }          // us
+    // workgroups, their key tiles and the longest list
+    double run(double wgs, double total, int32_t longest) const {
+        const double per_cu = wgs / num_cus, rounds = per_cu <= 1 ? 1.0 : (per_cu + std::ceil(per_cu)) / 2;   // (one more on some units than on others)
+        return 6.0 + 1.5 * (rounds - 1) + tile() * std::max<double>(longest, rounds * total / wgs * (d == 64 && rounds > 1 ? 0.8 : 1.0));
+    }
+    double merge(double pieces, double most) const { return 5.0 + 0.3 * most + pieces * (d == 64 ? 0.008 : 0.012); }
+};
+void split_lists(const pk_plan& plan, const std::vector<int64_t>& q_start, const std::vector<int64_t>& kv_start, int Hq, int head_shift, int num_cus, Builder& b,
+                 DeviceTables& t) {
+    constexpr int32_t SHORTEST = 13;               // key tiles: the second launch takes as long as six
+    DeviceTables::PrefillSched& s = t.packed;
+    const int32_t* desc0 = b.host.data() + s.tiles.offset / sizeof(int32_t);
+    const int64_t units0 = static_cast<int64_t>(t.Hkv) * ((Hq / t.Hkv << s.row_shift) / 4);        // workgroups of a query tile
+    int32_t longest = 0;
+    int64_t total = 0;
+    for (int32_t x = 0; x < s.n_tiles; ++x) {
+        longest = std::max(longest, desc0[kTileDescWords * x + 1]);
+        total += desc0[kTileDescWords * x + 1];
+    }
+    if (longest < SHORTEST) return;
+    const ListSplit est{t.d, num_cus};
+    const double whole = est.run(static_cast<double>(s.n_tiles * units0), static_cast<double>(total * units0), longest);
+    double best = 0.92 * whole;
+    if (est.run(num_cus, static_cast<double>(total * units0), 0) + est.merge(0, 2) >= best) return;       // (all units busy from the first to the last)
+    // the pieces are of tiles of several heads where there are such: none of their waves is idle but for a request's last rows
+    const int64_t units = static_cast<int64_t>(t.Hkv) * ((Hq / t.Hkv << head_shift) / 4);
+    const int32_t rows = 32 << head_shift;
+    std::vector<int32_t> lists;
+    for (int32_t i = 0; i < plan.n; ++i)
+        for (int32_t t0 = 0, lq = plan.q_lens[i]; t0 < lq; t0 += rows) lists.push_back(key_tiles_to(plan.kv_lens[i] - lq + std::min(lq, t0 + rows)));
+    total = std::accumulate(lists.begin(), lists.end(), int64_t{0});
+    int32_t most = 0;
+    for (int32_t len = 4; len < longest; len += std::max(1, len / 4)) {
+        int64_t n = 0, pieces = 0;
+        int32_t parts = 1, piece = 0;
+        for (const int32_t l : lists) {
+            const int32_t p = (l + len - 1) / len;
+            n += p;
+            pieces += p > 1 ? p : 0;
+            parts = std::max(parts, p);
+            piece = std::max(piece, (l + p - 1) / p);
+        }
+        const double time = est.run(static_cast<double>(n * units), static_cast<double>(total * units), piece) + est.merge(static_cast<double>(pieces * units), parts);
+        if (time < best) { best = time; most = len; }
+    }
+    if (most == 0) return;
+    std::vector<int32_t> host;
+    Builder own(host);
+    DeviceTables::PrefillSched h = s;
+    const bool other = head_shift != s.row_shift;
+    if (other) emit_head_tiles(plan, q_start, kv_start, t.Hkv, head_shift, own, h);
+    const int32_t* tables = (other ? host : b.host).data();
+    const int32_t *desc = tables + h.tiles.offset / sizeof(int32_t), *kv = tables + h.kvtiles.offset / sizeof(int32_t);
+    std::vector<int32_t> pieces, merges;
+    int32_t slots = 0;
+    for (int32_t x = 0; x < h.n_tiles; ++x, desc += kTileDescWords) {
+        const int32_t n_kv = desc[1], n = std::max(1, (n_kv + most - 1) / most);
+        if (n > 1) {
+            const int32_t entry[4] = {slots, n, desc[5], desc[4] & 0xFFFF};
+            merges.insert(merges.end(), entry, entry + 4);
+        }
+        for (int32_t p = 0; p < n; ++p) {
+            const int32_t e0 = static_cast<int32_t>(static_cast<int64_t>(n_kv) * p / n), e1 = static_cast<int32_t>(static_cast<int64_t>(n_kv) * (p + 1) / n);
+            int32_t piece[kTileDescWords];
+            std::copy(desc, desc + kTileDescWords, piece);
+            piece[0] = desc[0] + e0;
+            piece[1] = e1 - e0;
+            piece[2] = piece[3] = 0;
+            for (int w = 0; w < 4; ++w) {          // where this wave's key tiles begin and end
+                const int32_t lead = desc[2] >> (8 * w) & 0xFF, trail = desc[3] >> (8 * w) & 0xFF;
+                piece[2] |= std::min(255, std::max(0, std::min(lead, e1) - e0)) << (8 * w);
+                piece[3] |= std::min(255, std::max(0, e1 - std::max(n_kv - trail, e0))) << (8 * w);
+            }
+            for (int32_t e = 0; e < 3; ++e)
+                for (int word = 0; word < 2; ++word) {
+                    const size_t at = 2 * (static_cast<size_t>(desc[0]) + std::max(0, std::min(e0 + e, e1 - 1)));
+                    piece[8 + 3 * word + e] = n_kv > 0 ? kv[at + word] : 0;
+                }
+            piece[15] = n > 1 ? ++slots : 0;
+            pieces.insert(pieces.end(), piece, piece + kTileDescWords);
+        }
+    }
+    if (merges.empty()) return;
+    s.n_pieces = static_cast<int32_t>(pieces.size() / kTileDescWords);
+    s.n_merges = static_cast<int32_t>(merges.size() / 4);
+    s.piece_shift = head_shift;
+    s.piece_kvtiles = other ? b.add(std::vector<int32_t>(kv, kv + h.kvtiles.count)) : s.kvtiles;
+    s.pieces = b.add(pieces);
+    s.merges = b.add(merges);
+    s.whole_us = whole;
+    s.pieces_us = best;
+    t.prefill_part_bytes = static_cast<size_t>(slots) * units * 4 * 64 * (2 * t.d + 16);
+}
+
 // packed: tiles over each group's packed row stream, heaviest tile first
 void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_start,
                           const std::vector<int64_t>& kv_start, int Hq, int num_cus, Builder& b, DeviceTables& t) {
@@ -716,6 +821,7 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     if (!plan.decode_only && t.dtype == PK_BF16 && row_shift < 2 && !spread) {
         emit_head_tiles(plan, q_start, kv_start, t.Hkv, row_shift, b, s);
         s.n_query_tiles = static_cast<int32_t>(n_tiles);
+        if (s.light) split_lists(plan, q_start, kv_start, Hq, row_shift, num_cus, b, t);
         return;
     }
     SchedBuild sb;
@@ -783,6 +889,7 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
     // (with a compute unit for each of them all workgroups start at once, and no order ends earlier: 461, 852 and 403 rows with 16/2 heads 18.3 by halvings, 17.9 by request)
     if (n_tiles * Hq <= num_cus || stays_by_request(rounds, (end_of(by_request) - end_of(order)) * slots / (work * Hq), read_again / work, Hq / t.Hkv, t.d)) order = by_request;
     emit_sched(sb, order, b, s);
+    if (!plan.decode_only && t.dtype == PK_BF16 && s.light && !may_share) split_lists(plan, q_start, kv_start, Hq, row_shift, num_cus, b, t);
 }
 
 }  // namespace
@@ -862,7 +969,7 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
     t.host.resize((t.host.size() + 63) / 64 * 64, 0);
     t.tables_bytes = t.host.size() * sizeof(int32_t);
     t.partial_offset = t.tables_bytes;
-    t.partial_bytes = static_cast<size_t>(t.dec.n_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
+    t.partial_bytes = static_cast<size_t>(t.dec.n_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float) + t.prefill_part_bytes;   // (no plan has both)
     t.decode_only_bytes = t.partial_offset + t.partial_bytes;
     if (t.dec.group) {
         // what the plan would need with a wave per item decides whether it may use the fixed scratch
