@@ -319,6 +319,7 @@ static int prefill_common(pk_plan* plan, const void* q, const void* k, const voi
     if (tkv > INT32_MAX) return fail(PK_EUNSUPPORTED, std::string(who) + ": more than 2^31 KV rows");
     a.total_q_rows = tq; a.total_kv_rows = tkv;
     a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.scale = scale; a.out_f32 = out_dtype == PK_F32;
+    a.through = tq * Hq * d * (a.out_f32 ? 4 : 2) >= 2 << 20;
     a.pipeline = plan->tune_prefill_pipeline;
     // Beside a decode half that goes on for as long, whole lists cost a mixed step nothing, and what pieces write and read, and their second launch, does (whole / pieces:
     // 1 x 405 rows behind 2368 with 16/16 heads beside 47 rows of 85 us 93 / 101 us, 1 x 579 behind 1140 with 8/8 and d = 64 beside 45 us 49 / 55).  Beside a short one both

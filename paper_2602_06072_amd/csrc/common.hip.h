@@ -41,8 +41,14 @@ __device__ __forceinline__ float wave_sum(float x) {
     return x;
 }
 
-// Cache policy of a buffer store: through the L2 to memory, not left in it until it is evicted or the launch is over.  Beside work that streams at the rate of the memory
-// a line evicted later, alone, costs it many times its own time (64 workgroups' 4.4 MB beside 1.15 GB of reads: 13 us).
-constexpr int kWriteThrough = 16;
+// 16 bytes to memory through the L2, not left in it: the end of a launch waits for nothing that is still there, and beside work that
+// streams at the rate of the memory a line evicted later, alone, costs it many times its own time (64 workgroups' 4.4 MB beside 1.15 GB of reads: 13 us).
+// For stores of whole lines only: a line put together from several instructions goes to memory once for each.
+constexpr int kWriteThrough = 16;                  // cache policy of a buffer store
+// The same at an address of each lane's own; no builtin makes such a store of 16 bytes.  The compiler does not know what the statement reads: two wait states keep
+// the instruction behind it from writing the data registers too early, and data must not come straight from an MFMA.
+__device__ __forceinline__ void write_through(void* p, const u32x4& x) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(x) : "memory");
+}
 
 }  // namespace pk

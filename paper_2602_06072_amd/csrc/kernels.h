@@ -78,6 +78,7 @@ struct PrefillArgs {
     int eight;                                      // pipeline 0: workgroups of eight waves
     int row_shift;                                  // a query tile has 32 << row_shift rows; a workgroup's waves take them 32 at a time, for as many heads as there are waves
     int light;                                      // pipeline 0: a launch of little work, prefill_few_body.hip.h
+    int through;                                    // of those: the output is written through the L2
     // lists cut into pieces (light launches): `tiles` are the pieces then, and what they leave in `part` is put together by a second launch
     float* part;
     const int32_t* merges; int32_t n_merges;        // [n_merges][4] first slot, pieces, Q row of tile row 0, rows of a tile whose list is cut

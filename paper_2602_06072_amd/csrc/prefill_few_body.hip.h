@@ -182,63 +182,72 @@ __device__ __forceinline__ void store_partial(const PrefillArgs& a, const WorkUn
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, floatx4{l, m_ref, far, 0.f}), rec, 16 * u.lane, 4 * DB * 1024, kWriteThrough);
 }
 
-// o / l to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
-__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], const float l) {
+// o / l in fp32 to global memory; lane (n, hlf) owns columns 32b + 8q + 4hlf .. +3 of its query row.
+__device__ __forceinline__ void store_output_f32(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB], const float l) {
     const float inv = row_scale(l);
     if (u.qrow < 0) return;
-    const int64_t obase = (static_cast<int64_t>(u.qrow) * a.Hq + u.head) * D;
+    float* out = static_cast<float*>(a.out) + (static_cast<int64_t>(u.qrow) * a.Hq + u.head) * D + 4 * u.hlf;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const int col = 32 * b + 8 * q4 + 4 * u.hlf;
-            const float x0 = o[b][4 * q4] * inv, x1 = o[b][4 * q4 + 1] * inv;
-            const float x2 = o[b][4 * q4 + 2] * inv, x3 = o[b][4 * q4 + 3] * inv;
-            if (a.out_f32) {
-                *reinterpret_cast<float4*>(static_cast<float*>(a.out) + obase + col) = make_float4(x0, x1, x2, x3);
-            } else {
-                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + obase + col) =
-                    make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
-            }
-        }
+        for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<float4*>(out + 32 * b + 8 * q4) = make_float4(o[b][4 * q4] * inv, o[b][4 * q4 + 1] * inv, o[b][4 * q4 + 2] * inv, o[b][4 * q4 + 3] * inv);
 }
 
-// bf16 output through LDS, so that every row leaves as whole 16-byte pieces (four rows of 256
-// bytes, or eight of 128, per store instruction) instead of 8-byte pieces of 32 different rows.
+// o / l through LDS, so that every row leaves as whole 16-byte pieces of ROWB bytes (four rows of 256
+// bytes, or eight of 128, per store instruction) instead of 8- or 16-byte pieces of 32 different rows: bf16 rows at once, fp32 rows half by half.
 // The wave uses two pieces of LDS of 16 rows each that belong to it alone (rows 0..15 in qa, rows
 // 16..31 in qb); the 16-byte chunks of a row are XOR-swizzled with the row number, which keeps
 // both sides off bank conflicts.
-__device__ __forceinline__ void store_output_bf16(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB],
-                                                  const float l, unsigned char* qa, unsigned char* qb) {
+// Outputs of 2 MiB and more (PrefillArgs::through) are written through the L2.  What stays in it is written back when the launch is over, and beside decode work that streams its
+// lines are evicted one at a time.  us, before / now: 15 x 30 rows with 32/8 heads 6.24 / 5.89, 20 x 24 with 64/8 8.21 / 7.36, 8 x 113 with 64/8 8.95 / 8.14, 4 x 436 with 32/8 and
+// d = 64 20.1 / 19.1; the mixed step, 16 x 32 rows behind 100 with 32/8 beside 255 decode rows 216.8 / 202.7, 4 x 429 beside 276 64.6 / 58.9, 7 x 113 with 64/8 beside 3 12.1 / 10.7.  Smaller
+// outputs wait longer for the memory than for the L2 (1 x 95 rows with 32/8, 0.8 MB: 11.6 / 11.9), and in fp32 go straight from the registers (LDS 0.5 us more).
+template <bool F32>
+__device__ __forceinline__ void store_output(const PrefillArgs& a, const WorkUnit& u, const floatx16 (&o)[DB],
+                                             const float l, unsigned char* qa, unsigned char* qb) {
     constexpr int CPR = D / 8, RPI = 64 / CPR;     // 16-byte chunks per row; rows per store instruction
     const float inv = row_scale(l);
-    const int rr = u.n & 15;
-    unsigned char* wrow = (u.n < 16 ? qa : qb) + rr * ROWB + 8 * u.hlf;
-#pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {       // columns 32b + 8q4 + 4hlf .. +3: chunk 4b + q4, half hlf
-            const float x0 = o[b][4 * q4] * inv, x1 = o[b][4 * q4 + 1] * inv;
-            const float x2 = o[b][4 * q4 + 2] * inv, x3 = o[b][4 * q4 + 3] * inv;
-            *reinterpret_cast<uint2*>(wrow + (((4 * b + q4) ^ (rr & (CPR - 1))) << 4)) =
-                make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
-        }
-    // all look-ups and reads before the first store: one by one, each would wait for its own LDS round trips
-    const int chunk = u.lane & (CPR - 1);
+    const int rr = u.n & 15, chunk = u.lane & (CPR - 1);
+    unsigned char* wrow = (u.n < 16 ? qa : qb) + rr * ROWB;
     int q_row[32 / RPI];
-    u32x4 v[32 / RPI];
 #pragma unroll
-    for (int k = 0; k < 32 / RPI; ++k) {
-        const int row = RPI * k + u.lane / CPR, r2 = row & 15;
-        q_row[k] = __shfl(u.qrow, row, 64);
-        v[k] = *reinterpret_cast<const u32x4*>((row < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
+    for (int k = 0; k < 32 / RPI; ++k) q_row[k] = __shfl(u.qrow, RPI * k + u.lane / CPR, 64);
+#pragma unroll
+    for (int half = 0; half < (F32 ? 2 : 1); ++half) {
+        constexpr int BLOCKS = F32 ? DB / 2 : DB;
+#pragma unroll
+        for (int b = 0; b < BLOCKS; ++b)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {       // columns 32 b + 8 q4 + 4 hlf .. + 3 (fp32: of this half)
+                const floatx16& ob = o[half * BLOCKS + b];
+                const float x0 = ob[4 * q4] * inv, x1 = ob[4 * q4 + 1] * inv, x2 = ob[4 * q4 + 2] * inv, x3 = ob[4 * q4 + 3] * inv;
+                const int at = F32 ? 8 * b + 2 * q4 + u.hlf : 4 * b + q4;
+                unsigned char* p = wrow + ((at ^ (rr & (CPR - 1))) << 4);
+                if constexpr (F32) *reinterpret_cast<float4*>(p) = make_float4(x0, x1, x2, x3);
+                else *reinterpret_cast<uint2*>(p + 8 * u.hlf) = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+            }
+        // all reads before the first store: one by one, each would wait for its own LDS round trips
+        u32x4 v[32 / RPI];
+#pragma unroll
+        for (int k = 0; k < 32 / RPI; ++k) {
+            const int row = RPI * k + u.lane / CPR, r2 = row & 15;
+            v[k] = *reinterpret_cast<const u32x4*>((row < 16 ? qa : qb) + r2 * ROWB + ((chunk ^ (r2 & (CPR - 1))) << 4));
+        }
+        asm volatile("" ::: "memory");             // (the reads stay before the branches below)
+        auto at = [&](const int k) {
+            return static_cast<unsigned char*>(a.out) + (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * (F32 ? 2 * ROWB : ROWB) + half * ROWB + 16 * chunk;
+        };
+        if (F32 || a.through) {
+#pragma unroll
+            for (int k = 0; k < 32 / RPI; ++k)
+                if (q_row[k] >= 0) write_through(at(k), v[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 32 / RPI; ++k)
+                if (q_row[k] >= 0) *reinterpret_cast<u32x4*>(at(k)) = v[k];
+        }
     }
-    asm volatile("" ::: "memory");                 // (the reads stay before the branches below)
-#pragma unroll
-    for (int k = 0; k < 32 / RPI; ++k)
-        if (q_row[k] >= 0)
-            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) +
-                                      (static_cast<int64_t>(q_row[k]) * a.Hq + u.head) * D + 8 * chunk) = v[k];
 }
 
 // Copies of K/V tiles into LDS stages.  A tile is TILE_BYTES / 1024 instructions of 1 KiB, PIECES of
@@ -802,8 +811,9 @@ __device__ __forceinline__ void prefill_tile_body(const PrefillArgs& a, const in
     // the last is not used: quarters of a K and a V stage stage the waves' output.
     PK_WAIT_ALL_COPIES();                          // (none is outstanding here; kept as a guard)
     if (u.slot >= 0) store_partial(a, u, o, lsum[0], m_ref, far);
-    else if (a.out_f32) store_output(a, u, o, lsum[0]);
-    else store_output_bf16(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
+    else if (a.out_f32 && !a.through) store_output_f32(a, u, o, lsum[0]);
+    else if (a.out_f32) store_output<true>(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
+    else store_output<false>(a, u, o, lsum[0], lds + k_next + u.wave * WAVE_PART, lds + v_cur + u.wave * WAVE_PART);
 }
 
 #undef PK_COPY_TILE
