@@ -195,22 +195,26 @@ int ensure_bound(pk_plan* plan, int Hq, int Hkv, int d, int dtype, void* workspa
     plan->bound_bytes = workspace_bytes;
     plan->bound_stamp = claim_workspace(workspace);
     t.padded_uploaded = false;
+    t.packed_uploaded = !plan->decode_only;
     return PK_OK;
 }
 
-// The padded comparison schedule is built and copied on its first use only.
-int ensure_padded(pk_plan* plan, void* stream) {
+// The padded comparison schedule, and the packed prefill schedule of a decode plan, are built and copied on their first use only.
+int ensure_schedule(pk_plan* plan, bool padded, void* stream) {
     DeviceTables& t = plan->tables;
-    if (!t.padded_built) build_prefill_padded(*plan, t);
-    if (t.padded_uploaded) return PK_OK;
-    if (t.padded_offset + t.host_padded.size() * sizeof(int32_t) > plan->bound_bytes)
+    if (padded && !t.padded_built) build_prefill_padded(*plan, t);
+    if (!padded && !t.packed_built) build_prefill_of_decode(*plan, t);
+    bool& uploaded = padded ? t.padded_uploaded : t.packed_uploaded;
+    if (uploaded) return PK_OK;
+    const std::vector<int32_t>& host = padded ? t.host_padded : t.host_packed;
+    const size_t offset = padded ? t.padded_offset : t.packed_offset;
+    if (offset + host.size() * sizeof(int32_t) > plan->bound_bytes)
         return fail(PK_EINVAL, "workspace smaller than pk_workspace_bytes");
-    if (!t.host_padded.empty()) {
-        const int e = copy_tables(static_cast<char*>(plan->bound_ws) + t.padded_offset, t.host_padded.data(),
-                                  t.host_padded.size() * sizeof(int32_t), stream);
-        if (e != 0) return hip_fail("copy of the padded schedule", e);
+    if (!host.empty()) {
+        const int e = copy_tables(static_cast<char*>(plan->bound_ws) + offset, host.data(), host.size() * sizeof(int32_t), stream);
+        if (e != 0) return hip_fail("copy of a prefill schedule", e);
     }
-    t.padded_uploaded = true;
+    uploaded = true;
     return PK_OK;
 }
 
@@ -300,13 +304,13 @@ static int prefill_common(pk_plan* plan, const void* q, const void* k, const voi
     if (dtype == PK_F32 && d > 256) return fail(PK_EUNSUPPORTED, std::string(who) + ": fp32 path needs d <= 256");
     int rc = ensure_bound(plan, Hq, Hkv, d, dtype, workspace, workspace_bytes, stream);
     if (rc != PK_OK) return rc;
-    if (padded && dtype == PK_BF16) {
-        rc = ensure_padded(plan, stream);
+    if (dtype == PK_BF16) {
+        rc = ensure_schedule(plan, padded, stream);
         if (rc != PK_OK) return rc;
     }
     const DeviceTables& t = plan->tables;
     const DeviceTables::PrefillSched& s = padded ? t.padded : t.packed;
-    const size_t base = padded ? t.padded_offset : 0;
+    const size_t base = padded ? t.padded_offset : plan->decode_only ? t.packed_offset : 0;
     PrefillArgs a{};
     a.q = q; a.k = k; a.v = v; a.out = out;
     a.tiles = tab(plan, s.tiles, base); a.n_tiles = s.n_tiles;
@@ -584,6 +588,8 @@ extern "C" int pk_plan_tune(pk_plan* plan, int knob, int64_t value) {
 extern "C" int64_t pk_plan_stat(const pk_plan* plan, int what) {
     return pk::guarded<int64_t>(int64_t{0}, int64_t{0}, "pk_plan_stat", [&]() -> int64_t {
         if (!plan) return 0;
+        if ((what == 1 || what == 6 || what == 8 || what >= 11) && !plan->tables.packed_built && plan->tables.dtype >= 0)
+            build_prefill_of_decode(*plan, plan->tables);
         switch (what) {
             case 0: return plan->unmasked_pairs;
             case 1: return plan->tables.packed.issued_pairs;

@@ -97,6 +97,10 @@ struct DeviceTables {
         bool light = false;         // a launch of little work: prefill_few_body.hip.h (the schedule builder's choice)
     } packed, padded;
     int num_cus = 0;                // of the device the schedules are built for
+    // packed prefill schedule of a decode plan (one query row per request): built on first use like the padded one, uploaded behind the tables
+    std::vector<int32_t> host_packed;
+    bool packed_built = false, packed_uploaded = false;
+    size_t packed_offset = 0;
     // padded prefill schedule: built on first use, uploaded behind the partial results
     std::vector<int32_t> host_padded;
     bool padded_built = false, padded_uploaded = false;
@@ -162,6 +166,7 @@ R guarded(R on_alloc, R on_other, const char* who, F&& body) noexcept {
 // schedule.cpp
 void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, DeviceTables& out);
 void build_prefill_padded(const pk_plan& plan, DeviceTables& t);
+void build_prefill_of_decode(const pk_plan& plan, DeviceTables& t);    // the packed schedule of a decode plan
 size_t kv_buf_bytes(const pk_plan& plan, int Hkv, int d, int dtype);
 
 }  // namespace pk

@@ -62,37 +62,36 @@ int finish_plan(std::unique_ptr<pk_plan> plan, std::vector<Item>& items, const i
     const int64_t G0 = std::min<int64_t>((l_total + C - 1) / C, static_cast<int64_t>(items.size()));
     std::vector<int64_t> loads(static_cast<size_t>(G0), 0);
     std::vector<std::vector<int32_t>> assigned(static_cast<size_t>(G0));   // item indices
-    std::vector<int32_t> order(items.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        if (items[a].length != items[b].length) return items[a].length > items[b].length;
-        return items[a].first < items[b].first;
-    });
+    // by length, the longest first, and by lowest member among equals: no two items have the same lowest member
+    struct Key { int64_t length; int32_t first, item; };
+    std::vector<Key> order(items.size());
+    for (size_t x = 0; x < items.size(); ++x) order[x] = {items[x].length, items[x].first, static_cast<int32_t>(x)};
+    std::sort(order.begin(), order.end(), [](const Key& a, const Key& b) { return a.length != b.length ? a.length > b.length : a.first < b.first; });
     // arg min over the group loads (lowest index on ties) through a heap of (load, index): only the
     // chosen group's load changes, so a request costs O(log G) instead of a scan of all groups
     using Slot = std::pair<int64_t, size_t>;
     std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>> least;
     for (size_t g = 0; g < loads.size(); ++g) least.push({0, g});
-    for (int32_t idx : order) {
-        const Item& it = items[idx];
-        if (!least.empty() && least.top().first + it.length <= C) {
+    for (const Key& key : order) {
+        if (!least.empty() && least.top().first + key.length <= C) {
             const size_t g = least.top().second;
             least.pop();
-            loads[g] += it.length;
-            assigned[g].push_back(idx);
+            loads[g] += key.length;
+            assigned[g].push_back(key.item);
             least.push({loads[g], g});
         } else {                                                  // else-branch: open a new group
-            loads.push_back(it.length);
-            assigned.push_back({idx});
-            least.push({it.length, loads.size() - 1});
+            loads.push_back(key.length);
+            assigned.push_back({key.item});
+            least.push({key.length, loads.size() - 1});
         }
     }
 
     int64_t base = 0;
     for (size_t g = 0; g < loads.size(); ++g) {
         if (assigned[g].empty()) continue;
-        Group grp;
+        Group& grp = plan->groups.emplace_back();
         grp.load = loads[g];
+        grp.members.reserve(assigned[g].size());
         int64_t delta = 0;
         for (int32_t idx : assigned[g]) {
             const Item& it = items[idx];
@@ -129,13 +128,15 @@ int finish_plan(std::unique_ptr<pk_plan> plan, std::vector<Item>& items, const i
         grp.buf_base = base;
         base = (base + delta + PK_GROUP_ALIGN - 1) / PK_GROUP_ALIGN * PK_GROUP_ALIGN;
         plan->unique_tokens += grp.load;
-        plan->groups.push_back(std::move(grp));
     }
     plan->buf_tokens = base;
     if (base > INT32_MAX) { return fail("pk_pack_plan: buffer exceeds 2^31 tokens"); }
 
     // ---- canonical serialisation ---------------------------------------------
     std::vector<int32_t>& w = plan->words;
+    size_t n_words = 10;
+    for (const Group& grp : plan->groups) n_words += 8 + 4 * grp.nodes.size() + 5 * grp.members.size();
+    w.reserve(n_words);
     w.push_back(0x504B504C);
     w.push_back(plan->tree ? 2 : 1);
     w.push_back(plan->n);
@@ -160,8 +161,8 @@ int finish_plan(std::unique_ptr<pk_plan> plan, std::vector<Item>& items, const i
         } else {
             w.push_back(static_cast<int32_t>(grp.members.size()));
             for (const Member& m : grp.members) {
-                w.push_back(m.req); w.push_back(m.prefix_off); w.push_back(m.lp);
-                w.push_back(m.suffix_off); w.push_back(m.lq);
+                const int32_t entry[5] = {m.req, m.prefix_off, m.lp, m.suffix_off, m.lq};
+                w.insert(w.end(), entry, entry + 5);
             }
         }
     }
@@ -220,6 +221,7 @@ extern "C" int pk_pack_plan(const int32_t* kv_lens, const int32_t* q_lens,
         // ---- items: requests, and families cut into the fewest consecutive sub-families that fit ----
         const int64_t C = token_budget;
         std::vector<Item> items;
+        items.reserve(static_cast<size_t>(n));
         std::map<int32_t, std::vector<int32_t>> families;   // ordered by id; order is irrelevant after the sort
         for (int32_t i = 0; i < n; ++i) {
             const bool in_family = prefix_ids && prefix_ids[i] >= 0 && prefix_lens[i] > 0;

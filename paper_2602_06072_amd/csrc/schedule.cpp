@@ -45,6 +45,7 @@ struct Builder {
 void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
     struct Seg { int64_t dst0; int32_t ntok, req, src0; };
     std::vector<Seg> segs;
+    segs.reserve(static_cast<size_t>(plan.n));
     for (const Group& g : plan.groups) {
         for (const Node& nd : g.nodes)                            // a shared segment once, via its lowest request
             segs.push_back({g.buf_base + nd.off, nd.len, nd.reqs[0], nd.start});
@@ -53,23 +54,20 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
     }
     auto before = [](const Seg& x, const Seg& y) { return x.dst0 < y.dst0; };
     if (!std::is_sorted(segs.begin(), segs.end(), before)) std::sort(segs.begin(), segs.end(), before);   // (without shared segments they are)
-    std::vector<int32_t> flat;
-    flat.reserve(segs.size() * 4);
+    int32_t* flat = b.room(segs.size() * 4, t.reorg_seg);
     for (const Seg& s : segs) {
-        flat.push_back(static_cast<int32_t>(s.dst0)); flat.push_back(s.ntok);
-        flat.push_back(s.req); flat.push_back(s.src0);
+        *flat++ = static_cast<int32_t>(s.dst0); *flat++ = s.ntok;
+        *flat++ = s.req; *flat++ = s.src0;
     }
     const int64_t nb = plan.buf_tokens / kDecodeBlock;
-    std::vector<int32_t> first(static_cast<size_t>(nb), 0);
+    int32_t* first = b.room(static_cast<size_t>(nb), t.reorg_blk_first);
     size_t cur = 0;
     for (int64_t blk = 0; blk < nb; ++blk) {
         const int64_t t0 = blk * kDecodeBlock;
         while (cur < segs.size() && segs[cur].dst0 + segs[cur].ntok <= t0) ++cur;
-        first[static_cast<size_t>(blk)] = static_cast<int32_t>(cur);
+        first[blk] = static_cast<int32_t>(cur);
     }
     t.n_reorg_seg = static_cast<int32_t>(segs.size());
-    t.reorg_seg = b.add(flat);
-    t.reorg_blk_first = b.add(first);
 }
 
 // ---- decode ----------------------------------------------------------------
@@ -98,11 +96,13 @@ void build_reorg(const pk_plan& plan, Builder& b, DeviceTables& t) {
 // tokens keep the chip when everything else is done (12.52 instead of 12.23 ms for 32 chunks and 480 rows of a 70B-shaped
 // layer; with the limit as fast as with waves).
 int64_t group_split(const pk_plan& plan, int r, int Hkv, int d, int num_cus, int64_t from) {
-    std::vector<int64_t> blocks;
-    int64_t total = 0, longest = 0;
-    auto segment = [&](int64_t len) {
-        const int64_t k = (len + kDecodeBlock - 1) / kDecodeBlock;
-        if (k > 0 || plan.headroom > 0) blocks.push_back(std::max<int64_t>(k, 1));
+    std::vector<int32_t> blocks;
+    blocks.reserve(static_cast<size_t>(plan.n));
+    int64_t total = 0;
+    int32_t longest = 0;
+    auto segment = [&](int32_t len) {
+        const int32_t k = static_cast<int32_t>((static_cast<uint32_t>(len) + kDecodeBlock - 1) / kDecodeBlock);
+        if (k > 0 || plan.headroom > 0) blocks.push_back(std::max(k, 1));
         total += k;
         longest = std::max(longest, k);
     };
@@ -121,10 +121,17 @@ int64_t group_split(const pk_plan& plan, int r, int Hkv, int d, int num_cus, int
     const int64_t slots = static_cast<int64_t>(2 * num_cus / scale);
     double best = 0;
     int64_t split = 0, best_wgs = 0, best_parts = 0;
-    for (int64_t sp = std::max<int64_t>(from / kDecodeBlock, static_cast<int64_t>(12 / scale)); ; sp = sp * 5 / 4) {
-        int64_t items = 0, most = 0, parts = 0;
-        for (const int64_t b : blocks) {
-            const int64_t pieces = (b + sp - 1) / sp;
+    // (`from` is at most 8192 tokens and sp ends at 410 tiles of 16 KiB or so: 32 bits; most requests are whole, without a division)
+    for (int32_t sp = std::max(static_cast<int32_t>(from / kDecodeBlock), static_cast<int32_t>(12 / scale)); ; sp = sp * 5 / 4) {
+        int64_t items = 0;
+        int32_t most = 0, parts = 1;
+        for (const int32_t b : blocks) {
+            if (b <= sp) {
+                ++items;
+                most = std::max(most, b);
+                continue;
+            }
+            const int32_t pieces = static_cast<int32_t>((static_cast<uint32_t>(b) + static_cast<uint32_t>(sp) - 1) / static_cast<uint32_t>(sp));
             items += pieces;
             parts = std::max(parts, pieces);
             most = std::max(most, (b + pieces - 1) / pieces);
@@ -134,9 +141,9 @@ int64_t group_split(const pk_plan& plan, int r, int Hkv, int d, int num_cus, int
         // a compute unit streams no faster with two workgroups than with one: 24 requests of 1500 tokens in 192 workgroups 23.9 us,
         // in 384 29.1, in 576 30.3; 4 of 65536 in 192 150 us, in 256 160, in 352 175, in 512 165
         const double uneven = per_cu > 1 ? 0.5 + 0.5 * std::ceil(per_cu) / per_cu : 1.0;
-        const double t = (work * all + wgs * fixed) * std::max(uneven, alone / all / wgs) + std::max(0.0, most - share) * alone +
+        const double t = (work * all + wgs * fixed) * std::max(uneven, alone / all / wgs) + std::max(0.0, static_cast<double>(most) - share) * alone +
                          (items > plan.n ? merge : 0.0);
-        if (split == 0 || t < best) { best = t; split = sp * kDecodeBlock; best_wgs = items * Hkv; best_parts = parts; }
+        if (split == 0 || t < best) { best = t; split = int64_t{sp} * kDecodeBlock; best_wgs = items * Hkv; best_parts = parts; }
         if (sp >= longest || sp * scale >= 410) break;       // (the next one could exceed 512 tiles of 16 KiB)
     }
     if (best_wgs > 3 * num_cus && total * Hkv < 8 * best_wgs) return 0;
@@ -166,7 +173,8 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
         for (const Group& g : plan.groups)
             for (const Node& nd : g.nodes) wide = wide || static_cast<int>(std::min<size_t>(nd.reqs.size(), max_members)) * r > 16;
         const int64_t capacity = static_cast<int64_t>(d <= 64 && !wide ? 16 : 8) * num_cus * 9 / 10;
-        auto pieces_of = [&](int64_t len, int64_t sp) { return len <= 0 ? int64_t{0} : (whole_blocks(len) + sp - 1) / sp; };
+        // (no division where it is one: most requests are whole)
+        auto pieces_of = [&](int64_t len, int64_t sp) { return len <= 0 ? int64_t{0} : whole_blocks(len) <= sp ? int64_t{1} : (whole_blocks(len) + sp - 1) / sp; };
         auto fits = [&](int64_t sp, int64_t waves) {
             int64_t c = 0;
             for (const Group& g : plan.groups) {
@@ -200,12 +208,22 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
 
     struct Segment { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool suffix; };   // (reqs point into the plan)
     std::vector<Segment> segments;
+    segments.reserve(static_cast<size_t>(plan.n));
     std::vector<int32_t> req_seg(static_cast<size_t>(plan.n) * 4, 0);
     std::vector<std::vector<int32_t>> chain_of(static_cast<size_t>(plan.n));
     struct Piece { int32_t off; int32_t node, member; };
     std::vector<Piece> pieces;
     for (const Group& g : plan.groups) {
         // work items in layout order: a shared segment attends for every request below it
+        if (g.nodes.empty()) {                     // (members are in that order)
+            for (const Member& mm : g.members) {
+                segments.push_back({g.buf_base + mm.suffix_off, g.buf_base + mm.suffix_off + mm.lq, &mm.req, 1, true});
+                int32_t* rs = &req_seg[static_cast<size_t>(mm.req) * 4];
+                rs[0] = static_cast<int32_t>(g.buf_base + mm.prefix_off); rs[1] = mm.lp;
+                rs[2] = static_cast<int32_t>(g.buf_base + mm.suffix_off); rs[3] = mm.lq;
+            }
+            continue;
+        }
         pieces.clear();
         for (size_t k = 0; k < g.nodes.size(); ++k) pieces.push_back({g.nodes[k].off, static_cast<int32_t>(k), -1});
         for (size_t k = 0; k < g.members.size(); ++k) pieces.push_back({g.members[k].suffix_off, -1, static_cast<int32_t>(k)});
@@ -244,6 +262,7 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     // empty suffix with headroom still gets an item for them)
     auto cut = [&](int64_t split) {
         std::vector<Item> items;
+        items.reserve(segments.size() + segments.size() / 4);
         for (const auto& [a, e, reqs, n_reqs, suffix] : segments) {
             if (e <= a) {
                 if (suffix && plan.headroom > 0) items.push_back({a, a, reqs, n_reqs, true});
@@ -253,8 +272,8 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
             // piece next to a short remainder would set the pace of the launch for little work
             const int64_t a_blk = a / kDecodeBlock * kDecodeBlock;
             const int64_t blocks = (e - a_blk + kDecodeBlock - 1) / kDecodeBlock;
-            const int64_t pieces = (blocks * kDecodeBlock + split - 1) / split;
-            const int64_t piece = (blocks + pieces - 1) / pieces * kDecodeBlock;
+            const int64_t pieces = blocks * kDecodeBlock <= split ? 1 : (blocks * kDecodeBlock + split - 1) / split;
+            const int64_t piece = (pieces == 1 ? blocks : (blocks + pieces - 1) / pieces) * kDecodeBlock;
             for (int32_t m0 = 0; m0 < n_reqs; m0 += max_members)
                 for (int64_t p0 = a_blk; p0 < e; p0 += piece)
                     items.push_back({std::max(a, p0), std::min(e, p0 + piece), reqs + m0, std::min(n_reqs - m0, max_members),
@@ -262,20 +281,22 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
         }
         return items;
     };
-    auto parts_of = [&](const std::vector<Item>& items, std::vector<int32_t>& n_items_of) {
-        n_items_of.assign(static_cast<size_t>(plan.n), 0);
-        for (const Item& it : items)
-            for (int32_t x = 0; x < it.n_reqs; ++x) ++n_items_of[static_cast<size_t>(it.reqs[x])];
-        int32_t n_parts = 0;
-        for (int32_t c : n_items_of) n_parts += c > 1 ? c : 0;
-        return n_parts;
-    };
-    std::vector<int32_t> n_items_of;
+    std::vector<int32_t> n_items_of(static_cast<size_t>(plan.n), 0);
     DeviceTables::DecodeSched& s = t.dec;
-    if (by_group > 0) {                            // (an item of a wave has one member here)
-        const std::vector<Item> by_waves = cut(split);
-        s.wave_items = static_cast<int32_t>(by_waves.size());
-        s.wave_parts = parts_of(by_waves, n_items_of);
+    if (by_group > 0) {                            // (an item of a wave has one member here: a request's items are counted without building them)
+        for (const Segment& g : segments) {
+            if (g.e <= g.a && !(g.suffix && plan.headroom > 0)) continue;
+            const int64_t blocks = g.e <= g.a ? 1 : (g.e - g.a / kDecodeBlock * kDecodeBlock + kDecodeBlock - 1) / kDecodeBlock, pieces_at = split / kDecodeBlock;
+            // (whole pieces of equal length: fewer than pieces_of would say where the length is rounded up)
+            const int64_t pieces = blocks <= pieces_at ? 1 : (blocks + pieces_at - 1) / pieces_at, piece = (blocks + pieces - 1) / pieces;
+            const int32_t k = static_cast<int32_t>((blocks + piece - 1) / piece);
+            s.wave_items += k;
+            n_items_of[static_cast<size_t>(g.reqs[0])] += k;
+        }
+        for (int32_t& c : n_items_of) {
+            s.wave_parts += c > 1 ? c : 0;
+            c = 0;
+        }
         split = by_group;
     }
     s.split_tokens = static_cast<int32_t>(split);
@@ -284,46 +305,50 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     // items with more than 16 query rows first (they run the two-column-tile kernel), then
     // the others; inside each class the longest first (stable: deterministic)
     auto wide = [&](const Item& it) { return it.n_reqs * r > 16; };
-    std::vector<int32_t> order(items.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        if (wide(items[x]) != wide(items[y])) return wide(items[x]);
-        return items[x].e - items[x].a > items[y].e - items[y].a;
-    });
-    for (const Item& it : items) s.n_wide += wide(it) ? 1 : 0;
+    // (as one number: the class, the length from the longest down, the item)
+    std::vector<uint64_t> order(items.size());
+    for (size_t x = 0; x < items.size(); ++x) {
+        const uint64_t length = static_cast<uint64_t>(items[x].e - items[x].a);        // (under 2^31)
+        order[x] = (wide(items[x]) ? uint64_t{0} : uint64_t{1} << 63) | (0x7FFFFFFF - length) << 32 | x;
+        s.n_wide += wide(items[x]) ? 1 : 0;
+    }
+    std::sort(order.begin(), order.end());
     // Partial slots: the slots of one request are consecutive (the merge streams them without
     // indirection); a request covered by a single work item gets no slot: that item writes the
     // final output itself (slot -1).
     std::vector<int32_t> start(static_cast<size_t>(plan.n) + 1, 0);
-    parts_of(items, n_items_of);
+    size_t n_members = 0;
+    for (const Item& it : items) {
+        n_members += static_cast<size_t>(it.n_reqs);
+        for (int32_t x = 0; x < it.n_reqs; ++x) ++n_items_of[static_cast<size_t>(it.reqs[x])];
+    }
     int32_t n_parts = 0;
     for (int32_t i = 0; i < plan.n; ++i) {
         start[static_cast<size_t>(i)] = n_parts;
         if (n_items_of[static_cast<size_t>(i)] > 1) n_parts += n_items_of[static_cast<size_t>(i)];
     }
     start[static_cast<size_t>(plan.n)] = n_parts;
-    std::vector<int32_t> next_slot(start.begin(), start.end() - 1);
-    std::vector<int32_t> flat, members, member_slot;
-    flat.reserve(items.size() * 8);
-    for (int32_t idx : order) {
-        const Item& it = items[idx];
-        flat.push_back(static_cast<int32_t>(it.a));
-        flat.push_back(static_cast<int32_t>(it.e));
-        flat.push_back(static_cast<int32_t>(members.size()));
-        flat.push_back(it.n_reqs);
-        flat.push_back(it.grows ? 1 : 0); flat.push_back(0); flat.push_back(0); flat.push_back(0);
-        for (int32_t x = 0; x < it.n_reqs; ++x) {
-            const int32_t rq = it.reqs[x];
-            members.push_back(rq);
-            member_slot.push_back(n_items_of[static_cast<size_t>(rq)] > 1 ? next_slot[static_cast<size_t>(rq)]++ : -1);
-        }
-    }
     s.n_items = static_cast<int32_t>(items.size());
     s.n_parts = n_parts;
     for (int32_t c : n_items_of) s.max_parts = std::max(s.max_parts, c > 1 ? c : 0);
-    s.items = b.add(flat);
-    s.members = b.add(members);
-    s.member_slot = b.add(member_slot);
+    auto item_at = [&](size_t x) -> const Item& { return items[order[x] & 0xFFFFFFFFu]; };
+    int32_t first = 0;
+    int32_t* w = b.room(items.size() * 8, s.items);
+    for (size_t x = 0; x < items.size(); ++x, w += 8) {
+        const Item& it = item_at(x);
+        w[0] = static_cast<int32_t>(it.a); w[1] = static_cast<int32_t>(it.e); w[2] = first; w[3] = it.n_reqs;
+        w[4] = it.grows ? 1 : 0; w[5] = w[6] = w[7] = 0;
+        first += it.n_reqs;
+    }
+    w = b.room(n_members, s.members);
+    for (size_t x = 0; x < items.size(); ++x) w = std::copy(item_at(x).reqs, item_at(x).reqs + item_at(x).n_reqs, w);
+    std::vector<int32_t> next_slot(start.begin(), start.end() - 1);
+    w = b.room(n_members, s.member_slot);
+    for (size_t x = 0; x < items.size(); ++x)
+        for (int32_t y = 0; y < item_at(x).n_reqs; ++y) {
+            const size_t rq = static_cast<size_t>(item_at(x).reqs[y]);
+            *w++ = n_items_of[rq] > 1 ? next_slot[rq]++ : -1;
+        }
     s.req_part_start = b.add(start);
     if (s.group) s.arrived = b.add(std::vector<int32_t>(static_cast<size_t>(plan.n) * Hkv, 0));
 }
@@ -894,6 +919,22 @@ void build_prefill_packed(const pk_plan& plan, const std::vector<int64_t>& q_sta
 
 }  // namespace
 
+// packed, of a decode plan: hardly ever asked for, so it is built on first use into its own host image (uploaded behind the partial results).  Building the
+// tables of 48 / 400 decode requests took 11.4 / 36.5 us of the host with it among them, and takes 4.3 / 15.4 without.
+void build_prefill_of_decode(const pk_plan& plan, DeviceTables& t) {
+    std::vector<int64_t> q_start(static_cast<size_t>(plan.n) + 1, 0), kv_start(static_cast<size_t>(plan.n) + 1, 0);
+    for (int32_t i = 0; i < plan.n; ++i) {
+        q_start[i + 1] = q_start[i] + plan.q_lens[i];
+        kv_start[i + 1] = kv_start[i] + plan.kv_lens[i];
+    }
+    t.host_packed.clear();
+    t.packed = DeviceTables::PrefillSched();
+    Builder b(t.host_packed);
+    build_prefill_packed(plan, q_start, kv_start, t.Hq, t.num_cus, b, t);
+    t.host_packed.resize((t.host_packed.size() + 63) / 64 * 64, 0);
+    t.packed_built = true;
+}
+
 // padded: request-aligned grid (request, tile) sized by the longest request, natural order.
 // Built on first use into its own host image (uploaded behind the partial results).
 void build_prefill_padded(const pk_plan& plan, DeviceTables& t) {
@@ -943,6 +984,21 @@ size_t padded_bound_bytes(const pk_plan& plan) {
     return static_cast<size_t>((ints + 63) / 64 * 64) * sizeof(int32_t);
 }
 
+// Bytes of the packed prefill schedule of a decode plan, without building it: a tile is closed before a row that does not fit into what is left of it, so that
+// every request is one run of one row, and all its key tiles are listed once.
+size_t packed_bytes_of_decode(const pk_plan& plan, int Hq, int num_cus) {
+    constexpr int64_t BM = kPrefillBM;
+    const bool may_share = static_cast<int64_t>(plan.n) * Hq > 2 * static_cast<int64_t>(num_cus);
+    int64_t tiles = 0, key_tiles = 0;
+    for (const Group& g : plan.groups) {
+        const int64_t rows = static_cast<int64_t>(g.members.size());
+        tiles += may_share ? (rows + BM - 1) / BM : rows;
+    }
+    for (const int32_t kv : plan.kv_lens) key_tiles += key_tiles_to(kv);
+    auto aligned = [](int64_t ints) { return (ints + 63) / 64 * 64; };
+    return static_cast<size_t>(aligned(tiles * kTileDescWords) + aligned(tiles) + aligned(4 * (plan.n - tiles)) + aligned(2 * key_tiles)) * sizeof(int32_t);
+}
+
 }  // namespace
 
 size_t kv_buf_bytes(const pk_plan& plan, int Hkv, int d, int dtype) {
@@ -956,6 +1012,8 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
     t.Hq = Hq; t.Hkv = Hkv; t.d = d; t.dtype = dtype;
     t.num_cus = num_cus;
     Builder b(t.host);
+    // (room for most plans: grown table by table the image was copied, and its fresh pages touched, several times)
+    t.host.reserve(static_cast<size_t>(plan.n) * (plan.decode_only ? 40 + (may_group ? Hkv : 0) : 24) + static_cast<size_t>(plan.buf_tokens / kDecodeBlock) + 16 * 64);
     std::vector<int64_t> q_start(static_cast<size_t>(plan.n) + 1, 0), kv_start(static_cast<size_t>(plan.n) + 1, 0);
     for (int32_t i = 0; i < plan.n; ++i) {
         q_start[i + 1] = q_start[i] + plan.q_lens[i];
@@ -964,18 +1022,24 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
     t.q_start = b.add(std::vector<int32_t>(q_start.begin(), q_start.end()));
     t.kv_start = b.add(std::vector<int32_t>(kv_start.begin(), kv_start.end()));
     build_reorg(plan, b, t);
-    if (plan.decode_only) build_decode(plan, Hq, Hkv, d, dtype, num_cus, may_group, b, t);
-    build_prefill_packed(plan, q_start, kv_start, Hq, num_cus, b, t);
+    size_t packed_bytes = 0;                       // of tables that are built later
+    if (plan.decode_only) {
+        build_decode(plan, Hq, Hkv, d, dtype, num_cus, may_group, b, t);
+        packed_bytes = packed_bytes_of_decode(plan, Hq, num_cus);
+    } else {
+        build_prefill_packed(plan, q_start, kv_start, Hq, num_cus, b, t);
+        t.packed_built = t.packed_uploaded = true;
+    }
     t.host.resize((t.host.size() + 63) / 64 * 64, 0);
     t.tables_bytes = t.host.size() * sizeof(int32_t);
     t.partial_offset = t.tables_bytes;
     t.partial_bytes = static_cast<size_t>(t.dec.n_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float) + t.prefill_part_bytes;   // (no plan has both)
-    t.decode_only_bytes = t.partial_offset + t.partial_bytes;
+    t.decode_only_bytes = t.partial_offset + t.partial_bytes + packed_bytes;       // (whether a plan fits the fixed scratch counts all its tables)
     if (t.dec.group) {
         // what the plan would need with a wave per item decides whether it may use the fixed scratch
         auto aligned = [](size_t words) { return (words + 63) / 64 * 64; };
         auto words = [&](size_t items) { return aligned(8 * items) + 2 * aligned(items); };     // with their members and slots
-        const size_t by_waves = t.tables_bytes + sizeof(int32_t) * (words(static_cast<size_t>(t.dec.wave_items)) -
+        const size_t by_waves = t.tables_bytes + packed_bytes + sizeof(int32_t) * (words(static_cast<size_t>(t.dec.wave_items)) -
             words(static_cast<size_t>(t.dec.n_items)) - aligned(static_cast<size_t>(plan.n) * Hkv)) +
             static_cast<size_t>(t.dec.wave_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
         t.group_over_scratch = t.decode_only_bytes > PK_STATIC_SCRATCH_BYTES && by_waves <= PK_STATIC_SCRATCH_BYTES;
@@ -994,7 +1058,8 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
         const size_t pad_bytes = static_cast<size_t>(plan.n) * t.pad_n_splits * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
         t.partial_bytes = std::max(t.partial_bytes, pad_bytes);
     }
-    t.padded_offset = (t.partial_offset + t.partial_bytes + 255) / 256 * 256;
+    t.packed_offset = (t.partial_offset + t.partial_bytes + 255) / 256 * 256;
+    t.padded_offset = (t.packed_offset + packed_bytes + 255) / 256 * 256;
     t.total_bytes = (t.padded_offset + padded_bound_bytes(plan) + 255) / 256 * 256;
 }
 }  // namespace
