@@ -4,6 +4,8 @@
 #pragma once
 #include <cstdint>
 
+#include "arrival.h"
+
 namespace pk {
 
 // Copies `bytes` (a multiple of 16) from pinned host memory to device memory, then stores `stamp` to the
@@ -38,11 +40,9 @@ struct FastDiv {
         while ((1u << s) < d) ++s;
         return {static_cast<uint32_t>(((uint64_t{1} << (31 + s)) + d - 1) / d), s};
     }
-#if defined(__HIPCC__)
-    __device__ __forceinline__ int operator()(int x) const {
+    PK_HOST_DEVICE int operator()(int x) const {
         return static_cast<int>(static_cast<uint64_t>(static_cast<uint32_t>(x)) * mul >> (31 + shift));
     }
-#endif
 };
 
 struct DecodeArgs {

@@ -15,6 +15,7 @@
 // The query tiles are the prefill call's, also where that has eight waves and with fewer than eight heads per KV head twice the rows: 8 chunks with 32/8 heads
 // and 200 decode rows 2136 us with tiles of 64 rows and two heads, 2129 with 32 and four; 16 x 128 rows behind some 9000 tokens 512 and 515.
 #include "decode_body.hip.h"
+#include "mixed_order.h"
 #define PK_WAVES 4
 #define PK_D 128
 #define PK_DNS d128
@@ -41,33 +42,6 @@
 namespace pk {
 namespace {
 
-// Workgroup numbers are dealt in runs of kRun of one kind (kRun a multiple of 8: every workgroup keeps
-// its XCD).  `cycles` cycles of one decode run and `stride - 1` prefill runs come first, then what is
-// left of the longer kind.  Spread over the launch, the decode runs load the memory system evenly;
-// alternating one by one until the decode work is gone they saturate it for the first quarter of the
-// launch, and the prefill tiles of that stretch wait (spread 1.3 % faster for the step above, small steps
-// unchanged).  Runs of 128 measure the same (12.26 ms, of 256 12.30), runs of 64 0.7 % more, runs of 8 9 % (workgroups go
-// to the compute units of an XCD one per unit before any unit gets its second: short runs put two of a kind on one unit).
-constexpr int kRun = 256;
-
-struct MixedOrder {
-    int n_prefill;                      // prefill workgroups
-    int cycles, stride;                 // stretch in which both kinds are dealt: cycles x stride runs
-    int rest_is_decode;                 // which kind is left behind it
-    FastDiv by_stride;
-};
-
-// run `y` of the launch: the run's number among its kind
-__device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& decode) {
-    const int c = m.by_stride(y), r = y - c * m.stride;
-    if (c >= m.cycles) {
-        decode = m.rest_is_decode != 0;
-        return y - (decode ? m.cycles * (m.stride - 1) : m.cycles);
-    }
-    decode = r == 1;                    // a prefill run first: the heaviest tiles start at once
-    return decode ? c : c * (m.stride - 1) + (r == 0 ? 0 : r - 1);
-}
-
 // one kernel per head dimension and kind of decode workgroup (NS: the namespace of the prefill body, D: the head
 // dimension); the work items and the arithmetic are those of the decode launch
 #define PK_MIXED_STEP_KERNEL(NAME, NS, D, WPE, DECODE)                                                \
@@ -75,7 +49,7 @@ __device__ __forceinline__ int run_of(const MixedOrder& m, const int y, bool& de
         __shared__ __align__(1024) unsigned char lds[5 * NS::TILE_BYTES];                             \
         const int x = static_cast<int>(blockIdx.x);                                                   \
         bool decode;                                                                                  \
-        const int block = run_of(m, x / kRun, decode) * kRun + x % kRun;                              \
+        const int block = m.set_of(x >> 3, decode) * 8 + (x & 7);                                     \
         if (decode) {                                                                                 \
             DECODE<D>(pa.by_hkv, da, block, lds);                                                     \
             return;                                                                                   \
@@ -124,15 +98,10 @@ int launch_mixed_step_bf16(const PrefillArgs& args, const DecodeArgs& decode_arg
     const int64_t n_prefill = (pairs + 7) / 8 * 8 * r;                      // as in the prefill launch (XCD map)
     const int64_t units = static_cast<int64_t>(da.n_items) * da.Hkv;
     const int64_t n_decode = da.arrived ? units : (units + 3) / 4;
-    const int64_t p_runs = (n_prefill + kRun - 1) / kRun, d_runs = (n_decode + kRun - 1) / kRun;
-    const int64_t grid = (p_runs + d_runs) * kRun;
+    const int64_t P = n_prefill / 8, D = (n_decode + 7) / 8;
+    const int64_t grid = (P + D) * 8;
     if (grid > 0x7FFFFFFF) return static_cast<int>(hipErrorInvalidValue);
-    MixedOrder m{};
-    m.n_prefill = static_cast<int>(n_prefill);
-    m.cycles = static_cast<int>(p_runs < d_runs ? p_runs : d_runs);
-    m.stride = 1 + static_cast<int>(d_runs > 0 && p_runs > d_runs ? p_runs / d_runs : 1);
-    m.rest_is_decode = d_runs > p_runs;
-    m.by_stride = FastDiv::by(static_cast<uint32_t>(m.stride));
+    const MixedOrder m = MixedOrder::of(static_cast<int>(n_prefill), P, D);
     if (pa.d != da.d || (pa.d != 128 && pa.d != 64)) return static_cast<int>(hipErrorInvalidValue);
     if (grid > 0) {
         const dim3 wgs(static_cast<unsigned>(grid));
