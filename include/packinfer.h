@@ -407,7 +407,8 @@ int pk_padded_decode_attn(pk_plan* plan, const void* q,
  *             prefill schedule, per head
  *   what = 2: same for the padded prefill schedule
  *   what = 3: decode work items; 4: split-KV partial slots;
- *   what = 5: tokens per decode split chosen by the schedule builder
+ *   what = 5: tokens per decode split chosen by the schedule builder (shared
+ *             segments may have another unless PK_TUNE_DECODE_SPLIT says one)
  *   what = 6: query tiles of the packed prefill schedule, counted in tiles of
  *             128 rows whatever tiles the launch has (12); 7: of the padded
  *   what = 8: 1 if the packed bf16 prefill (also the prefill half of a mixed

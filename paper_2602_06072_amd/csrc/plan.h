@@ -64,10 +64,11 @@ struct DeviceTables {
         TableRef member_slot;       // partial slot of each (item, member), -1: the item writes the output
         TableRef req_part_start;    // [n+1] first slot of each request (slots of a request are consecutive)
         TableRef arrived;           // group: [n][Hkv] zeros, how many of its items have finished
-        int32_t n_items = 0, n_wide = 0, n_parts = 0, split_tokens = 0;
+        int32_t n_items = 0, n_members = 0, n_wide = 0, n_parts = 0, split_tokens = 0;   // (shared segments may have a split of their own)
         int32_t max_parts = 0;      // most partial results of one request
         bool group = false;         // a workgroup of several waves per (work item, KV head), not a wave
-        int32_t wave_items = 0, wave_parts = 0;     // group: work items and partial results with a wave each
+        bool chosen = false;        // group, or shared segments with a split of their own:
+        int32_t wave_items = 0, wave_members = 0, wave_parts = 0;   // work items, their members and partial results with a wave each and one split
     } dec;
     TableRef dec_req_seg;           // [n][4] absolute prefix_off, L_P, suffix_off, L_Q (innermost shared segment)
     TableRef dec_chain_start;       // [n+1] first entry of each request in dec_chain
@@ -112,8 +113,8 @@ struct DeviceTables {
     size_t prefill_part_bytes = 0;  // of them, partial results of pieces of key-tile lists
     size_t total_bytes = 0;
     size_t decode_only_bytes = 0;   // tables + the packed decode partials alone (what the static scratch must hold),
-                                    // dec.group: as they would be with a wave per work item
-    bool group_over_scratch = false;    // those of dec.group do not fit the static scratch, the others would
+                                    // dec.chosen: as they would be with a wave per work item and one split
+    bool group_over_scratch = false;    // those of dec.chosen do not fit the static scratch, the others would
 };
 
 }  // namespace pk

@@ -151,7 +151,66 @@ int64_t group_split(const pk_plan& plan, int r, int Hkv, int d, int num_cus, int
     return split;
 }
 
-void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_group, Builder& b, DeviceTables& t) {
+// Split length of the shared segments of a batch whose items have a wave each.  A piece of a shared segment leaves a partial result for every one of up
+// to 32 rows (16 KiB with d = 128, written and read again, beside 16 KiB of K/V a tile), and a wave alone takes 1.6 us (d = 64: 1.3) for a tile of such a piece: short pieces
+// cost the memory system, long ones outlast the launch.  The split of the suffixes knows neither: it is the shortest, 128 tokens, for small batches, and 2048 where the suffixes
+// alone are more waves than the chip holds.  Taken is the length with the least estimated time: bytes (K/V, of which the pieces of more requests than
+// one item takes read half again, and partial results twice) at 5.9 TB/s and 4.2 us for 2048 waves (half of it with d = 64, where twice as many run at a
+// time), or the longest item alone, whichever is more, and a sixth of the other.  us, with the split of the suffixes / with this one: 182 requests of 33 tokens, 11 segments of 2000 below one of 2843 with
+// 16/16 heads 77.5 / 58.0 (2048 and 512 tokens), 279 of 63 with 34 of 876 62.2 / 47.8, 321 of 55 with 40 of 1259 below 1667 88 / 73; 40 of 350 with 20 of 2743 and 16/2 heads 20.5 / 16.5 (128 and
+// 256), 268 of 130 with 67 of 1880 41.6 / 36.2.  The constants are fitted to 92 random batches at eleven lengths each: 1.03 times as fast as with one split for
+// all, with the best length of each 1.049.  Estimated gains of less than 3 %, 5 for shorter pieces, are left: of 58 other batches 23 had such, and six of those lost 2 to 11 %.
+// Where the length is changed, 80 other batches are 1.11 times as fast (0.945 to 1.79; eight of them more than 2 % slower).
+int64_t shared_split(const pk_plan& plan, int Hq, int Hkv, int d, int max_members, int64_t split) {
+    const double row_bytes = 4.0 * d * Hq, token_bytes = 4.0 * d * Hkv;
+    struct Shared { int32_t blocks, requests, chunks; };
+    std::vector<Shared> shared;
+    double waves = 0, bytes = 0;                   // of what has one request
+    int32_t longest = 0, longest_shared = 0;
+    const int32_t own = static_cast<int32_t>(split / kDecodeBlock);
+    auto blocks_of = [](int32_t len) { return static_cast<int32_t>((static_cast<uint32_t>(len) + kDecodeBlock - 1) / kDecodeBlock); };
+    auto single = [&](int32_t len) {
+        const int32_t blocks = blocks_of(len), pieces = std::max(1, blocks <= own ? 1 : (blocks + own - 1) / own);
+        waves += pieces;
+        bytes += len * token_bytes + 2 * pieces * row_bytes;
+        longest = std::max(longest, (blocks + pieces - 1) / pieces);
+    };
+    for (const Group& g : plan.groups) {
+        for (const Node& nd : g.nodes) {
+            const int32_t n = static_cast<int32_t>(nd.reqs.size());
+            if (n < 2) { single(nd.len); continue; }
+            const int32_t blocks = blocks_of(nd.len), chunks = (n + max_members - 1) / max_members;
+            shared.push_back({blocks, n, chunks});
+            bytes += nd.len * token_bytes * (1 + 0.5 * (chunks - 1));
+            longest_shared = std::max(longest_shared, blocks);
+        }
+        for (const Member& m : g.members) single(m.lq);
+    }
+    if (longest_shared * kDecodeBlock <= 128) return split;            // (whole at any length)
+    auto time = [&](int32_t sp) {
+        double w = waves, b = bytes;
+        int32_t most = 0;
+        for (const Shared& x : shared) {
+            const int32_t pieces = x.blocks <= sp ? 1 : (x.blocks + sp - 1) / sp;
+            w += pieces * x.chunks;
+            b += 2.0 * pieces * x.requests * row_bytes;
+            most = std::max(most, (x.blocks + pieces - 1) / pieces);
+        }
+        const double chip = b / 5.9e6 + (d <= 64 ? 2.1 : 4.2) / 2048 * w * Hkv, alone = std::max(1.56 * most, 1.05 * longest) * (d <= 64 ? 0.85 : 1.0);
+        return std::max(chip, alone) + 0.16 * std::min(chip, alone);
+    };
+    const double one = time(own);
+    double best = one;
+    int32_t taken = own;
+    for (int32_t sp = 4; ; sp = sp * 3 / 2) {      // 128 to 2016 tokens
+        const double t = time(sp);
+        if (t < best && t < one * (sp < own ? 0.95 : 0.97)) { best = t; taken = sp; }
+        if (sp >= longest_shared || sp >= 63) break;
+    }
+    return int64_t{taken} * kDecodeBlock;
+}
+
+void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_choose, Builder& b, DeviceTables& t) {
     const int r = Hq / Hkv;
     const int max_members = std::max(1, kDecodeMaxRows / r);
     // split length: about 1500 waves (work items x KV heads) keep enough loads in flight to fill
@@ -199,11 +258,17 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
         split = std::max(two_rounds, fits(raised, capacity) ? raised : std::min<int64_t>(2048, whole_blocks(split * 5 / 4)));
     }
     split = whole_blocks(split);
-    const bool may = may_group && dtype == PK_BF16 && r <= 16;
+    const bool may = may_choose && dtype == PK_BF16 && r <= 16;
     int64_t by_group = may ? group_split(plan, r, Hkv, d, num_cus, split) : 0;
     if (plan.tune_decode_split > 0) {              // pk_plan_tune (profiling sweeps): another split for the same kernel
         split = whole_blocks(plan.tune_decode_split);
         if (by_group > 0) by_group = split;
+    }
+    int64_t shared = split;                        // split of the shared segments
+    if (may && by_group == 0 && plan.tune_decode_split == 0) {
+        bool any = false;
+        for (const Group& g : plan.groups) any = any || !g.nodes.empty();
+        if (any) shared = shared_split(plan, Hq, Hkv, d, max_members, split);
     }
 
     struct Segment { int64_t a, e; const int32_t* reqs; int32_t n_reqs; bool suffix; };   // (reqs point into the plan)
@@ -272,7 +337,8 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
             // piece next to a short remainder would set the pace of the launch for little work
             const int64_t a_blk = a / kDecodeBlock * kDecodeBlock;
             const int64_t blocks = (e - a_blk + kDecodeBlock - 1) / kDecodeBlock;
-            const int64_t pieces = blocks * kDecodeBlock <= split ? 1 : (blocks * kDecodeBlock + split - 1) / split;
+            const int64_t most = n_reqs > 1 ? shared : split;
+            const int64_t pieces = blocks * kDecodeBlock <= most ? 1 : (blocks * kDecodeBlock + most - 1) / most;
             const int64_t piece = (pieces == 1 ? blocks : (blocks + pieces - 1) / pieces) * kDecodeBlock;
             for (int32_t m0 = 0; m0 < n_reqs; m0 += max_members)
                 for (int64_t p0 = a_blk; p0 < e; p0 += piece)
@@ -283,21 +349,23 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     };
     std::vector<int32_t> n_items_of(static_cast<size_t>(plan.n), 0);
     DeviceTables::DecodeSched& s = t.dec;
-    if (by_group > 0) {                            // (an item of a wave has one member here: a request's items are counted without building them)
+    s.chosen = by_group > 0 || shared != split;
+    if (s.chosen) {                                // (a wave each and one split: counted without building the items)
         for (const Segment& g : segments) {
             if (g.e <= g.a && !(g.suffix && plan.headroom > 0)) continue;
             const int64_t blocks = g.e <= g.a ? 1 : (g.e - g.a / kDecodeBlock * kDecodeBlock + kDecodeBlock - 1) / kDecodeBlock, pieces_at = split / kDecodeBlock;
             // (whole pieces of equal length: fewer than pieces_of would say where the length is rounded up)
             const int64_t pieces = blocks <= pieces_at ? 1 : (blocks + pieces_at - 1) / pieces_at, piece = (blocks + pieces - 1) / pieces;
             const int32_t k = static_cast<int32_t>((blocks + piece - 1) / piece);
-            s.wave_items += k;
-            n_items_of[static_cast<size_t>(g.reqs[0])] += k;
+            s.wave_items += k * ((g.n_reqs + max_members - 1) / max_members);
+            s.wave_members += k * g.n_reqs;
+            for (int32_t y = 0; y < g.n_reqs; ++y) n_items_of[static_cast<size_t>(g.reqs[y])] += k;
         }
         for (int32_t& c : n_items_of) {
             s.wave_parts += c > 1 ? c : 0;
             c = 0;
         }
-        split = by_group;
+        if (by_group > 0) split = by_group;
     }
     s.split_tokens = static_cast<int32_t>(split);
     s.group = by_group > 0;
@@ -329,6 +397,7 @@ void build_decode(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int nu
     }
     start[static_cast<size_t>(plan.n)] = n_parts;
     s.n_items = static_cast<int32_t>(items.size());
+    s.n_members = static_cast<int32_t>(n_members);
     s.n_parts = n_parts;
     for (int32_t c : n_items_of) s.max_parts = std::max(s.max_parts, c > 1 ? c : 0);
     auto item_at = [&](size_t x) -> const Item& { return items[order[x] & 0xFFFFFFFFu]; };
@@ -1007,13 +1076,13 @@ size_t kv_buf_bytes(const pk_plan& plan, int Hkv, int d, int dtype) {
 }
 
 namespace {
-void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_group, DeviceTables& t) {
+void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, bool may_choose, DeviceTables& t) {
     t = DeviceTables();
     t.Hq = Hq; t.Hkv = Hkv; t.d = d; t.dtype = dtype;
     t.num_cus = num_cus;
     Builder b(t.host);
     // (room for most plans: grown table by table the image was copied, and its fresh pages touched, several times)
-    t.host.reserve(static_cast<size_t>(plan.n) * (plan.decode_only ? 40 + (may_group ? Hkv : 0) : 24) + static_cast<size_t>(plan.buf_tokens / kDecodeBlock) + 16 * 64);
+    t.host.reserve(static_cast<size_t>(plan.n) * (plan.decode_only ? 40 + (may_choose ? Hkv : 0) : 24) + static_cast<size_t>(plan.buf_tokens / kDecodeBlock) + 16 * 64);
     std::vector<int64_t> q_start(static_cast<size_t>(plan.n) + 1, 0), kv_start(static_cast<size_t>(plan.n) + 1, 0);
     for (int32_t i = 0; i < plan.n; ++i) {
         q_start[i + 1] = q_start[i] + plan.q_lens[i];
@@ -1024,7 +1093,7 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
     build_reorg(plan, b, t);
     size_t packed_bytes = 0;                       // of tables that are built later
     if (plan.decode_only) {
-        build_decode(plan, Hq, Hkv, d, dtype, num_cus, may_group, b, t);
+        build_decode(plan, Hq, Hkv, d, dtype, num_cus, may_choose, b, t);
         packed_bytes = packed_bytes_of_decode(plan, Hq, num_cus);
     } else {
         build_prefill_packed(plan, q_start, kv_start, Hq, num_cus, b, t);
@@ -1035,12 +1104,12 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
     t.partial_offset = t.tables_bytes;
     t.partial_bytes = static_cast<size_t>(t.dec.n_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float) + t.prefill_part_bytes;   // (no plan has both)
     t.decode_only_bytes = t.partial_offset + t.partial_bytes + packed_bytes;       // (whether a plan fits the fixed scratch counts all its tables)
-    if (t.dec.group) {
-        // what the plan would need with a wave per item decides whether it may use the fixed scratch
+    if (t.dec.chosen) {
+        // what the plan would need with a wave per item and one split decides whether it may use the fixed scratch
         auto aligned = [](size_t words) { return (words + 63) / 64 * 64; };
-        auto words = [&](size_t items) { return aligned(8 * items) + 2 * aligned(items); };     // with their members and slots
-        const size_t by_waves = t.tables_bytes + packed_bytes + sizeof(int32_t) * (words(static_cast<size_t>(t.dec.wave_items)) -
-            words(static_cast<size_t>(t.dec.n_items)) - aligned(static_cast<size_t>(plan.n) * Hkv)) +
+        auto words = [&](int32_t items, int32_t members) { return aligned(8 * static_cast<size_t>(items)) + 2 * aligned(static_cast<size_t>(members)); };     // with their slots
+        const size_t by_waves = t.tables_bytes + packed_bytes + sizeof(int32_t) * (words(t.dec.wave_items, t.dec.wave_members) -
+            words(t.dec.n_items, t.dec.n_members) - (t.dec.group ? aligned(static_cast<size_t>(plan.n) * Hkv) : 0)) +
             static_cast<size_t>(t.dec.wave_parts) * Hq * (static_cast<size_t>(d) + 1) * sizeof(float);
         t.group_over_scratch = t.decode_only_bytes > PK_STATIC_SCRATCH_BYTES && by_waves <= PK_STATIC_SCRATCH_BYTES;
         t.decode_only_bytes = by_waves;
@@ -1065,6 +1134,7 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
 }  // namespace
 
 void build_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num_cus, DeviceTables& t) {
+    // (what may not be chosen in the second: workgroups for items, and a split for shared segments)
     fill_tables(plan, Hq, Hkv, d, dtype, num_cus, true, t);
     if (t.group_over_scratch) fill_tables(plan, Hq, Hkv, d, dtype, num_cus, false, t);
 }
