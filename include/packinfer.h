@@ -177,7 +177,16 @@ size_t pk_workspace_bytes(const pk_plan* plan, int Hq, int Hkv, int d, int dtype
  * into `workspace` (device, >= pk_workspace_bytes, 256-byte aligned) on
  * `stream`.  Optional: the compute calls bind on first use of a
  * (workspace, shape) pair; rebinding to another workspace is allowed.  The
- * caller must not modify the workspace while the plan is in use. */
+ * caller must not modify the workspace while the plan is in use.
+ * Two tables are built and copied later, by the first call that needs them,
+ * on its stream: those of pk_padded_prefill_attn, and for a plan whose q_lens
+ * are all 1 those of its packed prefill (pk_packed_prefill_attn, the prefill
+ * half of a mixed step).
+ * Under stream capture a copy of tables becomes a node of the graph, and the
+ * host memory that it reads stays with the graph.  It counts for the later
+ * calls of the same capture only: calls outside of it, or in another capture,
+ * copy again.  A captured call whose tables are already in place (the same
+ * call was made on the workspace before, eagerly) is kernel launches alone. */
 int pk_plan_bind(pk_plan* plan, int Hq, int Hkv, int d, int dtype,
                  void* workspace, size_t workspace_bytes, void* stream);
 

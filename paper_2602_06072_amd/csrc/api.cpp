@@ -119,16 +119,26 @@ void staging_release(Staging* s, bool recorded) {
 // 202 KB 24 / 28, of 246 KB 24 / 34: up to the line the kernel is the slower one in neither use.
 constexpr size_t kUploadKernelBytes = 160u << 10;
 
-// (when it cannot be told, the careful answer)
-bool capturing(hipStream_t st) {
+// The capture that a stream is part of, 0: none (when it cannot be told, the careful answer: one that is like no other).
+constexpr uint64_t kUnknownCapture = ~uint64_t{0};
+uint64_t capture_of(void* stream) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
-    return status != hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(static_cast<hipStream_t>(stream), &status, &id) != hipSuccess) { (void)hipGetLastError(); return kUnknownCapture; }
+    return status == hipStreamCaptureStatusNone ? 0 : id != 0 ? id : kUnknownCapture;
 }
 
-int copy_tables(void* dst, const void* src, size_t bytes, void* stream, bool may_allocate = true) {
+// Whether a call on `stream` finds tables that were copied in `capture` (0: outside of any).  What a capture records has not run: such a copy counts for the calls of the
+// same capture, which replay behind it, and for no other, be it eager or of another graph.
+bool copied_for(uint64_t capture, void* stream) {
+    return capture == 0 || (capture != kUnknownCapture && capture == capture_of(stream));
+}
+
+// capture: receives the capture that the copy became part of (0: none)
+int copy_tables(void* dst, const void* src, size_t bytes, void* stream, uint64_t& capture, bool may_allocate = true) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool captured = capturing(st);
+    capture = capture_of(stream);
+    const bool captured = capture != 0;
     // (asking an event or allocating would end a capture, unless this thread says that it is not part of it)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool relaxed = captured && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
@@ -198,7 +208,7 @@ int ensure_bound(pk_plan* plan, int Hq, int Hkv, int d, int dtype, void* workspa
     DeviceTables& t = plan->tables;
     const bool same_shape = t.Hq == Hq && t.Hkv == Hkv && t.d == d && t.dtype == dtype;
     if (same_shape && plan->bound_ws == workspace && plan->bound_bytes == workspace_bytes &&
-        owns_workspace(plan, workspace)) return PK_OK;
+        owns_workspace(plan, workspace) && copied_for(plan->bound_capture, stream)) return PK_OK;
     if (!workspace) return fail(PK_EINVAL, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return fail(PK_EINVAL, "workspace must be 256-byte aligned");
     if (!same_shape) build_tables(*plan, Hq, Hkv, d, dtype, device_cus(), t);
@@ -210,15 +220,17 @@ int ensure_bound(pk_plan* plan, int Hq, int Hkv, int d, int dtype, void* workspa
     } else if (workspace_bytes < t.total_bytes) {
         return fail(PK_EINVAL, "workspace smaller than pk_workspace_bytes");
     }
+    uint64_t capture = 0;
     if (t.tables_bytes) {
-        const int e = copy_tables(workspace, t.host.data(), t.tables_bytes, stream, !fixed_scratch);
+        const int e = copy_tables(workspace, t.host.data(), t.tables_bytes, stream, capture, !fixed_scratch);
         if (e != 0) return hip_fail("pk_plan_bind (copy of tables)", e);
     }
     plan->bound_ws = workspace;
     plan->bound_bytes = workspace_bytes;
     plan->bound_stamp = claim_workspace(workspace);
-    t.padded_uploaded = false;
-    t.packed_uploaded = !plan->decode_only;
+    plan->bound_capture = capture;
+    t.padded_copy = {};
+    t.packed_copy = {!plan->decode_only, 0};       // (among the others)
     return PK_OK;
 }
 
@@ -227,17 +239,18 @@ int ensure_schedule(pk_plan* plan, bool padded, void* stream) {
     DeviceTables& t = plan->tables;
     if (padded && !t.padded_built) build_prefill_padded(*plan, t);
     if (!padded && !t.packed_built) build_prefill_of_decode(*plan, t);
-    bool& uploaded = padded ? t.padded_uploaded : t.packed_uploaded;
-    if (uploaded) return PK_OK;
+    DeviceTables::Copy& copy = padded ? t.padded_copy : t.packed_copy;
+    if (copy.made && copied_for(copy.capture, stream)) return PK_OK;
     const std::vector<int32_t>& host = padded ? t.host_padded : t.host_packed;
     const size_t offset = padded ? t.padded_offset : t.packed_offset;
     if (offset + host.size() * sizeof(int32_t) > plan->bound_bytes)
         return fail(PK_EINVAL, "workspace smaller than pk_workspace_bytes");
+    copy = {};
     if (!host.empty()) {
-        const int e = copy_tables(static_cast<char*>(plan->bound_ws) + offset, host.data(), host.size() * sizeof(int32_t), stream);
+        const int e = copy_tables(static_cast<char*>(plan->bound_ws) + offset, host.data(), host.size() * sizeof(int32_t), stream, copy.capture);
         if (e != 0) return hip_fail("copy of a prefill schedule", e);
     }
-    uploaded = true;
+    copy.made = true;
     return PK_OK;
 }
 

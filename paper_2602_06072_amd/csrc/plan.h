@@ -98,13 +98,19 @@ struct DeviceTables {
         bool light = false;         // a launch of little work: prefill_few_body.hip.h (the schedule builder's choice)
     } packed, padded;
     int num_cus = 0;                // of the device the schedules are built for
+    struct Copy {                   // of a schedule into the workspace that the plan is bound to
+        bool made = false;
+        uint64_t capture = 0;       // the stream capture that it is part of (0: none); it has not run and counts inside that capture only
+    };
     // packed prefill schedule of a decode plan (one query row per request): built on first use like the padded one, uploaded behind the tables
     std::vector<int32_t> host_packed;
-    bool packed_built = false, packed_uploaded = false;
+    bool packed_built = false;
+    Copy packed_copy;
     size_t packed_offset = 0;
     // padded prefill schedule: built on first use, uploaded behind the partial results
     std::vector<int32_t> host_padded;
-    bool padded_built = false, padded_uploaded = false;
+    bool padded_built = false;
+    Copy padded_copy;
     size_t padded_offset = 0;
     // partial results (floats) live after the tables
     size_t tables_bytes = 0;
@@ -139,6 +145,7 @@ struct pk_plan {
     mutable void* bound_ws = nullptr;
     mutable size_t bound_bytes = 0;
     uint64_t bound_stamp = 0;       // stamp of the bind that wrote bound_ws (0: none)
+    uint64_t bound_capture = 0;     // the stream capture that its copy is part of, as in DeviceTables::Copy
 };
 
 namespace pk {

@@ -1097,7 +1097,7 @@ void fill_tables(const pk_plan& plan, int Hq, int Hkv, int d, int dtype, int num
         packed_bytes = packed_bytes_of_decode(plan, Hq, num_cus);
     } else {
         build_prefill_packed(plan, q_start, kv_start, Hq, num_cus, b, t);
-        t.packed_built = t.packed_uploaded = true;
+        t.packed_built = true;
     }
     t.host.resize((t.host.size() + 63) / 64 * 64, 0);
     t.tables_bytes = t.host.size() * sizeof(int32_t);

@@ -68,3 +68,45 @@ def test_first_prefill_call_captured():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref), f"replay {rep}"
+
+
+@pytest.mark.parametrize("inside", ["prefill", "bind and prefill"])
+def test_calls_behind_a_capture_that_has_not_run(inside):
+    """An eager call, and one of another capture, find their tables whether or not the first graph ever runs.  (Zeros as tables would leave the output as it is.)"""
+    kv = np.random.default_rng(3).integers(1, 400, size=60).astype(np.int32)
+    w = wl.make_ragged("captured", kv, np.ones_like(kv), 8, 2, 128, 2048, 25, device=DEV, keep_f32=False)
+    plans = [pk.pack_plan(kv, np.ones_like(kv), token_budget=2048) for _ in range(3)]
+    ws = [torch.zeros(p.workspace_bytes(8, 2, 128, pk.PK_BF16), dtype=torch.uint8, device=DEV) for p in plans]
+    outs = [torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV) for _ in range(5)]
+    pk.packed_prefill_attn(plans[0], w.q, w.k, w.v, outs[0], w.scale, ws[0])      # (eager all the way, and kernels that are loaded)
+    if inside == "prefill":
+        for p, x in zip(plans[1:], ws[1:]):
+            pk.plan_bind(p, 8, 2, 128, pk.PK_BF16, x)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+
+    def capture(p, x, out):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            if inside != "prefill":
+                pk.plan_bind(p, 8, 2, 128, pk.PK_BF16, x)
+            pk.packed_prefill_attn(p, w.q, w.k, w.v, out, w.scale, x)
+        return graph
+    graphs = [capture(p, x, outs[1]) for p, x in zip(plans[1:], ws[1:])]
+    pk.packed_prefill_attn(plans[1], w.q, w.k, w.v, outs[2], w.scale, ws[1])      # eager, behind a capture
+    graphs.append(capture(plans[2], ws[2], outs[3]))                               # captured, behind another capture
+    torch.cuda.synchronize()
+    graphs[2].replay()
+    pk.packed_prefill_attn(plans[2], w.q, w.k, w.v, outs[4], w.scale, ws[2])
+    torch.cuda.synchronize()
+    for x in (2, 3, 4):
+        assert torch.equal(outs[x], outs[0]), x
+    for rep in range(3):
+        for graph in graphs[:2]:
+            outs[1].fill_(float("nan"))
+            pk.packed_prefill_attn(plans[0], w.q, w.k, w.v, outs[0], w.scale, ws[0])
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(outs[1], outs[0]), rep
