@@ -1,6 +1,7 @@
 // C ABI: argument validation, binding of plan tables to a workspace, launches.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -45,7 +46,7 @@ bool shape_ok(int Hq, int Hkv, int d, int dtype, std::string& why) {
 // overlaps the kernels of the current one.  Buffers are recycled once the kernel that reads them has
 // stored its stamp behind them, or once the event recorded behind a copy command has completed; the
 // pool only grows while every buffer is still in flight.  A buffer whose copy has been captured into a graph
-// stays out of the pool: every replay reads it.
+// leaves the pool for good: every replay reads it.
 struct Staging {
     void* ptr = nullptr;
     size_t cap = 0;
@@ -54,6 +55,7 @@ struct Staging {
     hipEvent_t copied = nullptr;
     bool used = false;                              // `copied` has been recorded for it
     bool busy = false;                              // handed out and not yet released by copy_tables
+    bool of_graph = false;                          // read by the replays of a graph
 
     bool in_flight() const {
         return __atomic_load_n(done, __ATOMIC_ACQUIRE) != stamp || (used && hipEventQuery(copied) != hipSuccess);
@@ -61,6 +63,7 @@ struct Staging {
 };
 std::mutex g_staging_mutex;
 std::vector<Staging> g_staging;
+constexpr size_t kMostStaging = 64;                 // buffers of the pool; and of graphs, whose further copies are from pageable memory
 
 // A host that runs ahead of the GPU has this many buffers in flight and then waits for one of them, for half a millisecond at most: a longer queue gains nothing, and
 // growing the pool to its 64 buffers and then emptying the stream with the 65th copy, which is from pageable memory, costs bubbles.  300 decode steps of 48 requests, regrouped
@@ -68,18 +71,20 @@ std::vector<Staging> g_staging;
 constexpr size_t kStagingAhead = 16;
 constexpr std::chrono::microseconds kStagingWait{500};
 
-// may_allocate = false: only a buffer that already exists is handed out; may_wait = false: only one that is free now
-Staging* staging_acquire(size_t bytes, bool may_allocate, bool may_wait) {
+// may_allocate = false: only a buffer that already exists and is free is handed out; of_graph: for good, to a graph
+Staging* staging_acquire(size_t bytes, bool may_allocate, bool of_graph) {
     std::unique_lock<std::mutex> lock(g_staging_mutex);
+    const size_t with_graphs = static_cast<size_t>(std::count_if(g_staging.begin(), g_staging.end(), [](const Staging& s) { return s.of_graph; }));
+    if (of_graph && with_graphs >= kMostStaging) return nullptr;
     std::chrono::steady_clock::time_point until;
     for (bool waits = false;; ) {
         size_t fitting = 0;
         for (Staging& s : g_staging) {
-            if (s.cap < bytes) continue;
-            if (!s.busy && !s.in_flight()) { s.busy = true; return &s; }
+            if (s.cap < bytes || s.of_graph) continue;
+            if (!s.busy && !s.in_flight()) { s.busy = true; s.of_graph = of_graph; return &s; }
             ++fitting;
         }
-        if (!may_wait || fitting < kStagingAhead) break;
+        if (!may_allocate || of_graph || fitting < kStagingAhead) break;
         const auto now = std::chrono::steady_clock::now();
         if (!waits) until = now + kStagingWait;
         else if (now >= until) break;
@@ -88,7 +93,7 @@ Staging* staging_acquire(size_t bytes, bool may_allocate, bool may_wait) {
         std::this_thread::yield();
         lock.lock();
     }
-    if (!may_allocate || g_staging.size() >= 64) return nullptr;     // fall back to a pageable copy
+    if (!may_allocate || (!of_graph && g_staging.size() - with_graphs >= kMostStaging)) return nullptr;     // fall back to a pageable copy
     Staging s;
     s.cap = (bytes + (1u << 20) - 1) >> 20 << 20;
     // coherent: the upload kernel must not meet what an L2 kept of the buffer's last contents
@@ -101,7 +106,8 @@ Staging* staging_acquire(size_t bytes, bool may_allocate, bool may_wait) {
         (void)hipGetLastError(); (void)hipHostFree(s.ptr); return nullptr;
     }
     s.busy = true;
-    g_staging.reserve(64);                          // pointers into the vector stay valid
+    s.of_graph = of_graph;
+    g_staging.reserve(2 * kMostStaging);            // pointers into the vector stay valid
     g_staging.push_back(s);
     return &g_staging.back();
 }
@@ -142,8 +148,9 @@ int copy_tables(void* dst, const void* src, size_t bytes, void* stream, uint64_t
     // (asking an event or allocating would end a capture, unless this thread says that it is not part of it)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool relaxed = captured && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    Staging* s = staging_acquire(bytes, may_allocate, may_allocate && !captured);
+    Staging* s = staging_acquire(bytes, may_allocate, captured);
     if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!s && captured) src = std::memcpy(new char[bytes], src, bytes);     // the graph's from here on: what the plan holds may be gone when it is replayed
     if (!s) return static_cast<int>(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
     std::memcpy(s->ptr, src, bytes);
     if (may_allocate && !captured && bytes <= kUploadKernelBytes && launch_upload) {   // (a kernel's first launch may load its code)

@@ -201,9 +201,47 @@ static void captured() {
     }
 }
 
+// Buffers that graphs read from for good are no part of the pool: they neither use it up nor are they waited for.
+static void graphs() {
+    Batch b(6, 3);
+    Stream s;
+    Graph g;
+    int copies = 0;
+    auto capture = [&](int n) {
+        for (int x = 0; x < n; ++x) {
+            begin(s, g);
+            CHECK(b.call("bind", s) == PK_OK, "captured bind %d", x);
+            end(s);
+            ++copies;
+        }
+        CHECK(g.copies == copies, "%d copies of %d captured", g.copies, copies);
+    };
+    capture(20);
+    s.held = true;
+    for (int x = 0; x < 10; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
+    CHECK(yields == 0, "%d turns of waiting for buffers of graphs", yields);
+    s.run();
+    capture(100);
+    for (int x = 0; x < 10; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
+    CHECK(yields == 0 && pageable == 0, "behind 120 captured uploads: %d turns of waiting, %d copies from pageable memory", yields, pageable);
+    s.run();
+    s.held = false;
+    const std::vector<int32_t> host = b.plan->tables.host;
+    const pk::TableRef tiles = b.plan->tables.packed.tiles;
+    if (pk_workspace_bytes(b.plan, 64, 8, 64, PK_BF16) == 0) std::abort();         // (the plan's own memory has other tables)
+    launches = wrong = 0;
+    for (Work& w : g.nodes) {                      // every graph its own tables, whatever has gone through the pool since
+        std::memset(b.ws, 0xEE, b.bytes);
+        w();
+        expects(&s, b.ws + tiles.offset, host, tiles);
+    }
+    CHECK(launches == 120 && wrong == 0, "%d of %d replays without their tables", wrong, launches);
+}
+
 int main(int, char** argv) {
     const std::string check = argv[1];
     if (check == "captured") captured();
+    else if (check == "graphs") graphs();
     else return 2;
     return failures ? 1 : 0;
 }

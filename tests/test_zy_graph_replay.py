@@ -98,3 +98,28 @@ def test_captured_bind_keeps_its_tables():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref), f"replay {rep}"
+
+
+def test_more_captured_binds_than_there_are_staging_buffers():
+    """Each of them keeps the tables that it was captured with, whatever the plan holds by the time of the replay."""
+    w = wl.small_ragged(seed=11, n=12, lo=1, hi=300, Hq=8, Hkv=2, d=64, token_budget=512, device=DEV, keep_f32=False)
+    plan = pk.pack_plan(w.kv_lens, w.q_lens, token_budget=512)
+    ws = pk.new_workspace(plan, w.Hq, w.Hkv, w.d, pk.PK_BF16)
+    ref, out = torch.empty_like(w.q), torch.empty_like(w.q)
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, ref, w.scale, ws)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for _ in range(70):
+            pk.plan_bind(plan, w.Hq, w.Hkv, w.d, pk.PK_BF16, ws)
+        pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
+    plan.workspace_bytes(32, 2, 128, pk.PK_BF16)               # (the plan's own memory has other tables now)
+    for rep in range(3):
+        out.fill_(float("nan"))
+        ws.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), f"replay {rep}"
