@@ -22,7 +22,8 @@
  *   - Kernels are enqueued on the caller's hipStream_t (passed as void*,
  *     NULL = default stream) and the call returns without synchronising.
  *     Small integer tables are copied host->device on that stream when a
- *     plan is first used with a workspace (see pk_plan_bind).
+ *     plan is first used with a workspace (see pk_plan_bind); a host that is
+ *     64 such copies ahead of the GPU waits for one of the same stream.
  *   - All tensors are in CALLER REQUEST ORDER; the permutation into groups
  *     is internal.  Every tensor pointer (q, k, v, out, pages, kv_buf, new
  *     rows) must be 16-byte aligned (PK_EINVAL otherwise).

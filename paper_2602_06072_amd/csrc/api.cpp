@@ -56,6 +56,7 @@ struct Staging {
     bool used = false;                              // `copied` has been recorded for it
     bool busy = false;                              // handed out and not yet released by copy_tables
     bool of_graph = false;                          // read by the replays of a graph
+    const void* stream = nullptr;                   // of the last upload from it
 
     bool in_flight() const {
         return __atomic_load_n(done, __ATOMIC_ACQUIRE) != stamp || (used && hipEventQuery(copied) != hipSuccess);
@@ -65,35 +66,37 @@ std::mutex g_staging_mutex;
 std::vector<Staging> g_staging;
 constexpr size_t kMostStaging = 64;                 // buffers of the pool; and of graphs, whose further copies are from pageable memory
 
-// A host that runs ahead of the GPU has this many buffers in flight and then waits for one of them, for half a millisecond at most: a longer queue gains nothing, and
-// growing the pool to its 64 buffers and then emptying the stream with the 65th copy, which is from pageable memory, costs bubbles.  300 decode steps of 48 requests, regrouped
-// each, one after the other: 103.1 us a step without the wait, 97.1 with it (97.8 and 97.8 for 100 of them).
-constexpr size_t kStagingAhead = 16;
+// With the whole pool in flight an upload of a stream that has some of it waits for one of those, half a millisecond at most, before it is copied from pageable memory: for
+// such a copy the host waits until the stream has drained.  Nothing waits for the uploads of another stream, or while the pool may grow.  300 decode steps of 48 requests, regrouped
+// each, one after the other: 103.1 us a step with the copies from pageable memory, 97.7 with the wait (100 of them: 97.8 and 97.8).
 constexpr std::chrono::microseconds kStagingWait{500};
 
 // may_allocate = false: only a buffer that already exists and is free is handed out; of_graph: for good, to a graph
-Staging* staging_acquire(size_t bytes, bool may_allocate, bool of_graph) {
+Staging* staging_acquire(size_t bytes, bool may_allocate, bool of_graph, const void* stream) {
     std::unique_lock<std::mutex> lock(g_staging_mutex);
-    const size_t with_graphs = static_cast<size_t>(std::count_if(g_staging.begin(), g_staging.end(), [](const Staging& s) { return s.of_graph; }));
-    if (of_graph && with_graphs >= kMostStaging) return nullptr;
+    auto held_by_graphs = [] { return static_cast<size_t>(std::count_if(g_staging.begin(), g_staging.end(), [](const Staging& s) { return s.of_graph; })); };
+    if (of_graph && held_by_graphs() >= kMostStaging) return nullptr;
     std::chrono::steady_clock::time_point until;
     for (bool waits = false;; ) {
-        size_t fitting = 0;
+        bool behind = false;                        // a buffer that would do is read by an upload of this stream
         for (Staging& s : g_staging) {
-            if (s.cap < bytes || s.of_graph) continue;
-            if (!s.busy && !s.in_flight()) { s.busy = true; s.of_graph = of_graph; return &s; }
-            ++fitting;
+            if (s.cap < bytes || s.of_graph || s.busy) continue;
+            if (!s.in_flight()) {
+                s.busy = true; s.of_graph = of_graph; s.stream = stream;
+                return &s;
+            }
+            behind = behind || s.stream == stream;
         }
-        if (!may_allocate || of_graph || fitting < kStagingAhead) break;
+        if (!may_allocate) return nullptr;          // fall back to a pageable copy
+        if (of_graph || g_staging.size() - held_by_graphs() < kMostStaging) break;
         const auto now = std::chrono::steady_clock::now();
         if (!waits) until = now + kStagingWait;
-        else if (now >= until) break;
+        if (!behind || now >= until) return nullptr;
         waits = true;
-        lock.unlock();                              // (other threads bring buffers back meanwhile)
-        std::this_thread::yield();
+        lock.unlock();                              // (asleep: the pool is the other threads' meanwhile, and with so much queued the GPU does not notice)
+        std::this_thread::sleep_for(std::chrono::microseconds(10));
         lock.lock();
     }
-    if (!may_allocate || (!of_graph && g_staging.size() - with_graphs >= kMostStaging)) return nullptr;     // fall back to a pageable copy
     Staging s;
     s.cap = (bytes + (1u << 20) - 1) >> 20 << 20;
     // coherent: the upload kernel must not meet what an L2 kept of the buffer's last contents
@@ -107,6 +110,7 @@ Staging* staging_acquire(size_t bytes, bool may_allocate, bool of_graph) {
     }
     s.busy = true;
     s.of_graph = of_graph;
+    s.stream = stream;
     g_staging.reserve(2 * kMostStaging);            // pointers into the vector stay valid
     g_staging.push_back(s);
     return &g_staging.back();
@@ -148,7 +152,7 @@ int copy_tables(void* dst, const void* src, size_t bytes, void* stream, uint64_t
     // (asking an event or allocating would end a capture, unless this thread says that it is not part of it)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool relaxed = captured && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    Staging* s = staging_acquire(bytes, may_allocate, captured);
+    Staging* s = staging_acquire(bytes, may_allocate, captured, stream);
     if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (!s && captured) src = std::memcpy(new char[bytes], src, bytes);     // the graph's from here on: what the plan holds may be gone when it is replayed
     if (!s) return static_cast<int>(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));

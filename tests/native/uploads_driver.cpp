@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <ctime>
 #include <deque>
 #include <functional>
 #include <string>
@@ -37,8 +38,8 @@ struct Stream {
 };
 struct Event { bool reached = true; };
 static unsigned long long captures = 0;
-static int pageable = 0, yields = 0;               // copies from pageable memory outside of captures; turns of a wait
-static Work on_yield;
+static int pageable = 0, waits = 0;               // copies from pageable memory outside of captures; turns of waiting
+static Work on_wait;
 static std::vector<std::pair<char*, size_t>> pinned;
 static Stream* of(void* s) { return static_cast<Stream*>(s); }
 static Stream* of(hipStream_t s) { return reinterpret_cast<Stream*>(s); }
@@ -47,7 +48,7 @@ static void end(Stream& s) { s.graph = nullptr; s.capture = 0; }
 static void replay(Graph& g) { for (Work& w : g.nodes) w(); }
 
 extern "C" {
-int sched_yield() noexcept { ++yields; if (on_yield) on_yield(); return 0; }
+int nanosleep(const timespec*, timespec*) { ++waits; if (on_wait) on_wait(); return 0; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -219,11 +220,11 @@ static void graphs() {
     capture(20);
     s.held = true;
     for (int x = 0; x < 10; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
-    CHECK(yields == 0, "%d turns of waiting for buffers of graphs", yields);
+    CHECK(waits == 0, "%d turns of waiting for buffers of graphs", waits);
     s.run();
     capture(100);
     for (int x = 0; x < 10; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
-    CHECK(yields == 0 && pageable == 0, "behind 120 captured uploads: %d turns of waiting, %d copies from pageable memory", yields, pageable);
+    CHECK(waits == 0 && pageable == 0, "behind 120 captured uploads: %d turns of waiting, %d copies from pageable memory", waits, pageable);
     s.run();
     s.held = false;
     const std::vector<int32_t> host = b.plan->tables.host;
@@ -238,10 +239,47 @@ static void graphs() {
     CHECK(launches == 120 && wrong == 0, "%d of %d replays without their tables", wrong, launches);
 }
 
+// A host far ahead of the GPU: no upload waits while the pool may grow; then one waits for a buffer behind uploads of its own stream, in place of a copy from pageable
+// memory, for which the host would wait until the stream has drained; and never because of another stream.
+static void ahead() {
+    constexpr int POOL = 64;
+    Batch b(6, 3), c(6, 1);
+    Stream s, other;
+    s.held = true;
+    for (int x = 0; x < POOL; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
+    CHECK(waits == 0 && pageable == 0 && pinned.size() == POOL, "%d uploads: %d turns of waiting, %d copies from pageable memory, %zu buffers", POOL, waits, pageable, pinned.size());
+    int turns = 0;
+    on_wait = [&] { if (++turns % 3 == 0) s.run(1); };
+    for (int x = 0; x < 20; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", POOL + x);
+    CHECK(turns == 60 && pageable == 0 && s.queue.size() == POOL && pinned.size() == POOL, "with buffers that come back: %d turns of waiting, %d copies from pageable memory, %zu uploads in "
+          "flight, %zu buffers", turns, pageable, s.queue.size(), pinned.size());
+    on_wait = nullptr;
+    waits = 0;
+    CHECK(b.call("bind", other) == PK_OK, "bind on an idle stream");
+    CHECK(waits == 0 && pageable == 1 && s.queue.size() == POOL, "an idle stream: %d turns of waiting, %d copies from pageable memory, %zu uploads left", waits, pageable, s.queue.size());
+    CHECK(c.call("static", s) == PK_OK, "static");
+    CHECK(waits == 0 && pageable == 2, "the fixed scratch: %d turns of waiting, %d copies from pageable memory", waits, pageable);
+    s.run();
+    for (int x = 0; x < POOL; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
+    CHECK(waits == 0 && pageable == 2 && s.queue.size() == POOL, "again: %d turns of waiting, %d copies from pageable memory", waits, pageable);
+    CHECK(b.call("bind", s) == PK_OK, "bind on a stream that stands still");
+    CHECK(waits > 0 && pageable == 3, "a stream that stands still: %d turns of waiting, %d copies from pageable memory", waits, pageable);
+    Graph g;
+    s.run();
+    for (int x = 0; x < POOL; ++x) CHECK(b.call("bind", s) == PK_OK, "bind %d", x);
+    waits = 0;
+    begin(s, g);
+    CHECK(b.call("bind", s) == PK_OK && g.copies == 1, "captured bind");
+    end(s);
+    CHECK(waits == 0, "captured: %d turns of waiting", waits);
+    s.run();
+}
+
 int main(int, char** argv) {
     const std::string check = argv[1];
     if (check == "captured") captured();
     else if (check == "graphs") graphs();
+    else if (check == "ahead") ahead();
     else return 2;
     return failures ? 1 : 0;
 }

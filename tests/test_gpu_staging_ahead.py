@@ -1,5 +1,5 @@
-"""Tables of many plans bound one after the other while the stream is busy: the host runs out of staging buffers that are free, waits, and goes on in time;
-every plan's call finds its own tables."""
+"""Tables of many plans bound one after the other while the stream is busy: the host runs out of staging buffers, waits for one or copies from pageable memory, and
+every plan's call finds its own tables.  (When it waits and when it does not: test_table_uploads.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +16,7 @@ def test_many_binds_ahead_of_the_gpu(busy_first):
     Hq, Hkv, d = 8, 2, 64
     rng = np.random.default_rng(3)
     calls = []
-    for i in range(40):
+    for i in range(100):                            # (more than the 64 buffers of the pool)
         lens = rng.integers(1, 120, 6).astype(np.int32)
         w = wl.make_ragged("ahead", lens, lens, Hq, Hkv, d, 1024, 100 + i, device=DEV, keep_f32=False)
         calls.append((lens, w, torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)))
@@ -37,7 +37,7 @@ def test_many_binds_ahead_of_the_gpu(busy_first):
         del keep
     a = torch.randn(8192, 8192, device=DEV, dtype=torch.bfloat16)
     torch.cuda.synchronize()
-    for _ in range(12 if busy_first else 0):        # some 10 ms: longer than the host waits for a buffer
+    for _ in range(12 if busy_first else 0):        # some 10 ms: longer than the host takes to fill the pool, and than it waits for a buffer
         torch.mm(a, a)
     keep = [run(*c) for c in calls]
     torch.cuda.synchronize()

@@ -22,7 +22,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["captured", "graphs"])
+@pytest.mark.parametrize("check", ["captured", "graphs", "ahead"])
 def test_table_uploads(driver, check):
     run = subprocess.run([driver, check], capture_output=True, text=True, timeout=100)
     assert run.returncode == 0, (run.stdout[-3000:], run.stderr[-3000:])
