@@ -589,7 +589,8 @@ __device__ __forceinline__ bf16x8 stream_operand(const unsigned char* const (&kp
 // The rows of a tile whose list was cut: the partial results of its pieces, each weighted by its reference against the largest of them, in the order of
 // their slots.  A workgroup has the 32 rows and one head of a wave of prefill_tile_body, wave b of it the columns 32 b .. + 31: `unit` counts (list, KV head,
 // workgroup of the KV head, wave).  A reference is a score times sc and an offset (offset_of), so that those of far rows are subtracted before they are scaled.
-// Bound by latency, two round trips to memory for every four pieces and 4 to 7 us with the launch.  (In the first launch instead, by the workgroup that finishes the last
+// Bound by latency, two round trips to memory for every four pieces and 4 to 7 us with the launch.  A batch of four whole pieces has no checks between its sums and the last
+// batch adds what there is: 1 x 64 rows behind 8000 with 8/8 heads 20.9 us, with a check for every piece 21.5, with zeros for the pieces that are not there 23.3.  (In the first launch instead, by the workgroup that finishes the last
 // piece of a list: one workgroup then reads 68 KiB a piece, in a mixed step 3 x 90 rows behind some 9000 tokens with 4/1 heads 27.8 -> 43.3 us.)
 __device__ __forceinline__ void prefill_merge(const PrefillArgs& a, const int unit) {
     constexpr int BATCH = 4;                       // pieces whose accumulators are requested together
@@ -626,14 +627,22 @@ __device__ __forceinline__ void prefill_merge(const PrefillArgs& a, const int un
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) v[y][q4] = t.o[b][q4][lane];
         }
-#pragma unroll
-        for (int y = 0; y < BATCH; ++y) {
-            const float w = s + y < pieces && r[y][0] != 0.f ? __builtin_amdgcn_exp2f(beyond(r[y][1], r[y][2], m, far)) : 0.f;
+        asm volatile("" ::: "memory");             // (the reads stay before the branches below)
+        auto add = [&](const int y) {
+            const float w = r[y][0] != 0.f ? __builtin_amdgcn_exp2f(beyond(r[y][1], r[y][2], m, far)) : 0.f;
             l = __builtin_fmaf(w, r[y][0], l);
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) o[q4][c] = __builtin_fmaf(w, v[y][q4][c], o[q4][c]);
+        };
+        if (s + BATCH <= pieces) {
+#pragma unroll
+            for (int y = 0; y < BATCH; ++y) add(y);
+        } else {                                   // (not the last one repeated: a weight of zero would make NaNs of infinite values)
+#pragma unroll
+            for (int y = 0; y < BATCH - 1; ++y)
+                if (s + y < pieces) add(y);
         }
     }
     const float inv = row_scale(l);

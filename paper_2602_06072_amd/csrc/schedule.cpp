@@ -760,7 +760,7 @@ void emit_head_tiles(const pk_plan& plan, const std::vector<int64_t>& q_start, c
 // pieces of (nearly) the same length, a workgroup each, and a second launch puts the pieces together (prefill_merge).  A key tile takes a workgroup 0.87 us
 // whether it has a compute unit to itself or shares it, so that a launch takes as long as its longest list or, if that is more, as all lists dealt over the units; pieces cost
 // a launch, a start each, and 17 KiB per 32 rows and head (9 with d = 64) that are written and read.  us, whole lists / pieces of the length that ListSplit
-// finds best, d = 128: 1 x 64 rows behind 8000 with 8/8 heads (8 workgroups of 126 key tiles) 113 / 22; 32/8 heads 1 x 16 behind 16000 217 / 29, behind 2000 30.7 / 14.9,
+// finds best, d = 128: 1 x 64 rows behind 8000 with 8/8 heads (8 workgroups of 126 key tiles) 113 / 21; 32/8 heads 1 x 16 behind 16000 217 / 28, behind 2000 30.7 / 14.9,
 // 1 x 128 behind 8192 127 / 30, 1 x 512 behind 8192 134 / 83, 4 x 100 behind 3000 52.0 / 38.5; 4/1 heads 8 of 68..112 behind up to 4600 71 / 21, 1 x 4096 64.7 / 35.3;
 // 8/2 heads 1 x 1105 20.6 / 19.0; d = 64: 1 x 64 behind 8000 with 8/8 88.8 / 17.7.  Of 800 launches (1 to 40 requests, up to 20000 keys, eleven head
 // shapes) 173 get pieces, twice as fast on average; one of them lost (1 x 1124 with 12/2 heads 21.1 / 21.7).

@@ -77,6 +77,27 @@ def test_nonfinite_values_reach_only_the_rows_that_see_them(heads):
     assert torch.equal(got[: int(q0[1])], clean[: int(q0[1])]) and torch.equal(got[int(q0[4]):], clean[int(q0[4]):])
 
 
+@pytest.mark.parametrize("heads", [(8, 8, 128), (8, 2, 64), (12, 2, 128)])
+@pytest.mark.parametrize("ctx", [1500, 2000, 3000, 8000])
+def test_infinite_values_stay_infinite(heads, ctx):
+    """An infinite value among those that every row sees, in the last piece or in the first: every row of its KV head and column is infinite, as in whole lists."""
+    ql = np.asarray([64], dtype=np.int32)
+    w = wl.make_ragged("infinite", ql + ctx, ql, *heads, 16384, 97, device=DEV, keep_f32=False)
+    w.v[ctx - 10, 0, 3] = float("inf")
+    w.v[20, w.Hkv - 1, 40] = float("-inf")
+    plan, ws = ready(w)
+    assert plan.stat(13) > 1
+    r = w.Hq // w.Hkv
+    for pipeline in (0, 1):                        # (1: whole lists)
+        plan.tune(pk.TUNE_PREFILL_PIPELINE, pipeline)
+        out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+        pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
+        torch.cuda.synchronize()
+        assert (out[:, :r, 3] == float("inf")).all() and (out[:, -r:, 40] == float("-inf")).all(), (pipeline, plan.stat(13))
+        out[:, :r, 3] = out[:, -r:, 40] = 0
+        assert torch.isfinite(out).all()
+
+
 @pytest.mark.parametrize("heads", [(8, 2, 128), (8, 2, 64)])
 def test_pieces_in_the_mixed_step_and_in_a_graph(heads):
     """The same bits in every launch; two plans take turns on the tables and partial results of a workspace each."""
