@@ -141,3 +141,56 @@ def test_tuned_pipeline_takes_whole_lists():
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[2])
     assert (outs[0].float() - outs[1].float()).abs().max() <= 4e-2     # (each within 2e-2 of the reference)
+
+
+@pytest.mark.parametrize("heads", [(8, 8, 128), (8, 2, 64), (12, 2, 128)])
+def test_references_near_and_far_from_zero_meet(heads):
+    """Pieces whose scores are some octaves beside pieces whose scores are so large that their reference is a score, with either the greater, and pieces that all lie far below
+    zero.  The best key of a row is alone or has equals, bit for bit, and leads the others by far more than any rounding."""
+    w = batch("edges", heads, 98)
+    assert ready(w)[0].stat(13) > 0
+    q0, k0 = np.concatenate([[0], np.cumsum(w.q_lens)]), np.concatenate([[0], np.cumsum(w.kv_lens)])
+    for i in range(w.n):
+        q, k, ctx = w.q[int(q0[i]): int(q0[i + 1])], w.k[int(k0[i]): int(k0[i + 1])], int(w.kv_lens[i] - w.q_lens[i])
+        if i == 4:                                 # 32 factors, repeated, all below zero
+            q.fill_(1e16)
+            k.copy_((-1e15 * (2.0 - (torch.arange(k.shape[0], device=DEV) * 7 % 32).float() / 32)).view(-1, 1, 1).expand(k.shape))
+            continue
+        q.copy_(q.abs() * 1e3)
+        k.zero_()                                  # a score of zero, but for a few keys spread over the context: above (one after the other the best) or below
+        for j, pos in enumerate(np.linspace(0, ctx - 1, 9).astype(int)):
+            k[int(pos)] = (1e6 if i % 2 else -1e6) * 2.0 ** (j if i == 1 else 9 - j)
+    plan, ws = ready(w, 255)
+    out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, out, w.scale, ws)
+    torch.cuda.synchronize()
+    H.assert_close(out.cpu().numpy(), H.oracle_ragged(w, False), 0, f"near and far {heads}")
+
+
+@pytest.mark.parametrize("heads", [(8, 8, 128), (8, 8, 64)])
+def test_whole_lists_beside_a_decode_half_that_outlasts_them(heads):
+    """The mixed step's prefill half is that of whole lists (which the padded call has) beside long decode work, and in pieces beside short; the decode half is the decode call's."""
+    Hq, Hkv, d = heads
+    ql, ctx = np.asarray([64], dtype=np.int32), np.asarray([2000], dtype=np.int32)
+    w = wl.make_ragged("chunk", ql + ctx, ql, *heads, 16384, 99, device=DEV, keep_f32=False)
+    plan, ws = ready(w)
+    assert plan.stat(13) > 1
+    pieces, whole = (torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV) for _ in range(2))
+    pk.packed_prefill_attn(plan, w.q, w.k, w.v, pieces, w.scale, ws)
+    pk.padded_prefill_attn(plan, w.q, w.k, w.v, whole, w.scale, ws)
+    want = H.oracle_ragged(w, False)
+    torch.cuda.synchronize()
+    assert not torch.equal(pieces, whole)
+    for n, lo, hi, expected in ((3, 50, 400, pieces), (40, 3500 * 128 // d, 4500 * 128 // d, whole)):
+        dec = wl.small_paged(seed=100, n=n, lo=lo, hi=hi, Hq=Hq, Hkv=Hkv, d=d, token_budget=8192, device=DEV, keep_f32=False)
+        dplan = pk.pack_plan(dec.kv_lens, np.ones_like(dec.kv_lens), None, None, 8192)
+        dws = pk.new_workspace(dplan, Hq, Hkv, d, pk.PK_BF16)
+        buf = pk.new_kv_buf(dplan, Hkv, d, pk.PK_BF16)
+        pk.kv_reorganize(dplan, dec.k_pages, dec.v_pages, torch.from_numpy(dec.block_table).to(DEV), buf, dws)
+        out = torch.full(w.q.shape, float("nan"), dtype=torch.float32, device=DEV)
+        d_alone, d_fused = (torch.full(dec.q.shape, float("nan"), dtype=torch.float32, device=DEV) for _ in range(2))
+        pk.packed_decode_attn(dplan, dec.q, buf, d_alone, dec.scale, Hkv, dws)
+        pk.packed_mixed_step(plan, w.q, w.k, w.v, out, ws, dplan, dec.q, buf, d_fused, dws, w.scale)
+        torch.cuda.synchronize()
+        assert torch.equal(out, expected) and torch.equal(d_fused, d_alone), n
+        H.assert_close(out.cpu().numpy(), want, 0, f"beside {n} decode rows {heads}")
