@@ -30,7 +30,9 @@
  *   - A plan carries its device tables and the workspace it is bound to:
  *     calls on ONE plan must not run concurrently from several host threads,
  *     and launches that share a workspace must be ordered on the stream(s)
- *     by the caller (decode keeps partial results there).  Different plans
+ *     by the caller: decode keeps partial results there, a packed prefill that
+ *     works on pieces of key-tile lists does (pk_plan_stat 13), and a first
+ *     call may copy tables there.  Different plans
  *     may be used from different threads.  A workspace has ONE owner at a
  *     time, the plan that bound it last: a compute call of another plan on
  *     the same workspace uploads that plan's tables again (the library keeps
@@ -169,7 +171,8 @@ int64_t pk_plan_serialize(const pk_plan* plan, int32_t* out, int64_t cap);
  *   PK_F32 layout: K as [Hkv][buf_tokens][d] floats, then V likewise.
  *
  * pk_workspace_bytes: bytes of the workspace that carries the plan's device
- *   tables and the split-KV partial results for the given head shape.
+ *   tables and the partial results (of split-KV decode, of pieces of key-tile
+ *   lists in prefill) for the given head shape.
  */
 size_t pk_kv_buf_bytes(const pk_plan* plan, int Hkv, int d, int dtype);
 size_t pk_workspace_bytes(const pk_plan* plan, int Hq, int Hkv, int d, int dtype);
@@ -287,8 +290,9 @@ int pk_packed_mixed_step(pk_plan* prefill_plan, const void* q, const void* k, co
  *   - The first call of a plan on a device (and the first after another plan
  *     used the scratch) uploads the plan's tables with one host-to-device copy
  *     on `stream`; further calls of that plan only launch kernels.
- *   - A plan whose tables and partial results need more than
- *     PK_STATIC_SCRATCH_BYTES is rejected with PK_EUNSUPPORTED and a message
+ *   - A plan whose tables (those of its packed prefill count) and partial
+ *     results have more than PK_STATIC_SCRATCH_BYTES, with a wave for every
+ *     work item and one split, is rejected with PK_EUNSUPPORTED and a message
  *     that states both sizes (use pk_packed_decode_attn with a workspace).
  *   - All calls on one GPU share the one array, which keeps the contents of
  *     the last call: calls that overlap in time on one GPU (different

@@ -225,8 +225,8 @@ int ensure_bound(pk_plan* plan, int Hq, int Hkv, int d, int dtype, void* workspa
     if (!same_shape) build_tables(*plan, Hq, Hkv, d, dtype, device_cus(), t);
     if (fixed_scratch) {
         if (workspace_bytes < t.decode_only_bytes)
-            return fail(PK_EUNSUPPORTED, "pk_packed_decode_attn_static: the plan needs " + std::to_string(t.decode_only_bytes) +
-                        " bytes of tables and partial results, the fixed scratch holds " + std::to_string(workspace_bytes) +
+            return fail(PK_EUNSUPPORTED, "pk_packed_decode_attn_static: the plan has " + std::to_string(t.decode_only_bytes) +
+                        " bytes of tables (those of its packed prefill among them) and partial results, the fixed scratch is for plans of up to " + std::to_string(workspace_bytes) +
                         " (PK_STATIC_SCRATCH_BYTES); use pk_packed_decode_attn with a workspace");
     } else if (workspace_bytes < t.total_bytes) {
         return fail(PK_EINVAL, "workspace smaller than pk_workspace_bytes");

@@ -4,8 +4,9 @@
 // cycle's share of the prefill sets; the last cycle goes on to the end with what is left of either kind.  Spread over the launch, the decode runs load the memory system evenly;
 // alternating one by one until the decode work is gone they saturate it for the first quarter of the
 // launch, and the prefill tiles of that stretch wait (spread 1.3 % faster for 32 chunks and 480 rows of a 70B-shaped layer, small steps
-// unchanged).  Runs of 16 sets measure 0.7 % less there, of 64 1.3 % more, of 8 1 %, of 4 2 %; on smaller steps runs of 4 to 32 are level (workgroups go
-// to the compute units of an XCD one per unit before any unit gets its second: short runs put two of a kind on one unit).
+// unchanged).  Workgroups go to the compute units of an XCD one per unit before any unit gets its second: runs of 32 sets, one workgroup for every unit, put one of each kind on a unit in
+// launches of one round.  Runs of 4 / 8 / 16 / 32 / 64 sets: 32 chunks and 480 rows 11.97 / 11.90 / 11.64 / 11.75 / 12.04 ms, 8 chunks and 200 rows with 32/8 heads 1339 / 1339 /
+// 1331 / 1334 / 1358 us, 16 prompts of 30 to 300 rows beside 60 decode rows with 16/2 heads 31.0 / 29.4 / 29.6 / 26.8 / 33.3.
 // No set is padding: where runs were filled up with workgroups that end at once, the first decode workgroups of a small step met its few prefill workgroups on the same units
 // while others stayed idle.  us, filled up / now: 3 short prompts with 16/2 heads beside 3 decode rows 12.2 / 10.8, 2 with 32/8 beside 4 10.1 / 8.4, 1 with 16/2 beside 46
 // 10.2 / 8.8; 72 drawn steps 1.02 times as fast in the geometric mean, between 0.95 and 1.2.

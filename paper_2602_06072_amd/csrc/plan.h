@@ -89,7 +89,7 @@ struct DeviceTables {
         TableRef merges;            // [n_merges][4] first slot, pieces, Q row of tile row 0, rows of every tile whose list is cut
         TableRef piece_kvtiles;     // their key-tile lists
         int32_t n_pieces = 0, n_merges = 0, piece_shift = 2;      // (piece_shift: their row_shift)
-        double whole_us = 0, pieces_us = 0;                       // estimates of the launch with whole lists and in pieces
+        double whole_us = 0;                                      // estimate of the launch with whole lists
         int32_t n_tiles = 0;
         int64_t issued_pairs = 0;
         int32_t n_query_tiles = 0;  // packed: of 128 rows, whatever row_shift is
@@ -118,8 +118,9 @@ struct DeviceTables {
     size_t partial_bytes = 0;
     size_t prefill_part_bytes = 0;  // of them, partial results of pieces of key-tile lists
     size_t total_bytes = 0;
-    size_t decode_only_bytes = 0;   // tables + the packed decode partials alone (what the static scratch must hold),
-                                    // dec.chosen: as they would be with a wave per work item and one split
+    size_t decode_only_bytes = 0;   // what decides whether a plan may use the fixed scratch: its tables and the packed decode partials, dec.chosen: as they would
+                                    // be with a wave per work item and one split.  The tables of its packed prefill count, though they are never copied there:
+                                    // which plans are admitted does not depend on when these tables are made
     bool group_over_scratch = false;    // those of dec.chosen do not fit the static scratch, the others would
 };
 

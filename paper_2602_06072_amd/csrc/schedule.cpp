@@ -527,7 +527,7 @@ void add_idle_tile(SchedBuild& sb) {               // padded grid slot of a requ
 // Below one workgroup per unit (with d = 64 one and a half: three share a unit) the other body is the better one with any list: 7 x 57 rows
 // behind 2500 tokens with 32 heads (224 workgroups) 43.9 / 40.4 and 33.1 / 32.4, 1 x 512 behind 8192 (128) 142.4 / 134.3 and
 // 115.1 / 106.5, 1 x 64 behind 8000 with 8 heads (8) 124.5 / 114.0 and 94.0 / 91.8.
-// The prefill half of a mixed step follows the same line, so that its results are those of the prefill call bit for bit (64 x 200 with 32
+// The prefill half of a mixed step follows the same line, so that its results are those of the prefill call bit for bit, but for lists that only the call has in pieces (64 x 200 with 32
 // heads and 32 decode rows of 500 tokens 87.2 / 81.8, 8 x 1024 and 256 of 700 178 / 173; d = 64 98.7 / 94.5).
 bool light_launch(int64_t tiles, int64_t key_tiles, int Hq, int d, int num_cus) {
     if (tiles == 0) return true;
@@ -857,7 +857,6 @@ void split_lists(const pk_plan& plan, const std::vector<int64_t>& q_start, const
     s.pieces = b.add(pieces);
     s.merges = b.add(merges);
     s.whole_us = whole;
-    s.pieces_us = best;
     t.prefill_part_bytes = static_cast<size_t>(slots) * units * 4 * 64 * (2 * t.d + 16);
 }
 
